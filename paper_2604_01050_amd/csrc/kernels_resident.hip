@@ -12,6 +12,7 @@ using namespace csr;
 // ---------------------------------------------------------------------------
 // Register-resident CSR loop: many steps per launch.
 //
+// (Instances with few columns run kernels_narrow.hip instead.)
 // One workgroup of NT threads (512, or 1024 from 2048 padded rows: the same
 // rows in more waves hide more latency, 3-4% per step) owns RES_COLS consecutive replica
 // columns of one run (R a multiple of RES_COLS) for all N spins. Its x and y

@@ -785,10 +785,14 @@ sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, con
             HIP_TRY(hipMemcpyAsync(c->rcol, rc.data(), sizeof(int32_t) * rc.size(), hipMemcpyHostToDevice, c->stream));
             HIP_TRY(hipMemcpyAsync(c->rval, rv.data(), sizeof(double) * rv.size(), hipMemcpyHostToDevice, c->stream));
             HIP_TRY(hipMemcpyAsync(c->rh, rhv.data(), sizeof(double) * rhv.size(), hipMemcpyHostToDevice, c->stream));
-            HIP_TRY(dalloc(c, &c->xpub, (size_t)2 * c->res_nwg * 2 * NR));
-            HIP_TRY(dalloc(c, &c->flags, (size_t)c->res_nwg));
-            HIP_TRY(dalloc(c, &c->epoch_cnt, (size_t)c->res_nwg));
-            HIP_TRY(dalloc(c, &c->sbits, (size_t)c->res_nwg * NR));
+            if (c->res_W < resident_cols()) {
+                HIP_TRY(dalloc(c, &c->words, (size_t)2 * c->res_nwg * 2 * narrow_rows(N)));
+            } else {
+                HIP_TRY(dalloc(c, &c->xpub, (size_t)2 * c->res_nwg * 2 * NR));
+                HIP_TRY(dalloc(c, &c->flags, (size_t)c->res_nwg));
+                HIP_TRY(dalloc(c, &c->epoch_cnt, (size_t)c->res_nwg));
+                HIP_TRY(dalloc(c, &c->sbits, (size_t)c->res_nwg * NR));
+            }
             HIP_TRY(dalloc(c, &c->rd_cnt, (size_t)runs));
             HIP_TRY(hipMemcpyAsync(c->colpad, cp.data(), sizeof(int32_t) * cp.size(), hipMemcpyHostToDevice, c->stream));
             HIP_TRY(hipMemcpyAsync(c->valpad, vp.data(), sizeof(float) * vp.size(), hipMemcpyHostToDevice, c->stream));
@@ -1020,6 +1024,25 @@ static bool resident_plan(sbqa_ctx *c, const sbqa_coupling *J, std::string *why)
     c->res_D = D;
     c->res_rows = resident_rows(c->N);
     c->res_nwg = nwg;
+    c->res_W = resident_cols();
+    // Fewer columns per workgroup (the narrow loop) while the workgroups of
+    // four launches still fit on the device together: launches of different
+    // streams reach it through four hardware queues, each of which hands out
+    // its workgroups in order, so the ring neighbours of every launch then get
+    // to run whatever the other queues hold. Two columns up to a quarter of
+    // the CUs (128 columns), else four. us per step for W = 8 / 4 / 2: N =
+    // 1000, degree 3, C = 128 2.48 / 1.20 / 1.12; N = 4096, degree 6, C = 128
+    // 6.20 / 4.35 / 2.94; C = 256 6.33 / 4.41 / 3.81 (two columns do not fit
+    // four times there); N = 1000, degree 6, C = 512 2.81 / 1.41 / 1.93 (twice
+    // the edge words).
+    for (int W : {2, 4}) {
+        int nb = 0;
+        if (narrow_max_blocks(D, W, c->N, &nb) != hipSuccess || nb < 1) continue;
+        if ((int64_t)c->L.C / W * 4 > (int64_t)cus * (W == 2 ? 1 : nb)) continue;
+        c->res_W = W;
+        c->res_nwg = c->L.C / W;
+        break;
+    }
     return true;
 }
 
@@ -1315,7 +1338,13 @@ static sbqa_status ctx_step_resident(sbqa_ctx *c, uint32_t K) {
     a.epoch_cnt = c->epoch_cnt;
     a.epoch = ++c->epoch;
     a.err = c->err;
+    a.nr = c->res_rows;
     a.sbits = c->sbits;
+    if (c->res_W < resident_cols()) {
+        HIP_TRY(launch_csr_narrow(a, c->res_D, c->res_W, c->words, c->stream));
+        c->step += K;
+        return SBQA_OK;
+    }
     HIP_TRY(launch_csr_resident(a, c->res_D, c->stream));
     c->step += K;
     c->sbits_step = c->step;

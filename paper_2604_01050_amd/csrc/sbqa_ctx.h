@@ -159,6 +159,7 @@ struct sbqa_ctx {
     bool resident = false;
     float *Jsm = nullptr;               // small dense loop: J float32 [N][N]
     int res_D = 0, res_rows = 0, res_nwg = 0;
+    int res_W = 8;                      // columns per workgroup: 8, or 4 or 2 in the narrow loop
     int32_t *colpad = nullptr;          // [rows][D]
     std::vector<int32_t> pnew;          // CSR spins relabelled: row of the caller's spin i (empty: identity)
     int32_t *porig = nullptr;           // [N] the caller's spin index of each row (relabelled only)
@@ -170,6 +171,7 @@ struct sbqa_ctx {
     float *coefA = nullptr;             // [S]
     float *delta_tab = nullptr;         // [S+1]
     float *xpub = nullptr;              // [2][nwg][2][rows] published edge columns
+    uint64_t *words = nullptr;          // narrow loop: the same as tagged words
     // sign bytes of the state the resident loop left ([nwg][rows], bit k: x
     // of the block's column k is negative), valid while sbits_step == step
     uint8_t *sbits = nullptr;

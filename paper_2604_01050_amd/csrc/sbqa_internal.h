@@ -213,6 +213,7 @@ struct ResidentArgs {
     int *epoch_cnt;         // [nwg] launches started (monotonic)
     int epoch;              // this launch's number (>= 1)
     int *err;               // [1] set on a wait timeout
+    int nr;                 // padded rows of the state (NR)
     uint8_t *sbits;         // [nwg][NR] sign bytes of the final state (bit k: column k negative)
 };
 int resident_degree(int maxdeg);        // padded degree D, or -1 when too large
@@ -227,6 +228,13 @@ hipError_t resident_max_blocks(int D, int N, int *blocks_per_cu);
 // a mutex otherwise), so that launches do not pay for it every time.
 hipError_t ensure_dyn_lds(const void *fn, size_t lds);
 hipError_t launch_csr_resident(const ResidentArgs &a, int D, hipStream_t st);
+// The same loop with W = 2 or 4 columns per workgroup (kernels_narrow.hip),
+// nwg = C / W workgroups: words holds the tagged ring edges
+// [2][nwg][2][narrow_rows(N)], zero before the context's first launch (xpub,
+// flags, epoch_cnt and sbits are not used).
+int narrow_rows(int N);              // rows computed, at most NR
+hipError_t narrow_max_blocks(int D, int W, int N, int *blocks_per_cu);
+hipError_t launch_csr_narrow(const ResidentArgs &a, int D, int W, uint64_t *words, hipStream_t st);
 
 // Resident loop for small dense instances (kernels_small.hip): one
 // workgroup per run, K steps per launch, J float32 [N][N] row-major, state
