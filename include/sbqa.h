@@ -93,7 +93,11 @@ typedef enum {
 typedef enum { SBQA_JP_LINEAR = 0, SBQA_JP_PAPER = 1, SBQA_JP_TABLE = 2 } sbqa_jpkind;
 
 /* Step-loop kernel.
- *   AUTO      RESIDENT when the instance fits a resident loop, else STREAM.
+ *   AUTO      RESIDENT when the instance fits a resident loop, else STREAM;
+ *             dense +-1 instances of up to 2048 spins (R <= 32, f ternary or
+ *             sign, every precision but BF16X3) then also take many steps per
+ *             launch, J as one bit per coupling in registers (the same bits as
+ *             STREAM; sbqa_info_t.resident stays 0).
  *   STREAM    one fused launch per step, state streamed through HBM.
  *   RESIDENT  many steps per launch with the state on chip:
  *             - sparse (CSR): the register-resident loop (ternary or sign f,

@@ -28,6 +28,7 @@
 // belong to the same thread index in every workgroup) stored that word after
 // it had read this slot's step n - 1, so no unread word is overwritten.
 #include "csr_common.h"
+#include "ring_tags.h"
 
 #include <type_traits>
 
@@ -36,24 +37,12 @@ namespace {
 
 using namespace csr;
 
-constexpr int NARROW_SPIN_LIMIT = 1 << 20;   // polls of one wave for one step
-
 template <int W> struct HalfVec;
 template <> struct HalfVec<2> { typedef _Float16 type __attribute__((ext_vector_type(2))); };
 template <> struct HalfVec<4> { typedef _Float16 type __attribute__((ext_vector_type(4))); };
 template <int W> struct FloatVec;
 template <> struct FloatVec<2> { typedef float2 type; };
 template <> struct FloatVec<4> { typedef float4 type; };
-
-__device__ __forceinline__ uint64_t edge_word(float v, uint32_t tag) {
-    return ((uint64_t)tag << 32) | __float_as_uint(v);
-}
-__device__ __forceinline__ void put_word(uint64_t *p, uint64_t v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint64_t get_word(const uint64_t *p) {
-    return __hip_atomic_load(const_cast<uint64_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // Weights in LDS (one conflict-free read a term) where a thread's rows and
 // columns leave no registers for them (128 at four waves per SIMD); in
@@ -64,7 +53,8 @@ constexpr bool weights_in_lds(int RPT, int D, int W) { return W == 4 && RPT * D 
 // owns rows t + q * NT, q < RPT; RPT * NT >= N. Its neighbours' LDS offsets
 // stay in registers, two to a register.
 template <int RPT, int D, int NT, int W>
-__global__ __launch_bounds__(NT) void k_csr_narrow(const ResidentArgs a, uint64_t *__restrict__ words) {
+__global__ __launch_bounds__(NT) void k_csr_narrow(const ResidentArgs a, uint64_t *__restrict__ words,
+                                                 uint32_t *__restrict__ rings) {
     using HV = typename HalfVec<W>::type;
     using FV = typename FloatVec<W>::type;
     constexpr int ROWS = RPT * NT;
@@ -81,6 +71,7 @@ __global__ __launch_bounds__(NT) void k_csr_narrow(const ResidentArgs a, uint64_
     // words of parity b, workgroup v, edge e (0: first column, 1: last)
     auto slot = [&](int b, int v, int e) { return words + (((int64_t)b * a.nwg + v) * 2 + e) * ROWS; };
 
+    const uint32_t tag0 = ring_base(rings + 2 * run);   // step s of the launch: tag0 + s + 1
     float xs[RPT][W], ys[RPT][W], wt[WL ? 1 : RPT][WL ? 1 : D], hv[RPT];
     uint32_t off[RPT][D / 2];
 #pragma unroll
@@ -112,8 +103,8 @@ __global__ __launch_bounds__(NT) void k_csr_narrow(const ResidentArgs a, uint64_
 #pragma unroll
             for (int c = 0; c < W; ++c) f[c] = (_Float16)f_value(a.fmode, xs[q][c], d0);
             op[a.n0 & 1][r] = f;
-            put_word(pf + r, edge_word(xs[q][0], (uint32_t)a.n0 + 1u));
-            put_word(pl + r, edge_word(xs[q][W - 1], (uint32_t)a.n0 + 1u));
+            put_word(pf + r, tagged(__float_as_uint(xs[q][0]), tag0 + 1u));
+            put_word(pl + r, tagged(__float_as_uint(xs[q][W - 1]), tag0 + 1u));
         }
     }
     float kA = a.coefA[a.n0], dn = a.delta[a.n0 + 1], jpr = a.jp[(int64_t)run * a.S + a.n0];
@@ -137,7 +128,7 @@ __global__ __launch_bounds__(NT) void k_csr_narrow(const ResidentArgs a, uint64_
             jpr = a.jp[(int64_t)run * a.S + n + 1];
         }
         const uint8_t *opb = reinterpret_cast<const uint8_t *>(op[b]);
-        const uint32_t tag = (uint32_t)n + 1u;
+        const uint32_t tag = tag0 + (uint32_t)s + 1u;
         // (uniform base, 32-bit lane offset: no address registers per row)
         const uint64_t *el = slot(b, wl, 1), *er = slot(b, wr, 0);
         uint64_t *pf = slot(1 - b, w, 0), *pl = slot(1 - b, w, 1);
@@ -162,10 +153,9 @@ __global__ __launch_bounds__(NT) void k_csr_narrow(const ResidentArgs a, uint64_
                 }
             }
             // the neighbours' edges of step n: polled until every word of the
-            // wave carries the step's tag (bounded; once the error word is set
-            // every later wait ends within 16 polls)
+            // wave carries the step's tag
             uint64_t vl[G], vr[G];
-            for (int spins = 0;; ++spins) {
+            for (int polls = 0;; ++polls) {
                 bool ok = true;
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
@@ -175,12 +165,7 @@ __global__ __launch_bounds__(NT) void k_csr_narrow(const ResidentArgs a, uint64_
                 }
 #pragma unroll
                 for (int g = 0; g < G; ++g) ok = ok && (uint32_t)(vl[g] >> 32) == tag && (uint32_t)(vr[g] >> 32) == tag;
-                if (__all(ok)) break;
-                if ((spins & 15) == 15 && __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
-                if (spins > NARROW_SPIN_LIMIT) {
-                    __hip_atomic_store(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    break;
-                }
+                if (__all(ok) || stop_waiting(polls, a.err)) break;
             }
 #pragma unroll
             for (int g = 0; g < G; ++g) {
@@ -197,8 +182,8 @@ __global__ __launch_bounds__(NT) void k_csr_narrow(const ResidentArgs a, uint64_
                     f[c] = (_Float16)(fabsf(xo[c]) > d ? sg : 0.0f);   // f of Eq. 8 (d = 0 for sign)
                 }
                 if constexpr (!LAST) {
-                    put_word(pf + q * NT + (uint32_t)t, edge_word(xo[0], tag + 1u));
-                    put_word(pl + q * NT + (uint32_t)t, edge_word(xo[W - 1], tag + 1u));
+                    put_word(pf + q * NT + (uint32_t)t, tagged(__float_as_uint(xo[0]), tag + 1u));
+                    put_word(pl + q * NT + (uint32_t)t, tagged(__float_as_uint(xo[W - 1]), tag + 1u));
                     op[1 - b][t + q * NT] = f;
                 }
 #pragma unroll
@@ -214,6 +199,8 @@ __global__ __launch_bounds__(NT) void k_csr_narrow(const ResidentArgs a, uint64_
     };
     for (int s = 0; s + 1 < a.K; ++s) step(s, std::false_type{});
     step(a.K - 1, std::true_type{});
+    __syncthreads();   // the last words are read
+    if (t == 0) ring_done(rings + 2 * run, P, tag0, a.K);
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
         const int r = t + q * NT;
@@ -263,12 +250,12 @@ hipError_t with_narrow(int rows, int D, int W, F &&f) {
 // threads (at most the padded rows of the state)
 int narrow_rows(int N) { return N <= 512 ? 512 : (N + 1023) / 1024 * 1024; }
 
-hipError_t launch_csr_narrow(const ResidentArgs &a, int D, int W, uint64_t *words, hipStream_t st) {
+hipError_t launch_csr_narrow(const ResidentArgs &a, int D, int W, uint64_t *words, uint32_t *rings, hipStream_t st) {
     const int rows = narrow_rows(a.N);
     if ((W != 2 && W != 4) || a.R % W || 8 % W || a.nwg < 1 || a.nwg * W % a.R || rows > a.nr || a.N > rows || a.K < 1)
         return hipErrorInvalidValue;
     return with_narrow(rows, D, W, [&](auto kern, int threads) -> hipError_t {
-        hipLaunchKernelGGL(kern, dim3(a.nwg), dim3(threads), 0, st, a, words);
+        hipLaunchKernelGGL(kern, dim3(a.nwg), dim3(threads), 0, st, a, words, rings);
         return hipGetLastError();
     });
 }

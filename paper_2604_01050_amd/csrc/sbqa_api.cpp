@@ -624,6 +624,7 @@ static size_t state_elems(const sbqa_ctx *c) {
 // Build operand f(X) of the current step from the current state.
 sbqa_status rebuild_operand(sbqa_ctx *c) {
     const float d = delta_at(&c->s, c->step);
+    c->g_stale = false;
     if (c->facts.path == PATH_CSR) {
         // elementwise over the whole buffer: column-block order has C == Cs
         // and zero padded rows, whose operand is 0
@@ -787,6 +788,7 @@ sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, con
             HIP_TRY(hipMemcpyAsync(c->rh, rhv.data(), sizeof(double) * rhv.size(), hipMemcpyHostToDevice, c->stream));
             if (c->res_W < resident_cols()) {
                 HIP_TRY(dalloc(c, &c->words, (size_t)2 * c->res_nwg * 2 * narrow_rows(N)));
+                HIP_TRY(dalloc(c, &c->rings, (size_t)2 * runs));
             } else {
                 HIP_TRY(dalloc(c, &c->xpub, (size_t)2 * c->res_nwg * 2 * NR));
                 HIP_TRY(dalloc(c, &c->flags, (size_t)c->res_nwg));
@@ -868,6 +870,14 @@ sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, con
         HIP_TRY(hipStreamSynchronize(c->stream));   // tmp is freed at return
     }
     HIP_TRY(launch_convert_j(path, j64, Np, nkc, jd, jlo, c->stream));
+    if (c->mid.NT) {
+        HIP_TRY(dalloc(c, &c->Jmid, (size_t)((N + 15) / 16) * c->mid_ns * 64));
+        HIP_TRY(launch_mid_bits(j64, N, Np, c->mid_ns, c->Jmid, c->stream));
+        if (c->mid.G > 1) {
+            HIP_TRY(dalloc(c, &c->words, (size_t)2 * c->mid_groups * c->mid.MB * ((N + 127) / 128) * 256));
+            HIP_TRY(dalloc(c, &c->rings, (size_t)2 * c->mid_groups));
+        }
+    }
     HIP_TRY(hipStreamSynchronize(c->stream));   // the caller may free J on return
     return SBQA_OK;
 }
@@ -1053,6 +1063,53 @@ static bool small_plan(sbqa_ctx *c, std::string *why) {
     if ((int64_t)c->R * c->N > SMALL_MAX_ELEMS) { *why = "R*N is above the small dense loop's limit"; return false; }
     if (small_lds_bytes(c->N, c->R) > 160 * 1024) { *why = "the run state does not fit in LDS"; return false; }
     return true;
+}
+
+// The many-step loop of dense +-1 instances (kernels_mid.hip), taken with
+// LOOP_AUTO where no small loop fits: groups of 16 or 32 replica columns made
+// of whole runs, G workgroups per group. Every path but BF16X3 gives the same
+// bits as the loop (exact integer sums). Leaves c->mid.NT 0 when unfit.
+static void mid_plan(sbqa_ctx *c) {
+    c->mid = MidPlan{};
+    if (!c->facts.pm1 || c->facts.jbits || c->facts.path == PATH_BF16X3 || c->s.fmode == SBQA_F_BALLISTIC) return;
+    if (c->N > MID_MAX_N || c->R > 32) return;
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) return;
+    MidPlan p;
+    p.MB = c->R > 16 ? 2 : 1;
+    p.rot = c->R == 16 * p.MB;
+    const int cols = 16 * p.MB / c->R * c->R, groups = (c->L.C + cols - 1) / cols;
+    const int nrb = (c->N + 15) / 16;
+    const int ns = (c->N + 511) / 512;
+    p.NS = ns <= 2 ? ns : 4;
+    // Fewest row blocks per workgroup first, so that a step is short, while
+    // the workgroups of four launches still fit on the device together (see
+    // resident_plan); one workgroup per group needs nobody else's. us per
+    // step, one launch per step / this loop, at C = 128: N = 300 6.5 / 1.7, N
+    // = 601 7.2 / 1.9, N = 1024 7.2 / 2.2, N = 2048 8.6 / 3.0; C = 1600, N =
+    // 1000 11.1 / 6.1 (four row blocks per wave, one workgroup per group).
+    // Above MID_MAX_N the exchanged operand and the bits of J (registers)
+    // grow past what a step saves.
+    struct Shape { int NT, RBW; };
+    const Shape shapes[] = {{512, 1}, {1024, 1}, {1024, 2}, {1024, 4}};
+    auto fits = [&](const Shape &sh, bool alone) {
+        const int per = sh.NT / 64 * sh.RBW;
+        p.NT = sh.NT;
+        p.RBW = sh.RBW;
+        p.G = (nrb + per - 1) / per;
+        if ((p.G == 1) != alone) return false;
+        int nb = 0;
+        if (mid_max_blocks(p, &nb) != hipSuccess || nb < 1) return false;
+        return alone || (int64_t)groups * p.G * 4 <= (int64_t)cus * nb;
+    };
+    bool ok = fits({1024, 1}, true);                       // up to 256 spins
+    for (int q = 0; q < 3 && !ok; ++q) ok = fits(shapes[q], false);
+    for (int q = 2; q < 4 && !ok; ++q) ok = fits(shapes[q], true);
+    if (!ok) return;
+    c->mid = p;
+    c->mid_cols = cols;
+    c->mid_groups = groups;
+    c->mid_ns = ns;
 }
 
 // ---------------------------------------------------------------------------
@@ -1246,6 +1303,7 @@ sbqa_status ctx_create(const sbqa_coupling *J, const double *h, int32_t N, int32
             return fail(SBQA_EINVAL, "instance does not fit a resident loop: %s",
                         allow_resident ? why.c_str() : "contexts of the serving loop step one launch at a time");
         }
+        if (facts.path != PATH_CSR && !c->resident && allow_resident && s->loop_kernel == SBQA_LOOP_AUTO) mid_plan(c);
     }
     if (facts.path != PATH_CSR)
         set_tile(&c->L, s->dense_tile ? s->dense_tile / 64 : tune_dense_mbw(facts.path, c->L.C, c->L.Np, c->stream));
@@ -1280,8 +1338,7 @@ sbqa_status ctx_create(const sbqa_coupling *J, const double *h, int32_t N, int32
     return SBQA_OK;
 }
 
-// K steps of the small dense loop in one launch (one workgroup per run);
-// afterwards the fragment-tiled operand is rebuilt from the new state.
+// K steps of the small dense loop in one launch (one workgroup per run).
 static sbqa_status ctx_step_small(sbqa_ctx *c, uint32_t K) {
     SmallArgs a;
     a.N = c->N;
@@ -1305,13 +1362,50 @@ static sbqa_status ctx_step_small(sbqa_ctx *c, uint32_t K) {
     a.kD = k.kD;
     HIP_TRY(launch_dense_small(a, c->runs, c->stream));
     c->step += K;
-    return rebuild_operand(c);
+    c->g_stale = true;
+    return SBQA_OK;
+}
+
+// K steps of the many-step loop of a dense +-1 instance in one launch.
+static sbqa_status ctx_step_mid(sbqa_ctx *c, uint32_t K) {
+    MidArgs a;
+    a.N = c->N;
+    a.Np = c->L.Np;
+    a.R = c->R;
+    a.C = c->L.C;
+    a.S = (int)c->s.steps;
+    a.n0 = (int)c->step;
+    a.K = (int)K;
+    a.fmode = c->s.fmode;
+    a.G = c->mid.G;
+    a.groups = c->mid_groups;
+    a.cols = c->mid_cols;
+    a.ns = c->mid_ns;
+    a.J = c->Jmid;
+    a.h = c->h32;
+    a.x = c->x[c->cur];
+    a.y = c->y;
+    a.jp = c->jp;
+    a.coefA = c->coefA;
+    a.delta = c->delta_tab;
+    const StepCoef k = step_coef(&c->s, c->c0, c->R, c->step);
+    a.kB = k.kB;
+    a.dt = k.dt;
+    a.kD = k.kD;
+    a.words = c->words;
+    a.rings = c->rings;
+    a.err = c->err;
+    HIP_TRY(launch_dense_mid(c->mid, a, c->stream));
+    c->step += K;
+    c->g_stale = true;
+    return SBQA_OK;
 }
 
 // K steps of the register-resident loop in one launch. A wait that timed out
 // sets the error word of the readout block, which every synchronising call
 // copies back and reports.
 static sbqa_status ctx_step_resident(sbqa_ctx *c, uint32_t K) {
+    if (c->mid.NT) return ctx_step_mid(c, K);
     if (c->facts.path != PATH_CSR) return ctx_step_small(c, K);
     ResidentArgs a;
     a.N = c->N;
@@ -1341,7 +1435,7 @@ static sbqa_status ctx_step_resident(sbqa_ctx *c, uint32_t K) {
     a.nr = c->res_rows;
     a.sbits = c->sbits;
     if (c->res_W < resident_cols()) {
-        HIP_TRY(launch_csr_narrow(a, c->res_D, c->res_W, c->words, c->stream));
+        HIP_TRY(launch_csr_narrow(a, c->res_D, c->res_W, c->words, c->rings, c->stream));
         c->step += K;
         return SBQA_OK;
     }
@@ -1353,7 +1447,7 @@ static sbqa_status ctx_step_resident(sbqa_ctx *c, uint32_t K) {
 
 sbqa_status ctx_check_async(sbqa_ctx *c) {
     if (c->rhost && *reinterpret_cast<const int *>(c->rhost + (size_t)8 * c->runs))
-        return fail(SBQA_EDEVICE, "resident sparse loop: a ring-neighbour wait timed out; the state is invalid");
+        return fail(SBQA_EDEVICE, "many-step loop: a ring-neighbour wait timed out; the state is invalid");
     return SBQA_OK;
 }
 
@@ -1366,7 +1460,7 @@ sbqa_status ctx_sync(sbqa_ctx *c) {
 sbqa_status ctx_step(sbqa_ctx *c, uint32_t n) {
     if ((uint64_t)c->step + n > c->s.steps)
         return fail(SBQA_ESTATE, "step %u + %u exceeds the schedule of %u steps", c->step, n, c->s.steps);
-    if (c->resident) {
+    if (c->resident || c->mid.NT) {
         uint32_t left = n;
         while (left) {
             uint32_t K = left;
@@ -1600,6 +1694,10 @@ sbqa_status sbqa_fields(sbqa_ctx *c, float *phi) {
     float *sum = nullptr;
     HIP_TRY(hipMalloc(&sum, sizeof(float) * (size_t)C * Np));
     struct G1 { void *p; ~G1() { (void)hipFree(p); } } g1{sum};
+    if (c->g_stale) {
+        const sbqa_status st = rebuild_operand(c);
+        if (st != SBQA_OK) return st;
+    }
     DenseStepArgs a = dense_args(c, c->step, c->cur);
     a.phi = sum;
     HIP_TRY(launch_dense_step(c->facts.path, EPI_FIELDS, c->L.mbw, c->L.Cg, a, c->stream));

@@ -158,6 +158,14 @@ struct sbqa_ctx {
     // small dense loop (kernels_small.hip)
     bool resident = false;
     float *Jsm = nullptr;               // small dense loop: J float32 [N][N]
+    // many-step loop of a dense +-1 instance (kernels_mid.hip), in use when
+    // mid.NT > 0; Jmid its bits of J, words its operand exchange
+    sbqa::MidPlan mid;
+    int mid_cols = 0, mid_groups = 0, mid_ns = 0;
+    uint4 *Jmid = nullptr;
+    // the fragment-tiled operand lags behind the state (the dense many-step
+    // loops do not use it): rebuilt where it is read
+    bool g_stale = false;
     int res_D = 0, res_rows = 0, res_nwg = 0;
     int res_W = 8;                      // columns per workgroup: 8, or 4 or 2 in the narrow loop
     int32_t *colpad = nullptr;          // [rows][D]
@@ -171,7 +179,8 @@ struct sbqa_ctx {
     float *coefA = nullptr;             // [S]
     float *delta_tab = nullptr;         // [S+1]
     float *xpub = nullptr;              // [2][nwg][2][rows] published edge columns
-    uint64_t *words = nullptr;          // narrow loop: the same as tagged words
+    uint64_t *words = nullptr;          // narrow and many-step dense loops: tagged words
+    uint32_t *rings = nullptr;          // and the tags of their rings (ring_tags.h)
     // sign bytes of the state the resident loop left ([nwg][rows], bit k: x
     // of the block's column k is negative), valid while sbits_step == step
     uint8_t *sbits = nullptr;

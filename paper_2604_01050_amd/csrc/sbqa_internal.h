@@ -230,11 +230,12 @@ hipError_t ensure_dyn_lds(const void *fn, size_t lds);
 hipError_t launch_csr_resident(const ResidentArgs &a, int D, hipStream_t st);
 // The same loop with W = 2 or 4 columns per workgroup (kernels_narrow.hip),
 // nwg = C / W workgroups: words holds the tagged ring edges
-// [2][nwg][2][narrow_rows(N)], zero before the context's first launch (xpub,
+// [2][nwg][2][narrow_rows(N)], rings [runs][2] the step tags of the runs'
+// rings (ring_tags.h), both zero before the context's first launch (xpub,
 // flags, epoch_cnt and sbits are not used).
 int narrow_rows(int N);              // rows computed, at most NR
 hipError_t narrow_max_blocks(int D, int W, int N, int *blocks_per_cu);
-hipError_t launch_csr_narrow(const ResidentArgs &a, int D, int W, uint64_t *words, hipStream_t st);
+hipError_t launch_csr_narrow(const ResidentArgs &a, int D, int W, uint64_t *words, uint32_t *rings, hipStream_t st);
 
 // Resident loop for small dense instances (kernels_small.hip): one
 // workgroup per run, K steps per launch, J float32 [N][N] row-major, state
@@ -254,6 +255,37 @@ struct SmallArgs {
 };
 size_t small_lds_bytes(int N, int R);
 hipError_t launch_dense_small(const SmallArgs &a, int runs, hipStream_t st);
+
+// Many-step loop of dense +-1 instances with N <= MID_MAX_N spins and a
+// ternary or sign operand (kernels_mid.hip): groups of up to 16 * MB replica
+// columns (whole runs), G workgroups per group, state [C][Np] replica-major
+// updated in place.
+constexpr int MID_MAX_N = 2048;
+struct MidPlan {
+    int NT = 0, RBW = 0;  // threads; row blocks of 16 spins per wave
+    int NS = 0;           // superchunks of 512 spins the kernel is built for: 1, 2 or 4
+    int MB = 1;           // column blocks of 16
+    int G = 1;            // workgroups per column group, all of a launch co-resident when G > 1
+    bool rot = false;     // R == 16 * MB
+};
+struct MidArgs {
+    int N, Np, R, C, S, n0, K, fmode;
+    int G, groups, cols;  // cols: columns of a group (whole runs)
+    int ns;               // superchunks per row block in J
+    const uint4 *J;       // [ceil(N / 16)][ns][64] bits (launch_mid_bits)
+    const float *h;       // [Np]
+    float *x, *y;         // [C][Np]
+    const float *jp;      // [runs][S]
+    const float *coefA;   // [S]   (a0 - a_n)/R
+    const float *delta;   // [S+1] Delta_n
+    float kB, dt, kD;
+    uint64_t *words;      // G > 1: [2][groups][MB][ceil(N / 128) * 256], zero before the first launch
+    uint32_t *rings;      // G > 1: [groups][2] step tags (ring_tags.h), zero before the first launch
+    int *err;             // [1] set on a wait timeout
+};
+hipError_t launch_mid_bits(const double *J64, int N, int Np, int ns, uint4 *out, hipStream_t st);
+hipError_t mid_max_blocks(const MidPlan &p, int *blocks_per_cu);
+hipError_t launch_dense_mid(const MidPlan &p, const MidArgs &a, hipStream_t st);
 
 // CSR operand from state [N][Cs].
 hipError_t launch_csr_operand(int fmode, int N, int Cs, int C, const float *x, int8_t *g,

@@ -53,3 +53,64 @@ def test_resident_columns_per_workgroup(sb, N, d, R, runs, fmode):
         out.append(got + [*sb.sbqa_get_state(ctx), *sb.sbqa_best(ctx)])
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+# dense +-1 instances that AUTO steps in the many-step loop: every launch shape
+# (row blocks per wave, workgroups per group, one or two column blocks, whole
+# and part rings of 16 and 32, several runs in a group), edges of its tiles
+@pytest.mark.parametrize("N,R,runs,prec,fmode,ee", [
+    (129, 16, 8, "AUTO", 0, 0), (256, 4, 3, "FP8", 1, 7), (257, 16, 2, "FP32", 0, 0), (400, 1, 40, "AUTO", 0, 0),
+    (511, 10, 8, "AUTO", 1, 9), (512, 32, 4, "FP8", 0, 0), (513, 8, 9, "INT8", 0, 0), (601, 16, 8, "AUTO", 0, 11),
+    (640, 20, 3, "FP32", 1, 0), (1000, 32, 4, "AUTO", 0, 0), (1024, 5, 7, "AUTO", 0, 0), (1025, 16, 8, "FP8", 0, 0),
+    (1300, 24, 2, "AUTO", 1, 0), (2047, 16, 8, "AUTO", 0, 0), (2048, 16, 16, "FP8", 0, 0),
+    (300, 16, 200, "AUTO", 0, 0), (480, 16, 300, "AUTO", 0, 0), (1000, 16, 150, "FP8", 0, 0)])
+def test_dense_many_step_loop(sb, N, R, runs, prec, fmode, ee):
+    """The many-step loop equals one launch per step bit for bit: states,
+    fields, energies, best spins and steps, over launches of 1, 2 and 22 steps
+    and after a state overwrite."""
+    J, h = inst.sk_pm1(N, 11), np.round(inst.gaussian_fields(N, 1.0, 12))
+    out, size = [], []
+    for kern in (sb.LOOP_STREAM, sb.LOOP_AUTO):
+        _log("many-step loop N=%d R=%d runs=%d %s kernel %d" % (N, R, runs, prec, kern))
+        ctx = sb.sbqa_create(J=J, h=h, R=R, runs=runs, steps=50, fmode=fmode, loop_kernel=kern, seed=3, energy_every=ee,
+                             precision=getattr(sb, "PREC_" + prec))
+        size.append(sb.sbqa_info(ctx)["device_bytes"])
+        got = []
+        for n in (1, 2, 22):
+            sb.sbqa_step(ctx, n)
+            got += [*sb.sbqa_best(ctx), *sb.sbqa_get_state(ctx)]
+        got.append(sb.sbqa_fields(ctx))
+        sb.sbqa_set_state(ctx, 0.5 * got[-3], got[-2])
+        sb.sbqa_step(ctx, 25)
+        out.append(got + [*sb.sbqa_get_state(ctx), *sb.sbqa_best(ctx), sb.sbqa_best_step(ctx)])
+    assert size[1] > size[0], "AUTO did not take the many-step loop"
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("kind,N,R,runs,K", [("dense", 601, 16, 8, 1), ("dense", 601, 16, 8, 9), ("dense", 200, 8, 2, 4),
+                                             ("sparse", 1000, 16, 8, 1), ("sparse", 3000, 32, 4, 7)])
+def test_captured_steps_replay(sb, kind, N, R, runs, K):
+    """Steps captured into a graph and replayed from new states equal the same
+    steps taken directly (the words that workgroups exchange carry a tag that
+    no earlier replay used)."""
+    import torch
+    kw = dict(J=inst.sk_pm1(N, 21)) if kind == "dense" else dict(csr=_sparse(N, 4, 21)[0])
+    kw.update(R=R, runs=runs, steps=K, seed=4)
+    ctx = sb.sbqa_create(**kw)
+    stream = torch.cuda.Stream()
+    sb.sbqa_set_stream(ctx, stream)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        sb.sbqa_step(ctx, K)
+    for q in range(4):
+        _log("replay %d %s N=%d K=%d" % (q, kind, N, K))
+        X, Y = inst.uniform_state(N, R * runs, 0.3, 30 + q)
+        ref = sb.sbqa_create(**kw)
+        sb.sbqa_set_state(ref, X, Y)
+        sb.sbqa_step(ref, K)
+        sb.sbqa_set_state(ctx, X, Y)
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(sb.sbqa_get_state(ref), sb.sbqa_get_state(ctx)):
+            assert np.array_equal(a, b)
