@@ -366,8 +366,7 @@ hipError_t launch_mid_bits(const double *J64, int N, int Np, int ns, uint4 *out,
 
 hipError_t mid_max_blocks(const MidPlan &p, int *blocks_per_cu) {
     return with_mid(p, [&](auto kern, int threads) -> hipError_t {
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, reinterpret_cast<const void *>(kern), threads,
-                                                            0);
+        return max_blocks_per_cu(reinterpret_cast<const void *>(kern), threads, 0, blocks_per_cu);
     });
 }
 

@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <map>
 #include <mutex>
+#include <tuple>
 #include <utility>
 
 namespace sbqa {
@@ -57,12 +58,27 @@ __global__ void k_init_state(int N, int C, int order, int ld, uint32_t key_lo, u
     y[o] = uniform_sym(r.y, amp);
 }
 
-__global__ void k_state_reorder(int N, int C, int order_in, int ld_in, const float *__restrict__ src,
-                                int order_out, int ld_out, float *__restrict__ dst) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (int64_t)N * C) return;
-    const int i = (int)(e / C), c = (int)(e % C);
-    dst[state_off(order_out, ld_out, i, c)] = src[state_off(order_in, ld_in, i, c)];
+// 64 x 64 tiles through LDS: whichever way the two orders run, loads go along
+// the rows of src and stores along the rows of dst.
+constexpr int RT = 64;
+__global__ __launch_bounds__(256) void k_state_reorder(int N, int C, int order_in, int ld_in,
+                                                       const float *__restrict__ src,
+                                                       const int32_t *__restrict__ row_in, int order_out, int ld_out,
+                                                       float *__restrict__ dst, const int32_t *__restrict__ row_out) {
+    __shared__ float tile[RT][RT + 1];
+    const int cb = (C + RT - 1) / RT;
+    const int i0 = (int)(blockIdx.x / cb) * RT, c0 = (int)(blockIdx.x % cb) * RT;
+    const int t = threadIdx.x & (RT - 1), u = threadIdx.x / RT;
+    const bool in_c = order_in != ORDER_REPLICA_MAJOR, out_c = order_out != ORDER_REPLICA_MAJOR;   // columns innermost
+    for (int v = u; v < RT; v += 256 / RT) {
+        const int i = i0 + (in_c ? v : t), c = c0 + (in_c ? t : v);
+        if (i < N && c < C) tile[i - i0][c - c0] = src[state_off(order_in, ld_in, row_in ? row_in[i] : i, c)];
+    }
+    __syncthreads();
+    for (int v = u; v < RT; v += 256 / RT) {
+        const int i = i0 + (out_c ? v : t), c = c0 + (out_c ? t : v);
+        if (i < N && c < C) dst[state_off(order_out, ld_out, row_out ? row_out[i] : i, c)] = tile[i - i0][c - c0];
+    }
 }
 
 __global__ void k_readout_f64(int N, int Np, int C, int ld, int spin_major, const float *__restrict__ x,
@@ -642,12 +658,13 @@ hipError_t launch_init_state(int N, int C, int order, int ld, uint64_t seed, dou
     return hipGetLastError();
 }
 
-hipError_t launch_state_reorder(int N, int C, int order_in, int ld_in, const float *src, int order_out, int ld_out,
-                                float *dst, hipStream_t st) {
-    const int64_t n = (int64_t)N * C;
-    if (n == 0) return hipSuccess;
-    dim3 grid((unsigned)((n + 255) / 256)), block(256);
-    hipLaunchKernelGGL(k_state_reorder, grid, block, 0, st, N, C, order_in, ld_in, src, order_out, ld_out, dst);
+hipError_t launch_state_reorder(int N, int C, int order_in, int ld_in, const float *src, const int32_t *row_in,
+                                int order_out, int ld_out, float *dst, const int32_t *row_out, hipStream_t st) {
+    if (N <= 0 || C <= 0) return hipSuccess;
+    const int64_t blocks = (int64_t)((N + RT - 1) / RT) * ((C + RT - 1) / RT);
+    if (blocks >= ((int64_t)1 << 24)) return hipErrorInvalidValue;   // 2^32 threads
+    hipLaunchKernelGGL(k_state_reorder, dim3((unsigned)blocks), dim3(256), 0, st, N, C, order_in, ld_in, src, row_in,
+                       order_out, ld_out, dst, row_out);
     return hipGetLastError();
 }
 
@@ -698,6 +715,24 @@ hipError_t ensure_dyn_lds(const void *fn, size_t lds) {
     e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e == hipSuccess) cur = lds;
     return e;
+}
+
+hipError_t max_blocks_per_cu(const void *fn, int threads, size_t lds, int *blocks) {
+    static std::mutex mu;
+    static std::map<std::tuple<const void *, int, int, size_t>, int> known;   // (kernel, device, threads, lds)
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lk(mu);
+    const auto key = std::make_tuple(fn, dev, threads, lds);
+    auto it = known.find(key);
+    if (it == known.end()) {
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, fn, threads, lds);
+        if (e == hipSuccess) known[key] = *blocks;
+        return e;
+    }
+    *blocks = it->second;
+    return hipSuccess;
 }
 
 // rows of a row block in the coupling copy: rpb rounded up to the kernel's

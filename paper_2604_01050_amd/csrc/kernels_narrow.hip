@@ -262,8 +262,7 @@ hipError_t launch_csr_narrow(const ResidentArgs &a, int D, int W, uint64_t *word
 
 hipError_t narrow_max_blocks(int D, int W, int N, int *blocks_per_cu) {
     return with_narrow(narrow_rows(N), D, W, [&](auto kern, int threads) -> hipError_t {
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, reinterpret_cast<const void *>(kern), threads,
-                                                            0);
+        return max_blocks_per_cu(reinterpret_cast<const void *>(kern), threads, 0, blocks_per_cu);
     });
 }
 

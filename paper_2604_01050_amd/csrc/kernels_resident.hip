@@ -394,7 +394,7 @@ hipError_t resident_max_blocks(int D, int N, int *blocks_per_cu) {
         const void *fn = reinterpret_cast<const void *>(kern);
         hipError_t e = ensure_dyn_lds(fn, lds);
         if (e != hipSuccess) return e;
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, fn, threads, lds);
+        return max_blocks_per_cu(fn, threads, lds, blocks_per_cu);
     });
 }
 

@@ -1,0 +1,101 @@
+// Cached device and pinned host blocks (pool.h).
+#include "pool.h"
+
+#include <list>
+#include <map>
+#include <mutex>
+#include <utility>
+#include <vector>
+
+namespace sbqa {
+namespace {
+
+struct Cache {
+    std::list<Block> blocks;   // oldest first
+    size_t bytes = 0;
+};
+
+std::mutex g_pool_mu;
+// never destroyed: the HIP runtime may be gone when static objects are
+std::map<std::pair<int, bool>, Cache> &caches() {
+    static auto *m = new std::map<std::pair<int, bool>, Cache>();
+    return *m;
+}
+
+// Size classes: 64 KiB steps up to 512 KiB, then eighths of a power of two.
+size_t size_class(size_t bytes) {
+    size_t step = (size_t)64 << 10;
+    while (bytes > 8 * step) step *= 2;
+    return bytes == 0 ? step : (bytes + step - 1) / step * step;
+}
+
+hipError_t raw_get(bool host, size_t bytes, void **p) {
+    return host ? hipHostMalloc(p, bytes, hipHostMallocCoherent) : hipMalloc(p, bytes);
+}
+
+void raw_free(bool host, const std::vector<Block> &bs) {
+    for (const Block &b : bs) {
+        if (host) (void)hipHostFree(b.p);
+        else (void)hipFree(b.p);
+    }
+}
+
+}  // namespace
+
+hipError_t pool_get(int device, bool host, size_t bytes, Block *b) {
+    const size_t want = size_class(bytes);
+    {
+        std::lock_guard<std::mutex> lk(g_pool_mu);
+        Cache &c = caches()[{device, host}];
+        for (auto it = c.blocks.begin(); it != c.blocks.end(); ++it)
+            if (it->bytes == want) {
+                *b = *it;
+                c.bytes -= want;
+                c.blocks.erase(it);
+                return hipSuccess;
+            }
+    }
+    void *p = nullptr;
+    hipError_t e = raw_get(host, want, &p);
+    if (e != hipSuccess) {
+        // out of memory: give everything cached back and try once more
+        std::vector<Block> all;
+        {
+            std::lock_guard<std::mutex> lk(g_pool_mu);
+            Cache &c = caches()[{device, host}];
+            all.assign(c.blocks.begin(), c.blocks.end());
+            c.blocks.clear();
+            c.bytes = 0;
+        }
+        if (all.empty()) return e;
+        (void)hipGetLastError();
+        raw_free(host, all);
+        e = raw_get(host, want, &p);
+        if (e != hipSuccess) return e;
+    }
+    b->p = p;
+    b->bytes = want;
+    return hipSuccess;
+}
+
+void pool_put(int device, bool host, Block b) {
+    if (!b.p) return;
+    const size_t limit = host ? POOL_HOST_BYTES : POOL_DEVICE_BYTES;
+    std::vector<Block> out;
+    if (b.bytes > limit / 2) {
+        out.push_back(b);
+    } else {
+        std::lock_guard<std::mutex> lk(g_pool_mu);
+        Cache &c = caches()[{device, host}];
+        c.blocks.push_back(b);
+        c.bytes += b.bytes;
+        while (c.bytes > limit) {
+            out.push_back(c.blocks.front());
+            c.bytes -= c.blocks.front().bytes;
+            c.blocks.pop_front();
+        }
+    }
+    raw_free(host, out);
+}
+
+}  // namespace sbqa

@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstring>
 #include <cstdlib>
+#include <limits>
 #include <map>
 #include <mutex>
 #include <new>
@@ -72,6 +73,86 @@ struct DenseScan {
     double ss = 0.0, maxabs = 0.0;
 };
 
+// f(0), ..., f(nb - 1), on several threads when the work (matrix elements)
+// pays for starting them.
+template <class F>
+static void over_blocks(int64_t nb, int64_t work, F &&f) {
+    const int64_t nt = std::min<int64_t>({nb, work / (1 << 17), 16, (int64_t)std::thread::hardware_concurrency()});
+    if (nt <= 1) {
+        for (int64_t b = 0; b < nb; ++b) f(b);
+        return;
+    }
+    std::atomic<int64_t> next{0};
+    auto run = [&] {
+        for (int64_t b; (b = next.fetch_add(1)) < nb;) f(b);
+    };
+    std::vector<std::thread> pool;
+    for (int64_t t = 1; t < nt; ++t) pool.emplace_back(run);
+    run();
+    for (std::thread &t : pool) t.join();
+}
+
+// Transpose of a 64 x 64 bit matrix, row r in a[r] (bit c: column c): the
+// off-diagonal quadrants swapped at block sizes 32, 16, ..., 1.
+static void transpose64(uint64_t (&a)[64]) {
+    uint64_t m = 0x00000000FFFFFFFFull;
+    for (int w = 32; w; w >>= 1, m ^= m << w)
+        for (int k = 0; k < 64; k = ((k | w) + 1) & ~w) {
+            const uint64_t t = ((a[k] >> w) ^ a[k | w]) & m;
+            a[k] ^= t << w;
+            a[k | w] ^= t;
+        }
+}
+
+// Whether J is +-1 off the diagonal, zero on it and symmetric, from one pass
+// over its bits (80 MB, N = 3158: 1.6 ms on 16 threads, against 12.6 ms for
+// the general scan below, which a J that fails goes through for its message).
+// bits: row-major sign bits, words64 per row, bit j % 64 of word j / 64 set
+// where J_ij < 0.
+static bool scan_pm1(const double *A, int64_t N, std::vector<uint64_t> *bits) {
+    constexpr uint64_t SIGN = (uint64_t)1 << 63, ONE = 0x3FF0000000000000ull;
+    const int64_t words = (N + 63) / 64, nb = words;
+    bits->assign((size_t)(N * words), 0);
+    std::atomic<bool> good{N > 1};
+    auto raw = [](const double *p) {
+        uint64_t u;
+        std::memcpy(&u, p, sizeof u);
+        return u;
+    };
+    over_blocks(nb, N * N, [&](int64_t b) {
+        for (int64_t i = 64 * b; i < std::min(N, 64 * b + 64) && good.load(std::memory_order_relaxed); ++i) {
+            const double *row = A + i * N;
+            uint64_t *out = bits->data() + i * words, bad = raw(row + i) & ~SIGN;   // the diagonal: +-0
+            auto span = [&](int64_t j0, int64_t j1) {   // inside one word
+                uint64_t w = 0;
+                for (int64_t j = j0; j < j1; ++j) {
+                    const uint64_t u = raw(row + j);
+                    bad |= (u & ~SIGN) ^ ONE;
+                    w |= (u >> 63) << (j & 63);
+                }
+                return w;
+            };
+            for (int64_t q = 0; q < words; ++q) {
+                const int64_t j0 = 64 * q, j1 = std::min(N, j0 + 64);
+                out[q] = i >= j0 && i < j1 ? span(j0, i) | span(i + 1, j1) : span(j0, j1);
+            }
+            if (bad) good.store(false, std::memory_order_relaxed);
+        }
+    });
+    if (!good.load()) return false;
+    over_blocks(nb, N * N / 16, [&](int64_t b) {
+        for (int64_t q = b; q < nb && good.load(std::memory_order_relaxed); ++q) {
+            uint64_t t[64];
+            for (int k = 0; k < 64; ++k) t[k] = 64 * q + k < N ? (*bits)[(size_t)((64 * q + k) * words + b)] : 0;
+            transpose64(t);
+            uint64_t diff = 0;
+            for (int64_t k = 0; k < 64 && 64 * b + k < N; ++k) diff |= t[k] ^ (*bits)[(size_t)((64 * b + k) * words + q)];
+            if (diff) good.store(false, std::memory_order_relaxed);
+        }
+    });
+    return good.load();
+}
+
 static DenseScan scan_dense(const double *A, int64_t N) {
     constexpr int64_t TB = 64;
     const int64_t nb = (N + TB - 1) / TB;
@@ -88,13 +169,16 @@ static DenseScan scan_dense(const double *A, int64_t N) {
                     if (!r.bad) { r.bad = 2; r.i = i; r.j = j; }
                     continue;
                 }
-                if (v != std::floor(v) || std::fabs(v) > 2147483647.0) r.integral = false;
-                if (!(v == 0.0 || v == 1.0 || v == -1.0)) r.ternary = false;
-                if (j != i && !(v == 1.0 || v == -1.0)) r.pm1 = false;
+                if (r.integral) {   // (a real J leaves these at its first couplings)
+                    if (!(std::fabs(v) <= 2147483647.0) || (double)(int32_t)v != v) r.integral = false;
+                    if (!(v == 0.0 || v == 1.0 || v == -1.0)) r.ternary = false;
+                    if (j != i && !(v == 1.0 || v == -1.0)) r.pm1 = false;
+                }
                 r.maxabs = std::max(r.maxabs, std::fabs(v));
                 srow += v * v;
             }
             r.ss += srow;
+            if (!r.integral) r.ternary = r.pm1 = false;
         }
         for (int64_t bj = bi; bj < nb; ++bj) {
             const int64_t j0 = bj * TB, j1 = std::min(N, j0 + TB);
@@ -105,18 +189,7 @@ static DenseScan scan_dense(const double *A, int64_t N) {
                     }
         }
     };
-    const int nt = (int)std::min<int64_t>(nb, std::max(1u, std::min(16u, std::thread::hardware_concurrency())));
-    if (nt <= 1 || N < 512) {
-        for (int64_t bi = 0; bi < nb; ++bi) scan_block(bi);
-    } else {
-        std::vector<std::thread> pool;
-        std::atomic<int64_t> next{0};
-        for (int t = 0; t < nt; ++t)
-            pool.emplace_back([&] {
-                for (int64_t bi; (bi = next.fetch_add(1)) < nb;) scan_block(bi);
-            });
-        for (std::thread &t : pool) t.join();
-    }
+    over_blocks(nb, N * N, scan_block);
     DenseScan out;
     for (const DenseScan &r : part) {
         if (r.bad && !out.bad) { out.bad = r.bad; out.i = r.i; out.j = r.j; }
@@ -130,7 +203,7 @@ static DenseScan scan_dense(const double *A, int64_t N) {
 }
 
 sbqa_status validate_instance(const sbqa_coupling *J, const double *h, int32_t N, int32_t R, int32_t runs,
-                              const sbqa_schedule *s, InstanceFacts *facts) {
+                              const sbqa_schedule *s, InstanceFacts *facts, std::vector<uint32_t> *sign_bits) {
     if (!J || !s) return fail(SBQA_EINVAL, "J and schedule must be non-NULL");
     if (N < 1 || R < 1 || runs < 1) return fail(SBQA_EINVAL, "N, R and runs must be >= 1 (got %d, %d, %d)", N, R, runs);
     if ((int64_t)R * runs > (1 << 24)) return fail(SBQA_EINVAL, "runs*R too large");
@@ -184,7 +257,21 @@ sbqa_status validate_instance(const sbqa_coupling *J, const double *h, int32_t N
     };
     if (dense) {
         if ((int64_t)N * N > (int64_t)1 << 32) return fail(SBQA_EINVAL, "dense N too large");
-        const DenseScan d = scan_dense(J->dense, N);
+        DenseScan d;
+        std::vector<uint64_t> bits;
+        if (scan_pm1(J->dense, N, &bits)) {
+            d.maxabs = 1.0;
+            d.ss = (double)N * (double)(N - 1);
+            if (sign_bits) {   // 32-bit words, ceil(N / 32) per row
+                const int64_t w32 = (N + 31) / 32, w64 = (N + 63) / 64;
+                sign_bits->resize((size_t)(N * w32));
+                for (int64_t i = 0; i < N; ++i)
+                    for (int64_t q = 0; q < w32; ++q)
+                        (*sign_bits)[(size_t)(i * w32 + q)] = (uint32_t)(bits[(size_t)(i * w64 + q / 2)] >> (32 * (q & 1)));
+            }
+        } else {
+            d = scan_dense(J->dense, N);
+        }
         if (d.bad) {
             switch (d.bad) {
                 case 1: return fail(SBQA_EINVAL, "J has a non-zero diagonal at %lld", (long long)d.i);
@@ -287,26 +374,6 @@ sbqa_status validate_instance(const sbqa_coupling *J, const double *h, int32_t N
                                                  : PATH_F32;
     }
     return SBQA_OK;
-}
-
-void pack_sign_bits(const double *J, int32_t N, std::vector<uint32_t> *bits) {
-    const int64_t words = (N + 31) / 32;
-    bits->assign((size_t)(N * words), 0u);
-    auto rows = [&](int64_t i0, int64_t i1) {
-        for (int64_t i = i0; i < i1; ++i)
-            for (int64_t j = 0; j < N; ++j)
-                if (J[i * N + j] < 0.0) (*bits)[(size_t)(i * words + j / 32)] |= 1u << (j % 32);
-    };
-    const int nt = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-    if (nt <= 1 || N < 512) {
-        rows(0, N);
-        return;
-    }
-    std::vector<std::thread> pool;
-    const int64_t per = (N + nt - 1) / nt;
-    for (int t = 0; t < nt; ++t)
-        pool.emplace_back(rows, std::min<int64_t>(N, t * per), std::min<int64_t>(N, (t + 1) * per));
-    for (std::thread &t : pool) t.join();
 }
 
 // Geometry and byte count of a context (also used by the server's admission).
@@ -548,17 +615,39 @@ void build_schedule_host(const sbqa_schedule *s, int32_t runs, std::vector<doubl
         alpha[r] = s->alpha ? s->alpha[r] : s->alpha_lo + (s->alpha_hi - s->alpha_lo) * u2;
     }
     jp.assign((size_t)runs * S, 0.0f);
-    for (int r = 0; r < runs; ++r)
-        for (uint32_t n = 0; n < S; ++n) {
-            const double sn = (double)n / (double)S;   // t/T at the start of step n
-            double v;
-            if (s->jp_kind == SBQA_JP_LINEAR) v = s->jp_start + (s->jp_end - s->jp_start) * sn;
-            else if (s->jp_kind == SBQA_JP_PAPER) {
-                const double gx = s->gamma0_over_R * (std::pow(1.0 - sn, alpha[r]) + 1e-5);  // Eq. 5
-                v = -std::log(std::tanh(beta[r] * gx)) / (2.0 * beta[r]);
-            } else v = s->jp_table[(size_t)r * S + n];
-            jp[(size_t)r * S + n] = (float)v;
+    auto fill = [&](int64_t q0, int64_t q1) {   // entries [q0, q1), run-major
+        while (q0 < q1) {
+            const int r = (int)(q0 / S);
+            const uint32_t n0 = (uint32_t)(q0 - (int64_t)r * S), n1 = (uint32_t)std::min<int64_t>(S, n0 + (q1 - q0));
+            float *out = jp.data() + (size_t)r * S;
+            for (uint32_t n = n0; n < n1; ++n) {
+                const double sn = (double)n / (double)S;   // t/T at the start of step n
+                double v;
+                if (s->jp_kind == SBQA_JP_LINEAR) v = s->jp_start + (s->jp_end - s->jp_start) * sn;
+                else if (s->jp_kind == SBQA_JP_PAPER) {
+                    const double gx = s->gamma0_over_R * (std::pow(1.0 - sn, alpha[r]) + 1e-5);  // Eq. 5
+                    v = -std::log(std::tanh(beta[r] * gx)) / (2.0 * beta[r]);
+                } else v = s->jp_table[(size_t)r * S + n];
+                out[n] = (float)v;
+            }
+            q0 += n1 - n0;
         }
+    };
+    // Eq. 5 takes about 0.1 us an entry (0.8 ms for 8 runs of 1000 steps, more
+    // than the rest of a small context's creation): in parallel from 2048
+    // entries on, where it saves more than the threads cost to start (20 us each)
+    const int64_t total = (int64_t)runs * S;
+    const int nt = s->jp_kind != SBQA_JP_PAPER || total < 2048
+                       ? 1
+                       : (int)std::min<int64_t>({8, total / 1024, (int64_t)std::max(1u, std::thread::hardware_concurrency())});
+    if (nt <= 1) {
+        fill(0, total);
+        return;
+    }
+    std::vector<std::thread> pool;
+    for (int t = 1; t < nt; ++t) pool.emplace_back(fill, total * t / nt, total * (t + 1) / nt);
+    fill(0, total / nt);
+    for (std::thread &t : pool) t.join();
 }
 
 StepCoef step_coef(const sbqa_schedule *s, double c0, int R, uint32_t n) {
@@ -585,41 +674,113 @@ using namespace sbqa;
 // =========================================================================== //
 
 sbqa_ctx::~sbqa_ctx() {
-    for (void *p : allocs) (void)hipFree(p);
-    if (rhost) (void)hipHostFree(rhost);
+    // the pool hands the blocks to other contexts, on other streams: the work
+    // on them ends first (blocks of a stream that reports an error are left
+    // to the runtime, which waits for the device)
+    const bool done = idle || !stream || hipStreamSynchronize(stream) == hipSuccess;
+    auto back = [&](bool host, Block b) {
+        if (done) pool_put(device, host, b);
+        else if (host) (void)hipHostFree(b.p);
+        else (void)hipFree(b.p);
+    };
+    for (const Block &b : blocks) back(false, b);
+    for (const Chunk &k : chunks) {
+        back(false, k.dev);
+        back(true, k.host);
+    }
+    if (rhost_block.p) back(true, rhost_block);
 }
+
+// Zeroed device buffer of the context. During creation, buffers up to
+// SMALL_BYTES are packed into chunks of CHUNK_BYTES and become valid with the
+// next flush.
+constexpr size_t SMALL_BYTES = (size_t)256 << 10, CHUNK_BYTES = (size_t)1 << 20;
+// Largest copy that a call takes through pinned memory.
+constexpr size_t STAGE_BYTES = (size_t)8 << 20;
 
 template <class T>
 static hipError_t dalloc(sbqa_ctx *c, T **p, size_t n) {
-    void *q = nullptr;
-    const size_t bytes = std::max<size_t>(n * sizeof(T), 256);
-    hipError_t e = hipMalloc(&q, bytes);
-    if (e != hipSuccess) return e;
-    c->allocs.push_back(q);
+    const size_t bytes = std::max<size_t>(n * sizeof(T), 256), room = (bytes + 255) / 256 * 256;
+    hipError_t e;
+    if (c->creating && room <= SMALL_BYTES) {
+        if (c->chunks.empty() || c->chunks.back().used + room > CHUNK_BYTES) {
+            sbqa_ctx::Chunk k;
+            if ((e = pool_get(c->device, false, CHUNK_BYTES, &k.dev)) != hipSuccess) return e;
+            if ((e = pool_get(c->device, true, CHUNK_BYTES, &k.host)) != hipSuccess) {
+                pool_put(c->device, false, k.dev);
+                return e;
+            }
+            c->chunks.push_back(k);
+        }
+        sbqa_ctx::Chunk &k = c->chunks.back();
+        std::memset(static_cast<uint8_t *>(k.host.p) + k.used, 0, room);
+        *p = reinterpret_cast<T *>(static_cast<uint8_t *>(k.dev.p) + k.used);
+        k.used += room;
+        c->bytes += bytes;
+        return hipSuccess;
+    }
+    Block b;
+    if ((e = pool_get(c->device, false, bytes, &b)) != hipSuccess) return e;
+    c->blocks.push_back(b);
     c->bytes += bytes;
-    e = hipMemsetAsync(q, 0, bytes, c->stream);
-    *p = static_cast<T *>(q);
-    return e;
+    *p = static_cast<T *>(b.p);
+    return hipMemsetAsync(b.p, 0, bytes, c->stream);
+}
+
+// Host values into a device buffer of the context: through the mirror when
+// the buffer lies in the part of a chunk that is still to be sent, else
+// straight from src, which has to live until settle().
+static hipError_t upload(sbqa_ctx *c, void *dst, const void *src, size_t bytes) {
+    if (bytes == 0) return hipSuccess;
+    const uint8_t *d = static_cast<uint8_t *>(dst);
+    for (sbqa_ctx::Chunk &k : c->chunks) {
+        uint8_t *base = static_cast<uint8_t *>(k.dev.p);
+        if (d >= base + k.sent && d + bytes <= base + k.used) {
+            std::memcpy(static_cast<uint8_t *>(k.host.p) + (d - base), src, bytes);
+            return hipSuccess;
+        }
+    }
+    c->direct = true;
+    return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->stream);
+}
+
+// Sends what the mirrors have collected (before a kernel reads or writes the
+// small buffers; the mirrors live as long as the context).
+static hipError_t flush(sbqa_ctx *c) {
+    for (sbqa_ctx::Chunk &k : c->chunks) {
+        if (k.sent == k.used) continue;
+        const hipError_t e = hipMemcpyAsync(static_cast<uint8_t *>(k.dev.p) + k.sent,
+                                            static_cast<uint8_t *>(k.host.p) + k.sent, k.used - k.sent,
+                                            hipMemcpyHostToDevice, c->stream);
+        if (e != hipSuccess) return e;
+        k.sent = k.used;
+    }
+    return hipSuccess;
+}
+
+// Waits for copies straight from host memory (which may be freed afterwards).
+static hipError_t settle(sbqa_ctx *c) {
+    if (!c->direct) return hipSuccess;
+    c->direct = false;
+    return hipStreamSynchronize(c->stream);
 }
 
 static sbqa_status check_device(int *dev) {
     HIP_TRY(hipGetDevice(dev));
+    static std::mutex mu;
+    static std::set<int> good;   // devices found to be gfx950
+    std::lock_guard<std::mutex> lk(mu);
+    if (good.count(*dev)) return SBQA_OK;
     hipDeviceProp_t prop;
     HIP_TRY(hipGetDeviceProperties(&prop, *dev));
     if (std::strncmp(prop.gcnArchName, "gfx950", 6) != 0)
         return fail(SBQA_EDEVICE, "device %d is %s; this library is built for gfx950 (MI355X) only", *dev,
                     prop.gcnArchName);
+    good.insert(*dev);
     return SBQA_OK;
 }
 
 namespace sbqa {
-
-// Elements of one state buffer (x or y) including padding.
-static size_t state_elems(const sbqa_ctx *c) {
-    if (c->order == ORDER_REPLICA_MAJOR) return (size_t)c->L.C * c->ld;
-    if (c->order == ORDER_COLBLOCK8) return (size_t)c->L.C * c->ld;
-    return (size_t)c->N * c->ld;
-}
 
 // Build operand f(X) of the current step from the current state.
 sbqa_status rebuild_operand(sbqa_ctx *c) {
@@ -645,7 +806,7 @@ sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, con
     const int runs = c->runs;
     const uint32_t S = c->s.steps;
     HIP_TRY(dalloc(c, &c->jp, (size_t)runs * S));
-    HIP_TRY(hipMemcpyAsync(c->jp, c->jp_host.data(), sizeof(float) * runs * S, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(upload(c, c->jp, c->jp_host.data(), sizeof(float) * runs * S));
     {
         // per-step pump and threshold tables (a_n term and Delta_n of Eq. 8),
         // read on the device by the resident loops and the grouped steps
@@ -654,16 +815,17 @@ sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, con
         for (uint32_t n = 0; n <= S; ++n) dtab[n] = delta_at(&c->s, n);
         HIP_TRY(dalloc(c, &c->coefA, ca.size()));
         HIP_TRY(dalloc(c, &c->delta_tab, dtab.size()));
-        HIP_TRY(hipMemcpyAsync(c->coefA, ca.data(), sizeof(float) * ca.size(), hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(hipMemcpyAsync(c->delta_tab, dtab.data(), sizeof(float) * dtab.size(), hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(hipStreamSynchronize(c->stream));   // host staging buffers die here
+        HIP_TRY(upload(c, c->coefA, ca.data(), sizeof(float) * ca.size()));
+        HIP_TRY(upload(c, c->delta_tab, dtab.data(), sizeof(float) * dtab.size()));
+        HIP_TRY(settle(c));   // host staging buffers die here
     }
     HIP_TRY(dalloc(c, &c->E, (size_t)std::max(C, Cp)));
     HIP_TRY(dalloc(c, &c->bestStep, (size_t)runs));
     if (N > BEST_SPLIT_N) HIP_TRY(dalloc(c, &c->bsel, (size_t)runs));
     c->rbytes = (size_t)8 * runs + 8 + (size_t)runs * N;
     HIP_TRY(dalloc(c, &c->rdev, c->rbytes));
-    HIP_TRY(hipHostMalloc((void **)&c->rhost, c->rbytes, hipHostMallocCoherent));
+    HIP_TRY(pool_get(c->device, true, c->rbytes, &c->rhost_block));
+    c->rhost = static_cast<uint8_t *>(c->rhost_block.p);
     std::memset(c->rhost, 0, c->rbytes);
     {
         void *dp = nullptr;
@@ -684,8 +846,8 @@ sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, con
         }
     HIP_TRY(dalloc(c, &c->h32, (size_t)hrows));
     HIP_TRY(dalloc(c, &c->h64, (size_t)N));
-    HIP_TRY(hipMemcpyAsync(c->h32, h32.data(), sizeof(float) * hrows, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipMemcpyAsync(c->h64, h64.data(), sizeof(double) * N, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(upload(c, c->h32, h32.data(), sizeof(float) * hrows));
+    HIP_TRY(upload(c, c->h64, h64.data(), sizeof(double) * N));
     c->has_h = h != nullptr;
 
     if (path == PATH_CSR) {
@@ -737,19 +899,19 @@ sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, con
             HIP_TRY(dalloc(c, &c->t3ab, ab.size()));
             HIP_TRY(dalloc(c, &c->t3k, k32.size()));
             HIP_TRY(dalloc(c, &c->t3k64, k64.size()));
-            HIP_TRY(hipMemcpyAsync(c->t3ptr, tp.data(), sizeof(int32_t) * tp.size(), hipMemcpyHostToDevice, c->stream));
-            HIP_TRY(hipMemcpyAsync(c->t3ab, ab.data(), sizeof(int32_t) * ab.size(), hipMemcpyHostToDevice, c->stream));
-            HIP_TRY(hipMemcpyAsync(c->t3k, k32.data(), sizeof(float) * k32.size(), hipMemcpyHostToDevice, c->stream));
-            HIP_TRY(hipMemcpyAsync(c->t3k64, k64.data(), sizeof(double) * k64.size(), hipMemcpyHostToDevice, c->stream));
-            HIP_TRY(hipStreamSynchronize(c->stream));   // host staging buffers die here
+            HIP_TRY(upload(c, c->t3ptr, tp.data(), sizeof(int32_t) * tp.size()));
+            HIP_TRY(upload(c, c->t3ab, ab.data(), sizeof(int32_t) * ab.size()));
+            HIP_TRY(upload(c, c->t3k, k32.data(), sizeof(float) * k32.size()));
+            HIP_TRY(upload(c, c->t3k64, k64.data(), sizeof(double) * k64.size()));
+            HIP_TRY(settle(c));   // host staging buffers die here
         }
         if (!c->resident) HIP_TRY(dalloc(c, &c->phi, (size_t)N * Cs));
         std::vector<float> v32((size_t)nnz);
         for (int64_t p = 0; p < nnz; ++p) v32[p] = (float)J->val[p];
-        HIP_TRY(hipMemcpyAsync(c->rp, J->row_ptr, sizeof(int32_t) * (N + 1), hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(hipMemcpyAsync(c->col, J->col, sizeof(int32_t) * nnz, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(hipMemcpyAsync(c->val, v32.data(), sizeof(float) * nnz, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(hipMemcpyAsync(c->val64, J->val, sizeof(double) * nnz, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(upload(c, c->rp, J->row_ptr, sizeof(int32_t) * (N + 1)));
+        HIP_TRY(upload(c, c->col, J->col, sizeof(int32_t) * nnz));
+        HIP_TRY(upload(c, c->val, v32.data(), sizeof(float) * nnz));
+        HIP_TRY(upload(c, c->val64, J->val, sizeof(double) * nnz));
         std::vector<int32_t> cp, rc;
         std::vector<float> vp;
         std::vector<double> rv, rhv;
@@ -783,9 +945,9 @@ sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, con
             HIP_TRY(dalloc(c, &c->rcol, rc.size()));
             HIP_TRY(dalloc(c, &c->rval, rv.size()));
             HIP_TRY(dalloc(c, &c->rh, rhv.size()));
-            HIP_TRY(hipMemcpyAsync(c->rcol, rc.data(), sizeof(int32_t) * rc.size(), hipMemcpyHostToDevice, c->stream));
-            HIP_TRY(hipMemcpyAsync(c->rval, rv.data(), sizeof(double) * rv.size(), hipMemcpyHostToDevice, c->stream));
-            HIP_TRY(hipMemcpyAsync(c->rh, rhv.data(), sizeof(double) * rhv.size(), hipMemcpyHostToDevice, c->stream));
+            HIP_TRY(upload(c, c->rcol, rc.data(), sizeof(int32_t) * rc.size()));
+            HIP_TRY(upload(c, c->rval, rv.data(), sizeof(double) * rv.size()));
+            HIP_TRY(upload(c, c->rh, rhv.data(), sizeof(double) * rhv.size()));
             if (c->res_W < resident_cols()) {
                 HIP_TRY(dalloc(c, &c->words, (size_t)2 * c->res_nwg * 2 * narrow_rows(N)));
                 HIP_TRY(dalloc(c, &c->rings, (size_t)2 * runs));
@@ -796,10 +958,10 @@ sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, con
                 HIP_TRY(dalloc(c, &c->sbits, (size_t)c->res_nwg * NR));
             }
             HIP_TRY(dalloc(c, &c->rd_cnt, (size_t)runs));
-            HIP_TRY(hipMemcpyAsync(c->colpad, cp.data(), sizeof(int32_t) * cp.size(), hipMemcpyHostToDevice, c->stream));
-            HIP_TRY(hipMemcpyAsync(c->valpad, vp.data(), sizeof(float) * vp.size(), hipMemcpyHostToDevice, c->stream));
+            HIP_TRY(upload(c, c->colpad, cp.data(), sizeof(int32_t) * cp.size()));
+            HIP_TRY(upload(c, c->valpad, vp.data(), sizeof(float) * vp.size()));
         }
-        HIP_TRY(hipStreamSynchronize(c->stream));   // host staging buffers die here
+        HIP_TRY(settle(c));   // host staging buffers die here
         return SBQA_OK;
     }
 
@@ -824,8 +986,8 @@ sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, con
         std::vector<float> jsm((size_t)N * N);
         for (size_t q = 0; q < jsm.size(); ++q) jsm[q] = (float)J->dense[q];
         HIP_TRY(dalloc(c, &c->Jsm, jsm.size()));
-        HIP_TRY(hipMemcpyAsync(c->Jsm, jsm.data(), sizeof(float) * jsm.size(), hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(hipStreamSynchronize(c->stream));   // host staging buffers die here
+        HIP_TRY(upload(c, c->Jsm, jsm.data(), sizeof(float) * jsm.size()));
+        HIP_TRY(settle(c));   // host staging buffers die here
     }
 
     if (c->facts.jbits) {
@@ -838,9 +1000,10 @@ sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, con
         HIP_TRY(dalloc(c, &jd, (size_t)dense_j_bytes(path, Np)));
         HIP_TRY(dalloc(c, &sb, (size_t)N * words));
         c->Jd = jd;
-        HIP_TRY(hipMemcpyAsync(sb, jbits, sizeof(uint32_t) * N * words, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(upload(c, sb, jbits, sizeof(uint32_t) * N * words));
+        HIP_TRY(flush(c));
         HIP_TRY(launch_convert_j_bits(path, sb, N, Np, nkc, jd, c->stream));
-        HIP_TRY(hipStreamSynchronize(c->stream));   // the caller may free the bits on return
+        HIP_TRY(settle(c));   // the caller may free the bits on return
         return SBQA_OK;
     }
     // J in the contraction precision (fragment-tiled) and in float64
@@ -859,26 +1022,29 @@ sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, con
     // up in one contiguous copy (a pitched copy from pageable memory is split
     // into one transfer per row); when rows need padding it lands in a
     // temporary buffer first and is spread into the padded rows on the GPU.
+    PoolBlock tmp(c->device, false);
+    struct Wait { sbqa_ctx *c; ~Wait() { (void)settle(c); } } wait{c};   // before tmp goes back, on every path
     if (N == Np) {
-        HIP_TRY(hipMemcpyAsync(j64, A, sizeof(double) * N * N, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(upload(c, j64, A, sizeof(double) * N * N));
     } else {
-        double *tmp = nullptr;
-        HIP_TRY(hipMalloc(&tmp, sizeof(double) * (size_t)N * N));
-        struct Tmp { double *p; ~Tmp() { (void)hipFree(p); } } guard{tmp};
-        HIP_TRY(hipMemcpyAsync(tmp, A, sizeof(double) * N * N, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(launch_pad_rows(tmp, N, Np, j64, c->stream));
-        HIP_TRY(hipStreamSynchronize(c->stream));   // tmp is freed at return
+        HIP_TRY(tmp.get(sizeof(double) * (size_t)N * N));
+        c->direct = true;
+        HIP_TRY(hipMemcpyAsync(tmp.as<double>(), A, sizeof(double) * N * N, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(flush(c));
+        HIP_TRY(launch_pad_rows(tmp.as<double>(), N, Np, j64, c->stream));
     }
+    HIP_TRY(flush(c));
     HIP_TRY(launch_convert_j(path, j64, Np, nkc, jd, jlo, c->stream));
     if (c->mid.NT) {
         HIP_TRY(dalloc(c, &c->Jmid, (size_t)((N + 15) / 16) * c->mid_ns * 64));
+        HIP_TRY(flush(c));
         HIP_TRY(launch_mid_bits(j64, N, Np, c->mid_ns, c->Jmid, c->stream));
         if (c->mid.G > 1) {
             HIP_TRY(dalloc(c, &c->words, (size_t)2 * c->mid_groups * c->mid.MB * ((N + 127) / 128) * 256));
             HIP_TRY(dalloc(c, &c->rings, (size_t)2 * c->mid_groups));
         }
     }
-    HIP_TRY(hipStreamSynchronize(c->stream));   // the caller may free J on return
+    HIP_TRY(settle(c));   // the caller may free J on return
     return SBQA_OK;
 }
 
@@ -1004,10 +1170,12 @@ sbqa_status ctx_evaluate(sbqa_ctx *c, bool reset) {
     return SBQA_OK;
 }
 
+// No best solution yet. The values go up from the pinned readout block, which
+// the host writes nowhere else.
 sbqa_status ctx_reset_best(sbqa_ctx *c) {
-    std::vector<double> inf((size_t)c->runs, INFINITY);
-    HIP_TRY(hipMemcpyAsync(c->bestE, inf.data(), sizeof(double) * c->runs, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    double *inf = reinterpret_cast<double *>(c->rhost);
+    for (int r = 0; r < c->runs; ++r) inf[r] = INFINITY;
+    HIP_TRY(hipMemcpyAsync(c->bestE, inf, sizeof(double) * c->runs, hipMemcpyHostToDevice, c->stream));
     c->last_eval_step = -1;
     return SBQA_OK;
 }
@@ -1322,13 +1490,15 @@ sbqa_status ctx_create(const sbqa_coupling *J, const double *h, int32_t N, int32
         std::vector<int32_t> orig((size_t)N);
         for (int32_t i = 0; i < N; ++i) orig[(size_t)c->pnew[(size_t)i]] = i;
         hipError_t e = dalloc(c, &c->porig, (size_t)N);
-        if (e == hipSuccess) e = hipMemcpyAsync(c->porig, orig.data(), sizeof(int32_t) * N, hipMemcpyHostToDevice, c->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);   // the staging vector dies here
+        if (e == hipSuccess) e = upload(c, c->porig, orig.data(), sizeof(int32_t) * N);
+        if (e == hipSuccess) e = settle(c);   // the staging vector dies here
         if (e != hipSuccess) st = fail(SBQA_EDEVICE, "relabelling: %s", hipGetErrorString(e));
     }
+    c->creating = false;
     if (st == SBQA_OK) {
-        hipError_t e = launch_init_state(N, c->L.C, c->order, c->ld, s->seed, s->init_amp, c->porig, c->x[0], c->y,
-                                         c->stream);
+        hipError_t e = flush(c);
+        if (e == hipSuccess)
+            e = launch_init_state(N, c->L.C, c->order, c->ld, s->seed, s->init_amp, c->porig, c->x[0], c->y, c->stream);
         if (e != hipSuccess) st = fail(SBQA_EDEVICE, "init: %s", hipGetErrorString(e));
     }
     if (st == SBQA_OK) st = rebuild_operand(c);
@@ -1622,34 +1792,54 @@ sbqa_status sbqa_energy(sbqa_ctx *c, const int8_t *spins, int32_t count, double 
     if (count < 0) return fail(SBQA_EINVAL, "count must be >= 0");
     if (count == 0) return SBQA_OK;
     const int N = c->N;
-    for (int64_t q = 0; q < (int64_t)count * N; ++q)
-        if (spins[q] != 1 && spins[q] != -1) return fail(SBQA_EINVAL, "spins must be +-1 (index %lld)", (long long)q);
-    int8_t *ds = nullptr;
-    double *E = nullptr;
-    HIP_TRY(hipMalloc(&ds, (size_t)count * N));
-    hipError_t e = hipMalloc(&E, sizeof(double) * count);
-    if (e != hipSuccess) { (void)hipFree(ds); return fail(SBQA_ENOMEM, "hipMalloc: %s", hipGetErrorString(e)); }
-    struct Guard { void *a, *b, *c2, *d; ~Guard() { (void)hipFree(a); (void)hipFree(b); (void)hipFree(c2); (void)hipFree(d); } } gd{ds, E, nullptr, nullptr};
-    std::vector<int8_t> rows;
-    if (!c->pnew.empty()) {   // the caller's spin order to the internal rows
-        rows.resize((size_t)count * N);
-        for (int32_t m = 0; m < count; ++m)
-            for (int i = 0; i < N; ++i) rows[(size_t)m * N + c->pnew[(size_t)i]] = spins[(size_t)m * N + i];
+    const size_t total = (size_t)count * N;
+    for (size_t q0 = 0; q0 < total; q0 += 4096) {
+        const size_t q1 = std::min(total, q0 + 4096);
+        int bad = 0;
+        for (size_t q = q0; q < q1; ++q) bad |= (spins[q] != 1) & (spins[q] != -1);
+        for (size_t q = q0; bad && q < q1; ++q)
+            if (spins[q] != 1 && spins[q] != -1) return fail(SBQA_EINVAL, "spins must be +-1 (index %lld)", (long long)q);
     }
-    HIP_TRY(hipMemcpyAsync(ds, rows.empty() ? spins : rows.data(), (size_t)count * N, hipMemcpyHostToDevice, c->stream));
-    if (!rows.empty()) HIP_TRY(hipStreamSynchronize(c->stream));   // the staging vector dies at return
-    double *S = nullptr, *P = nullptr;
+    // pooled buffers; every use of them is behind the synchronisations below
+    // or, on a failure, behind the one that Wait makes
+    PoolBlock ds(c->device, false), E(c->device, false), S(c->device, false), P(c->device, false);
+    PoolBlock stage(c->device, true);
+    struct Wait { hipStream_t st; ~Wait() { if (st) (void)hipStreamSynchronize(st); } } wait{c->stream};
+    HIP_TRY(ds.get(total));
+    HIP_TRY(E.get(sizeof(double) * count));
+    // small inputs go up, and the energies come down, through pinned memory
+    // (a copy from pageable memory waits for the runtime's own staging)
+    const size_t espace = sizeof(double) * count;
+    const bool pinned = total <= STAGE_BYTES && espace <= STAGE_BYTES;
+    std::vector<int8_t> rows;
+    int8_t *host = nullptr;
+    if (pinned) {
+        HIP_TRY(stage.get(std::max(total, espace)));
+        host = stage.as<int8_t>();
+    } else if (!c->pnew.empty()) {
+        rows.resize(total);
+        host = rows.data();
+    }
+    if (!c->pnew.empty()) {   // the caller's spin order to the internal rows
+        for (int32_t m = 0; m < count; ++m)
+            for (int i = 0; i < N; ++i) host[(size_t)m * N + c->pnew[(size_t)i]] = spins[(size_t)m * N + i];
+    } else if (pinned) {
+        std::memcpy(host, spins, total);
+    }
+    HIP_TRY(hipMemcpyAsync(ds.as<int8_t>(), host ? host : spins, total, hipMemcpyHostToDevice, c->stream));
+    if (!pinned) HIP_TRY(hipStreamSynchronize(c->stream));
     if (c->facts.path != PATH_CSR) {
         const EnergyGemm g = energy_gemm(c, count);
-        HIP_TRY(hipMalloc(&S, sizeof(double) * g.cp * c->L.Np));
-        gd.c2 = S;
-        HIP_TRY(hipMalloc(&P, sizeof(double) * g.es * g.cp * c->L.Np));
-        gd.d = P;
+        HIP_TRY(S.get(sizeof(double) * g.cp * c->L.Np));
+        HIP_TRY(P.get(sizeof(double) * g.es * g.cp * c->L.Np));
     }
-    sbqa_status st = ctx_energies_dev(c, ds, count, E, S, P);
+    sbqa_status st = ctx_energies_dev(c, ds.as<int8_t>(), count, E.as<double>(), S.as<double>(), P.as<double>());
     if (st != SBQA_OK) return st;
-    HIP_TRY(hipMemcpyAsync(out, E, sizeof(double) * count, hipMemcpyDeviceToHost, c->stream));
+    // (the spins in the stage have been read by then: same stream)
+    HIP_TRY(hipMemcpyAsync(pinned ? stage.as<double>() : out, E.as<double>(), espace, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
+    wait.st = nullptr;
+    if (pinned) std::memcpy(out, stage.as<double>(), espace);
     return SBQA_OK;
 }
 
@@ -1675,7 +1865,7 @@ sbqa_status sbqa_fields(sbqa_ctx *c, float *phi) {
             }
             float *xsm = c->x[1 - c->cur];
             int8_t *gsm = (int8_t *)c->g[1 - c->cur];
-            HIP_TRY(launch_state_reorder(N, C, c->order, c->ld, xs, ORDER_SPIN_MAJOR, Cs, xsm, c->stream));
+            HIP_TRY(launch_state_reorder(N, C, c->order, c->ld, xs, nullptr, ORDER_SPIN_MAJOR, Cs, xsm, nullptr, c->stream));
             if (c->s.fmode != SBQA_F_BALLISTIC)
                 HIP_TRY(launch_csr_operand(c->s.fmode, N, Cs, C, xsm, gsm, delta_at(&c->s, c->step), c->stream));
             xs = xsm;
@@ -1691,9 +1881,10 @@ sbqa_status sbqa_fields(sbqa_ctx *c, float *phi) {
         return SBQA_OK;
     }
     const int Np = c->L.Np;
-    float *sum = nullptr;
-    HIP_TRY(hipMalloc(&sum, sizeof(float) * (size_t)C * Np));
-    struct G1 { void *p; ~G1() { (void)hipFree(p); } } g1{sum};
+    PoolBlock dev(c->device, false);
+    struct Wait { hipStream_t st; ~Wait() { if (st) (void)hipStreamSynchronize(st); } } wait{c->stream};
+    HIP_TRY(dev.get(sizeof(float) * (size_t)C * Np));
+    float *sum = dev.as<float>();
     if (c->g_stale) {
         const sbqa_status st = rebuild_operand(c);
         if (st != SBQA_OK) return st;
@@ -1712,23 +1903,26 @@ sbqa_status sbqa_fields(sbqa_ctx *c, float *phi) {
 sbqa_status sbqa_get_state(sbqa_ctx *c, float *x, float *y) {
     clear_error();
     if (!c) return fail(SBQA_EINVAL, "NULL context");
+    // brought into the caller's order (spin rows of C columns) on the device
     const int N = c->N, C = c->L.C;
-    const size_t tot = state_elems(c);
-    std::vector<float> bx(tot), by(tot);
-    HIP_TRY(hipMemcpyAsync(bx.data(), c->x[c->cur], sizeof(float) * tot, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipMemcpyAsync(by.data(), c->y, sizeof(float) * tot, hipMemcpyDeviceToHost, c->stream));
-    {
-        sbqa_status e = ctx_sync(c);
-        if (e != SBQA_OK) return e;
+    const size_t one = (size_t)N * C, bytes = sizeof(float) * one;
+    PoolBlock dev(c->device, false), stage(c->device, true);
+    struct Wait { hipStream_t st; ~Wait() { if (st) (void)hipStreamSynchronize(st); } } wait{c->stream};
+    const bool pinned = 2 * bytes <= STAGE_BYTES;
+    HIP_TRY(dev.get(2 * bytes));
+    if (pinned) HIP_TRY(stage.get(2 * bytes));
+    for (int q = 0; q < 2; ++q) {
+        float *to = q ? y : x, *d = dev.as<float>() + q * one;
+        if (!to) continue;
+        HIP_TRY(launch_state_reorder(N, C, c->order, c->ld, q ? c->y : c->x[c->cur], nullptr, ORDER_SPIN_MAJOR, C, d,
+                                     c->porig, c->stream));
+        HIP_TRY(hipMemcpyAsync(pinned ? stage.as<float>() + q * one : to, d, bytes, hipMemcpyDeviceToHost, c->stream));
     }
-    for (int i = 0; i < N; ++i) {
-        const int row = c->pnew.empty() ? i : c->pnew[(size_t)i];   // internal row of spin i
-        for (int cc = 0; cc < C; ++cc) {
-            const int64_t o = state_off(c->order, c->ld, row, cc);
-            if (x) x[(size_t)i * C + cc] = bx[(size_t)o];
-            if (y) y[(size_t)i * C + cc] = by[(size_t)o];
-        }
-    }
+    const sbqa_status e = ctx_sync(c);
+    if (e != SBQA_OK) return e;
+    wait.st = nullptr;
+    if (pinned && x) std::memcpy(x, stage.as<float>(), bytes);
+    if (pinned && y) std::memcpy(y, stage.as<float>() + one, bytes);
     return SBQA_OK;
 }
 
@@ -1736,25 +1930,36 @@ sbqa_status sbqa_set_state(sbqa_ctx *c, const float *x, const float *y) {
     clear_error();
     if (!c || !x || !y) return fail(SBQA_EINVAL, "NULL argument");
     const int N = c->N, C = c->L.C;
-    const size_t tot = state_elems(c);
-    for (size_t q = 0; q < (size_t)N * C; ++q)
-        if (!std::isfinite(x[q]) || !std::isfinite(y[q]) || std::fabs(x[q]) > 1.0f)
-            return fail(SBQA_EINVAL, "state must be finite with |x| <= 1 (index %zu)", q);
-    std::vector<float> bx(tot, 0.0f), by(tot, 0.0f);   // padding rows and columns stay zero
-    for (int i = 0; i < N; ++i) {
-        const int row = c->pnew.empty() ? i : c->pnew[(size_t)i];   // internal row of spin i
-        for (int cc = 0; cc < C; ++cc) {
-            const int64_t o = state_off(c->order, c->ld, row, cc);
-            bx[(size_t)o] = x[(size_t)i * C + cc];
-            by[(size_t)o] = y[(size_t)i * C + cc];
-        }
+    const size_t one = (size_t)N * C, bytes = sizeof(float) * one;
+    for (size_t q0 = 0; q0 < one; q0 += 4096) {
+        const size_t q1 = std::min(one, q0 + 4096);
+        int bad = 0;   // NaN and infinities fail the comparisons
+        for (size_t q = q0; q < q1; ++q)
+            bad |= !(std::fabs(x[q]) <= 1.0f) | !(std::fabs(y[q]) <= std::numeric_limits<float>::max());
+        for (size_t q = q0; bad && q < q1; ++q)
+            if (!std::isfinite(x[q]) || !std::isfinite(y[q]) || std::fabs(x[q]) > 1.0f)
+                return fail(SBQA_EINVAL, "state must be finite with |x| <= 1 (index %zu)", q);
     }
-    HIP_TRY(hipMemcpyAsync(c->x[c->cur], bx.data(), sizeof(float) * tot, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipMemcpyAsync(c->y, by.data(), sizeof(float) * tot, hipMemcpyHostToDevice, c->stream));
+    // the caller's order to the context's on the device; padding rows and
+    // columns hold zero and are not written
+    PoolBlock dev(c->device, false), stage(c->device, true);
+    struct Wait { hipStream_t st; ~Wait() { if (st) (void)hipStreamSynchronize(st); } } wait{c->stream};
+    const bool pinned = 2 * bytes <= STAGE_BYTES;
+    HIP_TRY(dev.get(2 * bytes));
+    if (pinned) HIP_TRY(stage.get(2 * bytes));
+    for (int q = 0; q < 2; ++q) {
+        const float *from = q ? y : x;
+        float *d = dev.as<float>() + q * one;
+        if (pinned) std::memcpy(stage.as<float>() + q * one, from, bytes);
+        HIP_TRY(hipMemcpyAsync(d, pinned ? stage.as<float>() + q * one : from, bytes, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(launch_state_reorder(N, C, ORDER_SPIN_MAJOR, C, d, c->porig, c->order, c->ld, q ? c->y : c->x[c->cur],
+                                     nullptr, c->stream));
+    }
     c->sbits_step = -1;
     sbqa_status st = rebuild_operand(c);
     if (st != SBQA_OK) return st;
     HIP_TRY(hipStreamSynchronize(c->stream));
+    wait.st = nullptr;
     c->last_eval_step = -1;
     return SBQA_OK;
 }
@@ -1820,8 +2025,7 @@ sbqa_status sbqa_inject_wait_timeout(sbqa_ctx *c) {
 
 void sbqa_destroy(sbqa_ctx *c) {
     if (!c) return;
-    (void)hipStreamSynchronize(c->stream);
-    delete c;
+    delete c;   // waits for the context's work
 }
 
 }  // extern "C"

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "../../include/sbqa.h"
+#include "pool.h"
 #include "sbqa_internal.h"
 
 #include <string>
@@ -32,10 +33,6 @@ struct InstanceFacts {
 constexpr bool path_energy_mfma(Path p) {
     return p == PATH_FP8 || p == PATH_FP8PK || p == PATH_I8 || p == PATH_FP4 || p == PATH_FP4PK;
 }
-// Row-major sign bits of a dense +-1 J (InstanceFacts::jbits), ceil(N/32)
-// words per row; parallel over row blocks for large N.
-void pack_sign_bits(const double *J, int32_t N, std::vector<uint32_t> *bits);
-
 // Device geometry of a context.
 struct Layout {
     int C = 0;        // runs * R
@@ -54,8 +51,11 @@ sbqa_status fail(sbqa_status st, const char *fmt, ...);
 void clear_error();
 const char *last_error();
 
+// sign_bits (may be null): for a dense +-1 J (facts->pm1), its row-major sign
+// bits, ceil(N/32) words per row.
 sbqa_status validate_instance(const sbqa_coupling *J, const double *h, int32_t N, int32_t R, int32_t runs,
-                              const sbqa_schedule *s, InstanceFacts *facts);
+                              const sbqa_schedule *s, InstanceFacts *facts,
+                              std::vector<uint32_t> *sign_bits = nullptr);
 void plan_layout(int32_t N, int32_t R, int32_t runs, const InstanceFacts &f, Layout *L);
 size_t instance_bytes(int32_t N, int32_t R, int32_t runs, const InstanceFacts &f, uint32_t steps);
 StepCoef step_coef(const sbqa_schedule *s, double c0, int R, uint32_t n);
@@ -107,7 +107,19 @@ struct sbqa_ctx {
     // context's work is issued
     hipStream_t default_stream = nullptr, stream = nullptr;
     size_t bytes = 0;
-    std::vector<void *> allocs;
+    // device buffers: whole blocks of the pool, and the small buffers of
+    // context creation packed into chunks whose pinned mirror collects the
+    // values to upload (one copy per chunk, dalloc / upload / flush)
+    std::vector<sbqa::Block> blocks;
+    struct Chunk {
+        sbqa::Block dev, host;
+        size_t used = 0, sent = 0;
+    };
+    std::vector<Chunk> chunks;
+    sbqa::Block rhost_block;
+    bool creating = true;   // small buffers go to chunks
+    bool direct = false;    // copies straight from the caller's memory are under way
+    bool idle = false;      // the context's work is known to have completed
     bool has_h = false;
 
     // state (dense: [C][Np] replica-major; CSR: [N][Cs] spin-major, or

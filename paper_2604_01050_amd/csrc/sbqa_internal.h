@@ -227,6 +227,9 @@ hipError_t resident_max_blocks(int D, int N, int *blocks_per_cu);
 // bytes. The runtime call is made only when the limit grows (one lookup under
 // a mutex otherwise), so that launches do not pay for it every time.
 hipError_t ensure_dyn_lds(const void *fn, size_t lds);
+// hipOccupancyMaxActiveBlocksPerMultiprocessor, asked once per kernel and
+// launch shape on each device (30 us a call).
+hipError_t max_blocks_per_cu(const void *fn, int threads, size_t lds, int *blocks);
 hipError_t launch_csr_resident(const ResidentArgs &a, int D, hipStream_t st);
 // The same loop with W = 2 or 4 columns per workgroup (kernels_narrow.hip),
 // nwg = C / W workgroups: words holds the tagged ring edges
@@ -303,9 +306,10 @@ hipError_t launch_init_state(int N, int C, int order, int ld, uint64_t seed, dou
                              float *x, float *y, hipStream_t st);
 
 // Copy of an N x C float state from one order to another (rows of dst outside
-// [0, N) are left as they are).
-hipError_t launch_state_reorder(int N, int C, int order_in, int ld_in, const float *src, int order_out, int ld_out,
-                                float *dst, hipStream_t st);
+// [0, N) are left as they are). row_in / row_out (nullptr: the identity): the
+// row of src / dst that copy row i is read from / written to.
+hipError_t launch_state_reorder(int N, int C, int order_in, int ld_in, const float *src, const int32_t *row_in,
+                                int order_out, int ld_out, float *dst, const int32_t *row_out, hipStream_t st);
 
 // Readout spins sign(x) (sign(0) = +1) as float64 +-1 into S[Cp][Np]
 // (zero padding) from the state, for the energy GEMM.

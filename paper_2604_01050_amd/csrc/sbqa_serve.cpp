@@ -212,6 +212,7 @@ static void end_retire(sbqa_server *srv, Slot &sl) {
         res.status = b;
         res.error = last_error();
     }
+    sl.ctx->idle = true;
     delete sl.ctx;
     sl.ctx = nullptr;
     sl.retiring = false;
@@ -566,7 +567,7 @@ sbqa_status sbqa_submit(sbqa_server *srv, const sbqa_coupling *J, const double *
     if (!srv || !ticket) return fail(SBQA_EINVAL, "NULL argument");
     std::unique_ptr<Request> r(new (std::nothrow) Request());
     if (!r) return fail(SBQA_ENOMEM, "out of host memory");
-    sbqa_status st = validate_instance(J, h, N, R, runs, s, &r->facts);
+    sbqa_status st = validate_instance(J, h, N, R, runs, s, &r->facts, &r->jbits);
     if (st != SBQA_OK) return st;
     // dense +-1 couplings on a bit-packed path travel as sign bits (N^2/8
     // bytes instead of N^2 float64) and keep no float64 copy on the device
@@ -578,8 +579,9 @@ sbqa_status sbqa_submit(sbqa_server *srv, const sbqa_coupling *J, const double *
     r->R = R;
     r->runs = runs;
     r->s = *s;
-    if (J->dense && r->facts.jbits) pack_sign_bits(J->dense, N, &r->jbits);
-    else if (J->dense) r->dense.assign(J->dense, J->dense + (size_t)N * N);
+    if (!r->facts.jbits) r->jbits.clear();
+    if (J->dense && r->facts.jbits) {   // validation has left the sign bits
+    } else if (J->dense) r->dense.assign(J->dense, J->dense + (size_t)N * N);
     else {
         r->row_ptr.assign(J->row_ptr, J->row_ptr + N + 1);
         r->col.assign(J->col, J->col + J->nnz);
