@@ -200,6 +200,14 @@ def dense_kernel_name(info):
     each in fp8, 256 in fp4; spins padded to a multiple of 512) split into
     two halves of an even count."""
     Np = -(-info["N"] // 512) * 512
+    # small grids: a finer tile (16 spins per workgroup up to one workgroup per
+    # CU, else 32 up to one, or two with bit-packed J)
+    if "R" in info and "runs" in info:
+        pad = 512 if "fp8" in info["path"] or "fp4" in info["path"] or "int8" in info["path"] else 128
+        rows = -(-info["N"] // pad) * pad
+        cb = -(-(info["R"] * info["runs"]) // info["tile_cols"]) * info["tile_cols"] // 64
+        if rows // 16 * cb <= 256 or rows // 32 * cb <= (512 if info["path"].endswith("_packed") else 256):
+            return "k_dense_step_fine"
     nkc = {"dense_fp8_packed": Np // 128, "dense_fp4_packed": Np // 256}.get(info["path"], 1)
     split = info["path"] in ("dense_fp8_packed", "dense_fp4_packed") and info["tile_cols"] == 128 and nkc % 4 == 0
     if split:

@@ -331,7 +331,7 @@ __device__ __forceinline__ UpdIn update_load(const DenseStepArgs &a, int c, int 
 }
 
 #pragma clang fp contract(off)
-template <int PATH, int MBW>
+template <int PATH, int GM>
 __device__ __forceinline__ void update_store(const DenseStepArgs &a, int c, int i4, const UpdIn &u, float4 ph) {
     const StepCoef k = a.k;
     const float xs[4] = {u.x.x, u.x.y, u.x.z, u.x.w}, ls[4] = {u.xl.x, u.xl.y, u.xl.z, u.xl.w};
@@ -355,32 +355,30 @@ __device__ __forceinline__ void update_store(const DenseStepArgs &a, int c, int 
     const int64_t o = (int64_t)c * a.Np + i4;
     *reinterpret_cast<float4 *>(a.x_out + o) = make_float4(xo[0], xo[1], xo[2], xo[3]);
     *reinterpret_cast<float4 *>(a.y + o) = make_float4(yo[0], yo[1], yo[2], yo[3]);
-    store_operand<PATH>(a.g_next, a.g_next_lo, op_offset<PATH>(c, i4, a.nkc, MBW),
+    store_operand<PATH>(a.g_next, a.g_next_lo, op_offset<PATH>(c, i4, a.nkc, GM ? GM : a.mbw),
                         make_float4(fo[0], fo[1], fo[2], fo[3]), a.fmode);
 }
 #pragma clang fp contract(on)
 
-// Epilogue of one workgroup tile: transpose each 16 x DENSE_TN block of Phi
-// through LDS (lds: at least 4 waves x 16 x (DENSE_TN + 4) floats) so that a
-// lane holds 4 consecutive spins of one replica column (f32 MFMA results:
+// Epilogue of one wave's tile, row blocks (replica columns) mb0 .. mb0 + MBW
+// - 1 by TN spins from n0: transpose each 16 x TN block of Phi through LDS
+// (lds: at least 16 x (TN + 4) floats for every wave of the workgroup) so that
+// a lane holds 4 consecutive spins of one replica column (f32 MFMA results:
 // register r of a lane is row 4*(lane/16) + r, column lane%16); then load
-// every input of the lane's items before the first store. wq: the wave's
-// index among the 4 waves of the tile's columns (default: its workgroup
-// index); the transpose buffer is indexed by the workgroup wave index.
-template <int PATH, int MBW, int EPI>
-__device__ __forceinline__ void dense_epilogue(const DenseStepArgs &a, f4 (&acc)[MBW][DENSE_TN / 16], int nt, int mchunk,
-                                               uint8_t *lds, int wq = -1) {
-    constexpr int RBT = DENSE_TN / 16;
-    constexpr int TS = DENSE_TN + 4;
+// every input of the lane's items before the first store. GM: row blocks per
+// operand group (0: a.mbw).
+template <int PATH, int MBW, int EPI, int TN = DENSE_TN, int GM = MBW>
+__device__ __forceinline__ void dense_epilogue(const DenseStepArgs &a, f4 (&acc)[MBW][TN / 16], int n0, int mb0,
+                                               uint8_t *lds) {
+    constexpr int RBT = TN / 16;
+    constexpr int TS = TN + 4;
     constexpr bool JPK = path_packed(Path(PATH));
-    const int lane = threadIdx.x & 63, wt = threadIdx.x >> 6, w = wq < 0 ? wt : wq;
-    const int n0 = nt * DENSE_TN;
-    const int mb0 = (mchunk * 4 + w) * MBW;
+    const int lane = threadIdx.x & 63, wt = threadIdx.x >> 6;
     const int nkc = a.nkc;
     __syncthreads();
     float *T = reinterpret_cast<float *>(lds) + wt * 16 * TS;
     const int g = lane >> 4, r16 = lane & 15;
-    constexpr int QPR = DENSE_TN / 4;         // spin quads per row
+    constexpr int QPR = TN / 4;               // spin quads per row
     constexpr int ITEMS = 16 * QPR / 64;      // (row, quad) items per lane and m-block
 #pragma unroll
     for (int mb = 0; mb < MBW; ++mb) {
@@ -406,7 +404,7 @@ __device__ __forceinline__ void dense_epilogue(const DenseStepArgs &a, f4 (&acc)
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it) {
                 if (cc[it] >= a.C) continue;
-                const uint8_t *fp = a.g + op_offset<PATH>(cc[it], ii[it], nkc, MBW);
+                const uint8_t *fp = a.g + op_offset<PATH>(cc[it], ii[it], nkc, GM ? GM : a.mbw);
                 constexpr int BITS = is_fp4<PATH> ? 4 : 8;
                 constexpr uint32_t MASK = (1u << BITS) - 1u, SIGN = 1u << (BITS - 1);
                 const uint32_t fb = is_fp4<PATH> ? (uint32_t)*reinterpret_cast<const uint16_t *>(fp)
@@ -428,7 +426,7 @@ __device__ __forceinline__ void dense_epilogue(const DenseStepArgs &a, f4 (&acc)
                 if (cc[it] < a.C) u[it] = update_load(a, cc[it], ii[it]);
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it)
-                if (cc[it] < a.C) update_store<PATH, MBW>(a, cc[it], ii[it], u[it], ph[it]);
+                if (cc[it] < a.C) update_store<PATH, GM>(a, cc[it], ii[it], u[it], ph[it]);
         } else {
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it)
@@ -603,7 +601,7 @@ __device__ __forceinline__ void dense_step_body(const DenseStepArgs &a, int nt, 
         }
     }
 
-    dense_epilogue<PATH, MBW, EPI>(a, acc, nt, mchunk, lds, w);
+    dense_epilogue<PATH, MBW, EPI>(a, acc, n0, mb0, lds);
 }
 
 template <int PATH, int MBW, int EPI>
@@ -616,6 +614,106 @@ __global__ __launch_bounds__(DENSE_THREADS) void k_dense_step(const DenseStepArg
 template <int PATH, int MBW, int EPI>
 __global__ __launch_bounds__(2 * DENSE_THREADS) void k_dense_step_cg2(const DenseStepArgs a) {
     dense_step_body<PATH, MBW, EPI, 2>(a, blockIdx.x, blockIdx.y);
+}
+
+// The same step for small grids: a wave owns 16 replica columns x 16*NB spins
+// and streams both operands straight into registers, PD K chunks ahead, with
+// no LDS and no barrier in the K loop; the 4 waves of a workgroup take 4
+// column blocks of the same spins, so that J is fetched into the CU's L1 once.
+// Every field sums the same terms in the same order as in k_dense_step. Bound
+// by the chain of MFMAs into one accumulator (fp32, N = 1500: 384 of 32 cycles,
+// 5.1 us of the 10.3 us a step takes; four such chains, LDS and barriers in the
+// 64-spin tile 32.2), then by the L1 fill.
+template <int PATH, int NB, int PD, int EPI>
+__global__ __launch_bounds__(DENSE_THREADS) void k_dense_step_fine(const DenseStepArgs a) {
+    constexpr int PL = Pipe<PATH>::planes;
+    constexpr int NT = Terms<PATH>::n;
+    constexpr int RBG = DENSE_TN / 16;            // row blocks per J group
+    constexpr bool JPK = path_packed(Path(PATH));
+    constexpr int JFRAG = JPK ? pk_frag_bytes(Path(PATH)) : FRAG_BYTES;
+    using JWord = std::conditional_t<is_fp4<PATH>, uint2, uint32_t>;
+    __shared__ __align__(16) uint8_t lds[4 * 16 * (16 * NB + 4) * 4];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int mb = blockIdx.y * 4 + w, rb0 = blockIdx.x * NB, nkc = a.nkc, l16 = lane * 16;
+    const int xstep = a.mbw * FRAG_BYTES;
+    const int64_t xo = (int64_t)(mb / a.mbw) * nkc * xstep + (mb % a.mbw) * FRAG_BYTES + l16;
+    const uint8_t *xsrc = a.g + xo, *xsrc_lo = (PL == 2) ? a.g_lo + xo : xsrc;
+    const uint8_t *jsrc[NB], *jsrc_lo[NB];
+#pragma unroll
+    for (int p = 0; p < NB; ++p) {
+        const int rb = rb0 + p;
+        const int64_t jo = (int64_t)(rb / RBG) * nkc * (RBG * JFRAG) + (rb % RBG) * JFRAG +
+                           (JPK ? lane * (int)sizeof(JWord) : l16);
+        jsrc[p] = a.J + jo;
+        jsrc_lo[p] = (PL == 2) ? a.J_lo + jo : jsrc[p];
+    }
+    const int rev = a.reverse;
+    auto chunk_at = [&](int kc) -> int64_t { return rev ? nkc - 1 - kc : kc; };
+    uint4 xr[PD][PL][2], jr[JPK ? 1 : PD][NB][PL][2];
+    JWord jw[JPK ? PD : 1][NB];
+    auto load = [&](int s, int kc) {
+        const int64_t k = chunk_at(kc);
+#pragma unroll
+        for (int p = 0; p < NB; ++p) {
+            if constexpr (JPK) {
+                jw[s][p] = *reinterpret_cast<const JWord *>(jsrc[p] + k * (RBG * JFRAG));
+            } else {
+                jr[s][p][0][0] = ld16(jsrc[p] + k * (RBG * JFRAG));
+                jr[s][p][0][1] = ld16(jsrc[p] + k * (RBG * JFRAG) + 1024);
+                if constexpr (PL == 2) {
+                    jr[s][p][PL - 1][0] = ld16(jsrc_lo[p] + k * (RBG * JFRAG));
+                    jr[s][p][PL - 1][1] = ld16(jsrc_lo[p] + k * (RBG * JFRAG) + 1024);
+                }
+            }
+        }
+        xr[s][0][0] = ld16(xsrc + k * xstep);
+        xr[s][0][1] = ld16(xsrc + k * xstep + 1024);
+        if constexpr (PL == 2) {
+            xr[s][PL - 1][0] = ld16(xsrc_lo + k * xstep);
+            xr[s][PL - 1][1] = ld16(xsrc_lo + k * xstep + 1024);
+        }
+    };
+    f4 acc[1][NB];
+#pragma unroll
+    for (int p = 0; p < NB; ++p) acc[0][p] = f4{0, 0, 0, 0};
+    // nkc is a multiple of PD; the last PD chunks load their own chunk again
+    // instead of the next, so that every chunk issues the same loads. A wave
+    // whose 16 columns are all padding has no chunks.
+    const int nk = 16 * mb < a.C ? nkc : 0;
+#pragma unroll
+    for (int s = 0; s < PD; ++s) {
+        load(s, s);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll 1
+    for (int kc0 = 0; kc0 < nk; kc0 += PD) {
+#pragma unroll
+        for (int s = 0; s < PD; ++s) {
+            const int kc = kc0 + s;
+            const Frag32 ax{xr[s][0][0], xr[s][0][1]}, ax2{xr[s][PL - 1][0], xr[s][PL - 1][1]};
+            Frag32 bj[NB], bj2[NB];
+#pragma unroll
+            for (int p = 0; p < NB; ++p) {
+                if constexpr (JPK) {
+                    if constexpr (is_fp4<PATH>) bj[p] = unpack_pm1_fp4(jw[s][p]);
+                    else bj[p] = unpack_pm1(jw[s][p]);
+                    bj2[p] = bj[p];
+                } else {
+                    bj[p] = Frag32{jr[s][p][0][0], jr[s][p][0][1]};
+                    bj2[p] = Frag32{jr[s][p][PL - 1][0], jr[s][p][PL - 1][1]};
+                }
+            }
+            static_for<0, NT>([&](auto tc) {
+                constexpr int T = decltype(tc)::value;
+#pragma unroll
+                for (int p = 0; p < NB; ++p) mma_term<PATH, T>(acc[0][p], ax, bj[p], ax2, bj2[p]);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+            load(s, kc + PD < nkc ? kc + PD : kc);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    dense_epilogue<PATH, 1, EPI, 16 * NB, 0>(a, acc, rb0 * 16, mb, lds);
 }
 
 // K chunks in flight per wave in the split-K kernel (fp8 and fp4 alike;
@@ -757,7 +855,7 @@ __global__ __launch_bounds__(2 * DENSE_THREADS) void k_dense_step_sk(const Dense
             const f4 m = h == 0 ? acc[mb][p] : acc[mb][RBG + p];
             mine[mb][p] = f4{m[0] + o[0], m[1] + o[1], m[2] + o[2], m[3] + o[3]};
         }
-    dense_epilogue<PATH, MBW, EPI>(a, mine, 2 * nt2 + h, mchunk, lds, w);
+    dense_epilogue<PATH, MBW, EPI>(a, mine, (2 * nt2 + h) * DENSE_TN, (mchunk * 4 + w) * MBW, lds);
 }
 
 // Grouped step of every dense instance of one serving group (same path and
@@ -885,6 +983,7 @@ __global__ __launch_bounds__(DENSE_THREADS) void k_group_dense(const GroupHeader
         a.R = t.R;
         a.C = t.C;
         a.nkc = t.nkc;
+        a.mbw = MBW;
         a.reverse = in;
         a.J = static_cast<const uint8_t *>(t.J);
         a.J_lo = static_cast<const uint8_t *>(t.J_lo);
@@ -937,8 +1036,38 @@ __global__ __launch_bounds__(256) void k_readout_operand(int N, int Np, int nkc,
     store_operand<PATH>(g, nullptr, op_offset<PATH>(c, i4, nkc, mbw), f, 0);
 }
 
+// The fine tile where the 64-spin tiles leave CUs idle: 16 spins per workgroup
+// while those workgroups are at most one per CU, else 32. Above that the bytes
+// every CU pulls through its L1 (16 + 64 rows of operands per 16 spins) cost
+// more than the shorter chain of MFMAs saves. us per step, 64-spin tile / 16 /
+// 32 spins: fp32 N = 1500, C = 60 32.2 / 10.3 / 16.2; N = 2000, C = 128 (256
+// and 128 workgroups) 41.8 / 13.7 / 21.4; N = 4096, C = 128 (512 and 256) 78.9
+// / 49.1 / 39.8; N = 5000, C = 128 (640 and 320) 97 / 89 / 127; bf16 hi+lo N =
+// 4096, C = 128 34.2 / 40.7 / 30.6; int8 N = 4096, C = 128 12.8 / 13.8 / 10.6, N
+// = 6000, C = 128 (384 of 32 spins) 17.0 / 24.7 / 22.9. Bit-packed J is a
+// fraction of the bytes, two workgroups of 32 spins per CU still gain: fp8 N =
+// 8192, C = 128 (512) 27.8 / 27.4 / 22.0, fp4 17.4 / 20.0 / 15.9; N = 6000, C =
+// 256 (768) fp4 17.9 / 23.5 / 18.5.
+constexpr int MI355X_CUS = 256;
+inline int fine_spins(Path path, int Np, int Cg) {
+    const int cb = Cg / 64, limit = path_packed(path) ? 2 * MI355X_CUS : MI355X_CUS;
+    if (Np / 16 * cb <= MI355X_CUS) return 16;
+    return Np / 32 * cb <= limit ? 32 : 0;
+}
+
+template <int PATH, int NB, int EPI>
+hipError_t launch_step_fine(int Cg, const DenseStepArgs &a, hipStream_t st) {
+    const dim3 grid(a.Np / (16 * NB), Cg / 64), block(DENSE_THREADS);
+    if (a.nkc % 4 == 0) hipLaunchKernelGGL((k_dense_step_fine<PATH, NB, 4, EPI>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((k_dense_step_fine<PATH, NB, 2, EPI>), grid, block, 0, st, a);
+    return hipGetLastError();
+}
+
 template <int PATH, int EPI>
-hipError_t launch_step_mbw(int mbw, dim3 grid, const DenseStepArgs &a, hipStream_t st) {
+hipError_t launch_step_mbw(int mbw, dim3 grid, const DenseStepArgs &a, bool coarse, hipStream_t st) {
+    const int Cg = (int)grid.y * 64 * mbw, fine = coarse ? 0 : fine_spins(Path(PATH), a.Np, Cg);
+    if (fine == 16) return launch_step_fine<PATH, 1, EPI>(Cg, a, st);
+    if (fine == 32) return launch_step_fine<PATH, 2, EPI>(Cg, a, st);
     // 128-column tile of a bit-packed path: the split-K form when both K
     // halves fill the prefetch pipeline (same fields, integer-valued sums)
     if constexpr (path_packed(Path(PATH))) {
@@ -966,9 +1095,10 @@ hipError_t launch_step_mbw(int mbw, dim3 grid, const DenseStepArgs &a, hipStream
 }
 
 template <int PATH>
-hipError_t launch_step_path(DenseEpilogue epi, int mbw, dim3 grid, const DenseStepArgs &a, hipStream_t st) {
-    return epi == EPI_UPDATE ? launch_step_mbw<PATH, EPI_UPDATE>(mbw, grid, a, st)
-                             : launch_step_mbw<PATH, EPI_FIELDS>(mbw, grid, a, st);
+hipError_t launch_step_path(DenseEpilogue epi, int mbw, dim3 grid, const DenseStepArgs &a, bool coarse,
+                            hipStream_t st) {
+    return epi == EPI_UPDATE ? launch_step_mbw<PATH, EPI_UPDATE>(mbw, grid, a, coarse, st)
+                             : launch_step_mbw<PATH, EPI_FIELDS>(mbw, grid, a, coarse, st);
 }
 
 }  // namespace
@@ -985,21 +1115,23 @@ hipError_t launch_gemm_f64(const double *A, const double *B, double *out, int Np
     return hipGetLastError();
 }
 
-hipError_t launch_dense_step(Path path, DenseEpilogue epi, int mbw, int Cg, const DenseStepArgs &a,
-                             hipStream_t st) {
+hipError_t launch_dense_step(Path path, DenseEpilogue epi, int mbw, int Cg, const DenseStepArgs &a, hipStream_t st,
+                             bool coarse) {
     const int tm = 64 * mbw;
     if (a.Np % DENSE_TN || Cg % tm || a.C > Cg || a.Np % path_kpc(path) || a.nkc != dense_nkc(path, a.Np) ||
         a.nkc % dense_depth(path))
         return hipErrorInvalidValue;
     const dim3 grid(a.Np / DENSE_TN, Cg / tm);
+    DenseStepArgs b = a;
+    b.mbw = mbw;
     switch (path) {
-        case PATH_F32: return launch_step_path<PATH_F32>(epi, mbw, grid, a, st);
-        case PATH_FP8: return launch_step_path<PATH_FP8>(epi, mbw, grid, a, st);
-        case PATH_BF16X3: return launch_step_path<PATH_BF16X3>(epi, mbw, grid, a, st);
-        case PATH_I8: return launch_step_path<PATH_I8>(epi, mbw, grid, a, st);
-        case PATH_FP8PK: return launch_step_path<PATH_FP8PK>(epi, mbw, grid, a, st);
-        case PATH_FP4: return launch_step_path<PATH_FP4>(epi, mbw, grid, a, st);
-        case PATH_FP4PK: return launch_step_path<PATH_FP4PK>(epi, mbw, grid, a, st);
+        case PATH_F32: return launch_step_path<PATH_F32>(epi, mbw, grid, b, coarse, st);
+        case PATH_FP8: return launch_step_path<PATH_FP8>(epi, mbw, grid, b, coarse, st);
+        case PATH_BF16X3: return launch_step_path<PATH_BF16X3>(epi, mbw, grid, b, coarse, st);
+        case PATH_I8: return launch_step_path<PATH_I8>(epi, mbw, grid, b, coarse, st);
+        case PATH_FP8PK: return launch_step_path<PATH_FP8PK>(epi, mbw, grid, b, coarse, st);
+        case PATH_FP4: return launch_step_path<PATH_FP4>(epi, mbw, grid, b, coarse, st);
+        case PATH_FP4PK: return launch_step_path<PATH_FP4PK>(epi, mbw, grid, b, coarse, st);
         default: return hipErrorInvalidValue;
     }
 }

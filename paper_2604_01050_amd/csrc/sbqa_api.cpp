@@ -571,9 +571,9 @@ static int tune_dense_mbw(Path path, int C, int Np, hipStream_t st) {
         for (int m : cand) {
             if (!ok) break;
             const int Cg = (int)round_up(C, 64 * m);
-            ok = launch_dense_step(path, EPI_UPDATE, m, Cg, a, st) == hipSuccess;   // warm-up
+            ok = launch_dense_step(path, EPI_UPDATE, m, Cg, a, st, true) == hipSuccess;   // warm-up
             ok = ok && hipEventRecord(e0, st) == hipSuccess;
-            for (int r = 0; r < 3 && ok; ++r) ok = launch_dense_step(path, EPI_UPDATE, m, Cg, a, st) == hipSuccess;
+            for (int r = 0; r < 3 && ok; ++r) ok = launch_dense_step(path, EPI_UPDATE, m, Cg, a, st, true) == hipSuccess;
             ok = ok && hipEventRecord(e1, st) == hipSuccess && hipEventSynchronize(e1) == hipSuccess;
             float ms = 0.0f;
             ok = ok && hipEventElapsedTime(&ms, e0, e1) == hipSuccess;

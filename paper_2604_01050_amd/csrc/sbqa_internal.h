@@ -103,6 +103,7 @@ enum DenseEpilogue : int32_t { EPI_UPDATE = 0, EPI_FIELDS = 1 };
 struct DenseStepArgs {
     int N, Np, R, C;
     int nkc;                        // K chunks of 128 bytes per row: dense_nkc(path, Np)
+    int mbw;                        // row blocks per operand group (set by launch_dense_step)
     int reverse;                    // traverse K chunks from the last one
     const uint8_t *J, *J_lo;        // fragment-tiled [Np/16][nkc]; J_lo: bf16 low part
     const uint8_t *g, *g_lo;        // operand f(X_n), fragment-tiled [Cg/16][nkc]
@@ -120,9 +121,11 @@ struct DenseStepArgs {
 // One step of the dense path: Phi = J f(X_n) on MFMA for a workgroup tile of
 // DENSE_TN spins x 64*mbw replica columns, then either the fused update
 // (Eqs. 6-7, wall, next operand) or a plain store of Phi.
-// grid = (Np / DENSE_TN, Cg / (64 * mbw)).
-hipError_t launch_dense_step(Path path, DenseEpilogue epi, int mbw, int Cg, const DenseStepArgs &a,
-                             hipStream_t st);
+// grid = (Np / DENSE_TN, Cg / (64 * mbw)). Small grids take a finer tile on the
+// same operand layout unless `coarse`: the tile autotuner times the mbw forms
+// themselves, which the grouped steps of the serving loop run at any grid.
+hipError_t launch_dense_step(Path path, DenseEpilogue epi, int mbw, int Cg, const DenseStepArgs &a, hipStream_t st,
+                             bool coarse = false);
 
 // ---- grouped steps of the serving loop ----------------------------------------
 // Three-body terms (the cubic part of Eq. 11) of a CSR instance, listed per

@@ -114,3 +114,35 @@ def test_captured_steps_replay(sb, kind, N, R, runs, K):
         torch.cuda.synchronize()
         for a, b in zip(sb.sbqa_get_state(ref), sb.sbqa_get_state(ctx)):
             assert np.array_equal(a, b)
+
+
+# the dense step's tile follows the grid: with few columns 16 or 32 spins per
+# workgroup, with many the 64-spin (or split-K) tiles
+@pytest.mark.parametrize("coup,prec,fmode,packing", [
+    ("gauss", "FP32", 0, 0), ("gauss", "BF16X3", 2, 0), ("sidon", "INT8", 0, 0), ("sk", "FP8", 0, 0), ("sk", "FP8", 1, 1),
+    ("sk", "FP4", 0, 0), ("sk", "FP4", 1, 1)])
+def test_dense_step_tiles_by_grid(sb, coup, prec, fmode, packing):
+    """A column's trajectory does not depend on how many columns are stepped
+    beside it, nor on the tile: few columns (fine tiles, padded columns and
+    rows) against the same columns among 768 (64-, 128- and 256-column tiles)."""
+    N = 700 if coup == "gauss" else 1100
+    J = {"gauss": inst.dense_gaussian, "sidon": inst.sidon28_dense, "sk": inst.sk_pm1}[coup](N, 41)
+    h = inst.gaussian_fields(N, 0.3, 42) if coup == "gauss" else np.round(inst.gaussian_fields(N, 2.0, 42))
+    R, runs = 8, 96 if coup != "gauss" else 192
+    X, Y = inst.uniform_state(N, R * runs, 0.4, 43)
+    kw = dict(J=J, h=h, R=R, steps=12, fmode=fmode, precision=getattr(sb, "PREC_" + prec), j_packing=packing,
+              jp_kind=sb.JP_LINEAR, jp_start=0.5, jp_end=0.0, loop_kernel=sb.LOOP_STREAM)
+    ref = None
+    for few, tile in ((runs, 64), (runs, 128), (runs, 256), (2, 64), (7, 64), (20, 64), (20, 128), (20, 256), (40, 64)):
+        C = R * few
+        _log("tiles by grid %s %s C=%d tile %d" % (coup, prec, C, tile))
+        ctx = sb.sbqa_create(runs=few, dense_tile=tile, **kw)
+        sb.sbqa_set_state(ctx, X[:, :C], Y[:, :C])
+        sb.sbqa_step(ctx, 11)
+        got = (*sb.sbqa_get_state(ctx), sb.sbqa_fields(ctx))
+        E, s = sb.sbqa_best(ctx)
+        if ref is None:
+            ref = (got, E, s)
+        for a, b in zip(ref[0], got):
+            assert np.array_equal(a[:, :C], b)
+        assert np.array_equal(ref[1][:few], E) and np.array_equal(ref[2][:few], s)
