@@ -81,41 +81,41 @@ __global__ __launch_bounds__(256) void k_state_reorder(int N, int C, int order_i
     }
 }
 
-__global__ void k_readout_f64(int N, int Np, int C, int ld, int spin_major, const float *__restrict__ x,
-                              double *__restrict__ S) {
-    const int c = blockIdx.y;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= Np) return;
-    double s = 0.0;
-    if (i < N && c < C) {
-        const float v = spin_major ? x[(int64_t)i * ld + c] : x[(int64_t)c * ld + i];
-        s = v >= 0.0f ? 1.0 : -1.0;
+// Rows of int8 spins with zero padding, 4 per thread (Np % 4 == 0): the
+// readout of a state, or given spins.
+__global__ __launch_bounds__(256) void k_readout_spins(int N, int Np, int C, const float *__restrict__ x,
+                                                       int8_t *__restrict__ S) {
+    const int c = blockIdx.y, i4 = 4 * (blockIdx.x * 256 + threadIdx.x);
+    if (i4 >= Np) return;
+    char4 s = make_char4(0, 0, 0, 0);
+    if (c < C) {
+        const float4 v = *reinterpret_cast<const float4 *>(x + (int64_t)c * Np + i4);
+        auto sg = [&](float xv, int i) { return (signed char)(i < N ? (xv >= 0.0f ? 1 : -1) : 0); };
+        s = make_char4(sg(v.x, i4), sg(v.y, i4 + 1), sg(v.z, i4 + 2), sg(v.w, i4 + 3));
     }
-    S[(int64_t)c * Np + i] = s;
+    *reinterpret_cast<char4 *>(S + (int64_t)c * Np + i4) = s;
 }
 
-__global__ void k_spins_to_f64(int N, int Np, int count, const int8_t *__restrict__ spins, double *__restrict__ S) {
-    const int m = blockIdx.y;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= Np) return;
-    S[(int64_t)m * Np + i] = (i < N && m < count) ? (double)spins[(int64_t)m * N + i] : 0.0;
+__global__ __launch_bounds__(256) void k_pad_spins(int N, int Np, int count, const int8_t *__restrict__ spins,
+                                                   int8_t *__restrict__ S) {
+    const int m = blockIdx.y, i4 = 4 * (blockIdx.x * 256 + threadIdx.x);
+    if (i4 >= Np) return;
+    signed char s[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] = (m < count && i4 + e < N) ? spins[(int64_t)m * N + i4 + e] : (int8_t)0;
+    *reinterpret_cast<char4 *>(S + (int64_t)m * Np + i4) = make_char4(s[0], s[1], s[2], s[3]);
 }
 
 // Block per configuration; per-thread strided sums, then a fixed LDS tree.
-__global__ __launch_bounds__(256) void k_energy_reduce(int N, int Np, int Cp, int splits,
-                                                       const double *__restrict__ phis,
-                                                       const double *__restrict__ S,
-                                                       const double *__restrict__ h, double *__restrict__ E) {
+__global__ __launch_bounds__(256) void k_energy_sum(int N, int Np, int cp, int units, const double *__restrict__ part,
+                                                    const int8_t *__restrict__ S, const double *__restrict__ h,
+                                                    double *__restrict__ E) {
     __shared__ double sq[256], sl[256];
     const int c = blockIdx.x, t = threadIdx.x;
     double q = 0.0, l = 0.0;
-    for (int i = t; i < N; i += 256) {
-        double phi = phis[(int64_t)c * Np + i];
-        for (int z = 1; z < splits; ++z) phi += phis[((int64_t)z * Cp + c) * Np + i];
-        const double s = S[(int64_t)c * Np + i];
-        q += s * phi;
-        if (h) l += h[i] * s;
-    }
+    for (int u = t; u < units; u += 256) q += part[(int64_t)u * cp + c];
+    if (h)
+        for (int i = t; i < N; i += 256) l += h[i] * (double)S[(int64_t)c * Np + i];
     sq[t] = q;
     sl[t] = l;
     __syncthreads();
@@ -126,13 +126,13 @@ __global__ __launch_bounds__(256) void k_energy_reduce(int N, int Np, int Cp, in
         }
         __syncthreads();
     }
-    if (t == 0) E[c] = -0.5 * sq[0] - sl[0];
+    if (t == 0) E[c] = sq[0] - sl[0];
 }
 
 // Energies from exact integer fields Phi = J s of the readout s = sign(x)
 // (sign(0) = +1), replica-major [C][Np]: E_c = -1/2 sum_i s_ci Phi_ci -
-// sum_i h_i s_ci, block per column, the same fixed-order reduction as
-// k_energy_reduce (every partial sum an integer for integer J and h).
+// sum_i h_i s_ci, block per column, per-thread strided sums and a fixed LDS
+// tree (every partial sum an integer for integer J and h).
 __global__ __launch_bounds__(256) void k_energy_fields(int N, int Np, const float *__restrict__ x,
                                                        const float *__restrict__ phi, const double *__restrict__ h,
                                                        double *__restrict__ E) {
@@ -668,25 +668,28 @@ hipError_t launch_state_reorder(int N, int C, int order_in, int ld_in, const flo
     return hipGetLastError();
 }
 
-hipError_t launch_readout_f64(int N, int Np, int C, int ld, bool spin_major, const float *x, double *S,
-                              hipStream_t st) {
-    // S has Cp >= C rows; rows c >= C are written as zero by the grid below.
-    const int Cp = (C + GEMM_BM - 1) / GEMM_BM * GEMM_BM;
-    dim3 grid((Np + 255) / 256, Cp), block(256);
-    hipLaunchKernelGGL(k_readout_f64, grid, block, 0, st, N, Np, C, ld, spin_major ? 1 : 0, x, S);
+// (grid y holds at most 65535 rows: larger counts go in slabs)
+hipError_t launch_readout_spins(int N, int Np, int C, int cp, const float *x, int8_t *S, hipStream_t st) {
+    for (int c0 = 0; c0 < cp; c0 += 65535) {
+        const dim3 grid((Np / 4 + 255) / 256, std::min(65535, cp - c0));
+        hipLaunchKernelGGL(k_readout_spins, grid, dim3(256), 0, st, N, Np, C - c0, x + (int64_t)c0 * Np,
+                           S + (int64_t)c0 * Np);
+    }
     return hipGetLastError();
 }
 
-hipError_t launch_spins_to_f64(int N, int Np, int count, const int8_t *spins, double *S, hipStream_t st) {
-    const int Cp = (count + GEMM_BM - 1) / GEMM_BM * GEMM_BM;
-    dim3 grid((Np + 255) / 256, Cp), block(256);
-    hipLaunchKernelGGL(k_spins_to_f64, grid, block, 0, st, N, Np, count, spins, S);
+hipError_t launch_pad_spins(int N, int Np, int count, int cp, const int8_t *spins, int8_t *S, hipStream_t st) {
+    for (int c0 = 0; c0 < cp; c0 += 65535) {
+        const dim3 grid((Np / 4 + 255) / 256, std::min(65535, cp - c0));
+        hipLaunchKernelGGL(k_pad_spins, grid, dim3(256), 0, st, N, Np, count - c0, spins + (int64_t)c0 * N,
+                           S + (int64_t)c0 * Np);
+    }
     return hipGetLastError();
 }
 
-hipError_t launch_energy_reduce(int N, int Np, int count, int Cp, int splits, const double *phis, const double *S,
-                                const double *h, double *E, hipStream_t st) {
-    hipLaunchKernelGGL(k_energy_reduce, dim3(count), dim3(256), 0, st, N, Np, Cp, splits, phis, S, h, E);
+hipError_t launch_energy_sum(const EnergyPlan &e, int N, int Np, int count, const double *part, const int8_t *S,
+                             const double *h, double *E, hipStream_t st) {
+    hipLaunchKernelGGL(k_energy_sum, dim3(count), dim3(256), 0, st, N, Np, e.cp, e.units, part, S, h, E);
     return hipGetLastError();
 }
 

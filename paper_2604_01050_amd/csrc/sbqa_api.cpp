@@ -376,6 +376,16 @@ sbqa_status validate_instance(const sbqa_coupling *J, const double *h, int32_t N
     return SBQA_OK;
 }
 
+// The planes of [count rounded up to GEMM_BM][Np] doubles that callers and the
+// server's admission allow for the partial sums of float64 energies (an upper
+// bound of what energy_plan takes).
+int energy_scratch_planes(int Np, int cp) {
+    const int64_t tiles = (int64_t)(Np / GEMM_BN) * (cp / GEMM_BM), nke = (int64_t)Np * 8 / GEMM_KB;
+    int es = 1;
+    while (tiles * es < 512 && es < 8 && nke % (2 * es) == 0 && nke / (2 * es) >= 4) es *= 2;
+    return es;
+}
+
 // Geometry and byte count of a context (also used by the server's admission).
 void plan_layout(int32_t N, int32_t R, int32_t runs, const InstanceFacts &f, Layout *L) {
     const int64_t C = (int64_t)R * runs;
@@ -386,7 +396,6 @@ void plan_layout(int32_t N, int32_t R, int32_t runs, const InstanceFacts &f, Lay
     L->Cg = (int)round_up(C, 64 * L->mbw);
     L->Np = (int)round_up(N, f.path == PATH_CSR ? GEMM_BN : dense_pad(f.path));
     L->Cs = (int)round_up(C, 4);
-    L->esplits = 1;
     int64_t b = 0;
     if (f.path == PATH_CSR) {
         b += 2 * (int64_t)N * L->Cs * 4 + (int64_t)N * L->Cs * 4;        // x ping-pong, y
@@ -410,11 +419,7 @@ void plan_layout(int32_t N, int32_t R, int32_t runs, const InstanceFacts &f, Lay
     } else {
         const int planes = f.path == PATH_BF16X3 ? 2 : 1;
         L->nkc = dense_nkc(f.path, L->Np);
-        const int64_t tiles = (int64_t)(L->Np / GEMM_BN) * (L->Cp / GEMM_BM);
-        const int64_t nke = (int64_t)L->Np * 8 / GEMM_KB;
-        int es = 1;
-        while (tiles * es < 512 && es < 8 && nke % (2 * es) == 0 && nke / (2 * es) >= 4) es *= 2;
-        L->esplits = es;
+        const int es = energy_scratch_planes(L->Np, L->Cp);
         b += 3 * C * (int64_t)L->Np * 4;                                  // x ping-pong, y
         b += 2 * dense_plane_bytes(f.path, L->Cg, L->Np) * planes;        // operand ping-pong
         b += dense_j_bytes(f.path, L->Np) * planes;                       // J
@@ -977,9 +982,9 @@ sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, con
         c->g[q] = gb;
         c->g_lo[q] = glo;
     }
-    if (!path_energy_mfma(path)) {   // float64 readout spins and energy GEMM partials
-        HIP_TRY(dalloc(c, &c->S64, (size_t)Cp * Np));
-        HIP_TRY(dalloc(c, &c->phis64, (size_t)c->L.esplits * Cp * Np));
+    if (!path_energy_mfma(path)) {   // readout spins and energy partials
+        HIP_TRY(dalloc(c, &c->rspins, (size_t)Cp * Np));
+        HIP_TRY(dalloc(c, &c->epart, (size_t)energy_plan(N, C).units * Cp));
     }
     if (c->resident) {
         // small dense loop: J float32 [N][N]
@@ -1127,25 +1132,15 @@ sbqa_status ctx_state_energies(sbqa_ctx *c) {
         HIP_TRY(launch_dense_step(c->facts.path, EPI_FIELDS, c->L.mbw, c->L.Cg, a, c->stream));
         HIP_TRY(launch_energy_fields(c->N, c->L.Np, c->L.C, c->x[in], c->x[sc], h64, c->E, c->stream));
     } else {
-        HIP_TRY(launch_readout_f64(c->N, c->L.Np, c->L.C, c->L.Np, false, c->x[c->cur], c->S64, c->stream));
-        HIP_TRY(launch_gemm_f64(c->S64, c->J64, c->phis64, c->L.Np, c->L.Cp, c->L.esplits, c->stream));
-        HIP_TRY(launch_energy_reduce(c->N, c->L.Np, c->L.C, c->L.Cp, c->L.esplits, c->phis64, c->S64, h64, c->E, c->stream));
+        const EnergyPlan e = energy_plan(c->N, c->L.C);
+        HIP_TRY(launch_readout_spins(c->N, c->L.Np, c->L.C, e.cp, c->x[c->cur], c->rspins, c->stream));
+        HIP_TRY(launch_energy_gemm(e, c->rspins, c->J64, c->L.Np, c->epart, c->stream));
+        HIP_TRY(launch_energy_sum(e, c->N, c->L.Np, c->L.C, c->epart, c->rspins, h64, c->E, c->stream));
     }
     return SBQA_OK;
 }
 
-EnergyGemm energy_gemm(const sbqa_ctx *c, int count) {
-    EnergyGemm g;
-    const int Np = c->L.Np;
-    g.cp = (int)round_up(count, GEMM_BM);
-    const int64_t tiles = (int64_t)(Np / GEMM_BN) * (g.cp / GEMM_BM);
-    const int64_t nke = (int64_t)Np * 8 / GEMM_KB;
-    g.es = 1;
-    while (tiles * g.es < 512 && g.es < 8 && nke % (2 * g.es) == 0 && nke / (2 * g.es) >= 4) g.es *= 2;
-    return g;
-}
-
-sbqa_status ctx_energies_dev(sbqa_ctx *c, const int8_t *ds, int32_t count, double *E, double *S, double *P) {
+sbqa_status ctx_energies_dev(sbqa_ctx *c, const int8_t *ds, int32_t count, double *E, int8_t *S, double *P) {
     const int N = c->N;
     if (c->facts.path != PATH_CSR && !c->J64)
         return fail(SBQA_EINVAL, "this context keeps no float64 copy of J (built from sign bits)");
@@ -1153,10 +1148,10 @@ sbqa_status ctx_energies_dev(sbqa_ctx *c, const int8_t *ds, int32_t count, doubl
     if (c->facts.path == PATH_CSR) {
         HIP_TRY(launch_csr_energy_spins(N, count, c->rp, c->col, c->val64, c->tri3(), h64, ds, E, c->stream));
     } else {
-        const EnergyGemm g = energy_gemm(c, count);
-        HIP_TRY(launch_spins_to_f64(N, c->L.Np, count, ds, S, c->stream));
-        HIP_TRY(launch_gemm_f64(S, c->J64, P, c->L.Np, g.cp, g.es, c->stream));
-        HIP_TRY(launch_energy_reduce(N, c->L.Np, count, g.cp, g.es, P, S, h64, E, c->stream));
+        const EnergyPlan e = energy_plan(N, count);
+        HIP_TRY(launch_pad_spins(N, c->L.Np, count, e.cp, ds, S, c->stream));
+        HIP_TRY(launch_energy_gemm(e, S, c->J64, c->L.Np, P, c->stream));
+        HIP_TRY(launch_energy_sum(e, N, c->L.Np, count, P, S, h64, E, c->stream));
     }
     return SBQA_OK;
 }
@@ -1829,11 +1824,11 @@ sbqa_status sbqa_energy(sbqa_ctx *c, const int8_t *spins, int32_t count, double 
     HIP_TRY(hipMemcpyAsync(ds.as<int8_t>(), host ? host : spins, total, hipMemcpyHostToDevice, c->stream));
     if (!pinned) HIP_TRY(hipStreamSynchronize(c->stream));
     if (c->facts.path != PATH_CSR) {
-        const EnergyGemm g = energy_gemm(c, count);
-        HIP_TRY(S.get(sizeof(double) * g.cp * c->L.Np));
-        HIP_TRY(P.get(sizeof(double) * g.es * g.cp * c->L.Np));
+        const EnergyPlan e = energy_plan(N, count);
+        HIP_TRY(S.get((size_t)e.cp * c->L.Np));
+        HIP_TRY(P.get(sizeof(double) * e.units * e.cp));
     }
-    sbqa_status st = ctx_energies_dev(c, ds.as<int8_t>(), count, E.as<double>(), S.as<double>(), P.as<double>());
+    sbqa_status st = ctx_energies_dev(c, ds.as<int8_t>(), count, E.as<double>(), S.as<int8_t>(), P.as<double>());
     if (st != SBQA_OK) return st;
     // (the spins in the stage have been read by then: same stream)
     HIP_TRY(hipMemcpyAsync(pinned ? stage.as<double>() : out, E.as<double>(), espace, hipMemcpyDeviceToHost, c->stream));

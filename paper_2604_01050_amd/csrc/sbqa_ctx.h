@@ -37,12 +37,11 @@ constexpr bool path_energy_mfma(Path p) {
 struct Layout {
     int C = 0;        // runs * R
     int Np = 0;       // N padded to dense_pad(path) (dense)
-    int Cp = 0;       // C padded to GEMM_BM (rows of the fp64 energy GEMM)
+    int Cp = 0;       // C padded to GEMM_BM (rows of the fp64 energies)
     int Cg = 0;       // C padded to 64 * mbw (rows of the contraction operand)
     int mbw = 1;      // m-blocks per wave of the dense step
     int nkc = 0;      // K chunks of 128 bytes per operand row (dense)
     int Cs = 0;       // C padded to 4 (CSR row stride)
-    int esplits = 1;  // K splits of the fp64 energy GEMM
     int csr_nrb = 0;  // row blocks of the CSR energy reduction
     size_t bytes = 0; // device bytes (without the schedule table)
 };
@@ -56,6 +55,7 @@ const char *last_error();
 sbqa_status validate_instance(const sbqa_coupling *J, const double *h, int32_t N, int32_t R, int32_t runs,
                               const sbqa_schedule *s, InstanceFacts *facts,
                               std::vector<uint32_t> *sign_bits = nullptr);
+int energy_scratch_planes(int Np, int cp);
 void plan_layout(int32_t N, int32_t R, int32_t runs, const InstanceFacts &f, Layout *L);
 size_t instance_bytes(int32_t N, int32_t R, int32_t runs, const InstanceFacts &f, uint32_t steps);
 StepCoef step_coef(const sbqa_schedule *s, double c0, int R, uint32_t n);
@@ -79,15 +79,10 @@ sbqa_status ctx_sync(sbqa_ctx *c);         // fetch the error word, synchronise,
 sbqa_status ctx_evaluate(sbqa_ctx *c, bool reset = false);
 // Energies of count spin rows already on the device in the internal spin
 // order (ds [count][N] int8 +-1) into E [count], on the context's stream.
-// Dense couplings need float64 scratch S [cp][Np] and P [es][cp][Np] with the
-// sizes energy_gemm gives (the GEMM's K splits follow the shape, so every
-// caller sums in the same order); CSR couplings need none (S, P unused).
-struct EnergyGemm {
-    int cp = 0;   // count padded to GEMM_BM
-    int es = 1;   // K splits
-};
-EnergyGemm energy_gemm(const sbqa_ctx *c, int count);
-sbqa_status ctx_energies_dev(sbqa_ctx *c, const int8_t *ds, int32_t count, double *E, double *S, double *P);
+// Dense couplings need scratch S int8 [cp][Np] and P float64 [units][cp] with
+// the sizes energy_plan gives (it follows the shape alone, so every caller sums
+// in the same order); CSR couplings need none (S, P unused).
+sbqa_status ctx_energies_dev(sbqa_ctx *c, const int8_t *ds, int32_t count, double *E, int8_t *S, double *P);
 
 }  // namespace sbqa
 
@@ -150,7 +145,8 @@ struct sbqa_ctx {
     float *h32 = nullptr;
     double *h64 = nullptr;
     float *jp = nullptr;                // device J_perp table [runs][steps]
-    double *S64 = nullptr, *phis64 = nullptr;
+    int8_t *rspins = nullptr;           // dense real J: readout spins [cp][Np] and
+    double *epart = nullptr;            // energy partials (EnergyPlan)
     double *csr_partial = nullptr;
     double *E = nullptr;
     int64_t *bestStep = nullptr;

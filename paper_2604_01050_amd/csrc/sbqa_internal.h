@@ -18,13 +18,12 @@ enum Path : int32_t {
 constexpr bool path_fp4(Path p) { return p == PATH_FP4 || p == PATH_FP4PK; }
 constexpr bool path_packed(Path p) { return p == PATH_FP8PK || p == PATH_FP4PK; }
 
-// Tiling of the fp64 energy GEMM (row-major operands).
-// Output tile: GEMM_BM columns c (replicas) x GEMM_BN rows i (spins);
-// each k-tile carries GEMM_KB bytes of K per row.
+// Tiling of the fp64 energies (row-major operands): GEMM_BM spin rows x
+// GEMM_BN spins, GEMM_KB bytes of J's rows per K tile.
 constexpr int GEMM_BM = 128;
 constexpr int GEMM_BN = 128;
 constexpr int GEMM_KB = 128;
-constexpr int GEMM_THREADS = 256;
+constexpr int GEMM_THREADS = 512;
 
 // Order of a state buffer (x, y, and the CSR operand) in device memory:
 //   ORDER_SPIN_MAJOR    [rows][ld]: CSR contexts stepped one launch per step;
@@ -50,11 +49,18 @@ struct StepCoef {
     float delta_next;  // Delta_{n+1} (Eq. 8) for the operand emitted by this step
 };
 
-// fp64 GEMM for energies: out[z][Cp][Np] = A[Cp][Np] x B[Np][Np] over the K
-// range of split z (both operands row-major, K-contiguous). Cp % GEMM_BM == 0,
-// Np % GEMM_BN == 0, Np*8 % (splits*GEMM_KB) == 0.
-hipError_t launch_gemm_f64(const double *A, const double *B, double *out, int Np, int Cp, int splits,
-                           hipStream_t st);
+// Energies of `count` spin rows with a dense J (kernels_dense.hip,
+// k_energy_gemm): S int8 [cp][Np], zero in the padding; J float64 [Np][Np]
+// symmetric, zero padded, Np >= 128 * T; part float64 [units][cp].
+struct EnergyPlan {
+    int T = 0;        // blocks of 128 spins
+    int Z = 1;        // K ranges of a pair of blocks
+    int units = 0;    // work units: pairs x Z
+    int cp = 0;       // count rounded up to GEMM_BM
+};
+EnergyPlan energy_plan(int N, int count);
+hipError_t launch_energy_gemm(const EnergyPlan &e, const int8_t *S, const double *J, int Np, double *part,
+                              hipStream_t st);
 
 // ---- dense contraction path -------------------------------------------------
 // The coupling matrix J and the operand f(X) of the dense paths are stored as
@@ -314,10 +320,9 @@ hipError_t launch_init_state(int N, int C, int order, int ld, uint64_t seed, dou
 hipError_t launch_state_reorder(int N, int C, int order_in, int ld_in, const float *src, const int32_t *row_in,
                                 int order_out, int ld_out, float *dst, const int32_t *row_out, hipStream_t st);
 
-// Readout spins sign(x) (sign(0) = +1) as float64 +-1 into S[Cp][Np]
-// (zero padding) from the state, for the energy GEMM.
-hipError_t launch_readout_f64(int N, int Np, int C, int ld, bool spin_major, const float *x,
-                              double *S, hipStream_t st);
+// Readout spins sign(x) (sign(0) = +1) of a replica-major state [C][Np] as int8
+// +-1 into S[cp][Np] (zero padding), for the dense energies.
+hipError_t launch_readout_spins(int N, int Np, int C, int cp, const float *x, int8_t *S, hipStream_t st);
 
 // Row-major N x N float64 src into the first N columns of the rows of dst
 // (row length Np >= N; the rest of dst is left as it is).
@@ -330,14 +335,12 @@ hipError_t launch_copy_to_host(const uint8_t *src, uint8_t *dst, size_t bytes, h
 // caller's spin orig[i]).
 hipError_t launch_spins_to_rows(int N, int count, const int32_t *orig, const int8_t *in, int8_t *out, hipStream_t st);
 
-// int8 spins [count][N] -> float64 S[Cp][Np].
-hipError_t launch_spins_to_f64(int N, int Np, int count, const int8_t *spins, double *S,
-                               hipStream_t st);
+// int8 spins [count][N] -> S[cp][Np], zero in the padding.
+hipError_t launch_pad_spins(int N, int Np, int count, int cp, const int8_t *spins, int8_t *S, hipStream_t st);
 
-// E[c] = sum_i s_ci (-1/2 sum_z phis[z][c][i] - h_i), fixed-order reduction.
-hipError_t launch_energy_reduce(int N, int Np, int count, int Cp, int splits,
-                                const double *phis, const double *S, const double *h,
-                                double *E, hipStream_t st);
+// E[c] = sum_u part[u][c] - sum_i h_i s_ci, fixed-order reduction.
+hipError_t launch_energy_sum(const EnergyPlan &e, int N, int Np, int count, const double *part, const int8_t *S,
+                             const double *h, double *E, hipStream_t st);
 
 // CSR energies of the readout of x (element (i, c) at state_off(order, ld, i, c))
 // or of given spins. The state energies are summed in one fixed order: per

@@ -63,15 +63,16 @@ extern "C" sbqa_status sbqa_energy_noalloc(sbqa_ctx *c, const int8_t *spins, int
     if (count < 0) return fail(SBQA_EINVAL, "count must be >= 0");
     if (count == 0) return SBQA_OK;
     const int N = c->N;
-    // scratch plan: relabelled rows (CSR), or S [cp][Np] and P [es][cp][Np] (dense)
+    // scratch plan: relabelled rows (CSR), or spin rows S and partial sums P (dense)
     size_t off_rows = 0, off_S = 0, off_P = 0, need = 0;
     const bool relabel = c->facts.path == PATH_CSR && !c->pnew.empty();
-    EnergyGemm g;
     if (c->facts.path != PATH_CSR) {
-        g = energy_gemm(c, count);
+        // the documented allowance; S int8 [cp][Np] and P [units][cp] take less
+        // (units <= 16 * ceil(N / 256), at most Np doubles per row of P)
+        const EnergyPlan e = energy_plan(N, count);
         off_S = 0;
-        off_P = align256(sizeof(double) * (size_t)g.cp * c->L.Np);
-        need = off_P + sizeof(double) * (size_t)g.es * g.cp * c->L.Np;
+        off_P = align256(sizeof(double) * (size_t)e.cp * c->L.Np);
+        need = off_P + sizeof(double) * (size_t)energy_scratch_planes(c->L.Np, e.cp) * e.cp * c->L.Np;
     } else if (relabel) {
         off_rows = 0;
         need = (size_t)count * N;
@@ -91,7 +92,7 @@ extern "C" sbqa_status sbqa_energy_noalloc(sbqa_ctx *c, const int8_t *spins, int
         if (e != hipSuccess) return fail(SBQA_EDEVICE, "spins to rows: %s", hipGetErrorString(e));
         ds = rows;
     }
-    double *S = c->facts.path != PATH_CSR ? reinterpret_cast<double *>(base + off_S) : nullptr;
+    int8_t *S = c->facts.path != PATH_CSR ? reinterpret_cast<int8_t *>(base + off_S) : nullptr;
     double *P = c->facts.path != PATH_CSR ? reinterpret_cast<double *>(base + off_P) : nullptr;
     return ctx_energies_dev(c, ds, count, out, S, P);
 }

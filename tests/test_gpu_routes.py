@@ -146,3 +146,26 @@ def test_dense_step_tiles_by_grid(sb, coup, prec, fmode, packing):
         for a, b in zip(ref[0], got):
             assert np.array_equal(a[:, :C], b)
         assert np.array_equal(ref[1][:few], E) and np.array_equal(ref[2][:few], s)
+
+
+@pytest.mark.parametrize("N,count", [(1, 1), (127, 3), (128, 128), (129, 129), (257, 5), (640, 300), (1000, 1), (2100, 130)])
+def test_energies_from_the_lower_triangle(sb, N, count):
+    """float64 energies of given spins with real and integer couplings: blocks
+    of 128 spins alone, in pairs and with a middle one, part rows; integer
+    couplings exact, real ones within 1e-13 of the sum of magnitudes."""
+    s = inst.spins_pm1(count, N, 51)
+    for J, h in ((inst.dense_gaussian(N, 52), inst.gaussian_fields(N, 0.5, 53)),
+                 (inst.sidon28_dense(N, 54) * 1001.0, np.round(inst.gaussian_fields(N, 9.0, 55)))):
+        _log("energies N=%d count=%d" % (N, count))
+        ctx = sb.sbqa_create(J=J, h=h, R=1, runs=1, steps=1, precision=sb.PREC_FP32)
+        E = sb.sbqa_energy(ctx, s)
+        sl, Jl, hl = s.astype(np.longdouble), J.astype(np.longdouble), h.astype(np.longdouble)
+        ref = np.array([-(r @ (Jl @ r)) / 2 - hl @ r for r in sl[:8]])
+        scale = np.abs(Jl).sum() / 2 + np.abs(hl).sum()
+        if np.array_equal(J, np.round(J)):
+            assert np.array_equal(E[:8], ref.astype(np.float64))
+        else:
+            assert np.all(np.abs(E[:8] - ref) <= 1e-13 * scale)
+        if count > 8:   # the rest against plain float64
+            f = s.astype(np.float64)
+            assert np.all(np.abs(E - (-0.5 * (f * (f @ J)).sum(1) - f @ h)) <= 1e-13 * float(scale))
