@@ -9,7 +9,7 @@
 //   * the fp64 energies of spin rows (Eq. 2 at the corners).
 // State is replica-major ([C][Np]); the contraction operands are
 // fragment-tiled (see sbqa_internal.h).
-#include "sbqa_internal.h"
+#include "csr_step.h"
 
 #include <type_traits>
 #include <utility>
@@ -655,7 +655,7 @@ __global__ __launch_bounds__(2 * DENSE_THREADS) void k_dense_step_cg2(const Dens
 // 5.1 us of the 10.3 us a step takes; four such chains, LDS and barriers in the
 // 64-spin tile 32.2), then by the L1 fill.
 template <int PATH, int NB, int PD, int EPI>
-__global__ __launch_bounds__(DENSE_THREADS) void k_dense_step_fine(const DenseStepArgs a) {
+__device__ __forceinline__ void dense_fine_body(const DenseStepArgs &a, int bx, int by) {
     constexpr int PL = Pipe<PATH>::planes;
     constexpr int NT = Terms<PATH>::n;
     constexpr int RBG = DENSE_TN / 16;            // row blocks per J group
@@ -664,7 +664,7 @@ __global__ __launch_bounds__(DENSE_THREADS) void k_dense_step_fine(const DenseSt
     using JWord = std::conditional_t<is_fp4<PATH>, uint2, uint32_t>;
     __shared__ __align__(16) uint8_t lds[4 * 16 * (16 * NB + 4) * 4];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int mb = blockIdx.y * 4 + w, rb0 = blockIdx.x * NB, nkc = a.nkc, l16 = lane * 16;
+    const int mb = by * 4 + w, rb0 = bx * NB, nkc = a.nkc, l16 = lane * 16;
     const int xstep = a.mbw * FRAG_BYTES;
     const int64_t xo = (int64_t)(mb / a.mbw) * nkc * xstep + (mb % a.mbw) * FRAG_BYTES + l16;
     const uint8_t *xsrc = a.g + xo, *xsrc_lo = (PL == 2) ? a.g_lo + xo : xsrc;
@@ -744,6 +744,11 @@ __global__ __launch_bounds__(DENSE_THREADS) void k_dense_step_fine(const DenseSt
         }
     }
     dense_epilogue<PATH, 1, EPI, 16 * NB, 0>(a, acc, rb0 * 16, mb, lds);
+}
+
+template <int PATH, int NB, int PD, int EPI>
+__global__ __launch_bounds__(DENSE_THREADS) void k_dense_step_fine(const DenseStepArgs a) {
+    dense_fine_body<PATH, NB, PD, EPI>(a, blockIdx.x, blockIdx.y);
 }
 
 // K chunks in flight per wave in the split-K kernel (fp8 and fp4 alike;
@@ -996,24 +1001,26 @@ __global__ __launch_bounds__(256) void k_convert_j_pk_bits(const uint32_t *__res
     });
 }
 
-template <int PATH, int MBW>
-__global__ __launch_bounds__(DENSE_THREADS) void k_group_dense(const GroupHeader *__restrict__ hdr,
-                                                               const GroupTask *__restrict__ tasks, int offset) {
+// Calls step(args, block of the task) for the virtual blocks blockIdx.x,
+// blockIdx.x + stride, ...
+template <class F>
+__device__ __forceinline__ void group_blocks(const GroupHeader *hdr, const GroupTask *tasks, int offset, int stride,
+                                             F &&step) {
     const int ntask = hdr->ntask, total = hdr->total_blocks;
-    for (int vb = blockIdx.x; vb < total; vb += gridDim.x) {
+    for (int vb = blockIdx.x; vb < total; vb += stride) {
         int q = 0;
         while (q + 1 < ntask && tasks[q + 1].first_block <= vb) ++q;
         const GroupTask &t = tasks[q];
         const int n = t.n_base + offset;
         if (n >= t.n_end) continue;
-        const int in = n & 1, lt = vb - t.first_block;
+        const int in = n & 1;
         DenseStepArgs a;
         a.N = t.N;
         a.Np = t.ld;
         a.R = t.R;
         a.C = t.C;
         a.nkc = t.nkc;
-        a.mbw = MBW;
+        a.mbw = t.mbw;
         a.reverse = in;
         a.J = static_cast<const uint8_t *>(t.J);
         a.J_lo = static_cast<const uint8_t *>(t.J_lo);
@@ -1034,9 +1041,38 @@ __global__ __launch_bounds__(DENSE_THREADS) void k_group_dense(const GroupHeader
         a.k.kD = t.kD;
         a.k.delta_next = t.delta[n + 1];
         a.fmode = t.fmode;
-        dense_step_body<PATH, MBW, EPI_UPDATE>(a, lt % t.nchunk, lt / t.nchunk);
+        const int lt = vb - t.first_block;
+        step(a, lt % t.nchunk, lt / t.nchunk);
     }
 }
+
+template <int PATH, int MBW>
+__global__ __launch_bounds__(DENSE_THREADS) void k_group_dense(const GroupHeader *__restrict__ hdr,
+                                                               const GroupTask *__restrict__ tasks, int offset) {
+    group_blocks(hdr, tasks, offset, gridDim.x,
+                 [](const DenseStepArgs &a, int bx, int by) { dense_step_body<PATH, MBW, EPI_UPDATE>(a, bx, by); });
+}
+
+// The same with the fine tiles (tasks whose nchunk counts tiles of 16 * NB
+// spins) in the first ndense workgroups; those behind step the sparse tasks
+// (ternary f, ring by lane reads) of chdr/ctasks.
+template <int PATH, int NB>
+__global__ __launch_bounds__(DENSE_THREADS) void k_group_dense_fine(const GroupHeader *__restrict__ hdr,
+                                                                    const GroupTask *__restrict__ tasks, int ndense,
+                                                                    const GroupHeader *__restrict__ chdr,
+                                                                    const GroupTask *__restrict__ ctasks,
+                                                                    int offset) {
+    if ((int)blockIdx.x >= ndense) {
+        csr::csr_group_blocks<false, true>(chdr, ctasks, offset, blockIdx.x - ndense, gridDim.x - ndense);
+        return;
+    }
+    // the chunk count of every instance is a multiple of it (dense_pad)
+    constexpr int PD = dense_pad(Path(PATH)) / path_kpc(Path(PATH)) % 4 == 0 ? 4 : 2;
+    group_blocks(hdr, tasks, offset, ndense, [](const DenseStepArgs &a, int bx, int by) {
+        dense_fine_body<PATH, NB, PD, EPI_UPDATE>(a, bx, by);
+    });
+}
+static_assert(DENSE_THREADS == csr::WAVES * 64, "sparse tasks ride in the dense launch");
 
 // Operand f(X) from the state: one thread per 4 consecutive spins of column c.
 template <int PATH>
@@ -1080,9 +1116,9 @@ __global__ __launch_bounds__(256) void k_readout_operand(int N, int Np, int nkc,
 // 256 (768) fp4 17.9 / 23.5 / 18.5.
 constexpr int MI355X_CUS = 256;
 inline int fine_spins(Path path, int Np, int Cg) {
-    const int cb = Cg / 64, limit = path_packed(path) ? 2 * MI355X_CUS : MI355X_CUS;
-    if (Np / 16 * cb <= MI355X_CUS) return 16;
-    return Np / 32 * cb <= limit ? 32 : 0;
+    const int64_t blocks = (int64_t)Np / 16 * (Cg / 64);
+    if (blocks <= MI355X_CUS) return 16;
+    return blocks / 2 <= (path_packed(path) ? 2 : 1) * MI355X_CUS ? 32 : 0;
 }
 
 template <int PATH, int NB, int EPI>
@@ -1216,8 +1252,8 @@ hipError_t launch_convert_j(Path path, const double *J64, int Np, int nkc, void 
     return hipGetLastError();
 }
 
-hipError_t launch_group_dense(Path path, int mbw, const GroupHeader *hdr, const GroupTask *tasks, int grid,
-                              int offset, hipStream_t st) {
+hipError_t launch_group_dense(Path path, int mbw, const GroupHeader *hdr, const GroupTask *tasks, int grid, int offset,
+                              hipStream_t st) {
     if (grid < 1) return hipErrorInvalidValue;
 #define SBQA_GD(P, M) hipLaunchKernelGGL((k_group_dense<P, M>), dim3(grid), dim3(DENSE_THREADS), 0, st, hdr, tasks, offset)
 #define SBQA_GD_PATH(P)                 \
@@ -1239,6 +1275,27 @@ hipError_t launch_group_dense(Path path, int mbw, const GroupHeader *hdr, const 
     }
 #undef SBQA_GD_PATH
 #undef SBQA_GD
+    return hipGetLastError();
+}
+
+hipError_t launch_group_fine(Path path, int spins, const GroupHeader *hdr, const GroupTask *tasks, int grid,
+                             const GroupHeader *chdr, const GroupTask *ctasks, int cgrid, int offset, hipStream_t st) {
+    if (grid < 1 || cgrid < 0 || (spins != 16 && spins != 32)) return hipErrorInvalidValue;
+#define SBQA_GFN(P, NB)                                                                                            \
+    hipLaunchKernelGGL((k_group_dense_fine<P, NB>), dim3(grid + cgrid), dim3(DENSE_THREADS), 0, st, hdr, tasks, grid, \
+                       chdr, ctasks, offset)
+#define SBQA_GF(P)                      \
+    case P:                             \
+        if (spins == 16) SBQA_GFN(P, 1); \
+        else SBQA_GFN(P, 2);            \
+        break;
+    switch (path) {
+        SBQA_GF(PATH_F32) SBQA_GF(PATH_FP8) SBQA_GF(PATH_BF16X3) SBQA_GF(PATH_I8) SBQA_GF(PATH_FP8PK)
+        SBQA_GF(PATH_FP4) SBQA_GF(PATH_FP4PK)
+        default: return hipErrorInvalidValue;
+    }
+#undef SBQA_GF
+#undef SBQA_GFN
     return hipGetLastError();
 }
 

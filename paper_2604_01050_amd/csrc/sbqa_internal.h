@@ -158,7 +158,7 @@ struct GroupTask {
     int N, ld;               // spins; state row stride (CSR: Cs, dense: Np)
     int R, C;
     int nchunk;              // CSR: column chunks of the step; dense: spin tiles (Np / DENSE_TN)
-    int nkc, fmode;
+    int nkc, mbw, fmode;     // dense: K chunks; row blocks per operand group
     float kB, dt, kD;
     float *x[2];
     float *y;
@@ -177,8 +177,15 @@ int csr_step_chunks(int C);
 bool csr_ring_shfl(int R);
 hipError_t launch_group_csr(bool ballistic, bool shfl, const GroupHeader *hdr, const GroupTask *tasks, int grid,
                             int offset, hipStream_t st);
-hipError_t launch_group_dense(Path path, int mbw, const GroupHeader *hdr, const GroupTask *tasks, int grid,
-                              int offset, hipStream_t st);
+// One wave that ends after us microseconds.
+hipError_t launch_hold(int us, hipStream_t st);
+hipError_t launch_group_dense(Path path, int mbw, const GroupHeader *hdr, const GroupTask *tasks, int grid, int offset,
+                              hipStream_t st);
+// The fine form: tiles of 16 or 32 spins (the tasks' nchunk counts them, their
+// mbw may differ), and in cgrid further workgroups the sparse tasks of
+// chdr/ctasks (ternary f, csr_ring_shfl).
+hipError_t launch_group_fine(Path path, int spins, const GroupHeader *hdr, const GroupTask *tasks, int grid,
+                             const GroupHeader *chdr, const GroupTask *ctasks, int cgrid, int offset, hipStream_t st);
 
 // J in the contraction precision (fragment-tiled, groups of DENSE_TN/16 row
 // blocks) from the zero-padded row-major float64 J64 [Np][Np].

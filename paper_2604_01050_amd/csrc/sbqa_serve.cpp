@@ -5,8 +5,9 @@
 // the head of the queue is admitted as soon as a slot is free and its device
 // footprint fits the remaining budget. All resident instances then advance
 // together in step blocks of up to STEP_BLOCK steps: every step is one
-// grouped launch per kernel specialisation (dense path x m-blocks per wave,
-// CSR ballistic x ring by lane reads), a grid-stride loop over the workgroups
+// grouped launch per kernel specialisation (dense path, with 64-spin tiles x
+// m-blocks per wave, with fine tiles together with a sparse group; CSR
+// ballistic x ring by lane reads), a grid-stride loop over the workgroups
 // of all instances of the group, driven by a device task table that the
 // scheduler rewrites between blocks. Each instance runs exactly the
 // workgroups its standalone kernel would run, so its result does not depend
@@ -41,24 +42,46 @@ constexpr Path DENSE_PATHS[7] = {PATH_F32, PATH_FP8, PATH_BF16X3, PATH_I8, PATH_
 constexpr int NDENSE_GROUPS = 21;
 constexpr int NGROUPS = NDENSE_GROUPS + 4;
 constexpr int DENSE_GRID_CAP = 512;   // workgroups of one grouped dense launch at most
-// Groups present in a step block run as parallel branches (one side stream
-// each, forked from and joined to the server stream): they touch disjoint
-// instances, so the GPU may overlap them.
-constexpr int NBRANCH = 4;
+constexpr int FINE_GRID_CAP = 1024;   // the same with the fine tiles (a third of the registers)
 constexpr int CSR_GRID_CAP = 2048;
+// The sparse group of ternary f and ring by lane reads, which rides in the
+// launches of the first dense group with fine tiles
+constexpr int RIDER = NDENSE_GROUPS + 1;
 typedef std::chrono::steady_clock Clock;
 
-int group_of(const sbqa_ctx *c) {
-    if (c->facts.path == PATH_CSR)
-        return NDENSE_GROUPS + 2 * (c->s.fmode == SBQA_F_BALLISTIC ? 1 : 0) + (csr_ring_shfl(c->R) ? 1 : 0);
-    const int mi = c->L.mbw == 1 ? 0 : c->L.mbw == 2 ? 1 : 2;
+int path_index(const sbqa_ctx *c) {
     int pi = 0;
     while (DENSE_PATHS[pi] != c->facts.path) ++pi;
+    return pi;
+}
+
+// Group of a context; fine: the tile of its path's groups, whose fine form
+// takes every m-block count in one launch.
+int group_of(const sbqa_ctx *c, const int *fine) {
+    if (c->facts.path == PATH_CSR)
+        return NDENSE_GROUPS + 2 * (c->s.fmode == SBQA_F_BALLISTIC ? 1 : 0) + (csr_ring_shfl(c->R) ? 1 : 0);
+    const int pi = path_index(c), mi = fine[pi] ? 0 : c->L.mbw == 1 ? 0 : c->L.mbw == 2 ? 1 : 2;
     return pi * 3 + mi;
 }
 
-// Table entry of context c for steps [c->step, n_end).
-GroupTask make_task(const sbqa_ctx *c, int first_block, uint32_t n_end) {
+// Spins per tile of a dense path's steps from its 16-spin x 64-column blocks
+// over all instances (0: the 64-spin tiles). The finer tiles shorten the chain
+// that an instance's step is, fill the CUs, and take every m-block count and
+// the sparse group in the same launch; with bit-packed J they pay until the
+// blocks are many times the CUs. A batch of 16 (half of it dense fp8, N up to
+// 4096, C = 128, 400 steps): 16.9 ms with 64-spin tiles, the groups as branches
+// of one graph; 14.3 so (15.7 / 14.2 / 13.9 with a limit of 1024 / 1600 / 2400
+// blocks and the sparse group on a branch, which cost 17 and more where the
+// streams that branches need shared a queue with the creator's). 32 with N up to
+// 8192 (150 steps): 23.9, now 22. Other J: one tile of 32 spins per CU, as for a
+// single instance.
+int group_fine(Path path, int64_t blocks16) {
+    return blocks16 <= 256 ? 16 : blocks16 <= (path_packed(path) ? 2400 : 512) ? 32 : 0;
+}
+int64_t dense_blocks16(const sbqa_ctx *c) { return (int64_t)c->L.Np / 16 * (c->L.Cg / 64); }
+
+// Table entry of context c for steps [c->step, n_end); fine: its group's tile.
+GroupTask make_task(const sbqa_ctx *c, int first_block, uint32_t n_end, int fine) {
     GroupTask t;
     std::memset(&t, 0, sizeof t);
     const StepCoef k = step_coef(&c->s, c->c0, c->R, c->step);
@@ -95,8 +118,9 @@ GroupTask make_task(const sbqa_ctx *c, int first_block, uint32_t n_end) {
     } else {
         t.ld = c->L.Np;
         t.nkc = c->L.nkc;
-        t.nchunk = c->L.Np / DENSE_TN;
-        t.nblocks = t.nchunk * (c->L.Cg / (64 * c->L.mbw));
+        t.mbw = c->L.mbw;
+        t.nchunk = c->L.Np / (fine ? fine : DENSE_TN);
+        t.nblocks = t.nchunk * (c->L.Cg / (fine ? 64 : 64 * c->L.mbw));
         t.J = c->Jd;
         t.J_lo = c->Jd_lo;
     }
@@ -170,10 +194,8 @@ struct sbqa_server {
     GroupTask *d_tasks = nullptr;
     GroupHeader *d_hdr = nullptr;
     // full step blocks are replayed from HIP graphs, one per set of groups
-    // present (the kernels read membership from the task table)
-    std::map<uint32_t, hipGraphExec_t> graphs;
-    hipStream_t side[NBRANCH] = {};
-    hipEvent_t fork_ev = nullptr, join_ev[NBRANCH] = {};
+    // present and their tiles (the kernels read membership from the task table)
+    std::map<uint64_t, hipGraphExec_t> graphs;
     // stats (guarded by mu)
     uint64_t completed = 0;
     double updates = 0.0;
@@ -240,20 +262,26 @@ static void finish(sbqa_server *srv, Slot &sl, sbqa_status st, const char *msg) 
 }
 
 // One step block for every resident instance: rewrite the task table, then
-// per step one grouped launch per group present. Returns the first failure.
+// per step one grouped launch per group present (a sparse group may ride in a
+// dense one's). Returns the first failure.
 static sbqa_status step_block(sbqa_server *srv, std::vector<Slot> &slots, int parity) {
     GroupTask *ht = srv->h_tasks[parity];
     GroupHeader *hh = srv->h_hdr[parity];
     HIP_CHECK_SERVE(hipEventSynchronize(srv->h_free[parity]));   // host table q no longer read by a copy
-    int cnt[NGROUPS] = {0}, total[NGROUPS] = {0};
+    int cnt[NGROUPS] = {0}, total[NGROUPS] = {0}, fine[7] = {0};
+    int64_t blocks16[7] = {0};
     uint32_t steps = 0;
+    for (Slot &sl : slots)
+        if (sl.ctx && sl.ctx->step < sl.ctx->s.steps && sl.ctx->facts.path != PATH_CSR)
+            blocks16[path_index(sl.ctx)] += dense_blocks16(sl.ctx);
+    for (int p = 0; p < 7; ++p) fine[p] = group_fine(DENSE_PATHS[p], blocks16[p]);
     for (Slot &sl : slots) {
         sbqa_ctx *c = sl.ctx;
         if (!c || c->step >= c->s.steps) continue;
         uint32_t n_end = std::min(c->s.steps, c->step + STEP_BLOCK);
         if (c->s.energy_every) n_end = std::min(n_end, (c->step / c->s.energy_every + 1) * c->s.energy_every);
-        const int g = group_of(c);
-        ht[g * srv->max_slots + cnt[g]] = make_task(c, total[g], n_end);
+        const int g = group_of(c, fine);
+        ht[g * srv->max_slots + cnt[g]] = make_task(c, total[g], n_end, g < NDENSE_GROUPS ? fine[g / 3] : 0);
         total[g] += ht[g * srv->max_slots + cnt[g]].nblocks;
         ++cnt[g];
         steps = std::max(steps, n_end - c->step);
@@ -264,42 +292,40 @@ static sbqa_status step_block(sbqa_server *srv, std::vector<Slot> &slots, int pa
     HIP_CHECK_SERVE(hipMemcpyAsync(srv->d_tasks, ht, sizeof(GroupTask) * NGROUPS * srv->max_slots,
                                    hipMemcpyHostToDevice, srv->stream));
     HIP_CHECK_SERVE(hipEventRecord(srv->h_free[parity], srv->stream));
-    uint32_t mask = 0;
-    for (int g = 0; g < NGROUPS; ++g)
-        if (cnt[g]) mask |= 1u << g;
-    // full grids (capped) inside graphs, so that a graph serves any membership;
-    // the k-th group present runs on branch k % NBRANCH, its steps in order
-    int present[NGROUPS], np = 0;
-    for (int g = 0; g < NGROUPS; ++g)
-        if (mask & (1u << g)) present[np++] = g;
-    const int nb = std::min(np, NBRANCH);
+    int present[NGROUPS], np = 0, host = -1;
+    uint64_t key = 0;   // 4 values per group: absent, present with 64-, 16- or 32-spin tiles
+    for (int g = 0; g < NGROUPS; ++g) {
+        if (!cnt[g]) continue;
+        const int f = g < NDENSE_GROUPS ? fine[g / 3] : 0;
+        key |= (uint64_t)(1 + f / 16) << (2 * g);
+        if (f && host < 0) host = g;
+        if (g != RIDER || host < 0) present[np++] = g;
+    }
+    // full_grid: the capped grids whatever the membership, as a graph that
+    // serves any needs
     auto launch_all = [&](uint32_t nsteps, bool full_grid) -> sbqa_status {
-        HIP_CHECK_SERVE(hipEventRecord(srv->fork_ev, srv->stream));
-        for (int b = 0; b < nb; ++b) {
-            hipStream_t bs = srv->side[b];
-            HIP_CHECK_SERVE(hipStreamWaitEvent(bs, srv->fork_ev, 0));
-            for (uint32_t off = 0; off < nsteps; ++off)
-                for (int k = b; k < np; k += NBRANCH) {
-                    const int g = present[k];
-                    const GroupHeader *dh = srv->d_hdr + g;
-                    const GroupTask *dt = srv->d_tasks + (size_t)g * srv->max_slots;
-                    if (g < NDENSE_GROUPS) {
-                        const int mbw = (g % 3 == 0) ? 1 : (g % 3 == 1) ? 2 : 4;
-                        const int grid = full_grid ? DENSE_GRID_CAP : std::min(total[g], DENSE_GRID_CAP);
-                        HIP_CHECK_SERVE(launch_group_dense(DENSE_PATHS[g / 3], mbw, dh, dt, grid, (int)off, bs));
-                    } else {
-                        const int q = g - NDENSE_GROUPS;
-                        const int grid = full_grid ? CSR_GRID_CAP : std::min(total[g], CSR_GRID_CAP);
-                        HIP_CHECK_SERVE(launch_group_csr(q >= 2, q & 1, dh, dt, grid, (int)off, bs));
-                    }
-                }
-            HIP_CHECK_SERVE(hipEventRecord(srv->join_ev[b], bs));
-            HIP_CHECK_SERVE(hipStreamWaitEvent(srv->stream, srv->join_ev[b], 0));
+        auto hdr = [&](int g) { return srv->d_hdr + g; };
+        auto tasks = [&](int g) { return srv->d_tasks + (size_t)g * srv->max_slots; };
+        auto grid = [&](int g, int cap) { return full_grid ? cap : std::min(total[g], cap); };
+        for (int k = 0; k < np; ++k) {
+            const int g = present[k], f = g < NDENSE_GROUPS ? fine[g / 3] : 0;
+            const int riders = g == host && cnt[RIDER] ? grid(RIDER, CSR_GRID_CAP) : 0;
+            for (int off = 0; off < (int)nsteps; ++off) {
+                if (f)
+                    HIP_CHECK_SERVE(launch_group_fine(DENSE_PATHS[g / 3], f, hdr(g), tasks(g), grid(g, FINE_GRID_CAP),
+                                                      hdr(RIDER), tasks(RIDER), riders, off, srv->stream));
+                else if (g < NDENSE_GROUPS)
+                    HIP_CHECK_SERVE(launch_group_dense(DENSE_PATHS[g / 3], 1 << (g % 3), hdr(g), tasks(g),
+                                                       grid(g, DENSE_GRID_CAP), off, srv->stream));
+                else
+                    HIP_CHECK_SERVE(launch_group_csr(g >= NDENSE_GROUPS + 2, (g - NDENSE_GROUPS) & 1, hdr(g), tasks(g),
+                                                     grid(g, CSR_GRID_CAP), off, srv->stream));
+            }
         }
         return SBQA_OK;
     };
     if (steps == STEP_BLOCK) {
-        auto it = srv->graphs.find(mask);
+        auto it = srv->graphs.find(key);
         if (it == srv->graphs.end()) {
             hipGraph_t graph = nullptr;
             hipGraphExec_t exec = nullptr;
@@ -314,7 +340,7 @@ static sbqa_status step_block(sbqa_server *srv, std::vector<Slot> &slots, int pa
             const hipError_t ei = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
             (void)hipGraphDestroy(graph);
             HIP_CHECK_SERVE(ei);
-            it = srv->graphs.emplace(mask, exec).first;
+            it = srv->graphs.emplace(key, exec).first;
         }
         HIP_CHECK_SERVE(hipGraphLaunch(it->second, srv->stream));
     } else {
@@ -501,6 +527,32 @@ static void scheduler(sbqa_server *srv) {
     }
 }
 
+// The stream that contexts are built on, on another hardware queue than the
+// steps: the runtime deals streams out over a few queues, and where the two met
+// every context waited for a whole step block (a batch of 16 took 29 ms instead
+// of 14). A candidate that finishes a launch while the step stream is held for
+// 200 us is on another queue; the refused ones are kept until the end, so that
+// the next one is dealt a further queue. On a busy GPU none may show itself: the
+// last one serves as well, only later.
+static hipError_t open_create_stream(sbqa_server *srv, hipEvent_t held) {
+    hipStream_t tried[4] = {};
+    hipError_t e = hipSuccess;
+    int n = 0;
+    for (bool apart = false; n < 4 && !apart && e == hipSuccess; ++n) {
+        if ((e = hipStreamCreateWithFlags(&tried[n], hipStreamNonBlocking)) != hipSuccess) break;
+        if ((e = launch_hold(0, tried[n])) != hipSuccess || (e = hipStreamSynchronize(tried[n])) != hipSuccess) continue;
+        if ((e = launch_hold(200, srv->stream)) != hipSuccess || (e = hipEventRecord(held, srv->stream)) != hipSuccess)
+            continue;
+        if ((e = launch_hold(0, tried[n])) != hipSuccess || (e = hipStreamSynchronize(tried[n])) != hipSuccess) continue;
+        apart = hipEventQuery(held) == hipErrorNotReady;
+        e = hipStreamSynchronize(srv->stream);
+    }
+    if (e == hipSuccess) srv->create_stream = tried[--n];
+    for (int k = 0; k < 4; ++k)
+        if (tried[k] && tried[k] != srv->create_stream) (void)hipStreamDestroy(tried[k]);
+    return e;
+}
+
 static void release(sbqa_server *srv) {
     if (srv->stream) (void)hipStreamSynchronize(srv->stream);
     for (auto &kv : srv->graphs) (void)hipGraphExecDestroy(kv.second);
@@ -511,12 +563,6 @@ static void release(sbqa_server *srv) {
     }
     if (srv->d_tasks) (void)hipFree(srv->d_tasks);
     if (srv->d_hdr) (void)hipFree(srv->d_hdr);
-    for (int b = 0; b < NBRANCH; ++b) {
-        if (srv->side[b]) (void)hipStreamSynchronize(srv->side[b]);
-        if (srv->side[b]) (void)hipStreamDestroy(srv->side[b]);
-        if (srv->join_ev[b]) (void)hipEventDestroy(srv->join_ev[b]);
-    }
-    if (srv->fork_ev) (void)hipEventDestroy(srv->fork_ev);
     if (srv->stream) (void)hipStreamDestroy(srv->stream);
     if (srv->create_stream) (void)hipStreamDestroy(srv->create_stream);
     delete srv;
@@ -537,17 +583,14 @@ sbqa_status sbqa_server_create(size_t hbm_budget_bytes, int32_t max_slots, sbqa_
     if (e != hipSuccess) { delete srv; return fail(SBQA_EDEVICE, "hipGetDevice: %s", hipGetErrorString(e)); }
     const size_t ntask = (size_t)NGROUPS * max_slots;
     e = hipStreamCreateWithFlags(&srv->stream, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&srv->create_stream, hipStreamNonBlocking);
-    for (int b = 0; b < NBRANCH && e == hipSuccess; ++b) {
-        e = hipStreamCreateWithFlags(&srv->side[b], hipStreamNonBlocking);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&srv->join_ev[b], hipEventDisableTiming);
-    }
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&srv->fork_ev, hipEventDisableTiming);
     for (int q = 0; q < 2 && e == hipSuccess; ++q) {
         e = hipHostMalloc((void **)&srv->h_tasks[q], sizeof(GroupTask) * ntask, hipHostMallocDefault);
         if (e == hipSuccess) e = hipHostMalloc((void **)&srv->h_hdr[q], sizeof(GroupHeader) * NGROUPS, hipHostMallocDefault);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&srv->h_free[q], hipEventDisableTiming);
     }
+    if (e == hipSuccess) e = launch_hold(0, srv->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(srv->stream);
+    if (e == hipSuccess) e = open_create_stream(srv, srv->h_free[0]);
     if (e == hipSuccess) e = hipMalloc(&srv->d_tasks, sizeof(GroupTask) * ntask);
     if (e == hipSuccess) e = hipMalloc(&srv->d_hdr, sizeof(GroupHeader) * NGROUPS);
     if (e != hipSuccess) {

@@ -169,3 +169,31 @@ def test_energies_from_the_lower_triangle(sb, N, count):
         if count > 8:   # the rest against plain float64
             f = s.astype(np.float64)
             assert np.all(np.abs(E - (-0.5 * (f * (f @ J)).sum(1) - f @ h)) <= 1e-13 * float(scale))
+
+
+# mixes whose grouped dense step takes tiles of 16, 32 and 64 spins
+@pytest.mark.parametrize("mix", [[(200, 2), (300, 7)], [(300, 9), (1100, 8), (700, 3)], [(1100, 48), (2300, 48), (300, 3)]])
+@pytest.mark.parametrize("coup,prec,packing", [("gauss", "FP32", 0), ("gauss", "BF16X3", 0), ("sidon", "INT8", 0),
+                                               ("sk", "FP8", 0), ("sk", "FP8", 1), ("sk", "FP4", 0), ("sk", "FP4", 1)])
+def test_served_mix_tiles(sb, coup, prec, packing, mix):
+    """Instances of one precision served together (m-block counts and a sparse
+    instance side by side in a launch, whole and part step blocks) equal their
+    standalone runs."""
+    import time
+    gen = {"gauss": inst.dense_gaussian, "sidon": inst.sidon28_dense, "sk": inst.sk_pm1}[coup]
+    items = [dict(J=gen(N, 61 + q), R=16, runs=runs, steps=70 + 3 * q, seed=65 + q, dense_tile=64 << (q % 3),
+                  precision=getattr(sb, "PREC_" + prec), j_packing=packing) for q, (N, runs) in enumerate(mix)]
+    items.append(dict(csr=_sparse(777, 5, 60)[0], R=16, runs=mix[0][1], steps=90, seed=60))
+    srv = sb.sbqa_server_create(4 << 30, 4)
+    _log("served mix %s %s %s" % (coup, prec, mix))
+    tickets = [sb.sbqa_submit(srv, **kw) for kw in items]
+    for t, kw in zip(tickets, items):
+        ctx = sb.sbqa_create(loop_kernel=sb.LOOP_STREAM, **kw)
+        sb.sbqa_step(ctx, kw["steps"])
+        E, s = sb.sbqa_best(ctx)
+        got, t0 = None, time.time()
+        while got is None and time.time() - t0 < 60:
+            got = sb.sbqa_poll(srv, t)
+            time.sleep(0.002)
+        assert got is not None and np.array_equal(got[0], E) and np.array_equal(got[1], s)
+    sb.sbqa_server_destroy(srv)
