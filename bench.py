@@ -195,22 +195,26 @@ def small_kernel_name(w):
 
 
 def dense_kernel_name(info):
-    """The dense step kernel the library launches: bit-packed +-1 J at the
-    128-column tile runs as the split-K kernel when the K chunks (128 spins
-    each in fp8, 256 in fp4; spins padded to a multiple of 512) split into
-    two halves of an even count."""
-    Np = -(-info["N"] // 512) * 512
-    # small grids: a finer tile (16 spins per workgroup up to one workgroup per
-    # CU, else 32 up to one, or two with bit-packed J)
+    """The dense step kernel the library launches. Exact paths (spins padded to a
+    multiple of 512): a finer tile on small grids, else K split over the waves
+    (from 128 tiles of 64 spins x 64 columns on; bit-packed fp4 from 256). The
+    others: 16 spins per workgroup up to one workgroup per CU, else 32 up to
+    one. Without R and runs, by the tile alone: split-K where bit-packed J at the
+    128-column tile has an even count of K chunks (128 spins each in fp8, 256
+    in fp4) in either half."""
+    exact = "fp8" in info["path"] or "fp4" in info["path"] or "int8" in info["path"]
     if "R" in info and "runs" in info:
-        pad = 512 if "fp8" in info["path"] or "fp4" in info["path"] or "int8" in info["path"] else 128
+        pad = 512 if exact else 128
         rows = -(-info["N"] // pad) * pad
         cb = -(-(info["R"] * info["runs"]) // info["tile_cols"]) * info["tile_cols"] // 64
-        if rows // 16 * cb <= 256 or rows // 32 * cb <= (512 if info["path"].endswith("_packed") else 256):
+        if exact:
+            least = 256 if info["path"] == "dense_fp4_packed" else 128
+            return "k_dense_step_sk" if rows // 64 * cb >= least else "k_dense_step_fine"
+        if rows // 32 * cb <= 256:
             return "k_dense_step_fine"
+    Np = -(-info["N"] // 512) * 512
     nkc = {"dense_fp8_packed": Np // 128, "dense_fp4_packed": Np // 256}.get(info["path"], 1)
-    split = info["path"] in ("dense_fp8_packed", "dense_fp4_packed") and info["tile_cols"] == 128 and nkc % 4 == 0
-    if split:
+    if info["path"] in ("dense_fp8_packed", "dense_fp4_packed") and info["tile_cols"] == 128 and nkc % 4 == 0:
         return "k_dense_step_sk"
     # two J planes at the 128-column tile: two column groups per workgroup
     # when the padded columns make whole pairs of 128-column chunks
@@ -229,7 +233,7 @@ def algorithmic_flops(w):
 _CS = "paper_2604_01050_amd/csrc/"
 # Source files that hold each dominant kernel's code (the kernel file and the
 # device helpers it includes); counter summaries record their hash.
-KERNEL_SOURCES = {"csr_fp32": [_CS + "kernels_csr.hip", _CS + "csr_common.h"],
+KERNEL_SOURCES = {"csr_fp32": [_CS + "kernels_csr.hip", _CS + "csr_step.h", _CS + "csr_common.h"],
                   "csr_resident": [_CS + "kernels_resident.hip", _CS + "csr_common.h"]}
 for _p in ("dense_fp8", "dense_fp8_packed", "dense_int8", "dense_fp4", "dense_fp4_packed", "dense_fp32",
            "dense_bf16x3"):

@@ -21,17 +21,20 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef int i8v __attribute__((ext_vector_type(8)));
 typedef int i4v __attribute__((ext_vector_type(4)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef int i16v __attribute__((ext_vector_type(16)));
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 
-// e4m3 and int8 encodings of the ternary values.
+// e4m3 encodings of J = +-1, and e2m1 (fp4) nibbles (sign bit 3, exponent 01,
+// mantissa 0).
 constexpr uint8_t FP8_P1 = 0x38, FP8_M1 = 0xB8;
-constexpr uint8_t I8_P1 = 0x01, I8_M1 = 0xFF;
-// e2m1 (fp4) nibbles of +1 and -1 (sign bit 3, exponent 01, mantissa 0).
 constexpr uint32_t FP4_P1 = 0x2, FP4_M1 = 0xA;
-// E8M0 block scale 2^(127-127) = 1 for the scaled fp8 MFMA.
-constexpr int E8M0_ONE = 127;
+// E8M0 block scales 2^(127-127) = 1 and 1/2 of the scaled fp8 and fp4 MFMA.
+constexpr int E8M0_ONE = 127, E8M0_HALF = 126;
 
 struct Frag32 { uint4 lo, hi; };  // the 32 K bytes of one lane for a 16x16 block
+
+__device__ __forceinline__ uint4 ld16(const uint8_t *p) { return *reinterpret_cast<const uint4 *>(p); }
 
 template <int PATH> constexpr bool is_fp8 = PATH == PATH_FP8 || PATH == PATH_FP8PK;
 template <int PATH> constexpr bool is_fp4 = PATH == PATH_FP4 || PATH == PATH_FP4PK;
@@ -39,8 +42,14 @@ template <int PATH> constexpr bool is_fp4 = PATH == PATH_FP4 || PATH == PATH_FP4
 // Bit-packed +-1 J: lane l of a fragment owns the dword at 4*l; its bit
 // 8*i + k encodes byte i of dword k (k = 0..7) of the lane's 32 fp8 K bytes,
 // set for -1. Dword k is then ((w << (7 - k)) & 0x80808080) | e4m3(+1) x 4.
+// (in_vgpr: with both constants literal an and-or would be two instructions.)
+__device__ __forceinline__ uint32_t in_vgpr(uint32_t v) {
+    asm("" : "+v"(v));
+    return v;
+}
 __device__ __forceinline__ Frag32 unpack_pm1(uint32_t w) {
-    auto d = [w](int k) { return ((w << (7 - k)) & 0x80808080u) | 0x38383838u; };
+    const uint32_t one = in_vgpr(0x38383838u);
+    auto d = [w, one](int k) { return ((w << (7 - k)) & 0x80808080u) | one; };
     return Frag32{make_uint4(d(0), d(1), d(2), d(3)), make_uint4(d(4), d(5), d(6), d(7))};
 }
 
@@ -49,7 +58,8 @@ __device__ __forceinline__ Frag32 unpack_pm1(uint32_t w) {
 // k (k = 0..3) of that half, set for -1, so dword k is
 // ((w << (3 - k)) & 0x88888888) | e2m1(+1) x 8.
 __device__ __forceinline__ Frag32 unpack_pm1_fp4(uint2 w) {
-    auto d = [](uint32_t v, int k) { return ((v << (3 - k)) & 0x88888888u) | 0x22222222u; };
+    const uint32_t one = in_vgpr(0x22222222u);
+    auto d = [one](uint32_t v, int k) { return ((v << (3 - k)) & 0x88888888u) | one; };
     return Frag32{make_uint4(d(w.x, 0), d(w.x, 1), d(w.x, 2), d(w.x, 3)),
                   make_uint4(d(w.y, 0), d(w.y, 1), d(w.y, 2), d(w.y, 3))};
 }
@@ -209,30 +219,82 @@ __device__ __forceinline__ uint16_t bf16_rne(float v) {
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
+// Operand of the exact paths (ternary f): 2 bits per value, 0 / 01 / 11 for
+// 0 / +1 / -1, 16 consecutive K elements to a dword. A lane's 32 K bytes are then
+// 8 (fp8, int8) or 16 bytes (fp4), and one shift and mask per dword expands them
+// to +-2 (fp8, fp4: the MFMA's block scale halves it) or +-64 (int8: the sum is
+// shifted back), which are exact. The reads of a step are mostly operand reads
+// and 2 bits are 4 (fp4: 2) times fewer; the split-K step has no other way to
+// feed its waves.
+// Bit of element 4q + e of a dword's 16: byte e, bits 2q.. for bytes; nibble
+// 4 (q % 2) + e, its upper two bits for q < 2, for fp4.
+template <int PATH>
+__device__ __forceinline__ int op2_bit(int q, int e) {
+    if constexpr (is_fp4<PATH>) return 16 * (q & 1) + 4 * e + (q < 2 ? 2 : 0);
+    else return 8 * e + 2 * q;
+}
+
+// A lane's 32 K bytes of the operand as they lie in memory, and expanded.
+template <int PATH> struct OpRaw {
+    typedef std::conditional_t<is_fp4<PATH>, uint4, uint2> type;
+};
+template <> struct OpRaw<PATH_F32> { typedef Frag32 type; };
+template <> struct OpRaw<PATH_BF16X3> { typedef Frag32 type; };
+template <int PATH> constexpr int OP_LANE = path_op2(Path(PATH)) ? op_frag_bytes(Path(PATH)) / 64 : 16;
+
+template <int PATH>
+__device__ __forceinline__ typename OpRaw<PATH>::type load_op(const uint8_t *p) {
+    if constexpr (path_op2(Path(PATH))) return *reinterpret_cast<const typename OpRaw<PATH>::type *>(p);
+    else return Frag32{ld16(p), ld16(p + 1024)};
+}
+
+__device__ __forceinline__ uint4 op2_bytes(uint32_t w) {
+    constexpr uint32_t M = 0xC0C0C0C0u;
+    return make_uint4((w << 6) & M, (w << 4) & M, (w << 2) & M, w & M);
+}
+__device__ __forceinline__ uint4 op2_nibbles(uint32_t a, uint32_t b) {
+    constexpr uint32_t M = 0xCCCCCCCCu;
+    return make_uint4(a & M, (a << 2) & M, b & M, (b << 2) & M);
+}
+template <int PATH>
+__device__ __forceinline__ Frag32 expand_op(const typename OpRaw<PATH>::type &r) {
+    if constexpr (is_fp4<PATH>) return Frag32{op2_nibbles(r.x, r.y), op2_nibbles(r.z, r.w)};
+    else if constexpr (path_op2(Path(PATH))) return Frag32{op2_bytes(r.x), op2_bytes(r.y)};
+    else return r;
+}
+
+// Byte offset of the operand's elements (row, k..k+3), k a multiple of 4
+// (exact paths: of the dword that holds them).
+template <int PATH>
+__device__ __forceinline__ int64_t x_offset(int row, int k, int nkc, int G) {
+    if constexpr (path_op2(Path(PATH))) {
+        constexpr int KPC = path_kpc(Path(PATH)), SL = KPC / 4;   // spins of a chunk, of a lane
+        const int kc = k / KPC, kb = k % KPC, rb = row >> 4, l = (kb / SL) * 16 + (row & 15);
+        return (((int64_t)(rb / G) * nkc + kc) * G + rb % G) * op_frag_bytes(Path(PATH)) + l * OP_LANE<PATH> +
+               (kb % SL) / 16 * 4;
+    } else {
+        return op_offset<PATH>(row, k, nkc, G);
+    }
+}
+
 // Four consecutive operand values (same row, K positions k..k+3) at byte
-// offset o of the fragment-tiled operand (o from tf_offset: the four values
-// are contiguous there).
+// offset o (from x_offset); the exact paths call it with the lanes 4j..4j+3 of a
+// wave holding 16 aligned consecutive values.
 template <int PATH>
 __device__ __forceinline__ void store_operand(void *g, void *g_lo, int64_t o, float4 f, int fmode) {
     uint8_t *gb = reinterpret_cast<uint8_t *>(g);
     if constexpr (PATH == PATH_F32) {
         *reinterpret_cast<float4 *>(gb + o) = f;
-    } else if constexpr (is_fp8<PATH> || PATH == PATH_I8) {
-        constexpr uint32_t P1 = is_fp8<PATH> ? FP8_P1 : I8_P1, M1 = is_fp8<PATH> ? FP8_M1 : I8_M1;
+    } else if constexpr (path_op2(Path(PATH))) {
+        // the four lanes of 16 consecutive spins add their codes together
         const float v[4] = {f.x, f.y, f.z, f.w};
+        const int q = threadIdx.x & 3;
         uint32_t w = 0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint32_t b = v[e] > 0.0f ? P1 : (v[e] < 0.0f ? M1 : 0u);
-            w |= b << (8 * e);
-        }
-        *reinterpret_cast<uint32_t *>(gb + o) = w;
-    } else if constexpr (is_fp4<PATH>) {
-        const float v[4] = {f.x, f.y, f.z, f.w};
-        uint32_t w = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) w |= (v[e] > 0.0f ? FP4_P1 : (v[e] < 0.0f ? FP4_M1 : 0u)) << (4 * e);
-        *reinterpret_cast<uint16_t *>(gb + o) = (uint16_t)w;
+        for (int e = 0; e < 4; ++e) w |= (v[e] > 0.0f ? 1u : (v[e] < 0.0f ? 3u : 0u)) << op2_bit<PATH>(q, e);
+        w |= (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0xB1, 0xF, 0xF, true);   // lanes 1 0 3 2
+        w |= (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0x4E, 0xF, 0xF, true);   // lanes 2 3 0 1
+        if (q == 0) *reinterpret_cast<uint32_t *>(gb + o) = w;
     } else {  // BF16X3
         const float v[4] = {f.x, f.y, f.z, f.w};
         uint16_t hi[4], lo[4];
@@ -276,7 +338,7 @@ __device__ __forceinline__ void mma_term(f4 &acc, const Frag32 &a, const Frag32 
         i8v av, bv;
         __builtin_memcpy(&av, &a, 32);
         __builtin_memcpy(&bv, &b, 32);
-        acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(av, bv, acc, 0, 0, 0, E8M0_ONE, 0, E8M0_ONE);
+        acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(av, bv, acc, 0, 0, 0, E8M0_HALF, 0, E8M0_ONE);
     } else if constexpr (PATH == PATH_I8) {
         // int32 accumulation, carried in the float accumulator's bits; term T
         // takes the lane's K bytes of half T (each 16x16x64 product pairs the
@@ -295,7 +357,7 @@ __device__ __forceinline__ void mma_term(f4 &acc, const Frag32 &a, const Frag32 
         const uint4 &ys = T ? b.hi : b.lo;
         const i8v xv = {(int)xs.x, (int)xs.y, (int)xs.z, (int)xs.w, 0, 0, 0, 0};
         const i8v yv = {(int)ys.x, (int)ys.y, (int)ys.z, (int)ys.w, 0, 0, 0, 0};
-        acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(xv, yv, acc, 4, 4, 0, E8M0_ONE, 0, E8M0_ONE);
+        acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(xv, yv, acc, 4, 4, 0, E8M0_HALF, 0, E8M0_ONE);
     } else {
         // small products first: lo*hi, hi*lo, then hi*hi; each over both halves
         const Frag32 &x = (T < 2) ? a2 : a;
@@ -309,18 +371,39 @@ __device__ __forceinline__ void mma_term(f4 &acc, const Frag32 &a, const Frag32 
     }
 }
 
+// The 32 x 32 products of the exact paths, rows from a (J), columns from b (the
+// operand), with the 32 K bytes of this lane.
+template <int PATH>
+__device__ __forceinline__ void mma32(f16v &acc, const Frag32 &a, const Frag32 &b) {
+    i8v av, bv;
+    __builtin_memcpy(&av, &a, 32);
+    __builtin_memcpy(&bv, &b, 32);
+    const i4v al = {av[0], av[1], av[2], av[3]}, ah = {av[4], av[5], av[6], av[7]};
+    const i4v bl = {bv[0], bv[1], bv[2], bv[3]}, bh = {bv[4], bv[5], bv[6], bv[7]};
+    if constexpr (is_fp8<PATH>) {
+        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, acc, 0, 0, 0, E8M0_ONE, 0, E8M0_HALF);
+    } else if constexpr (is_fp4<PATH>) {
+        auto wide = [](const i4v &v) { return i8v{v[0], v[1], v[2], v[3], 0, 0, 0, 0}; };
+        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(wide(al), wide(bl), acc, 4, 4, 0, E8M0_ONE, 0, E8M0_HALF);
+        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(wide(ah), wide(bh), acc, 4, 4, 0, E8M0_ONE, 0, E8M0_HALF);
+    } else {
+        i16v c = __builtin_bit_cast(i16v, acc);
+        c = __builtin_amdgcn_mfma_i32_32x32x32_i8(al, bl, c, 0, 0, 0);
+        acc = __builtin_bit_cast(f16v, __builtin_amdgcn_mfma_i32_32x32x32_i8(ah, bh, c, 0, 0, 0));
+    }
+}
+
 template <int PATH> struct Pipe {
     static constexpr int planes = (PATH == PATH_BF16X3) ? 2 : 1;  // bf16: hi and lo
     static constexpr int depth = dense_depth(Path(PATH));          // K chunks in flight
 };
 
-__device__ __forceinline__ uint4 ld16(const uint8_t *p) { return *reinterpret_cast<const uint4 *>(p); }
-
-// Field value of one accumulator element (int8 path: the exact int32 sum,
-// rounded once to float32).
+// Field value of one accumulator element (int8 path: the exact int32 sum of 64
+// times the products, at most 64 * 127 * 65536 < 2^31, shifted back and rounded
+// once to float32).
 template <int PATH>
 __device__ __forceinline__ float acc_field(float v) {
-    if constexpr (PATH == PATH_I8) return (float)__builtin_bit_cast(int, v);
+    if constexpr (PATH == PATH_I8) return (float)(__builtin_bit_cast(int, v) >> 6);
     else return v;
 }
 
@@ -345,18 +428,26 @@ struct UpdIn {
     float jp;
 };
 
-__device__ __forceinline__ UpdIn update_load(const DenseStepArgs &a, int c, int i4) {
+__device__ __forceinline__ void update_load_own(const DenseStepArgs &a, int c, int i4, UpdIn &u) {
+    u.x = *reinterpret_cast<const float4 *>(a.x_in + (int64_t)c * a.Np + i4);
+    u.y = *reinterpret_cast<const float4 *>(a.y + (int64_t)c * a.Np + i4);
+}
+
+__device__ __forceinline__ void update_load_rest(const DenseStepArgs &a, int c, int i4, UpdIn &u) {
     const int Np = a.Np, R = a.R;
     const int r = c / R, kk = c - r * R;
     const int cl = r * R + (kk == 0 ? R - 1 : kk - 1);
     const int cr = r * R + (kk == R - 1 ? 0 : kk + 1);
-    UpdIn u;
-    u.x = *reinterpret_cast<const float4 *>(a.x_in + (int64_t)c * Np + i4);
     u.xl = *reinterpret_cast<const float4 *>(a.x_in + (int64_t)cl * Np + i4);
     u.xr = *reinterpret_cast<const float4 *>(a.x_in + (int64_t)cr * Np + i4);
-    u.y = *reinterpret_cast<const float4 *>(a.y + (int64_t)c * Np + i4);
     u.h = *reinterpret_cast<const float4 *>(a.h + i4);
     u.jp = a.jp[(int64_t)r * a.jp_stride];
+}
+
+__device__ __forceinline__ UpdIn update_load(const DenseStepArgs &a, int c, int i4) {
+    UpdIn u;
+    update_load_own(a, c, i4, u);
+    update_load_rest(a, c, i4, u);
     return u;
 }
 
@@ -385,10 +476,25 @@ __device__ __forceinline__ void update_store(const DenseStepArgs &a, int c, int 
     const int64_t o = (int64_t)c * a.Np + i4;
     *reinterpret_cast<float4 *>(a.x_out + o) = make_float4(xo[0], xo[1], xo[2], xo[3]);
     *reinterpret_cast<float4 *>(a.y + o) = make_float4(yo[0], yo[1], yo[2], yo[3]);
-    store_operand<PATH>(a.g_next, a.g_next_lo, op_offset<PATH>(c, i4, a.nkc, GM ? GM : a.mbw),
+    store_operand<PATH>(a.g_next, a.g_next_lo, x_offset<PATH>(c, i4, a.nkc, GM ? GM : a.mbw),
                         make_float4(fo[0], fo[1], fo[2], fo[3]), a.fmode);
 }
 #pragma clang fp contract(on)
+
+// Bit-packed J holds +1 on the diagonal and in the padding: takes the diagonal
+// term J'_ii f_i = f_i out of the fields of spins i4.. (fw: the dword of the
+// operand this step read) and zeroes those of padded spins, so that their x and
+// f stay 0.
+template <int PATH>
+__device__ __forceinline__ float4 less_diagonal(const DenseStepArgs &a, int i4, uint32_t fw, float4 ph) {
+    float v[4] = {ph.x, ph.y, ph.z, ph.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float f = (float)((int)(fw << (30 - op2_bit<PATH>(threadIdx.x & 3, e))) >> 30);
+        v[e] = (i4 + e < a.N) ? v[e] - f : 0.0f;
+    }
+    return make_float4(v[0], v[1], v[2], v[3]);
+}
 
 // Epilogue of one wave's tile, row blocks (replica columns) mb0 .. mb0 + MBW
 // - 1 by TN spins from n0: transpose each 16 x TN block of Phi through LDS
@@ -427,26 +533,12 @@ __device__ __forceinline__ void dense_epilogue(const DenseStepArgs &a, f4 (&acc)
             ii[it] = n0 + 4 * q;
         }
         if constexpr (JPK) {
-            // bit-packed J holds +1 on the diagonal and in the padding: take
-            // the diagonal term J'_ii f_i = f_i (the operand byte this step
-            // read) back out, and zero the fields of padded spins so that
-            // their x and f stay 0
 #pragma unroll
             for (int it = 0; it < ITEMS; ++it) {
                 if (cc[it] >= a.C) continue;
-                const uint8_t *fp = a.g + op_offset<PATH>(cc[it], ii[it], nkc, GM ? GM : a.mbw);
-                constexpr int BITS = is_fp4<PATH> ? 4 : 8;
-                constexpr uint32_t MASK = (1u << BITS) - 1u, SIGN = 1u << (BITS - 1);
-                const uint32_t fb = is_fp4<PATH> ? (uint32_t)*reinterpret_cast<const uint16_t *>(fp)
-                                                 : *reinterpret_cast<const uint32_t *>(fp);
-                float v[4] = {ph[it].x, ph[it].y, ph[it].z, ph[it].w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const uint32_t b = (fb >> (BITS * e)) & MASK;
-                    const float f = b == 0u ? 0.0f : ((b & SIGN) ? -1.0f : 1.0f);
-                    v[e] = (ii[it] + e < a.N) ? v[e] - f : 0.0f;
-                }
-                ph[it] = make_float4(v[0], v[1], v[2], v[3]);
+                const uint32_t fw = *reinterpret_cast<const uint32_t *>(
+                    a.g + x_offset<PATH>(cc[it], ii[it], nkc, GM ? GM : a.mbw));
+                ph[it] = less_diagonal<PATH>(a, ii[it], fw, ph[it]);
             }
         }
         if constexpr (EPI == EPI_UPDATE) {
@@ -503,12 +595,13 @@ __device__ __forceinline__ void dense_step_body(const DenseStepArgs &a, int nt, 
     constexpr int JFRAG = JPK ? pk_frag_bytes(Path(PATH)) : FRAG_BYTES;
     using JWord = std::conditional_t<is_fp4<PATH>, uint2, uint32_t>;   // a lane's packed J of one chunk
     constexpr int JCH = RBT * JFRAG;        // J bytes of one tile and K chunk
-    constexpr int XCH = MBW * FRAG_BYTES;   // operand bytes of one wave and K chunk
+    constexpr int XF = op_frag_bytes(Path(PATH));
+    constexpr int XCH = MBW * XF;           // operand bytes of one wave and K chunk
 
     // this wave stages J row block w of tile nt (both planes); its operand
     // group is m-blocks mb0..mb0+MBW-1
     const int64_t jgrp = (int64_t)nt * nkc * JCH + w * JFRAG + (JPK ? lane * (int)sizeof(JWord) : l16);
-    const int64_t xgrp = (int64_t)(mchunk * 4 + w) * nkc * XCH + l16;
+    const int64_t xgrp = (int64_t)(mchunk * 4 + w) * nkc * XCH + lane * OP_LANE<PATH>;
     const uint8_t *jsrc = a.J + jgrp;
     const uint8_t *jsrc_lo = (PL == 2) ? a.J_lo + jgrp : jsrc;
     const uint8_t *xsrc = a.g + xgrp;
@@ -516,7 +609,7 @@ __device__ __forceinline__ void dense_step_body(const DenseStepArgs &a, int nt, 
 
     uint4 jr[JPK ? 1 : PD][PL][2];
     JWord jw[JPK ? PD : 1];
-    uint4 xr[PD][MBW][PL][2];
+    typename OpRaw<PATH>::type xr[PD][MBW][PL];
     f4 acc[MBW][RBT];
 #pragma unroll
     for (int i = 0; i < MBW; ++i)
@@ -542,16 +635,12 @@ __device__ __forceinline__ void dense_step_body(const DenseStepArgs &a, int nt, 
             }
         }
     };
-    auto load_x = [&](uint4 (&d)[MBW][PL][2], int kc) {
+    auto load_x = [&](typename OpRaw<PATH>::type (&d)[MBW][PL], int kc) {
         const int64_t o = chunk_at(kc) * XCH;
 #pragma unroll
         for (int mb = 0; mb < MBW; ++mb) {
-            d[mb][0][0] = ld16(xsrc + o + mb * FRAG_BYTES);
-            d[mb][0][1] = ld16(xsrc + o + mb * FRAG_BYTES + 1024);
-            if constexpr (PL == 2) {
-                d[mb][PL - 1][0] = ld16(xsrc_lo + o + mb * FRAG_BYTES);
-                d[mb][PL - 1][1] = ld16(xsrc_lo + o + mb * FRAG_BYTES + 1024);
-            }
+            d[mb][0] = load_op<PATH>(xsrc + o + mb * XF);
+            if constexpr (PL == 2) d[mb][PL - 1] = load_op<PATH>(xsrc_lo + o + mb * XF);
         }
     };
 
@@ -610,6 +699,12 @@ __device__ __forceinline__ void dense_step_body(const DenseStepArgs &a, int nt, 
                 }
             };
             read_j(bjb[0], 0);
+            Frag32 ax[MBW], ax2[MBW];
+#pragma unroll
+            for (int mb = 0; mb < MBW; ++mb) {
+                ax[mb] = expand_op<PATH>(xr[s][mb][0]);
+                ax2[mb] = expand_op<PATH>(xr[s][mb][PL - 1]);
+            }
 #pragma unroll
             for (int p = 0; p < RBT; ++p) {
                 if (p + 1 < RBT) read_j(bjb[(p + 1) & 1], p + 1);
@@ -618,11 +713,7 @@ __device__ __forceinline__ void dense_step_body(const DenseStepArgs &a, int nt, 
                 static_for<0, NT>([&](auto tc) {
                     constexpr int T = decltype(tc)::value;
 #pragma unroll
-                    for (int mb = 0; mb < MBW; ++mb) {
-                        const Frag32 ax{xr[s][mb][0][0], xr[s][mb][0][1]};
-                        const Frag32 ax2{xr[s][mb][PL - 1][0], xr[s][mb][PL - 1][1]};
-                        mma_term<PATH, T>(acc[mb][p], ax, bj, ax2, bj2);
-                    }
+                    for (int mb = 0; mb < MBW; ++mb) mma_term<PATH, T>(acc[mb][p], ax[mb], bj, ax2[mb], bj2);
                 });
                 // keeps the fragment reads two row blocks deep (register pressure)
                 __builtin_amdgcn_sched_barrier(0);
@@ -665,8 +756,9 @@ __device__ __forceinline__ void dense_fine_body(const DenseStepArgs &a, int bx, 
     __shared__ __align__(16) uint8_t lds[4 * 16 * (16 * NB + 4) * 4];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int mb = by * 4 + w, rb0 = bx * NB, nkc = a.nkc, l16 = lane * 16;
-    const int xstep = a.mbw * FRAG_BYTES;
-    const int64_t xo = (int64_t)(mb / a.mbw) * nkc * xstep + (mb % a.mbw) * FRAG_BYTES + l16;
+    const int xstep = a.mbw * op_frag_bytes(Path(PATH));
+    const int64_t xo = (int64_t)(mb / a.mbw) * nkc * xstep + (mb % a.mbw) * op_frag_bytes(Path(PATH)) +
+                       lane * OP_LANE<PATH>;
     const uint8_t *xsrc = a.g + xo, *xsrc_lo = (PL == 2) ? a.g_lo + xo : xsrc;
     const uint8_t *jsrc[NB], *jsrc_lo[NB];
 #pragma unroll
@@ -679,7 +771,8 @@ __device__ __forceinline__ void dense_fine_body(const DenseStepArgs &a, int bx, 
     }
     const int rev = a.reverse;
     auto chunk_at = [&](int kc) -> int64_t { return rev ? nkc - 1 - kc : kc; };
-    uint4 xr[PD][PL][2], jr[JPK ? 1 : PD][NB][PL][2];
+    typename OpRaw<PATH>::type xr[PD][PL];
+    uint4 jr[JPK ? 1 : PD][NB][PL][2];
     JWord jw[JPK ? PD : 1][NB];
     auto load = [&](int s, int kc) {
         const int64_t k = chunk_at(kc);
@@ -696,12 +789,8 @@ __device__ __forceinline__ void dense_fine_body(const DenseStepArgs &a, int bx, 
                 }
             }
         }
-        xr[s][0][0] = ld16(xsrc + k * xstep);
-        xr[s][0][1] = ld16(xsrc + k * xstep + 1024);
-        if constexpr (PL == 2) {
-            xr[s][PL - 1][0] = ld16(xsrc_lo + k * xstep);
-            xr[s][PL - 1][1] = ld16(xsrc_lo + k * xstep + 1024);
-        }
+        xr[s][0] = load_op<PATH>(xsrc + k * xstep);
+        if constexpr (PL == 2) xr[s][PL - 1] = load_op<PATH>(xsrc_lo + k * xstep);
     };
     f4 acc[1][NB];
 #pragma unroll
@@ -720,7 +809,7 @@ __device__ __forceinline__ void dense_fine_body(const DenseStepArgs &a, int bx, 
 #pragma unroll
         for (int s = 0; s < PD; ++s) {
             const int kc = kc0 + s;
-            const Frag32 ax{xr[s][0][0], xr[s][0][1]}, ax2{xr[s][PL - 1][0], xr[s][PL - 1][1]};
+            const Frag32 ax = expand_op<PATH>(xr[s][0]), ax2 = expand_op<PATH>(xr[s][PL - 1]);
             Frag32 bj[NB], bj2[NB];
 #pragma unroll
             for (int p = 0; p < NB; ++p) {
@@ -751,146 +840,189 @@ __global__ __launch_bounds__(DENSE_THREADS) void k_dense_step_fine(const DenseSt
     dense_fine_body<PATH, NB, PD, EPI>(a, blockIdx.x, blockIdx.y);
 }
 
-// K chunks in flight per wave in the split-K kernel (fp8 and fp4 alike;
-// measured: four fp8 chunks in flight 3% slower, four fp4 chunks 4% slower)
-constexpr int SK_DEPTH = 2;
+// One step with K split over the waves, for the exact contractions
+// (integer-valued sums: the order does not change the result). A wave owns 64
+// spins x 64 replica columns and one of KS ranges of K, and streams both operands
+// straight into registers: no LDS and no barrier in the K loop. A workgroup of 8
+// waves is SG spin groups x CG column groups x KS ranges; the ranges' sums are
+// added through LDS, and each wave then updates 1/KS of its tile's columns.
+// Workgroups are numbered so that the column tiles of one J tile run on one XCD
+// and read J from its L2.
+// Expanding J and the operand takes about as many vector instructions as the
+// products leave room for, and the two overlap only beside 32 x 32 products: on
+// one SIMD, 32 16x16x128 fp4 products with 4 vector instructions each take 981 x 2
+// clocks, 16 32x32x64 products of the same work with 7 each 682 x 2. Then the
+// epilogue's state traffic at the end of a launch. us per step before (64-spin or
+// fine tile; at 16384 x 256 split-K through LDS) and now, N x C:
+//            16384 x 256  16384 x 128  8192 x 256  8192 x 128  4096 x 256
+//   fp4      53.0  44.3   35.4  27.3   22.9  19.4  16.3  12.4  11.2   9.5
+//   fp8      78.9  71.7   58.6  38.0   34.4  24.3  22.6  14.0  14.5  10.6
+//   int8     6000 x 256: 24.1  22.4; 4096 x 256: 14.3  11.8; 3000 x 256: 11.9  10.2
+template <int PATH, int SG, int CG, int EPI>
+__global__ __launch_bounds__(2 * DENSE_THREADS) void k_dense_step_sk(const DenseStepArgs a, int nx, int ny) {
+    constexpr int KS = 8 / (SG * CG), MB = 4, RB = DENSE_TN / 16;
+    constexpr bool JPK = path_packed(Path(PATH));
+    constexpr int PD = JPK && KS > 2 ? 4 : 2;   // K chunks in flight
+    constexpr int JFRAG = JPK ? pk_frag_bytes(Path(PATH)) : FRAG_BYTES, JCH = RB * JFRAG;
+    constexpr int XF = op_frag_bytes(Path(PATH));
+    using JRaw = std::conditional_t<JPK, std::conditional_t<is_fp4<PATH>, uint2, uint32_t>, Frag32>;
+    __shared__ __align__(16) f4 red[8 * MB * RB * 64];
 
-// Split-K step for exact contractions: a 128-spin tile (8 row blocks) x
-// 64*MBW columns, 8 waves; waves 0-3 sum the first half of K and waves 4-7
-// the second, each wave owning MBW m-blocks and all 8 row blocks, so every
-// operand fragment feeds 8 row blocks. The halves are added through LDS
-// (integer-valued sums: the order does not change the result), then wave
-// (h, w) runs the update epilogue of the 64-spin half h. J is staged through
-// LDS two K chunks at a time (four slots per half), one barrier per pair.
-template <int PATH, int MBW, int EPI>
-__global__ __launch_bounds__(2 * DENSE_THREADS) void k_dense_step_sk(const DenseStepArgs a) {
-    static_assert(path_packed(Path(PATH)), "split-K kernel: bit-packed exact paths only");
-    constexpr int PD = SK_DEPTH;
-    constexpr int NT = Terms<PATH>::n;
-    constexpr int RBG = DENSE_TN / 16;            // row blocks per 64-spin J group
-    constexpr int RB = 2 * RBG;                   // row blocks per tile
-    constexpr int SLOT = RB * FRAG_BYTES;         // expanded J of one K chunk
-    constexpr int TS = DENSE_TN + 4;
-    constexpr int TBYTES = 8 * 16 * TS * 4;
-    constexpr int RBYTES = 2 * 4 * MBW * RBG * 64 * 16;
-    constexpr int JB = 8 * SLOT;                  // 4 slots per K half: one barrier per 2 chunks
-    static_assert(PD % 2 == 0, "chunks are staged in pairs");
-    constexpr int LDS_BYTES = JB > TBYTES ? (JB > RBYTES ? JB : RBYTES) : (TBYTES > RBYTES ? TBYTES : RBYTES);
-    __shared__ __align__(16) uint8_t lds[LDS_BYTES];
-
-    const int nt2 = blockIdx.x, mchunk = blockIdx.y;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, h = wv >> 2, w = wv & 3;
-    const int nkc = a.nkc, nkh = nkc / 2;
-    const int l16 = lane * 16;
-    constexpr int JFRAG = pk_frag_bytes(Path(PATH));
-    using JWord = std::conditional_t<is_fp4<PATH>, uint2, uint32_t>;
-    constexpr int JCH = RBG * JFRAG;
-    constexpr int XCH = MBW * FRAG_BYTES;
-    // this wave stages row blocks 2w and 2w+1 of the tile (J group 2*nt2 + w/2)
-    const int64_t jgrp = (int64_t)(2 * nt2 + (w >> 1)) * nkc * JCH + ((2 * w) & 3) * JFRAG + lane * (int)sizeof(JWord);
-    const int64_t xgrp = (int64_t)(mchunk * 4 + w) * nkc * XCH + l16;
-    const uint8_t *jsrc = a.J + jgrp;
-    const uint8_t *xsrc = a.g + xgrp;
-
-    JWord jw[PD][2];
-    uint4 xr[PD][MBW][2];
-    f4 acc[MBW][RB];
+    const int slot = blockIdx.x >> 3, bx = (slot / ny) * 8 + (blockIdx.x & 7), by = slot % ny;
+    if (bx >= nx) return;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kp = wv / (SG * CG), t = wv % (SG * CG), jt = bx * SG + t % SG, mb0 = (by * CG + t / SG) * MB;
+    const int nkc = a.nkc, rev = a.reverse, xstep = a.mbw * XF;
+    // A lane's operand of a 32 x 32 product is the share of lane sl(T) of a
+    // 16-row fragment, T = 0, 1: rows 16q.. of a fragment pair (q = lane / 16 %
+    // 2), K slice 2T + lane / 32. Scalar bases and chunk offsets, the lane's part
+    // 32 bits.
+    const uint32_t sl = (lane & 15) + 16 * (lane >> 5), q = (lane >> 4) & 1;
+    constexpr int JL = JPK ? (int)sizeof(JRaw) : 16, XL = OP_LANE<PATH>;
+    const uint8_t *jsrc = a.J + (int64_t)jt * nkc * JCH;
+    const uint32_t jl = q * JFRAG + sl * JL;
+    // row blocks 2m and 2m + 1 of the operand: one group's, or (mbw 1) two
+    const uint8_t *xsrc[2];
+    const uint32_t xl = (a.mbw == 1 ? q * (uint32_t)nkc * XF : q * XF) + sl * XL;
 #pragma unroll
-    for (int i = 0; i < MBW; ++i)
+    for (int m = 0; m < 2; ++m) {
+        const int mb = mb0 + 2 * m;
+        xsrc[m] = a.g + (int64_t)(mb / a.mbw) * nkc * xstep + (mb % a.mbw) * XF;
+    }
+    // this wave's chunks; none where its 64 columns are all padding
+    const int k0 = kp * nkc / KS, k1 = 16 * mb0 < a.C ? (kp + 1) * nkc / KS : k0;
+    JRaw jr[PD][2][2];
+    typename OpRaw<PATH>::type xr[PD][2][2];
+    auto load = [&](int s, int kc) {
+        const int k = rev ? nkc - 1 - kc : kc;
+        const uint8_t *src = jsrc + (int64_t)k * JCH;
 #pragma unroll
-        for (int j = 0; j < RB; ++j) acc[i][j] = f4{0, 0, 0, 0};
-
-    const int rev = a.reverse;
-    auto chunk_at = [&](int j) -> int64_t { const int kc = h * nkh + j; return rev ? nkc - 1 - kc : kc; };
-    auto load_j = [&](int s, int j) {
-        const int64_t o = chunk_at(j) * JCH;
-        jw[s][0] = *reinterpret_cast<const JWord *>(jsrc + o);
-        jw[s][1] = *reinterpret_cast<const JWord *>(jsrc + o + JFRAG);
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int T = 0; T < 2; ++T) {
+                const uint8_t *at = src + (2 * p * JFRAG + 32 * T * JL) + jl;
+                if constexpr (JPK) jr[s][p][T] = *reinterpret_cast<const JRaw *>(at);
+                else jr[s][p][T] = Frag32{ld16(at), ld16(at + 1024)};
+            }
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int T = 0; T < 2; ++T) xr[s][m][T] = load_op<PATH>(xsrc[m] + (int64_t)k * xstep + 32 * T * XL + xl);
     };
-    auto load_x = [&](uint4 (&d)[MBW][2], int j) {
-        const int64_t o = chunk_at(j) * XCH;
+    // This wave's items after the sum over the KS ranges: 64 / KS columns, a lane
+    // four spins of every fourth. Their x and y are on the way during the K loop
+    // where registers allow (8 items would spill).
+    constexpr int IT = 16 / KS;
+    constexpr bool EARLY = KS > 2;
+    const int cw = (64 / KS) * kp + (lane >> 4), i4 = jt * DENSE_TN + 4 * (lane & 15);
+    auto item_c = [&](int it) { return 16 * mb0 + cw + 4 * it; };
+    UpdIn u[IT];
+    f16v acc[2][2];
 #pragma unroll
-        for (int mb = 0; mb < MBW; ++mb) {
-            d[mb][0] = ld16(xsrc + o + mb * FRAG_BYTES);
-            d[mb][1] = ld16(xsrc + o + mb * FRAG_BYTES + 1024);
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[m][p][e] = 0.0f;
+    auto compute = [&](int s) {
+#pragma unroll
+        for (int T = 0; T < 2; ++T) {
+            Frag32 ax[2], bj[2];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) ax[m] = expand_op<PATH>(xr[s][m][T]);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                if constexpr (!JPK) bj[p] = jr[s][p][T];
+                else if constexpr (is_fp4<PATH>) bj[p] = unpack_pm1_fp4(jr[s][p][T]);
+                else bj[p] = unpack_pm1(jr[s][p][T]);
+            }
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int m = 0; m < 2; ++m) mma32<PATH>(acc[m][p], bj[p], ax[m]);
         }
     };
-#pragma unroll
-    for (int s = 0; s < PD; ++s) {
-        load_j(s, s);
-        __builtin_amdgcn_sched_barrier(0);
-        load_x(xr[s], s);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll 1
-    for (int j0 = 0; j0 < nkh; j0 += PD) {
+    if (k0 < k1) {
 #pragma unroll
         for (int s = 0; s < PD; ++s) {
-            const int j = j0 + s;
-            const int jn = (j + PD < nkh) ? j + PD : j;
-            uint8_t *slot = lds + (h * 4 + (j & 3)) * SLOT;
-            // chunks j and j + 1 are staged together (slots j % 4 and
-            // (j + 1) % 4 were last read for chunks j - 4 and j - 3, which
-            // every wave finished before the barrier of chunk pair j - 2)
-            if (s % 2 == 0) {
+            load(s, min(k0 + s, k1 - 1));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (EPI == EPI_UPDATE && EARLY) {
 #pragma unroll
-                for (int q = 0; q < 2; ++q)
+            for (int it = 0; it < IT; ++it)
+                if (item_c(it) < a.C) update_load_own(a, item_c(it), i4, u[it]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        int kc = k0;
+#pragma unroll 1
+        for (; kc + PD <= k1; kc += PD) {
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) {
-                        Frag32 f;
-                        if constexpr (is_fp4<PATH>) f = unpack_pm1_fp4(jw[s + q][e]);
-                        else f = unpack_pm1(jw[s + q][e]);
-                        uint8_t *dst = lds + (h * 4 + ((j + q) & 3)) * SLOT + (2 * w + e) * FRAG_BYTES + l16;
-                        *reinterpret_cast<uint4 *>(dst) = f.lo;
-                        *reinterpret_cast<uint4 *>(dst + 1024) = f.hi;
-                    }
-                const int jn1 = (j + 1 + PD < nkh) ? j + 1 + PD : j + 1;
-                load_j(s, jn);
-                load_j(s + 1, jn1);
-                __syncthreads();
-            }
-            Frag32 bjb[2];
-            auto read_j = [&](Frag32 &d, int p) {
-                d.lo = *reinterpret_cast<const uint4 *>(slot + p * FRAG_BYTES + l16);
-                d.hi = *reinterpret_cast<const uint4 *>(slot + p * FRAG_BYTES + 1024 + l16);
-            };
-            read_j(bjb[0], 0);
-#pragma unroll
-            for (int p = 0; p < RB; ++p) {
-                if (p + 1 < RB) read_j(bjb[(p + 1) & 1], p + 1);
-                const Frag32 &bj = bjb[p & 1];
-                static_for<0, NT>([&](auto tc) {
-                    constexpr int T = decltype(tc)::value;
-#pragma unroll
-                    for (int mb = 0; mb < MBW; ++mb) {
-                        const Frag32 ax{xr[s][mb][0], xr[s][mb][1]};
-                        mma_term<PATH, T>(acc[mb][p], ax, bj, ax, bj);
-                    }
-                });
+            for (int s = 0; s < PD; ++s) {
+                compute(s);
+                __builtin_amdgcn_sched_barrier(0);
+                load(s, min(kc + s + PD, k1 - 1));
                 __builtin_amdgcn_sched_barrier(0);
             }
-            load_x(xr[s], jn);
         }
+#pragma unroll
+        for (int s = 0; s < PD - 1; ++s)
+            if (kc + s < k1) compute(s);
     }
-    // add the two K halves: wave (h, w) keeps row blocks [4h, 4h + 4)
-    __syncthreads();
-    f4 *red = reinterpret_cast<f4 *>(lds);
-#pragma unroll
-    for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-        for (int p = 0; p < RBG; ++p)
-            red[(((h * 4 + w) * MBW + mb) * RBG + p) * 64 + lane] = h == 0 ? acc[mb][RBG + p] : acc[mb][p];
-    __syncthreads();
-    f4 mine[MBW][RBG];
-#pragma unroll
-    for (int mb = 0; mb < MBW; ++mb)
-#pragma unroll
-        for (int p = 0; p < RBG; ++p) {
-            const f4 o = red[((((1 - h) * 4 + w) * MBW + mb) * RBG + p) * 64 + lane];
-            const f4 m = h == 0 ? acc[mb][p] : acc[mb][RBG + p];
-            mine[mb][p] = f4{m[0] + o[0], m[1] + o[1], m[2] + o[2], m[3] + o[3]};
+    // Add the KS ranges through LDS. Registers 4e.. of a lane of product (p, m) are
+    // spins 32p + 8e + 4 (lane / 32).. of column 32m + lane % 32: four consecutive
+    // spins go to row `column`, place (spin / 4) ^ (column % 16) of the wave's share,
+    // so that neither writes nor reads meet on a bank.
+    // The rest of the items' inputs arrives meanwhile (of 8 items, half before and
+    // half after the sums have left their registers).
+    uint32_t fw[IT];
+    auto fetch = [&](int it) {
+        if (item_c(it) >= a.C) return;
+        if constexpr (EPI == EPI_UPDATE) {
+            if (!EARLY || k0 == k1) update_load_own(a, item_c(it), i4, u[it]);
+            update_load_rest(a, item_c(it), i4, u[it]);
         }
-    dense_epilogue<PATH, MBW, EPI>(a, mine, (2 * nt2 + h) * DENSE_TN, (mchunk * 4 + w) * MBW, lds);
+        if constexpr (JPK) fw[it] = *reinterpret_cast<const uint32_t *>(a.g + x_offset<PATH>(item_c(it), i4, nkc, a.mbw));
+    };
+    constexpr int BEFORE = IT < 4 ? IT : 4;
+#pragma unroll
+    for (int it = 0; it < BEFORE; ++it) fetch(it);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const f16v &v = acc[m][p];
+                const int col = 32 * m + (lane & 31), quad = 8 * p + 2 * e + (lane >> 5);
+                red[((kp * SG * CG + t) * 64 + col) * 16 + (quad ^ (col & 15))] =
+                    f4{v[4 * e], v[4 * e + 1], v[4 * e + 2], v[4 * e + 3]};
+            }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int it = BEFORE; it < IT; ++it) fetch(it);
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int c = item_c(it), col = cw + 4 * it;
+        if (c >= a.C) continue;
+        const f4 *src = red + (t * 64 + col) * 16 + ((lane & 15) ^ (col & 15));
+        f4 v = src[0];
+#pragma unroll
+        for (int r = 1; r < KS; ++r) {
+            const f4 o = src[r * SG * CG * 1024];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if constexpr (PATH == PATH_I8) v[e] = __int_as_float(__float_as_int(v[e]) + __float_as_int(o[e]));
+                else v[e] += o[e];
+            }
+        }
+        float4 ph = make_float4(acc_field<PATH>(v[0]), acc_field<PATH>(v[1]), acc_field<PATH>(v[2]), acc_field<PATH>(v[3]));
+        if constexpr (JPK) ph = less_diagonal<PATH>(a, i4, fw[it], ph);
+        if constexpr (EPI == EPI_UPDATE) update_store<PATH, 0>(a, c, i4, u[it], ph);
+        else *reinterpret_cast<float4 *>(a.phi + (int64_t)c * a.Np + i4) = ph;
+    }
 }
 
 // Grouped step of every dense instance of one serving group (same path and
@@ -1084,7 +1216,7 @@ __global__ __launch_bounds__(256) void k_dense_operand(int Np, int nkc, int mbw,
     const float4 v = *reinterpret_cast<const float4 *>(x + (int64_t)c * Np + i4);
     const float4 f = make_float4(f_value(fmode, v.x, delta), f_value(fmode, v.y, delta),
                                  f_value(fmode, v.z, delta), f_value(fmode, v.w, delta));
-    store_operand<PATH>(g, g_lo, op_offset<PATH>(c, i4, nkc, mbw), f, fmode);
+    store_operand<PATH>(g, g_lo, x_offset<PATH>(c, i4, nkc, mbw), f, fmode);
 }
 
 // Readout operand s = sign(x) with sign(0) = +1 (the energy convention of
@@ -1099,26 +1231,30 @@ __global__ __launch_bounds__(256) void k_readout_operand(int N, int Np, int nkc,
     const float4 v = *reinterpret_cast<const float4 *>(x + (int64_t)c * Np + i4);
     auto s = [N](float xv, int i) { return i < N ? (xv >= 0.0f ? 1.0f : -1.0f) : 0.0f; };
     const float4 f = make_float4(s(v.x, i4), s(v.y, i4 + 1), s(v.z, i4 + 2), s(v.w, i4 + 3));
-    store_operand<PATH>(g, nullptr, op_offset<PATH>(c, i4, nkc, mbw), f, 0);
+    store_operand<PATH>(g, nullptr, x_offset<PATH>(c, i4, nkc, mbw), f, 0);
 }
 
 // The fine tile where the 64-spin tiles leave CUs idle: 16 spins per workgroup
 // while those workgroups are at most one per CU, else 32. Above that the bytes
-// every CU pulls through its L1 (16 + 64 rows of operands per 16 spins) cost
 // more than the shorter chain of MFMAs saves. us per step, 64-spin tile / 16 /
 // 32 spins: fp32 N = 1500, C = 60 32.2 / 10.3 / 16.2; N = 2000, C = 128 (256
 // and 128 workgroups) 41.8 / 13.7 / 21.4; N = 4096, C = 128 (512 and 256) 78.9
 // / 49.1 / 39.8; N = 5000, C = 128 (640 and 320) 97 / 89 / 127; bf16 hi+lo N =
-// 4096, C = 128 34.2 / 40.7 / 30.6; int8 N = 4096, C = 128 12.8 / 13.8 / 10.6, N
-// = 6000, C = 128 (384 of 32 spins) 17.0 / 24.7 / 22.9. Bit-packed J is a
-// fraction of the bytes, two workgroups of 32 spins per CU still gain: fp8 N =
-// 8192, C = 128 (512) 27.8 / 27.4 / 22.0, fp4 17.4 / 20.0 / 15.9; N = 6000, C =
-// 256 (768) fp4 17.9 / 23.5 / 18.5.
+// 4096, C = 128 34.2 / 40.7 / 30.6.
+// The exact paths take it until the split-K step's 64 x 64 tiles fill half the CUs
+// (bit-packed fp4: all). us per step, fine / split-K at 96, 128, 192 and 256
+// such tiles: fp4 6.9 / 8.2, 8.0 / 8.7, 9.0 / 9.8, 11.1 / 9.5; fp8 8.6 / 8.6, 11.2 /
+// 9.7, 11.7 / 9.0, 15.8 / 10.6; int8 8.4 / 9.2, 10.0 / 10.4, 11.9 (64-spin) / 10.2,
+// 14.3 (64-spin) / 11.8.
 constexpr int MI355X_CUS = 256;
 inline int fine_spins(Path path, int Np, int Cg) {
     const int64_t blocks = (int64_t)Np / 16 * (Cg / 64);
+    if (path_op2(path)) {
+        if (blocks / 4 * (path == PATH_FP4PK ? 1 : 2) >= MI355X_CUS) return 0;
+        return blocks <= MI355X_CUS ? 16 : 32;
+    }
     if (blocks <= MI355X_CUS) return 16;
-    return blocks / 2 <= (path_packed(path) ? 2 : 1) * MI355X_CUS ? 32 : 0;
+    return blocks / 2 <= MI355X_CUS ? 32 : 0;
 }
 
 template <int PATH, int NB, int EPI>
@@ -1129,18 +1265,40 @@ hipError_t launch_step_fine(int Cg, const DenseStepArgs &a, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <int PATH, int SG, int CG, int EPI>
+hipError_t launch_step_sk(int Cg, const DenseStepArgs &a, hipStream_t st) {
+    const int nx = a.Np / (DENSE_TN * SG), ny = Cg / (64 * CG);
+    hipLaunchKernelGGL((k_dense_step_sk<PATH, SG, CG, EPI>), dim3((nx + 7) / 8 * 8 * ny), dim3(2 * DENSE_THREADS), 0, st,
+                       a, nx, ny);
+    return hipGetLastError();
+}
+
+// The tile of the split-K step: rounds of one workgroup per CU, each F + u k Np for
+// k 64 x 64 tiles (F about 6 us: launch, first loads, sums, state; the figures at
+// k_dense_step_sk), so rounds (F / u + k Np) is least.
+template <int PATH, int EPI>
+hipError_t launch_step_split(int Cg, const DenseStepArgs &a, hipStream_t st) {
+    constexpr int64_t FU = PATH == PATH_FP4PK ? 10000 : PATH == PATH_FP8PK ? 6500 : 2500;
+    const int64_t n = (int64_t)a.Np / 64 * (Cg / 64);   // 64 x 64 tiles
+    auto cost = [&](int k) { return (n / k + MI355X_CUS - 1) / MI355X_CUS * (FU + (int64_t)k * a.Np); };
+    const bool wide = Cg % 128 == 0;
+    if (cost(1) <= cost(2) && (!wide || cost(1) <= cost(4))) return launch_step_sk<PATH, 1, 1, EPI>(Cg, a, st);
+    if (wide && cost(4) < cost(2)) return launch_step_sk<PATH, 2, 2, EPI>(Cg, a, st);
+    return wide ? launch_step_sk<PATH, 1, 2, EPI>(Cg, a, st) : launch_step_sk<PATH, 2, 1, EPI>(Cg, a, st);
+}
+
 template <int PATH, int EPI>
 hipError_t launch_step_mbw(int mbw, dim3 grid, const DenseStepArgs &a, bool coarse, hipStream_t st) {
     const int Cg = (int)grid.y * 64 * mbw, fine = coarse ? 0 : fine_spins(Path(PATH), a.Np, Cg);
     if (fine == 16) return launch_step_fine<PATH, 1, EPI>(Cg, a, st);
     if (fine == 32) return launch_step_fine<PATH, 2, EPI>(Cg, a, st);
-    // 128-column tile of a bit-packed path: the split-K form when both K
-    // halves fill the prefetch pipeline (same fields, integer-valued sums)
-    if constexpr (path_packed(Path(PATH))) {
-        if (mbw == 2 && a.nkc % (2 * SK_DEPTH) == 0 && grid.x % 2 == 0) {
-            hipLaunchKernelGGL((k_dense_step_sk<PATH, 2, EPI>), dim3(grid.x / 2, grid.y), dim3(2 * DENSE_THREADS), 0, st, a);
-            return hipGetLastError();
-        }
+    if constexpr (path_op2(Path(PATH))) {
+        // (with J in bytes, where the split-K step's third round of 64 x 64 tiles is a part
+        // one, the 64-spin tiles stay: int8 N = 5000 and 6000, C = 512 30.0 and 36.6 us per
+        // step, split-K 31.3 and 37.2)
+        const int64_t n = (int64_t)grid.x * (Cg / 64);
+        const bool stay = !path_packed(Path(PATH)) && mbw == 1 && n > 2 * MI355X_CUS && n <= 3 * MI355X_CUS;
+        if (!coarse && !stay) return launch_step_split<PATH, EPI>(Cg, a, st);
     }
     // two J planes: two column groups per workgroup read each J fragment once
     // for 256 columns (half the J traffic of two 128-column workgroups)

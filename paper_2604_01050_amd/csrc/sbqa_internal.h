@@ -87,6 +87,13 @@ constexpr int dense_nkc(Path p, int Np) { return Np / path_kpc(p); }
 // Bit-packed J: a 16 x kpc fragment in 256 (fp8) or 512 (fp4) bytes, one or
 // two dwords per lane.
 constexpr int pk_frag_bytes(Path p) { return path_kpc(p) * 2; }
+// The operand of the exact paths holds ternary values at 2 bits: a 16 x kpc
+// fragment in 512 (fp8, int8) or 1024 (fp4) bytes, 16 consecutive K elements of a
+// row to a dword, a lane's dwords adjacent.
+constexpr bool path_op2(Path p) {
+    return p == PATH_FP8 || p == PATH_FP8PK || p == PATH_I8 || p == PATH_FP4 || p == PATH_FP4PK;
+}
+constexpr int op_frag_bytes(Path p) { return path_op2(p) ? path_kpc(p) * 4 : FRAG_BYTES; }
 // Device bytes of one plane of a [rows][Np] fragment-tiled matrix.
 inline int64_t dense_plane_bytes(Path p, int64_t rows, int Np) { return rows * (int64_t)dense_nkc(p, Np) * 128; }
 // Device bytes of the contraction copy of J (one plane).

@@ -197,3 +197,32 @@ def test_served_mix_tiles(sb, coup, prec, packing, mix):
             time.sleep(0.002)
         assert got is not None and np.array_equal(got[0], E) and np.array_equal(got[1], s)
     sb.sbqa_server_destroy(srv)
+
+
+# the split-K step at its four workgroup shapes (64 x 64 up to 128 x 128), K
+# ranges of uneven and no chunks, padded spins and columns, a lone column tile
+@pytest.mark.parametrize("N,C,other", [(2049, 350, 64), (3000, 700, 128), (1100, 1300, 64), (4500, 320, 64), (6100, 500, 256)])
+@pytest.mark.parametrize("coup,prec,packing,fmode", [("sidon", "INT8", 0, 0), ("sk", "FP8", 0, 1), ("sk", "FP8", 1, 0),
+                                                     ("sk", "FP4", 0, 0), ("sk", "FP4", 1, 1)])
+def test_split_k_shapes(sb, N, C, other, coup, prec, packing, fmode):
+    """Fields of many columns (split-K) equal those of 32 of them alone (the fine
+    tile) and, on sampled spins, the integer product; the steps that follow are
+    equal too."""
+    R, few = 2, 32
+    J = {"sidon": inst.sidon28_dense, "sk": inst.sk_pm1}[coup](N, 71)
+    X, Y = inst.uniform_state(N, C, 0.4, 72)
+    rows = np.random.default_rng(73).integers(0, N, 40)
+    got = []
+    for c in (C, few):
+        _log("split-K %s %s N=%d C=%d" % (coup, prec, N, c))
+        ctx = sb.sbqa_create(J=J, R=R, runs=c // R, steps=8, fmode=fmode, precision=getattr(sb, "PREC_" + prec),
+                             j_packing=packing, dense_tile=other, loop_kernel=sb.LOOP_STREAM, jp_kind=sb.JP_LINEAR,
+                             jp_start=0.5, jp_end=0.0)
+        sb.sbqa_set_state(ctx, X[:, :c], Y[:, :c])
+        phi = sb.sbqa_fields(ctx)
+        if fmode == 1:   # f = sign(x)
+            assert np.array_equal(phi[rows], (J[rows] @ np.sign(X[:, :c]).astype(np.float64)).astype(np.float32))
+        sb.sbqa_step(ctx, 5)
+        got.append([phi, *sb.sbqa_get_state(ctx), sb.sbqa_fields(ctx)])
+    for a, b in zip(*got):
+        assert np.array_equal(a[:, :few], b)
