@@ -169,7 +169,13 @@ __device__ __forceinline__ double tri_psi(const Tri3 &t3, int i, SpinOf spin) {
 
 // CSR energies of the readout of a state (element (i, c) at
 // state_off(order, ld, i, c)). Stage 1: block (row block rb, up to 256
-// columns) accumulates per column over its rows in row order.
+// columns) accumulates per column over its rows in row order. With few columns
+// there are 2 waves per SIMD or fewer: the loads of EROWS rows and EB neighbours
+// each are in flight together. The sums of a column lie together, so that stage 2
+// reads them in whole lines. us before (one load at a time; a column's sums 24 C
+// bytes apart) and now, both stages: cubic N = 262144, C = 128 334 and 213; degree 3
+// N = 10000, C = 64 21.4 and 15.4, C = 512 40.0 and 34.0; three-body lists 60 and 54.
+constexpr int EROWS = 4, EB = 8;
 __global__ __launch_bounds__(256) void k_csr_energy_partial(int N, int order, int ld, int C, int rows_per_blk,
                                                             const int32_t *__restrict__ row_ptr,
                                                             const int32_t *__restrict__ col,
@@ -181,22 +187,42 @@ __global__ __launch_bounds__(256) void k_csr_energy_partial(int N, int order, in
     const int rb = blockIdx.y;
     if (c >= C) return;
     double q = 0.0, l = 0.0, q3 = 0.0;
-    auto spin = [&](int j) { return x[state_off(order, ld, j, c)] >= 0.0f ? 1.0 : -1.0; };
+    auto at = [&](int j) { return x[state_off(order, ld, j, c)]; };
+    auto sign = [](float v) { return v >= 0.0f ? 1.0 : -1.0; };
+    auto spin = [&](int j) { return sign(at(j)); };
     const int i0 = rb * rows_per_blk, i1 = min(N, i0 + rows_per_blk);
-    for (int i = i0; i < i1; ++i) {
-        double phi = 0.0;
-        for (int p = row_ptr[i]; p < row_ptr[i + 1]; ++p) {
-            const float xv = x[state_off(order, ld, col[p], c)];
-            phi += val[p] * (xv >= 0.0f ? 1.0 : -1.0);
+    for (int i = i0; i < i1; i += EROWS) {
+        const int nu = min(EROWS, i1 - i);
+        float own[EROWS], nb[EROWS][EB];
+        int p0[EROWS + 1];
+#pragma unroll
+        for (int u = 0; u <= EROWS; ++u) p0[u] = row_ptr[min(i + u, i1)];
+#pragma unroll
+        for (int u = 0; u < EROWS; ++u) {
+            if (u >= nu) continue;
+            own[u] = at(i + u);
+#pragma unroll
+            for (int e = 0; e < EB; ++e)
+                if (p0[u] + e < p0[u + 1]) nb[u][e] = at(col[p0[u] + e]);
         }
-        const double s = x[state_off(order, ld, i, c)] >= 0.0f ? 1.0 : -1.0;
-        q += s * phi;
-        if (h) l += h[i] * s;
-        if (t3.ptr) q3 += s * tri_psi(t3, i, spin);
+#pragma unroll
+        for (int u = 0; u < EROWS; ++u) {
+            if (u >= nu) continue;
+            double phi = 0.0;
+#pragma unroll
+            for (int e = 0; e < EB; ++e)
+                if (p0[u] + e < p0[u + 1]) phi += val[p0[u] + e] * sign(nb[u][e]);
+            for (int p = p0[u] + EB; p < p0[u + 1]; ++p) phi += val[p] * spin(col[p]);
+            const double s = sign(own[u]);
+            q += s * phi;
+            if (h) l += h[i + u] * s;
+            if (t3.ptr) q3 += s * tri_psi(t3, i + u, spin);
+        }
     }
-    partial[((int64_t)rb * C + c) * 3] = q;
-    partial[((int64_t)rb * C + c) * 3 + 1] = l;
-    partial[((int64_t)rb * C + c) * 3 + 2] = q3;
+    double *dst = partial + ((int64_t)c * gridDim.y + rb) * 3;
+    dst[0] = q;
+    dst[1] = l;
+    dst[2] = q3;
 }
 
 // The pairwise tree over ENERGY_SLOTS = 1024 slots (slot t += slot t + w for
@@ -231,9 +257,10 @@ __global__ __launch_bounds__(ENERGY_SLOTS) void k_csr_energy_final(int C, int nr
     const int c = blockIdx.x, t = threadIdx.x;
     double q = 0.0, l = 0.0, q3 = 0.0;
     for (int rb = t; rb < nrb; rb += ENERGY_SLOTS) {
-        q += partial[((int64_t)rb * C + c) * 3];
-        l += partial[((int64_t)rb * C + c) * 3 + 1];
-        q3 += partial[((int64_t)rb * C + c) * 3 + 2];
+        const double *src = partial + ((int64_t)c * nrb + rb) * 3;
+        q += src[0];
+        l += src[1];
+        q3 += src[2];
     }
     sq[t] = q;
     sl[t] = l;
@@ -804,7 +831,7 @@ hipError_t launch_energy_fields(int N, int Np, int C, const float *x, const floa
 hipError_t launch_best_update(int N, int R, int runs, int order, int ld, const float *x, const double *E,
                               double *best_E, int64_t *best_step, int8_t *best_spins, int64_t step, bool reset,
                               int *sel, hipStream_t st) {
-    if (N > BEST_SPLIT_N && sel) {
+    if (sel && N > (ld >= 32 ? BEST_SPLIT_N : BEST_SCRATCH_N)) {
         hipLaunchKernelGGL(k_best_select, dim3(runs), dim3(64), 0, st, R, E, best_E, best_step, sel, step,
                            reset ? 1 : 0);
         const int chunks = std::min(1024, (N + 256 * 8 - 1) / (256 * 8));

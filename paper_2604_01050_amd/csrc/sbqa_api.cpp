@@ -826,7 +826,7 @@ sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, con
     }
     HIP_TRY(dalloc(c, &c->E, (size_t)std::max(C, Cp)));
     HIP_TRY(dalloc(c, &c->bestStep, (size_t)runs));
-    if (N > BEST_SPLIT_N) HIP_TRY(dalloc(c, &c->bsel, (size_t)runs));
+    if (N > BEST_SCRATCH_N) HIP_TRY(dalloc(c, &c->bsel, (size_t)runs));
     c->rbytes = (size_t)8 * runs + 8 + (size_t)runs * N;
     HIP_TRY(dalloc(c, &c->rdev, c->rbytes));
     HIP_TRY(pool_get(c->device, true, c->rbytes, &c->rhost_block));
@@ -1159,8 +1159,10 @@ sbqa_status ctx_energies_dev(sbqa_ctx *c, const int8_t *ds, int32_t count, doubl
 sbqa_status ctx_evaluate(sbqa_ctx *c, bool reset) {
     sbqa_status st = ctx_state_energies(c);
     if (st != SBQA_OK) return st;
+    // (the partials of the energies just summed are free again)
+    int *sel = c->bsel ? c->bsel : reinterpret_cast<int *>(c->csr_partial);
     HIP_TRY(launch_best_update(c->N, c->R, c->runs, c->order, c->ld, c->x[c->cur], c->E, c->bestE, c->bestStep,
-                               c->bestSpins, (int64_t)c->step, reset, c->bsel, c->stream));
+                               c->bestSpins, (int64_t)c->step, reset, sel, c->stream));
     c->last_eval_step = c->step;
     return SBQA_OK;
 }

@@ -420,10 +420,16 @@ hipError_t launch_energy_fields(int N, int Np, int C, const float *x, const floa
 // Per-run best over replicas with tie -> lowest k; updates best_E/best_step
 // when strictly lower (than +inf when reset: the previous best is discarded)
 // and copies the winning readout spins; one launch, one workgroup per run.
-// Above BEST_SPLIT_N spins the update runs as two launches (selection, then
-// the spin copy over many workgroups) with sel [runs] int scratch; the
-// results are the same.
-constexpr int BEST_SPLIT_N = 32768;
+// Above BEST_SPLIT_N spins and with sel [runs] int scratch (may be null) the
+// update runs as two launches (selection, then the spin copy over many
+// workgroups); the results are the same. A column of a spin-major state of 32
+// columns or more is a cache line per spin, which one CU takes 1.6 ns for: N =
+// 24850, C = 128 41 us in one launch, 11 in two; about equal at 8192. Rows of fewer
+// columns share lines: N = 10000, C = 4 4.8 and 7.6 us; those above BEST_SCRATCH_N.
+constexpr int BEST_SPLIT_N = 8192;
+// (spins above which a context has scratch of its own for it; sparse ones use
+// their energy partials)
+constexpr int BEST_SCRATCH_N = 32768;
 hipError_t launch_best_update(int N, int R, int runs, int order, int ld, const float *x, const double *E,
                               double *best_E, int64_t *best_step, int8_t *best_spins, int64_t step, bool reset,
                               int *sel, hipStream_t st);

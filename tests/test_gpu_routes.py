@@ -226,3 +226,25 @@ def test_split_k_shapes(sb, N, C, other, coup, prec, packing, fmode):
         got.append([phi, *sb.sbqa_get_state(ctx), sb.sbqa_fields(ctx)])
     for a, b in zip(*got):
         assert np.array_equal(a[:, :few], b)
+
+
+@pytest.mark.parametrize("N,d,R,runs", [(8192, 3, 4, 5), (8193, 3, 4, 5), (9001, 9, 16, 20), (40000, 12, 8, 9)])
+def test_sparse_readout_batches(sb, N, d, R, runs):
+    """Readout of a streamed sparse state around the split of the best update, with
+    rows of fewer and more than 8 neighbours and a part last group of rows: the
+    best replica's spins and its energy, integer couplings exact."""
+    _log("sparse readout N=%d d=%d" % (N, d))
+    (rp, col, val), h = _sparse(N, d, 91)
+    val, h = np.sign(val) * np.ceil(np.abs(val) * 3), np.round(h * 40)
+    ctx = sb.sbqa_create(csr=(rp, col, val), h=h, R=R, runs=runs, steps=4, seed=92, loop_kernel=sb.LOOP_STREAM)
+    sb.sbqa_step(ctx, 3)
+    E, s = sb.sbqa_best(ctx)
+    X, _ = sb.sbqa_get_state(ctx)
+    S = np.where(X >= 0, 1.0, -1.0)
+    rows = np.repeat(np.arange(N), np.diff(rp))
+    phi = np.zeros((N, R * runs))
+    np.add.at(phi, rows, val[:, None] * S[col])
+    Eall = (-0.5 * (S * phi).sum(0) - h @ S).reshape(runs, R)
+    k = Eall.argmin(1)
+    assert np.array_equal(E, Eall.min(1))
+    assert np.array_equal(s, np.stack([S[:, r * R + k[r]] for r in range(runs)]).astype(np.int8))
