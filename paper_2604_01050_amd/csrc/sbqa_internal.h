@@ -63,8 +63,8 @@ hipError_t launch_energy_gemm(const EnergyPlan &e, const int8_t *S, const double
                               hipStream_t st);
 
 // ---- dense contraction path -------------------------------------------------
-// The coupling matrix J and the operand f(X) of the dense paths are stored as
-// 2 KiB fragments ("fragment-tiled"): fragment (rb, kc) holds rows
+// The coupling matrix J and the operand f(X) of the dense paths (the exact paths'
+// operand: path_op2 below) are stored as 2 KiB fragments ("fragment-tiled"): fragment (rb, kc) holds rows
 // 16rb..16rb+15 and K bytes [128kc, 128kc+128); inside it, byte
 // h*1024 + l*16 + e holds row 16rb + l%16, K byte 32*(l/16) + 16h + e.
 // Lane l of a wave loads bytes l*16 and 1024 + l*16 of a fragment: exactly
@@ -134,9 +134,10 @@ struct DenseStepArgs {
 // One step of the dense path: Phi = J f(X_n) on MFMA for a workgroup tile of
 // DENSE_TN spins x 64*mbw replica columns, then either the fused update
 // (Eqs. 6-7, wall, next operand) or a plain store of Phi.
-// grid = (Np / DENSE_TN, Cg / (64 * mbw)). Small grids take a finer tile on the
-// same operand layout unless `coarse`: the tile autotuner times the mbw forms
-// themselves, which the grouped steps of the serving loop run at any grid.
+// grid = (Np / DENSE_TN, Cg / (64 * mbw)). Small grids take a finer tile, and the
+// exact paths above those the step with K split over the waves, on the same operand
+// layout unless `coarse`: the tile autotuner times the mbw forms themselves, which
+// the grouped steps of the serving loop run at any grid.
 hipError_t launch_dense_step(Path path, DenseEpilogue epi, int mbw, int Cg, const DenseStepArgs &a, hipStream_t st,
                              bool coarse = false);
 

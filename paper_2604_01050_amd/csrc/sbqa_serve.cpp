@@ -545,6 +545,7 @@ static hipError_t open_create_stream(sbqa_server *srv, hipEvent_t held) {
             continue;
         if ((e = launch_hold(0, tried[n])) != hipSuccess || (e = hipStreamSynchronize(tried[n])) != hipSuccess) continue;
         apart = hipEventQuery(held) == hipErrorNotReady;
+        (void)hipGetLastError();   // "not ready" is no failure of the next launch
         e = hipStreamSynchronize(srv->stream);
     }
     if (e == hipSuccess) srv->create_stream = tried[--n];
