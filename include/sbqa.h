@@ -190,11 +190,13 @@ typedef struct {
     uint32_t energy_every;   /* 0: best over the final state only; K > 0: also
                                 track the best after every K-th step              */
     int32_t loop_kernel;     /* sbqa_loop_kernel                                   */
-    int32_t dense_tile;      /* dense path: replica columns per workgroup tile,
-                                64, 128 or 256; 0 = autotuned (each candidate's
+    int32_t dense_tile;      /* dense path: replica columns of the 64-spin workgroup
+                                tile, 64, 128 or 256; grids that leave it idle
+                                take 16 or 32 spins x 64 columns or split K instead.
+                                0 = kernel and tile autotuned (each candidate's
                                 step timed on scratch buffers of the instance's
-                                shape once per device and shape; every tile
-                                gives the same bits). Choices persist across
+                                shape once per device and shape). Every choice
+                                gives the same bits. Choices persist across
                                 processes in a text file: the path in the
                                 environment variable SBQA_TUNE_CACHE ("off":
                                 none), else $XDG_CACHE_HOME/sbqa/dense_tiles.txt,
@@ -224,7 +226,8 @@ typedef struct {
     size_t device_bytes;     /* device memory held by the context                  */
     int32_t resident;        /* 1 when steps run in a resident loop
                                 (sbqa_loop_kernel), 0 otherwise                   */
-    int32_t tile_cols;       /* dense path: replica columns per workgroup tile   */
+    int32_t tile_cols;       /* dense path: replica columns of the 64-spin tile,
+                                whether or not the step takes it               */
     int32_t reordered;       /* 1 when CSR spins are relabelled internally
                                 (sbqa_reorder), 0 otherwise                       */
 } sbqa_info_t;

@@ -1234,28 +1234,7 @@ __global__ __launch_bounds__(256) void k_readout_operand(int N, int Np, int nkc,
     store_operand<PATH>(g, nullptr, x_offset<PATH>(c, i4, nkc, mbw), f, 0);
 }
 
-// The fine tile where the 64-spin tiles leave CUs idle: 16 spins per workgroup
-// while those workgroups are at most one per CU, else 32. Above that the bytes
-// more than the shorter chain of MFMAs saves. us per step, 64-spin tile / 16 /
-// 32 spins: fp32 N = 1500, C = 60 32.2 / 10.3 / 16.2; N = 2000, C = 128 (256
-// and 128 workgroups) 41.8 / 13.7 / 21.4; N = 4096, C = 128 (512 and 256) 78.9
-// / 49.1 / 39.8; N = 5000, C = 128 (640 and 320) 97 / 89 / 127; bf16 hi+lo N =
-// 4096, C = 128 34.2 / 40.7 / 30.6.
-// The exact paths take it until the split-K step's 64 x 64 tiles fill half the CUs
-// (bit-packed fp4: all). us per step, fine / split-K at 96, 128, 192 and 256
-// such tiles: fp4 6.9 / 8.2, 8.0 / 8.7, 9.0 / 9.8, 11.1 / 9.5; fp8 8.6 / 8.6, 11.2 /
-// 9.7, 11.7 / 9.0, 15.8 / 10.6; int8 8.4 / 9.2, 10.0 / 10.4, 11.9 (64-spin) / 10.2,
-// 14.3 (64-spin) / 11.8.
 constexpr int MI355X_CUS = 256;
-inline int fine_spins(Path path, int Np, int Cg) {
-    const int64_t blocks = (int64_t)Np / 16 * (Cg / 64);
-    if (path_op2(path)) {
-        if (blocks / 4 * (path == PATH_FP4PK ? 1 : 2) >= MI355X_CUS) return 0;
-        return blocks <= MI355X_CUS ? 16 : 32;
-    }
-    if (blocks <= MI355X_CUS) return 16;
-    return blocks / 2 <= MI355X_CUS ? 32 : 0;
-}
 
 template <int PATH, int NB, int EPI>
 hipError_t launch_step_fine(int Cg, const DenseStepArgs &a, hipStream_t st) {
@@ -1273,32 +1252,21 @@ hipError_t launch_step_sk(int Cg, const DenseStepArgs &a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// The tile of the split-K step: rounds of one workgroup per CU, each F + u k Np for
-// k 64 x 64 tiles (F about 6 us: launch, first loads, sums, state; the figures at
-// k_dense_step_sk), so rounds (F / u + k Np) is least.
 template <int PATH, int EPI>
-hipError_t launch_step_split(int Cg, const DenseStepArgs &a, hipStream_t st) {
-    constexpr int64_t FU = PATH == PATH_FP4PK ? 10000 : PATH == PATH_FP8PK ? 6500 : 2500;
-    const int64_t n = (int64_t)a.Np / 64 * (Cg / 64);   // 64 x 64 tiles
-    auto cost = [&](int k) { return (n / k + MI355X_CUS - 1) / MI355X_CUS * (FU + (int64_t)k * a.Np); };
-    const bool wide = Cg % 128 == 0;
-    if (cost(1) <= cost(2) && (!wide || cost(1) <= cost(4))) return launch_step_sk<PATH, 1, 1, EPI>(Cg, a, st);
-    if (wide && cost(4) < cost(2)) return launch_step_sk<PATH, 2, 2, EPI>(Cg, a, st);
-    return wide ? launch_step_sk<PATH, 1, 2, EPI>(Cg, a, st) : launch_step_sk<PATH, 2, 1, EPI>(Cg, a, st);
-}
-
-template <int PATH, int EPI>
-hipError_t launch_step_mbw(int mbw, dim3 grid, const DenseStepArgs &a, bool coarse, hipStream_t st) {
-    const int Cg = (int)grid.y * 64 * mbw, fine = coarse ? 0 : fine_spins(Path(PATH), a.Np, Cg);
-    if (fine == 16) return launch_step_fine<PATH, 1, EPI>(Cg, a, st);
-    if (fine == 32) return launch_step_fine<PATH, 2, EPI>(Cg, a, st);
-    if constexpr (path_op2(Path(PATH))) {
-        // (with J in bytes, where the split-K step's third round of 64 x 64 tiles is a part
-        // one, the 64-spin tiles stay: int8 N = 5000 and 6000, C = 512 30.0 and 36.6 us per
-        // step, split-K 31.3 and 37.2)
-        const int64_t n = (int64_t)grid.x * (Cg / 64);
-        const bool stay = !path_packed(Path(PATH)) && mbw == 1 && n > 2 * MI355X_CUS && n <= 3 * MI355X_CUS;
-        if (!coarse && !stay) return launch_step_split<PATH, EPI>(Cg, a, st);
+hipError_t launch_step_form(DenseForm form, int mbw, dim3 grid, const DenseStepArgs &a, hipStream_t st) {
+    const int Cg = (int)grid.y * 64 * mbw;
+    switch (form) {
+        case FORM_FINE16: return launch_step_fine<PATH, 1, EPI>(Cg, a, st);
+        case FORM_FINE32: return launch_step_fine<PATH, 2, EPI>(Cg, a, st);
+        case FORM_TILE: break;
+        default:
+            if constexpr (path_op2(Path(PATH))) {
+                if (form == FORM_SK11) return launch_step_sk<PATH, 1, 1, EPI>(Cg, a, st);
+                if (form == FORM_SK21) return launch_step_sk<PATH, 2, 1, EPI>(Cg, a, st);
+                if (form == FORM_SK12 && Cg % 128 == 0) return launch_step_sk<PATH, 1, 2, EPI>(Cg, a, st);
+                if (form == FORM_SK22 && Cg % 128 == 0) return launch_step_sk<PATH, 2, 2, EPI>(Cg, a, st);
+            }
+            return hipErrorInvalidValue;
     }
     // two J planes: two column groups per workgroup read each J fragment once
     // for 256 columns (half the J traffic of two 128-column workgroups)
@@ -1319,10 +1287,10 @@ hipError_t launch_step_mbw(int mbw, dim3 grid, const DenseStepArgs &a, bool coar
 }
 
 template <int PATH>
-hipError_t launch_step_path(DenseEpilogue epi, int mbw, dim3 grid, const DenseStepArgs &a, bool coarse,
+hipError_t launch_step_path(DenseEpilogue epi, DenseForm form, int mbw, dim3 grid, const DenseStepArgs &a,
                             hipStream_t st) {
-    return epi == EPI_UPDATE ? launch_step_mbw<PATH, EPI_UPDATE>(mbw, grid, a, coarse, st)
-                             : launch_step_mbw<PATH, EPI_FIELDS>(mbw, grid, a, coarse, st);
+    return epi == EPI_UPDATE ? launch_step_form<PATH, EPI_UPDATE>(form, mbw, grid, a, st)
+                             : launch_step_form<PATH, EPI_FIELDS>(form, mbw, grid, a, st);
 }
 
 }  // namespace
@@ -1348,8 +1316,32 @@ hipError_t launch_energy_gemm(const EnergyPlan &e, const int8_t *S, const double
     return hipGetLastError();
 }
 
-hipError_t launch_dense_step(Path path, DenseEpilogue epi, int mbw, int Cg, const DenseStepArgs &a, hipStream_t st,
-                             bool coarse) {
+// us per step of the forms, measured (update form, N a multiple of 512):
+//   fine / split-K at 96, 128, 192 and 256 tiles of 64 x 64: fp4 6.9 / 8.2, 8.0 / 8.7,
+//     9.0 / 9.8, 11.1 / 9.5; fp8 8.6 / 8.6, 11.2 / 9.7, 11.7 / 9.0, 15.8 / 10.6; int8
+//     8.4 / 9.2, 10.0 / 10.4 (64-spin tile at the next two) 11.9 / 10.2, 14.3 / 11.8;
+//   64-spin tile / split-K, +-1 J in fp4 at N = 4096 and C = 512 .. 3072 (tiles per CU):
+//     2: 14.6 / 14.1, 2.25: 17.3 / 21.3, 3: 18.5 / 19.5, 3.5: 21.6 / 19.9, 4: 23.1 / 23.3,
+//     5: 28.3 / 34.2, 6: 31.3 / 35.1, 8: 39.7 / 40.6, 12: 55.1 / 68.0; N = 8192 at 4 and 8:
+//     31.4 / 27.0, 56.5 / 49.9; N = 16384 at 4: 51.0 / 41.4;
+//   the same with J in bytes (int8): N = 16384, C = 1024 265 / 326, N = 5120, C = 512 26.8 / 28.3.
+// A split-K workgroup has a CU to itself, so its rounds have to be full; several
+// 64-spin workgroups share one and take any count.
+//   Real J: fp32, 64-spin tile / 16 / 32 spins: N = 1500, C = 60 32.2 / 10.3 / 16.2; N =
+//     2000, C = 128 41.8 / 13.7 / 21.4; N = 4096, C = 128 (512 and 256 fine workgroups) 78.9 /
+//     49.1 / 39.8; N = 5000, C = 128 97 / 89 / 127; bf16 hi+lo N = 4096, C = 128 34.2 / 40.7 / 30.6.
+DenseForm default_dense_form(Path path, int Np, int Cg) {
+    const int64_t n16 = (int64_t)Np / 16 * (Cg / 64), n = n16 / 4;   // fine workgroups; 64 x 64 tiles
+    if (!path_op2(path)) return n16 <= MI355X_CUS ? FORM_FINE16 : n16 / 2 <= MI355X_CUS ? FORM_FINE32 : FORM_TILE;
+    if (n < (path == PATH_FP4PK ? MI355X_CUS : MI355X_CUS / 2)) return n16 <= MI355X_CUS ? FORM_FINE16 : FORM_FINE32;
+    if (n <= MI355X_CUS) return FORM_SK11;
+    if (n <= 2 * MI355X_CUS) return Cg % 128 == 0 ? FORM_SK12 : FORM_SK21;
+    const int64_t round = 4 * MI355X_CUS, rounds = (n + round - 1) / round;
+    return path_packed(path) && Cg % 128 == 0 && 20 * n >= 17 * rounds * round ? FORM_SK22 : FORM_TILE;
+}
+
+hipError_t launch_dense_step(Path path, DenseEpilogue epi, DenseForm form, int mbw, int Cg, const DenseStepArgs &a,
+                             hipStream_t st) {
     const int tm = 64 * mbw;
     if (a.Np % DENSE_TN || Cg % tm || a.C > Cg || a.Np % path_kpc(path) || a.nkc != dense_nkc(path, a.Np) ||
         a.nkc % dense_depth(path))
@@ -1358,13 +1350,13 @@ hipError_t launch_dense_step(Path path, DenseEpilogue epi, int mbw, int Cg, cons
     DenseStepArgs b = a;
     b.mbw = mbw;
     switch (path) {
-        case PATH_F32: return launch_step_path<PATH_F32>(epi, mbw, grid, b, coarse, st);
-        case PATH_FP8: return launch_step_path<PATH_FP8>(epi, mbw, grid, b, coarse, st);
-        case PATH_BF16X3: return launch_step_path<PATH_BF16X3>(epi, mbw, grid, b, coarse, st);
-        case PATH_I8: return launch_step_path<PATH_I8>(epi, mbw, grid, b, coarse, st);
-        case PATH_FP8PK: return launch_step_path<PATH_FP8PK>(epi, mbw, grid, b, coarse, st);
-        case PATH_FP4: return launch_step_path<PATH_FP4>(epi, mbw, grid, b, coarse, st);
-        case PATH_FP4PK: return launch_step_path<PATH_FP4PK>(epi, mbw, grid, b, coarse, st);
+        case PATH_F32: return launch_step_path<PATH_F32>(epi, form, mbw, grid, b, st);
+        case PATH_FP8: return launch_step_path<PATH_FP8>(epi, form, mbw, grid, b, st);
+        case PATH_BF16X3: return launch_step_path<PATH_BF16X3>(epi, form, mbw, grid, b, st);
+        case PATH_I8: return launch_step_path<PATH_I8>(epi, form, mbw, grid, b, st);
+        case PATH_FP8PK: return launch_step_path<PATH_FP8PK>(epi, form, mbw, grid, b, st);
+        case PATH_FP4: return launch_step_path<PATH_FP4>(epi, form, mbw, grid, b, st);
+        case PATH_FP4PK: return launch_step_path<PATH_FP4PK>(epi, form, mbw, grid, b, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -434,19 +434,20 @@ void plan_layout(int32_t N, int32_t R, int32_t runs, const InstanceFacts &f, Lay
     L->bytes = (size_t)b;
 }
 
-void set_tile(Layout *L, int mbw) {
-    L->mbw = mbw;
-    L->Cg = (int)round_up(L->C, 64 * mbw);
-}
-
 // ------------------------------------------------------------ tile autotuner
-// Dense workgroup tile: 64 * mbw replica columns (mbw m-blocks per wave).
-// Candidates that pad C by at most 2x are timed once per (device, path, C, Np
-// rounded up to a power of two), on scratch buffers of the instance's shape
-// (the MFMA step's time does not depend on the values); the fastest is kept.
-// Every tile sums each field in the same K order, so the choice never changes
-// results. Choices persist across processes in a tile file (below), so a new
-// process (a server restart) does not time them again.
+// Kernel form of a context's dense step (DenseForm) and row blocks per operand
+// group, mbw. Candidates that pad C by at most 2x are timed once per (device,
+// path, C, Np) on scratch buffers of the instance's shape (the MFMA step's time
+// does not depend on the values); the fastest is kept. Contexts of the serving
+// loop are stepped by the grouped launches, whose 64-spin tiles have 64 * mbw
+// columns: their mbw alone is timed, per power of two that holds Np. Every form
+// gives the same bits, so a choice never changes results. Choices persist across
+// processes in a tile file (below), so a new process (a server restart) does not
+// time them again.
+struct DenseChoice {
+    int mbw = 0;
+    int form = 0;   // DenseForm; 0: served
+};
 
 // The device a choice was timed on: architecture and compute-unit count.
 static std::string tile_device_tag() {
@@ -468,8 +469,8 @@ static std::string tile_device_tag() {
 // The tile file: SBQA_TUNE_CACHE names it ("" or "off": choices stay in the
 // process), else $XDG_CACHE_HOME/sbqa/dense_tiles.txt, else
 // $HOME/.cache/sbqa/dense_tiles.txt. One line per choice,
-//   sbqa-tile-v1 <arch> <CUs> <path> <C> <padded N> <mbw>
-// appended with one write; unreadable files and malformed lines are ignored
+//   sbqa-tile-v1 <arch> <CUs> <path + 16 form> <C> <padded N> <mbw>
+// (form 0: served) appended with one write; unreadable files and malformed lines are ignored
 // (a choice is used only when it is one of the key's candidates).
 static std::string tile_file(bool make_dir) {
     const char *env = std::getenv("SBQA_TUNE_CACHE");
@@ -486,7 +487,10 @@ static std::string tile_file(bool make_dir) {
     return dir + "/dense_tiles.txt";
 }
 
-static void load_tile_file(const std::string &dev, std::map<std::tuple<std::string, int, int, int>, int> *cache) {
+// (device, path, C, padded N, served)
+typedef std::tuple<std::string, int, int, int, bool> ChoiceKey;
+
+static void load_tile_file(const std::string &dev, std::map<ChoiceKey, DenseChoice> *cache) {
     const std::string f = tile_file(false);
     if (f.empty()) return;
     FILE *fp = std::fopen(f.c_str(), "r");
@@ -497,7 +501,9 @@ static void load_tile_file(const std::string &dev, std::map<std::tuple<std::stri
         int cus = 0, path = 0, C = 0, npb = 0, mbw = 0;
         if (std::sscanf(line, "%31s %255s %d %d %d %d %d", tag, arch, &cus, &path, &C, &npb, &mbw) != 7) continue;
         if (std::strcmp(tag, "sbqa-tile-v1") != 0 || std::string(arch) + " " + std::to_string(cus) != dev) continue;
-        if (mbw == 1 || mbw == 2 || mbw == 4) (*cache)[std::make_tuple(dev, path, C, npb)] = mbw;
+        const int form = path >> 4;
+        if (path < 0 || form > FORM_SK22) continue;
+        if (mbw == 1 || mbw == 2 || mbw == 4) (*cache)[ChoiceKey(dev, path & 15, C, npb, form == 0)] = DenseChoice{mbw, form};
     }
     std::fclose(fp);
 }
@@ -514,18 +520,39 @@ static void append_tile_file(const std::string &dev, int path, int C, int npb, i
     ::close(fd);
 }
 
-static int tune_dense_mbw(Path path, int C, int Np, hipStream_t st) {
-    static std::mutex mu;
-    static std::map<std::tuple<std::string, int, int, int>, int> cache;
-    static std::set<std::string> loaded;
-    int npb = 128;
-    while (npb < Np) npb *= 2;
-    const int fallback = dense_mbw(C);
-    std::vector<int> cand;
+// The candidates of a shape. The operand grouping hardly matters outside the
+// 64-spin tile: there the largest that adds no padding. Forms that were nowhere near
+// the fastest at a grid's size are left out.
+static std::vector<DenseChoice> dense_candidates(Path path, int C, int Np, bool served) {
+    std::vector<int> ms;
     for (int m : {1, 2, 4})
-        if (m == fallback || round_up(C, 64 * m) <= 2 * round_up(C, 64)) cand.push_back(m);
+        if (m == dense_mbw(C) || round_up(C, 64 * m) <= 2 * round_up(C, 64)) ms.push_back(m);
+    std::vector<DenseChoice> out;
+    if (!served) {
+        const int64_t C64 = round_up(C, 64);
+        const int m0 = C64 % 256 == 0 ? 4 : C64 % 128 == 0 ? 2 : 1;
+        const int64_t n = (int64_t)Np / 64 * (C64 / 64);
+        if (n <= 1024)
+            for (int f : {FORM_FINE16, FORM_FINE32}) out.push_back({m0, f});
+        if (path_op2(path) && n >= 64)
+            for (int f : {FORM_SK11, FORM_SK21, FORM_SK12, FORM_SK22})
+                if (m0 > 1 || f <= FORM_SK21) out.push_back({m0, f});
+        if (n < 96) return out;
+    }
+    for (int m : ms) out.push_back({m, served ? 0 : (int)FORM_TILE});
+    return out;
+}
+
+static DenseChoice tune_dense(Path path, int C, int Np, bool served, hipStream_t st) {
+    static std::mutex mu;
+    static std::map<ChoiceKey, DenseChoice> cache;
+    static std::set<std::string> loaded;
+    int npk = Np;
+    if (served)
+        for (npk = 128; npk < Np;) npk *= 2;
+    const std::vector<DenseChoice> cand = dense_candidates(path, C, Np, served);
     const std::string dev = tile_device_tag();
-    const auto key = std::make_tuple(dev, (int)path, C, npb);
+    const ChoiceKey key(dev, (int)path, C, npk, served);
     {
         std::lock_guard<std::mutex> lk(mu);
         if (!dev.empty() && !loaded.count(dev)) {
@@ -533,9 +560,17 @@ static int tune_dense_mbw(Path path, int C, int Np, hipStream_t st) {
             loaded.insert(dev);
         }
         auto it = cache.find(key);
-        if (it != cache.end() && std::find(cand.begin(), cand.end(), it->second) != cand.end()) return it->second;
+        if (it != cache.end()) {
+            const DenseChoice k = it->second;
+            const int64_t Cg = round_up(C, 64 * k.mbw);
+            if (Cg <= std::max<int64_t>(2 * round_up(C, 64), round_up(C, 64 * dense_mbw(C))) &&
+                (k.form < FORM_SK11 || path_op2(path)) && (k.form < FORM_SK12 || Cg % 128 == 0))
+                return k;
+        }
     }
-    int best = fallback;
+    DenseChoice best;
+    best.mbw = dense_mbw(C);
+    best.form = served ? 0 : (int)default_dense_form(path, Np, (int)round_up(C, 64 * best.mbw));
     bool timed = false;
     if (cand.size() > 1) {
         const int planes = path == PATH_BF16X3 ? 2 : 1;
@@ -572,33 +607,44 @@ static int tune_dense_mbw(Path path, int C, int Np, hipStream_t st) {
         hipEvent_t e0 = nullptr, e1 = nullptr;
         bool ok = a.J && a.g && a.g_next && a.h && a.x_in && a.x_out && a.y && a.jp && (planes == 1 || (a.J_lo && a.g_lo && a.g_next_lo)) &&
                   hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess;
-        float best_ms = 0.0f;
-        for (int m : cand) {
-            if (!ok) break;
-            const int Cg = (int)round_up(C, 64 * m);
-            ok = launch_dense_step(path, EPI_UPDATE, m, Cg, a, st, true) == hipSuccess;   // warm-up
-            ok = ok && hipEventRecord(e0, st) == hipSuccess;
-            for (int r = 0; r < 3 && ok; ++r) ok = launch_dense_step(path, EPI_UPDATE, m, Cg, a, st, true) == hipSuccess;
-            ok = ok && hipEventRecord(e1, st) == hipSuccess && hipEventSynchronize(e1) == hipSuccess;
-            float ms = 0.0f;
-            ok = ok && hipEventElapsedTime(&ms, e0, e1) == hipSuccess;
-            if (ok && (m == cand.front() || ms < best_ms)) {
-                best_ms = ms;
-                best = m;
+        auto launch = [&](const DenseChoice &k) {
+            return launch_dense_step(path, EPI_UPDATE, served ? FORM_TILE : (DenseForm)k.form, k.mbw,
+                                     (int)round_up(C, 64 * k.mbw), a, st) == hipSuccess;
+        };
+        // (each once for the clocks and the caches, then twice three launches)
+        std::vector<float> us(cand.size(), INFINITY);
+        for (size_t q = 0; q < cand.size() && ok; ++q) ok = launch(cand[q]);
+        for (int round = 0; round < 2; ++round)
+            for (size_t q = 0; q < cand.size() && ok; ++q) {
+                ok = launch(cand[q]) && hipEventRecord(e0, st) == hipSuccess;
+                for (int r = 0; r < 3 && ok; ++r) ok = launch(cand[q]);
+                ok = ok && hipEventRecord(e1, st) == hipSuccess && hipEventSynchronize(e1) == hipSuccess;
+                float ms = 0.0f;
+                ok = ok && hipEventElapsedTime(&ms, e0, e1) == hipSuccess;
+                if (ok) us[q] = std::min(us[q], ms * 1000.0f / 3.0f);
             }
-        }
+        if (ok) best = cand[(size_t)(std::min_element(us.begin(), us.end()) - us.begin())];
         (void)hipStreamSynchronize(st);
         if (e0) (void)hipEventDestroy(e0);
         if (e1) (void)hipEventDestroy(e1);
         for (void *p : bufs) (void)hipFree(p);
-        if (!ok) best = fallback;
         timed = ok;
         (void)hipGetLastError();
     }
     std::lock_guard<std::mutex> lk(mu);
     cache[key] = best;
-    if (timed && !dev.empty()) append_tile_file(dev, (int)path, C, npb, best);
+    if (timed && !dev.empty()) append_tile_file(dev, (int)path + 16 * best.form, C, npk, best.mbw);
     return best;
+}
+
+// Tile of a context: the caller's (dense_tile columns, 0: chosen by timing).
+static void set_tile(Layout *L, Path path, int dense_tile, bool served, hipStream_t st) {
+    DenseChoice k;
+    if (dense_tile) k.mbw = dense_tile / 64;
+    else k = tune_dense(path, L->C, L->Np, served, st);
+    L->mbw = k.mbw;
+    L->Cg = (int)round_up(L->C, 64 * L->mbw);
+    L->form = k.form ? (DenseForm)k.form : default_dense_form(path, L->Np, L->Cg);
 }
 
 size_t instance_bytes(int32_t N, int32_t R, int32_t runs, const InstanceFacts &f, uint32_t steps) {
@@ -1093,7 +1139,7 @@ sbqa_status ctx_step_once(sbqa_ctx *c) {
                                 c->stream));
     } else {
         const DenseStepArgs a = dense_args(c, n, in);
-        HIP_TRY(launch_dense_step(c->facts.path, EPI_UPDATE, c->L.mbw, c->L.Cg, a, c->stream));
+        HIP_TRY(launch_dense_step(c->facts.path, EPI_UPDATE, c->L.form, c->L.mbw, c->L.Cg, a, c->stream));
     }
     c->cur = out;
     c->step = n + 1;
@@ -1129,7 +1175,7 @@ sbqa_status ctx_state_energies(sbqa_ctx *c) {
         DenseStepArgs a = dense_args(c, c->step, in);
         a.g = static_cast<const uint8_t *>(c->g[sc]);
         a.phi = c->x[sc];
-        HIP_TRY(launch_dense_step(c->facts.path, EPI_FIELDS, c->L.mbw, c->L.Cg, a, c->stream));
+        HIP_TRY(launch_dense_step(c->facts.path, EPI_FIELDS, c->L.form, c->L.mbw, c->L.Cg, a, c->stream));
         HIP_TRY(launch_energy_fields(c->N, c->L.Np, c->L.C, c->x[in], c->x[sc], h64, c->E, c->stream));
     } else {
         const EnergyPlan e = energy_plan(c->N, c->L.C);
@@ -1458,6 +1504,7 @@ sbqa_status ctx_create(const sbqa_coupling *J, const double *h, int32_t N, int32
             h = h ? rl.h.data() : nullptr;
         }
     }
+    const bool served = !allow_resident;       // stepped by the grouped launches
     if (facts.jbits) allow_resident = false;   // the small dense loop needs J in float32
     {
         std::string why;
@@ -1471,7 +1518,7 @@ sbqa_status ctx_create(const sbqa_coupling *J, const double *h, int32_t N, int32
         if (facts.path != PATH_CSR && !c->resident && allow_resident && s->loop_kernel == SBQA_LOOP_AUTO) mid_plan(c);
     }
     if (facts.path != PATH_CSR)
-        set_tile(&c->L, s->dense_tile ? s->dense_tile / 64 : tune_dense_mbw(facts.path, c->L.C, c->L.Np, c->stream));
+        set_tile(&c->L, facts.path, s->dense_tile, served, c->stream);
     if (facts.path != PATH_CSR) {
         c->order = ORDER_REPLICA_MAJOR;
         c->ld = c->L.Np;
@@ -1888,7 +1935,7 @@ sbqa_status sbqa_fields(sbqa_ctx *c, float *phi) {
     }
     DenseStepArgs a = dense_args(c, c->step, c->cur);
     a.phi = sum;
-    HIP_TRY(launch_dense_step(c->facts.path, EPI_FIELDS, c->L.mbw, c->L.Cg, a, c->stream));
+    HIP_TRY(launch_dense_step(c->facts.path, EPI_FIELDS, c->L.form, c->L.mbw, c->L.Cg, a, c->stream));
     buf.resize((size_t)C * Np);
     HIP_TRY(hipMemcpyAsync(buf.data(), sum, sizeof(float) * buf.size(), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));

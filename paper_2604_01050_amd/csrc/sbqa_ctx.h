@@ -39,7 +39,8 @@ struct Layout {
     int Np = 0;       // N padded to dense_pad(path) (dense)
     int Cp = 0;       // C padded to GEMM_BM (rows of the fp64 energies)
     int Cg = 0;       // C padded to 64 * mbw (rows of the contraction operand)
-    int mbw = 1;      // m-blocks per wave of the dense step
+    int mbw = 1;      // row blocks per operand group (m-blocks per wave of the 64-spin tile)
+    DenseForm form = FORM_TILE;   // kernel form of the dense step
     int nkc = 0;      // K chunks of 128 bytes per operand row (dense)
     int Cs = 0;       // C padded to 4 (CSR row stride)
     int csr_nrb = 0;  // row blocks of the CSR energy reduction

@@ -134,12 +134,18 @@ struct DenseStepArgs {
 // One step of the dense path: Phi = J f(X_n) on MFMA for a workgroup tile of
 // DENSE_TN spins x 64*mbw replica columns, then either the fused update
 // (Eqs. 6-7, wall, next operand) or a plain store of Phi.
-// grid = (Np / DENSE_TN, Cg / (64 * mbw)). Small grids take a finer tile, and the
-// exact paths above those the step with K split over the waves, on the same operand
-// layout unless `coarse`: the tile autotuner times the mbw forms themselves, which
-// the grouped steps of the serving loop run at any grid.
-hipError_t launch_dense_step(Path path, DenseEpilogue epi, int mbw, int Cg, const DenseStepArgs &a, hipStream_t st,
-                             bool coarse = false);
+// grid = (Np / DENSE_TN, Cg / (64 * mbw)). The other forms, on the same operand layout
+// and with the same bits: tiles of 16 or 32 spins x 64 columns for small grids, and, on the
+// exact paths, K split over the waves of workgroups of 1 x 1, 2 x 1, 1 x 2 or 2 x 2 tiles of 64
+// spins x 64 columns (the last two take columns in whole pairs: Cg % 128 == 0).
+enum DenseForm : int32_t {
+    FORM_FINE16 = 1, FORM_FINE32 = 2, FORM_TILE = 3, FORM_SK11 = 4, FORM_SK21 = 5, FORM_SK12 = 6, FORM_SK22 = 7
+};
+// The form where none has been timed: with a tile given by the caller, and for the
+// readouts of served instances.
+DenseForm default_dense_form(Path path, int Np, int Cg);
+hipError_t launch_dense_step(Path path, DenseEpilogue epi, DenseForm form, int mbw, int Cg, const DenseStepArgs &a,
+                             hipStream_t st);
 
 // ---- grouped steps of the serving loop ----------------------------------------
 // Three-body terms (the cubic part of Eq. 11) of a CSR instance, listed per

@@ -1,0 +1,83 @@
+"""GPU tests of the library's choices between kernels for a call: every choice
+gives the same bits."""
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+import sbqa_instances as inst
+
+pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def sb():
+    import paper_2604_01050_amd as sb
+    return sb
+
+
+def _log(msg):
+    print(msg, flush=True)
+
+
+_FORMS = """
+import os, sys
+sys.path.insert(0, %r)
+import numpy as np, torch
+import paper_2604_01050_amd as sb
+import sbqa_instances as inst
+p = torch.cuda.get_device_properties(0)
+dev = "%%s %%d" %% (p.gcnArchName, p.multi_processor_count)
+N, R, few = 1500, 2, 32
+cases = [("sidon", "INT8", 0, 4, 0), ("sk", "FP8", 0, 5, 1), ("sk", "FP8", 1, 1, 0), ("sk", "FP4", 0, 7, 0),
+         ("sk", "FP4", 1, 6, 1), ("gauss", "FP32", 0, 0, 2), ("gauss", "BF16X3", 0, 2, 2)]
+keys = {}   # (case, columns): form and operand grouping named in the tile file
+with open(os.environ["SBQA_TUNE_CACHE"], "w") as f:
+    for coup, prec, packing, path, fmode in cases:
+        q = 0
+        for form in (range(1, 8) if coup != "gauss" else range(1, 4)):
+            for mbw in (1, 2, 4):
+                q += 1
+                keys[prec, packing, 128 * q] = (form, mbw)
+                f.write("sbqa-tile-v1 %%s %%d %%d 1536 %%d\\n" %% (dev, path + 16 * form, 128 * q, mbw))
+J = {c: {"sidon": inst.sidon28_dense, "sk": inst.sk_pm1, "gauss": inst.dense_gaussian}[c](N, 71) for c in ("sidon", "sk", "gauss")}
+X, Y = inst.uniform_state(N, 128 * 21, 0.4, 72)
+X[:, 0] = 0.0
+h = np.round(inst.gaussian_fields(N, 2.0, 73))
+for coup, prec, packing, path, fmode in cases:
+    ref = None
+    for C in [few] + sorted(c for p_, k, c in keys if (p_, k) == (prec, packing)):
+        form, mbw = keys.get((prec, packing, C), (0, 0))
+        print(coup, prec, packing, "C=%%d form %%d mbw %%d" %% (C, form, mbw), flush=True)
+        ctx = sb.sbqa_create(J=J[coup], h=h, R=R, runs=C // R, steps=8, fmode=fmode, precision=getattr(sb, "PREC_" + prec),
+                             j_packing=packing, dense_tile=64 if C == few else 0, loop_kernel=sb.LOOP_STREAM,
+                             jp_kind=sb.JP_LINEAR, jp_start=0.5, jp_end=0.0)
+        assert C == few or sb.sbqa_info(ctx)["tile_cols"] == 64 * mbw
+        sb.sbqa_set_state(ctx, X[:, :C], Y[:, :C])
+        phi = sb.sbqa_fields(ctx)
+        if coup != "gauss":   # the threshold is 0 at the first step: f = sign(x)
+            assert np.array_equal(phi, (J[coup] @ np.sign(X[:, :C]).astype(np.float64)).astype(np.float32))
+        sb.sbqa_step(ctx, 5)
+        E, s = sb.sbqa_best(ctx)
+        got = [phi, *sb.sbqa_get_state(ctx), sb.sbqa_fields(ctx), E[None], s.T]
+        if ref is None:
+            ref = got
+        for a, b in zip(ref, got):
+            assert np.array_equal(a, b[:, :a.shape[1]])
+print("forms agree")
+"""
+
+
+def test_every_form_of_the_dense_step(tmp_path):
+    """The dense step in each of its forms (16- and 32-spin tiles, the 64-spin
+    tile, split-K at its four workgroup shapes) and operand groupings, named
+    through the tile file: fields exact for integer couplings, then fields, states
+    and readouts equal to those of 32 columns alone."""
+    _log("forms of the dense step")
+    r = subprocess.run([sys.executable, "-u", "-c", _FORMS % ROOT], capture_output=True, text=True, timeout=110,
+                       env=dict(os.environ, SBQA_TUNE_CACHE=str(tmp_path / "tiles.txt")))
+    assert r.returncode == 0 and "forms agree" in r.stdout, r.stdout[-500:] + r.stderr[-2000:]
