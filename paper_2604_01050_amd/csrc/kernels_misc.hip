@@ -58,26 +58,64 @@ __global__ void k_init_state(int N, int C, int order, int ld, uint32_t key_lo, u
     y[o] = uniform_sym(r.y, amp);
 }
 
-// 64 x 64 tiles through LDS: whichever way the two orders run, loads go along
-// the rows of src and stores along the rows of dst.
+// Tiles of TR rows x 64 columns through LDS: whichever way the two orders run,
+// loads go along the rows of src and stores along the rows of dst; whole rows of
+// fewer than 64 columns that follow each other are taken as one run (src or dst may
+// be host memory, which wants long accesses). 64 rows; 16 where src is host
+// memory, which a CU reads at about 1 GB/s: 60 x 60 floats in one tile took 15 us.
 constexpr int RT = 64;
+template <int TR>
 __global__ __launch_bounds__(256) void k_state_reorder(int N, int C, int order_in, int ld_in,
                                                        const float *__restrict__ src,
                                                        const int32_t *__restrict__ row_in, int order_out, int ld_out,
                                                        float *__restrict__ dst, const int32_t *__restrict__ row_out) {
-    __shared__ float tile[RT][RT + 1];
+    __shared__ float tile[TR][RT + 1];
     const int cb = (C + RT - 1) / RT;
-    const int i0 = (int)(blockIdx.x / cb) * RT, c0 = (int)(blockIdx.x % cb) * RT;
-    const int t = threadIdx.x & (RT - 1), u = threadIdx.x / RT;
+    const int i0 = (int)(blockIdx.x / cb) * TR, c0 = (int)(blockIdx.x % cb) * RT;
+    // place k of this thread in the tile, rows or columns innermost
+    auto place = [](bool cols_inner, int k, int &v, int &w) {
+        const int e = threadIdx.x + 256 * k;
+        v = cols_inner ? e / RT : e % TR;
+        w = cols_inner ? e % RT : e / TR;
+    };
     const bool in_c = order_in != ORDER_REPLICA_MAJOR, out_c = order_out != ORDER_REPLICA_MAJOR;   // columns innermost
-    for (int v = u; v < RT; v += 256 / RT) {
-        const int i = i0 + (in_c ? v : t), c = c0 + (in_c ? t : v);
-        if (i < N && c < C) tile[i - i0][c - c0] = src[state_off(order_in, ld_in, row_in ? row_in[i] : i, c)];
+    const int run = min(TR, N - i0) * C;
+    constexpr int IT = TR * RT / 256;   // elements per thread, all loads before the first use
+    float val[IT];
+    const bool in_run = order_in == ORDER_SPIN_MAJOR && ld_in == C && C < RT && !row_in;
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+        if (in_run) {
+            const int e = threadIdx.x + 256 * k;
+            if (e < run) val[k] = src[(int64_t)i0 * C + e];
+        } else {
+            int v, w;
+            place(in_c, k, v, w);
+            const int i = i0 + v, c = c0 + w;
+            if (i < N && c < C) val[k] = src[state_off(order_in, ld_in, row_in ? row_in[i] : i, c)];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+        if (in_run) {
+            const int e = threadIdx.x + 256 * k;
+            if (e < run) tile[e / C][e % C] = val[k];
+        } else {
+            int v, w;
+            place(in_c, k, v, w);
+            tile[v][w] = val[k];   // (past N or C: never read)
+        }
     }
     __syncthreads();
-    for (int v = u; v < RT; v += 256 / RT) {
-        const int i = i0 + (out_c ? v : t), c = c0 + (out_c ? t : v);
-        if (i < N && c < C) dst[state_off(order_out, ld_out, row_out ? row_out[i] : i, c)] = tile[i - i0][c - c0];
+    if (order_out == ORDER_SPIN_MAJOR && ld_out == C && C < RT && !row_out) {
+        for (int e = threadIdx.x; e < run; e += 256) dst[(int64_t)i0 * C + e] = tile[e / C][e % C];
+    } else {
+        for (int k = 0; k < IT; ++k) {
+            int v, w;
+            place(out_c, k, v, w);
+            const int i = i0 + v, c = c0 + w;
+            if (i < N && c < C) dst[state_off(order_out, ld_out, row_out ? row_out[i] : i, c)] = tile[v][w];
+        }
     }
 }
 
@@ -686,12 +724,18 @@ hipError_t launch_init_state(int N, int C, int order, int ld, uint64_t seed, dou
 }
 
 hipError_t launch_state_reorder(int N, int C, int order_in, int ld_in, const float *src, const int32_t *row_in,
-                                int order_out, int ld_out, float *dst, const int32_t *row_out, hipStream_t st) {
+                                int order_out, int ld_out, float *dst, const int32_t *row_out, bool from_host,
+                                hipStream_t st) {
     if (N <= 0 || C <= 0) return hipSuccess;
-    const int64_t blocks = (int64_t)((N + RT - 1) / RT) * ((C + RT - 1) / RT);
+    const int tr = from_host ? 16 : RT;
+    const int64_t blocks = (int64_t)((N + tr - 1) / tr) * ((C + RT - 1) / RT);
     if (blocks >= ((int64_t)1 << 24)) return hipErrorInvalidValue;   // 2^32 threads
-    hipLaunchKernelGGL(k_state_reorder, dim3((unsigned)blocks), dim3(256), 0, st, N, C, order_in, ld_in, src, row_in,
-                       order_out, ld_out, dst, row_out);
+    if (from_host)
+        hipLaunchKernelGGL(k_state_reorder<16>, dim3((unsigned)blocks), dim3(256), 0, st, N, C, order_in, ld_in, src,
+                           row_in, order_out, ld_out, dst, row_out);
+    else
+        hipLaunchKernelGGL(k_state_reorder<RT>, dim3((unsigned)blocks), dim3(256), 0, st, N, C, order_in, ld_in, src,
+                           row_in, order_out, ld_out, dst, row_out);
     return hipGetLastError();
 }
 

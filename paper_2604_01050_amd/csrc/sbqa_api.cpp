@@ -748,6 +748,8 @@ sbqa_ctx::~sbqa_ctx() {
 constexpr size_t SMALL_BYTES = (size_t)256 << 10, CHUNK_BYTES = (size_t)1 << 20;
 // Largest copy that a call takes through pinned memory.
 constexpr size_t STAGE_BYTES = (size_t)8 << 20;
+// Device buffer of a larger state on its way in (of those that the pool keeps).
+constexpr size_t BULK_BYTES = (size_t)64 << 20;
 
 template <class T>
 static hipError_t dalloc(sbqa_ctx *c, T **p, size_t n) {
@@ -1534,7 +1536,9 @@ sbqa_status ctx_create(const sbqa_coupling *J, const double *h, int32_t N, int32
         std::vector<int32_t> orig((size_t)N);
         for (int32_t i = 0; i < N; ++i) orig[(size_t)c->pnew[(size_t)i]] = i;
         hipError_t e = dalloc(c, &c->porig, (size_t)N);
+        if (e == hipSuccess) e = dalloc(c, &c->pos, (size_t)N);
         if (e == hipSuccess) e = upload(c, c->porig, orig.data(), sizeof(int32_t) * N);
+        if (e == hipSuccess) e = upload(c, c->pos, c->pnew.data(), sizeof(int32_t) * N);
         if (e == hipSuccess) e = settle(c);   // the staging vector dies here
         if (e != hipSuccess) st = fail(SBQA_EDEVICE, "relabelling: %s", hipGetErrorString(e));
     }
@@ -1761,6 +1765,92 @@ sbqa_status ctx_best(sbqa_ctx *c, double *energies, int8_t *spins) {
     return ctx_readout_collect(c, energies, spins);
 }
 
+// The state from (set) or to the caller's arrays x, y (spin rows of C columns;
+// null: skipped), through pinned memory that the device reads or writes itself,
+// larger ones in slabs of rows: no device memory is taken, whatever the state's
+// size, and a small state costs two launches and a wait (N * C = 8000: get 25 us, set
+// 28; two copies through a device buffer 61). Padding rows and columns hold zero
+// and are not written. Returns with the work completed; set rebuilds the operand.
+// A state above twice the pinned size is set by copies into a device buffer where
+// there is room for one (N = 200000, C = 256: 22 ms, through pinned slabs 31).
+static sbqa_status transfer_state(sbqa_ctx *c, float *x, float *y, bool set) {
+    const int N = c->N, C = c->L.C;
+    const size_t row = sizeof(float) * C;
+    const bool whole = 2 * row * N <= STAGE_BYTES;
+    const int per = whole ? N : (int)std::max<size_t>(1, STAGE_BYTES / 2 / row);   // rows of a slab
+    PoolBlock stage(c->device, true), dev(c->device, false);
+    struct Wait { hipStream_t st; ~Wait() { (void)hipStreamSynchronize(st); } } wait{c->stream};
+    // n rows from the caller's row r0 on, between buf (rows of C columns) and the state
+    auto reorder = [&](float *state, float *buf, int r0, int n, bool host) -> sbqa_status {
+        const int32_t *rows = c->pos ? c->pos + r0 : nullptr;
+        if (!rows) state += state_off(c->order, c->ld, r0, 0);
+        if (set) HIP_TRY(launch_state_reorder(n, C, ORDER_SPIN_MAJOR, C, buf, nullptr, c->order, c->ld, state, rows, host, c->stream));
+        else HIP_TRY(launch_state_reorder(n, C, c->order, c->ld, state, rows, ORDER_SPIN_MAJOR, C, buf, nullptr, false, c->stream));
+        return SBQA_OK;
+    };
+    if (set && 2 * row * N > 2 * STAGE_BYTES) {
+        const int bulk = (int)std::min<size_t>(N, std::max<size_t>(1, BULK_BYTES / row));
+        if (dev.get(row * bulk) == hipSuccess) {
+            for (int q = 0; q < 2; ++q)
+                for (int r0 = 0; r0 < N; r0 += bulk) {
+                    const int n = std::min(bulk, N - r0);
+                    HIP_TRY(hipMemcpyAsync(dev.as<float>(), (q ? y : x) + (size_t)r0 * C, row * n, hipMemcpyHostToDevice,
+                                           c->stream));
+                    const sbqa_status st = reorder(q ? c->y : c->x[c->cur], dev.as<float>(), r0, n, false);
+                    if (st != SBQA_OK) return st;
+                }
+            const sbqa_status st = rebuild_operand(c);
+            if (st != SBQA_OK) return st;
+            HIP_TRY(hipStreamSynchronize(c->stream));
+            return SBQA_OK;
+        }
+        (void)hipGetLastError();   // no room: through the pinned slabs
+    }
+    HIP_TRY(stage.get(2 * row * per));
+    void *mapped = nullptr;
+    HIP_TRY(hipHostGetDevicePointer(&mapped, stage.as<void>(), 0));
+    struct Slab { float *user, *state; int r0, n; };
+    std::vector<Slab> slabs;
+    for (int q = 0; q < 2; ++q)
+        for (int r0 = 0; (q ? y : x) && r0 < N; r0 += per)
+            slabs.push_back({q ? y : x, q ? c->y : c->x[c->cur], r0, std::min(per, N - r0)});
+    auto half = [&](void *base, size_t k) { return static_cast<float *>(base) + (k & 1) * (size_t)per * C; };
+    auto move = [&](size_t k) {   // between the caller's array and the slab's half of the stage
+        float *user = slabs[k].user + (size_t)slabs[k].r0 * C, *mine = half(stage.as<void>(), k);
+        std::memcpy(set ? mine : user, set ? user : mine, row * slabs[k].n);
+    };
+    if (!set && !whole) {   // (the error word before anything is handed out)
+        const sbqa_status st = ctx_sync(c);
+        if (st != SBQA_OK) return st;
+    }
+    for (size_t k = 0; k < slabs.size(); ++k) {
+        // each half is free again before it is written; otherwise one slab is
+        // copied by the host while the device works on the next
+        if (set) {
+            if (k >= 2) HIP_TRY(hipStreamSynchronize(c->stream));
+            move(k);
+        }
+        const sbqa_status st = reorder(slabs[k].state, half(mapped, k), slabs[k].r0, slabs[k].n, true);
+        if (st != SBQA_OK) return st;
+        if (!set && !whole) {
+            if (k) move(k - 1);
+            HIP_TRY(hipStreamSynchronize(c->stream));
+        }
+    }
+    if (set) {
+        const sbqa_status st = rebuild_operand(c);
+        if (st != SBQA_OK) return st;
+        HIP_TRY(hipStreamSynchronize(c->stream));
+        return SBQA_OK;
+    }
+    if (whole) {
+        const sbqa_status st = ctx_sync(c);
+        if (st != SBQA_OK) return st;
+    }
+    for (size_t k = whole ? 0 : slabs.size() - std::min<size_t>(slabs.size(), 1); k < slabs.size(); ++k) move(k);
+    return SBQA_OK;
+}
+
 }  // namespace sbqa
 
 // =========================================================================== //
@@ -1909,7 +1999,7 @@ sbqa_status sbqa_fields(sbqa_ctx *c, float *phi) {
             }
             float *xsm = c->x[1 - c->cur];
             int8_t *gsm = (int8_t *)c->g[1 - c->cur];
-            HIP_TRY(launch_state_reorder(N, C, c->order, c->ld, xs, nullptr, ORDER_SPIN_MAJOR, Cs, xsm, nullptr, c->stream));
+            HIP_TRY(launch_state_reorder(N, C, c->order, c->ld, xs, nullptr, ORDER_SPIN_MAJOR, Cs, xsm, nullptr, false, c->stream));
             if (c->s.fmode != SBQA_F_BALLISTIC)
                 HIP_TRY(launch_csr_operand(c->s.fmode, N, Cs, C, xsm, gsm, delta_at(&c->s, c->step), c->stream));
             xs = xsm;
@@ -1947,34 +2037,13 @@ sbqa_status sbqa_fields(sbqa_ctx *c, float *phi) {
 sbqa_status sbqa_get_state(sbqa_ctx *c, float *x, float *y) {
     clear_error();
     if (!c) return fail(SBQA_EINVAL, "NULL context");
-    // brought into the caller's order (spin rows of C columns) on the device
-    const int N = c->N, C = c->L.C;
-    const size_t one = (size_t)N * C, bytes = sizeof(float) * one;
-    PoolBlock dev(c->device, false), stage(c->device, true);
-    struct Wait { hipStream_t st; ~Wait() { if (st) (void)hipStreamSynchronize(st); } } wait{c->stream};
-    const bool pinned = 2 * bytes <= STAGE_BYTES;
-    HIP_TRY(dev.get(2 * bytes));
-    if (pinned) HIP_TRY(stage.get(2 * bytes));
-    for (int q = 0; q < 2; ++q) {
-        float *to = q ? y : x, *d = dev.as<float>() + q * one;
-        if (!to) continue;
-        HIP_TRY(launch_state_reorder(N, C, c->order, c->ld, q ? c->y : c->x[c->cur], nullptr, ORDER_SPIN_MAJOR, C, d,
-                                     c->porig, c->stream));
-        HIP_TRY(hipMemcpyAsync(pinned ? stage.as<float>() + q * one : to, d, bytes, hipMemcpyDeviceToHost, c->stream));
-    }
-    const sbqa_status e = ctx_sync(c);
-    if (e != SBQA_OK) return e;
-    wait.st = nullptr;
-    if (pinned && x) std::memcpy(x, stage.as<float>(), bytes);
-    if (pinned && y) std::memcpy(y, stage.as<float>() + one, bytes);
-    return SBQA_OK;
+    return transfer_state(c, x, y, false);
 }
 
 sbqa_status sbqa_set_state(sbqa_ctx *c, const float *x, const float *y) {
     clear_error();
     if (!c || !x || !y) return fail(SBQA_EINVAL, "NULL argument");
-    const int N = c->N, C = c->L.C;
-    const size_t one = (size_t)N * C, bytes = sizeof(float) * one;
+    const size_t one = (size_t)c->N * c->L.C;
     for (size_t q0 = 0; q0 < one; q0 += 4096) {
         const size_t q1 = std::min(one, q0 + 4096);
         int bad = 0;   // NaN and infinities fail the comparisons
@@ -1984,26 +2053,10 @@ sbqa_status sbqa_set_state(sbqa_ctx *c, const float *x, const float *y) {
             if (!std::isfinite(x[q]) || !std::isfinite(y[q]) || std::fabs(x[q]) > 1.0f)
                 return fail(SBQA_EINVAL, "state must be finite with |x| <= 1 (index %zu)", q);
     }
-    // the caller's order to the context's on the device; padding rows and
-    // columns hold zero and are not written
-    PoolBlock dev(c->device, false), stage(c->device, true);
-    struct Wait { hipStream_t st; ~Wait() { if (st) (void)hipStreamSynchronize(st); } } wait{c->stream};
-    const bool pinned = 2 * bytes <= STAGE_BYTES;
-    HIP_TRY(dev.get(2 * bytes));
-    if (pinned) HIP_TRY(stage.get(2 * bytes));
-    for (int q = 0; q < 2; ++q) {
-        const float *from = q ? y : x;
-        float *d = dev.as<float>() + q * one;
-        if (pinned) std::memcpy(stage.as<float>() + q * one, from, bytes);
-        HIP_TRY(hipMemcpyAsync(d, pinned ? stage.as<float>() + q * one : from, bytes, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(launch_state_reorder(N, C, ORDER_SPIN_MAJOR, C, d, c->porig, c->order, c->ld, q ? c->y : c->x[c->cur],
-                                     nullptr, c->stream));
-    }
     c->sbits_step = -1;
-    sbqa_status st = rebuild_operand(c);
+    // (transfer_state only reads what it is given in this direction)
+    sbqa_status st = transfer_state(c, const_cast<float *>(x), const_cast<float *>(y), true);
     if (st != SBQA_OK) return st;
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    wait.st = nullptr;
     c->last_eval_step = -1;
     return SBQA_OK;
 }

@@ -180,6 +180,7 @@ struct sbqa_ctx {
     int32_t *colpad = nullptr;          // [rows][D]
     std::vector<int32_t> pnew;          // CSR spins relabelled: row of the caller's spin i (empty: identity)
     int32_t *porig = nullptr;           // [N] the caller's spin index of each row (relabelled only)
+    int32_t *pos = nullptr;             // [N] the row of each of the caller's spins (relabelled only)
     float *valpad = nullptr;            // [D][rows]
     // readout energies of the resident loop: the couplings grouped by the
     // energy row blocks, row block innermost (launch_csr_energy_colblock)

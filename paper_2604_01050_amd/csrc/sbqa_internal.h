@@ -337,9 +337,11 @@ hipError_t launch_init_state(int N, int C, int order, int ld, uint64_t seed, dou
 
 // Copy of an N x C float state from one order to another (rows of dst outside
 // [0, N) are left as they are). row_in / row_out (nullptr: the identity): the
-// row of src / dst that copy row i is read from / written to.
+// row of src / dst that copy row i is read from / written to. from_host: src is
+// pinned host memory (its device address).
 hipError_t launch_state_reorder(int N, int C, int order_in, int ld_in, const float *src, const int32_t *row_in,
-                                int order_out, int ld_out, float *dst, const int32_t *row_out, hipStream_t st);
+                                int order_out, int ld_out, float *dst, const int32_t *row_out, bool from_host,
+                                hipStream_t st);
 
 // Readout spins sign(x) (sign(0) = +1) of a replica-major state [C][Np] as int8
 // +-1 into S[cp][Np] (zero padding), for the dense energies.

@@ -81,3 +81,42 @@ def test_every_form_of_the_dense_step(tmp_path):
     r = subprocess.run([sys.executable, "-u", "-c", _FORMS % ROOT], capture_output=True, text=True, timeout=110,
                        env=dict(os.environ, SBQA_TUNE_CACHE=str(tmp_path / "tiles.txt")))
     assert r.returncode == 0 and "forms agree" in r.stdout, r.stdout[-500:] + r.stderr[-2000:]
+
+
+# one slab and several (rows of 8 to 4100 columns; above 8 MB for x and y), all three
+# orders of the state in memory, relabelled rows
+@pytest.mark.parametrize("kind,N,R,runs", [("dense", 60, 1, 1), ("dense", 300, 10, 6), ("dense", 700, 4, 1025),
+                                           ("resident", 777, 8, 1), ("resident", 600, 16, 130), ("stream", 3001, 3, 5),
+                                           ("relabelled", 9000, 4, 2), ("relabelled", 9001, 7, 33),
+                                           ("stream", 40000, 4, 16)])
+def test_state_transfer(sb, kind, N, R, runs):
+    """A state handed in comes back bit for bit, whole or one half of it, the
+    start of a context is the same draw in every order, and a refused state
+    changes nothing."""
+    _log("state transfer %s N=%d C=%d" % (kind, N, R * runs))
+    if kind == "dense":
+        kw = dict(J=inst.sk_pm1(N, 5))
+    else:
+        E = inst.regular_graph(N, 3 if N % 2 == 0 else 4, 6)
+        kw = dict(csr=inst.edges_to_csr(N, E, inst.gaussian_edges(len(E), 7)), seed=8,
+                  reorder=sb.REORDER_ON if kind == "relabelled" else sb.REORDER_OFF,
+                  loop_kernel=sb.LOOP_RESIDENT if kind == "resident" else sb.LOOP_STREAM)
+    ctx = sb.sbqa_create(R=R, runs=runs, steps=4, **kw)
+    assert sb.sbqa_info(ctx)["reordered"] == (kind == "relabelled")
+    x0, y0 = sb.sbqa_get_state(ctx)
+    if kind in ("relabelled", "resident"):
+        ref = sb.sbqa_create(R=R, runs=runs, steps=4, **dict(kw, reorder=sb.REORDER_OFF, loop_kernel=sb.LOOP_STREAM))
+        assert all(np.array_equal(a, b) for a, b in zip((x0, y0), sb.sbqa_get_state(ref)))
+    x, y = inst.uniform_state(N, R * runs, 0.7, 9)
+    sb.sbqa_set_state(ctx, x, y)
+    bad = y.copy()
+    bad[-1, -1] = np.inf
+    with pytest.raises(sb.SbqaError):
+        sb.sbqa_set_state(ctx, x0, bad)
+    gx, gy = sb.sbqa_get_state(ctx)
+    assert np.array_equal(gx, x) and np.array_equal(gy, y)
+    only = np.full_like(y, 7.0)
+    assert sb.lib.sbqa_get_state(ctx.ptr, None, only.ctypes.data) == sb.OK and np.array_equal(only, y)
+    only[:] = 7.0
+    assert sb.lib.sbqa_get_state(ctx.ptr, only.ctypes.data, None) == sb.OK and np.array_equal(only, x)
+    assert sb.lib.sbqa_get_state(ctx.ptr, None, None) == sb.OK
