@@ -853,6 +853,16 @@ sbqa_status rebuild_operand(sbqa_ctx *c) {
     return SBQA_OK;
 }
 
+// Buffers of the 8-column loop: its published edges, counters and sign bytes.
+static hipError_t alloc_wide(sbqa_ctx *c) {
+    const size_t nwg = (size_t)c->L.C / resident_cols(), NR = (size_t)c->res_rows;
+    hipError_t e = dalloc(c, &c->xpub, 2 * nwg * 2 * NR);
+    if (e == hipSuccess) e = dalloc(c, &c->flags, nwg);
+    if (e == hipSuccess) e = dalloc(c, &c->epoch_cnt, nwg);
+    if (e == hipSuccess) e = dalloc(c, &c->sbits, nwg * NR);
+    return e;
+}
+
 sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, const uint32_t *jbits) {
     const int N = c->N, Np = c->L.Np, Cs = c->L.Cs, C = c->L.C, Cp = c->L.Cp;
     const Path path = c->facts.path;
@@ -1005,10 +1015,7 @@ sbqa_status ctx_upload(sbqa_ctx *c, const sbqa_coupling *J, const double *h, con
                 HIP_TRY(dalloc(c, &c->words, (size_t)2 * c->res_nwg * 2 * narrow_rows(N)));
                 HIP_TRY(dalloc(c, &c->rings, (size_t)2 * runs));
             } else {
-                HIP_TRY(dalloc(c, &c->xpub, (size_t)2 * c->res_nwg * 2 * NR));
-                HIP_TRY(dalloc(c, &c->flags, (size_t)c->res_nwg));
-                HIP_TRY(dalloc(c, &c->epoch_cnt, (size_t)c->res_nwg));
-                HIP_TRY(dalloc(c, &c->sbits, (size_t)c->res_nwg * NR));
+                HIP_TRY(alloc_wide(c));
             }
             HIP_TRY(dalloc(c, &c->rd_cnt, (size_t)runs));
             HIP_TRY(upload(c, c->colpad, cp.data(), sizeof(int32_t) * cp.size()));
@@ -1584,6 +1591,38 @@ static sbqa_status ctx_step_small(sbqa_ctx *c, uint32_t K) {
     return SBQA_OK;
 }
 
+// The fewest steps for which a launch of the many-step loop is the faster way;
+// fewer are taken one launch of the step kernel each, whose operand the state then
+// carries. us for 1 / 2 / 4 / 8 / 16 steps, step kernel and loop:
+//   one row block per wave: N = 700, C = 128 5 10 20 40 81 and 7 8 12 21 38; N = 130, C = 640
+//     5.8 11 23 43 92 and 4.8 5.6 7.4 11 19
+//   two column blocks above 1024 spins: N = 2048, R = 32, C = 256 6.6 13 27 52 105 and 12.5 18 30 53 98
+//   two row blocks, several workgroups: N = 1500, C = 320 6.6 14 26 53 104 and 11 16 25 44 83
+//   four row blocks, one workgroup per group (a * N + b + (c * N + d) K against the
+//     step kernel's time): N = 1000, C = 640 7 14 28 55 114 and 22 28 40 64 114;
+//     N = 700, C = 640 6.7 14 27 56 107 and 18 22 31 48 82; N = 1000, C = 1600
+//     11 22 44 88 177 and 23 29 41 66 114.
+static uint32_t mid_min_steps(const sbqa_ctx *c) {
+    const double N = c->N, C = c->L.C;
+    if (c->N <= 256 && c->mid.MB == 1 && C >= 512) return 1;
+    if (c->mid.RBW == 4) {
+        const double gain = (4.3 + 0.0042 * C) - (0.1 + 0.006 * N);
+        return (uint32_t)std::min(64.0, std::ceil((7.2 + 0.009 * N) / std::max(gain, 0.1)));
+    }
+    if (c->mid.MB == 2 && c->N > 1024) return 6;
+    return c->mid.RBW == 2 && c->mid.G > 1 ? (c->N > 1024 ? 4 : 3) : 2;
+}
+
+// Whether steps of the context have been recorded into a graph. Its many-step
+// loops step the state in place and, when recorded, can be replayed; once they have
+// been, every call keeps to them.
+static bool recorded(sbqa_ctx *c) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
+    c->recorded = c->recorded || st != hipStreamCaptureStatusNone;
+    return c->recorded;
+}
+
 // K steps of the many-step loop of a dense +-1 instance in one launch.
 static sbqa_status ctx_step_mid(sbqa_ctx *c, uint32_t K) {
     MidArgs a;
@@ -1619,12 +1658,35 @@ static sbqa_status ctx_step_mid(sbqa_ctx *c, uint32_t K) {
     return SBQA_OK;
 }
 
+// Whether a context of the narrow loop takes K steps with 8 columns per
+// workgroup: a launch of the narrow loop reads the couplings by more workgroups
+// and ends with the ring's count, which few steps of it do not make up for. us for
+// 1 and 4 steps, 8 columns / narrow: N = 200, C = 1024 5.6, 13.1 / 10.0, 14.6; N =
+// 1000, C = 512 6.5, 15.4 / 9.6, 15.0; C = 256 6.1, 14.8 / 7.4, 11.7; N = 4096, C = 128
+// 13.7, 31.2 / 16.1, 24.5; but N = 1000, C = 64 5.5 / 5.8, C = 32 5.5 / 5.2. Not when recorded:
+// the counters of the 8-column loop tell a launch from the one before it, not from
+// the same one replayed. Its buffers are taken at the first such call.
+static bool wide_step(sbqa_ctx *c, uint32_t K) {
+    if (c->L.C < 128 || recorded(c) || (int64_t)K > c->L.C / 256 + (c->L.C < 256)) return false;
+    if (c->sbits) return true;
+    if (alloc_wide(c) == hipSuccess) return true;
+    (void)hipGetLastError();   // no room: the narrow loop does it
+    c->sbits = nullptr;
+    return false;
+}
+
 // K steps of the register-resident loop in one launch. A wait that timed out
 // sets the error word of the readout block, which every synchronising call
 // copies back and reports.
 static sbqa_status ctx_step_resident(sbqa_ctx *c, uint32_t K) {
-    if (c->mid.NT) return ctx_step_mid(c, K);
+    if (c->mid.NT) {
+        if (recorded(c) || K >= mid_min_steps(c)) return ctx_step_mid(c, K);
+        sbqa_status st = c->g_stale ? rebuild_operand(c) : SBQA_OK;
+        for (uint32_t q = 0; q < K && st == SBQA_OK; ++q) st = ctx_step_once(c);
+        return st;
+    }
     if (c->facts.path != PATH_CSR) return ctx_step_small(c, K);
+    const bool narrow = c->res_W < resident_cols() && !wide_step(c, K);
     ResidentArgs a;
     a.N = c->N;
     a.R = c->R;
@@ -1632,7 +1694,7 @@ static sbqa_status ctx_step_resident(sbqa_ctx *c, uint32_t K) {
     a.n0 = (int)c->step;
     a.K = (int)K;
     a.fmode = c->s.fmode;
-    a.nwg = c->res_nwg;
+    a.nwg = narrow ? c->res_nwg : c->L.C / resident_cols();
     a.colpad = c->colpad;
     a.valpad = c->valpad;
     a.h = c->h32;
@@ -1652,7 +1714,7 @@ static sbqa_status ctx_step_resident(sbqa_ctx *c, uint32_t K) {
     a.err = c->err;
     a.nr = c->res_rows;
     a.sbits = c->sbits;
-    if (c->res_W < resident_cols()) {
+    if (narrow) {
         HIP_TRY(launch_csr_narrow(a, c->res_D, c->res_W, c->words, c->rings, c->stream));
         c->step += K;
         return SBQA_OK;
@@ -1767,16 +1829,16 @@ sbqa_status ctx_best(sbqa_ctx *c, double *energies, int8_t *spins) {
 
 // The state from (set) or to the caller's arrays x, y (spin rows of C columns;
 // null: skipped), through pinned memory that the device reads or writes itself,
-// larger ones in slabs of rows: no device memory is taken, whatever the state's
-// size, and a small state costs two launches and a wait (N * C = 8000: get 25 us, set
-// 28; two copies through a device buffer 61). Padding rows and columns hold zero
-// and are not written. Returns with the work completed; set rebuilds the operand.
-// A state above twice the pinned size is set by copies into a device buffer where
-// there is room for one (N = 200000, C = 256: 22 ms, through pinned slabs 31).
+// larger ones to the caller in slabs of rows: no device memory is needed, whatever
+// the state's size, and a small state costs two launches and a wait (N * C = 8000:
+// get 25 us, set 23; two copies through a device buffer 61). A larger state is set by
+// copies into a device buffer where there is room for one (N = 200000, C = 256: 22
+// ms, through pinned memory 31). Padding rows and columns hold zero and are not
+// written. Returns with the work completed; set rebuilds the operand.
 static sbqa_status transfer_state(sbqa_ctx *c, float *x, float *y, bool set) {
     const int N = c->N, C = c->L.C;
     const size_t row = sizeof(float) * C;
-    const bool whole = 2 * row * N <= STAGE_BYTES;
+    const bool whole = set || 2 * row * N <= STAGE_BYTES;
     const int per = whole ? N : (int)std::max<size_t>(1, STAGE_BYTES / 2 / row);   // rows of a slab
     PoolBlock stage(c->device, true), dev(c->device, false);
     struct Wait { hipStream_t st; ~Wait() { (void)hipStreamSynchronize(st); } } wait{c->stream};
@@ -1788,7 +1850,7 @@ static sbqa_status transfer_state(sbqa_ctx *c, float *x, float *y, bool set) {
         else HIP_TRY(launch_state_reorder(n, C, c->order, c->ld, state, rows, ORDER_SPIN_MAJOR, C, buf, nullptr, false, c->stream));
         return SBQA_OK;
     };
-    if (set && 2 * row * N > 2 * STAGE_BYTES) {
+    if (set && 2 * row * N > STAGE_BYTES) {
         const int bulk = (int)std::min<size_t>(N, std::max<size_t>(1, BULK_BYTES / row));
         if (dev.get(row * bulk) == hipSuccess) {
             for (int q = 0; q < 2; ++q)
@@ -1804,7 +1866,7 @@ static sbqa_status transfer_state(sbqa_ctx *c, float *x, float *y, bool set) {
             HIP_TRY(hipStreamSynchronize(c->stream));
             return SBQA_OK;
         }
-        (void)hipGetLastError();   // no room: through the pinned slabs
+        (void)hipGetLastError();   // no room: like a small one
     }
     HIP_TRY(stage.get(2 * row * per));
     void *mapped = nullptr;
@@ -1819,20 +1881,15 @@ static sbqa_status transfer_state(sbqa_ctx *c, float *x, float *y, bool set) {
         float *user = slabs[k].user + (size_t)slabs[k].r0 * C, *mine = half(stage.as<void>(), k);
         std::memcpy(set ? mine : user, set ? user : mine, row * slabs[k].n);
     };
-    if (!set && !whole) {   // (the error word before anything is handed out)
+    if (!whole) {   // (the error word before anything is handed out)
         const sbqa_status st = ctx_sync(c);
         if (st != SBQA_OK) return st;
     }
     for (size_t k = 0; k < slabs.size(); ++k) {
-        // each half is free again before it is written; otherwise one slab is
-        // copied by the host while the device works on the next
-        if (set) {
-            if (k >= 2) HIP_TRY(hipStreamSynchronize(c->stream));
-            move(k);
-        }
+        if (set) move(k);
         const sbqa_status st = reorder(slabs[k].state, half(mapped, k), slabs[k].r0, slabs[k].n, true);
         if (st != SBQA_OK) return st;
-        if (!set && !whole) {
+        if (!whole) {   // the host copies one slab while the device works on the next
             if (k) move(k - 1);
             HIP_TRY(hipStreamSynchronize(c->stream));
         }

@@ -175,6 +175,7 @@ struct sbqa_ctx {
     // the fragment-tiled operand lags behind the state (the dense many-step
     // loops do not use it): rebuilt where it is read
     bool g_stale = false;
+    bool recorded = false;              // steps have been captured into a graph
     int res_D = 0, res_rows = 0, res_nwg = 0;
     int res_W = 8;                      // columns per workgroup: 8, or 4 or 2 in the narrow loop
     int32_t *colpad = nullptr;          // [rows][D]

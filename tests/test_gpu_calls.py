@@ -120,3 +120,63 @@ def test_state_transfer(sb, kind, N, R, runs):
     only[:] = 7.0
     assert sb.lib.sbqa_get_state(ctx.ptr, only.ctypes.data, None) == sb.OK and np.array_equal(only, x)
     assert sb.lib.sbqa_get_state(ctx.ptr, None, None) == sb.OK
+
+
+# the loops of every shape that takes few steps another way
+@pytest.mark.parametrize("kind,N,R,runs", [("sk", 200, 16, 8), ("sk", 601, 16, 8), ("sk", 700, 16, 40), ("sk", 1000, 16, 30),
+                                           ("sk", 1500, 32, 8), ("sparse", 200, 8, 4), ("sparse", 1000, 16, 8),
+                                           ("sparse", 200, 64, 16), ("sparse", 2500, 16, 2)])
+def test_calls_of_few_and_many_steps(sb, kind, N, R, runs):
+    """Steps taken in calls of 1 to 40, with readouts, fields and a state
+    overwrite between them, equal one launch per step."""
+    if kind == "sk":
+        kw = dict(J=inst.sk_pm1(N, 31), h=np.round(inst.gaussian_fields(N, 1.0, 32)))
+    else:
+        E = inst.regular_graph(N, 4, 33)
+        kw = dict(csr=inst.edges_to_csr(N, E, inst.gaussian_edges(len(E), 34)), h=inst.gaussian_fields(N, 0.1, 35))
+    out = []
+    for kern in (sb.LOOP_STREAM, sb.LOOP_AUTO):
+        _log("calls of few and many steps %s N=%d C=%d kernel %d" % (kind, N, R * runs, kern))
+        ctx = sb.sbqa_create(R=R, runs=runs, steps=150, loop_kernel=kern, seed=36, **kw)
+        got = []
+        for q, K in enumerate((1, 1, 3, 40, 1, 2, 1, 5, 20, 4, 1, 1, 30, 1)):
+            sb.sbqa_step(ctx, K)
+            if q % 3 == 0:
+                got += [*sb.sbqa_best(ctx)]
+            if q % 3 == 1:
+                got += [sb.sbqa_fields(ctx), *sb.sbqa_get_state(ctx)]
+            if q in (4, 8):
+                sb.sbqa_set_state(ctx, *inst.uniform_state(N, R * runs, 0.5, 37 + q))
+        out.append(got + [*sb.sbqa_get_state(ctx), *sb.sbqa_best(ctx)])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("kind,N", [("dense", 601), ("sparse", 1000)])
+def test_recorded_steps_between_direct_ones(sb, kind, N):
+    """Steps recorded into a graph replay on the context's state after direct
+    steps, of one and of several, taken before and after the recording."""
+    import torch
+    E = inst.regular_graph(N + N % 2, 4, 41)
+    kw = dict(J=inst.sk_pm1(N, 41)) if kind == "dense" else dict(csr=inst.edges_to_csr(N, E, inst.gaussian_edges(len(E), 42)))
+    kw.update(R=16, runs=8, steps=40, seed=4, jp_kind=sb.JP_LINEAR, jp_start=0.5, jp_end=0.0)
+    ctx = sb.sbqa_create(**kw)
+    sb.sbqa_step(ctx, 1)
+    stream = torch.cuda.Stream()
+    sb.sbqa_set_stream(ctx, stream)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        sb.sbqa_step(ctx, 7)        # steps 1..7
+    X, Y = inst.uniform_state(N, 128, 0.3, 43)
+    for q in range(3):
+        _log("replay %d after direct steps %s" % (q, kind))
+        sb.sbqa_step(ctx, 1 + q)    # (the state they leave is overwritten)
+        sb.sbqa_set_state(ctx, X, Y)
+        graph.replay()
+        torch.cuda.synchronize()
+        ref = sb.sbqa_create(loop_kernel=sb.LOOP_STREAM, **kw)
+        sb.sbqa_step(ref, 1)
+        sb.sbqa_set_state(ref, X, Y)
+        sb.sbqa_step(ref, 7)
+        for a, b in zip(sb.sbqa_get_state(ref), sb.sbqa_get_state(ctx)):
+            assert np.array_equal(a, b)
