@@ -82,9 +82,9 @@ __device__ __forceinline__ Frag32 lds_frag(const uint8_t *tile, int row, int g) 
 // -1/2 s^T J s of GEMM_BM spin rows at a time, from the lower triangle of the
 // symmetric J alone: part[u][c] = -sum over work unit u of s_n (L_n + D_n / 2),
 // L_n the sum over the 128-spin blocks below n's and D_n the one over its own.
-// A unit is a pair of spin blocks (p, T - 1 - p), so that all units are equally
-// long, and one of Z ranges of their K tiles; the sums over n happen here, so
-// that no field is written. 8 waves in 2 (rows) x 4 (spins) tiles of 64 x 32,
+// A unit is one of Z ranges of the K tiles of a pair of spin blocks (p, T - 1 - p),
+// so that all units are equally long; the sums over n happen here, so that no
+// field is written. 8 waves in 2 (rows) x 4 (spins) tiles of 64 x 32,
 // K tiles of 16 spins double-buffered in LDS with one barrier each. Bound by
 // the fp64 matrix rate: N = 8192, 512 rows 3.5e10 flop in 0.64 ms, 54 of the 70
 // TFLOP/s of a large library product (the full product by 4 waves took 1.79 ms:
@@ -108,10 +108,14 @@ __global__ __launch_bounds__(GEMM_THREADS, 4) void k_energy_gemm(const int8_t *_
     const int so = (tid >> 2) * LDS_STRIDE + (tid & 3) * 32;
     const int jr = tid >> 3, jc = tid & 7, jo = TILE_BYTES + jr * LDS_STRIDE + jc * 16;
     red[tid] = 0.0;
+    // this unit's K tiles of the pair's, the longer block's first
+    const int64_t all = KPB * (T - p) + (2 * p == T - 1 ? 0 : KPB * (p + 1));
+    const int r0 = (int)(all * z / Z), r1 = (int)(all * (z + 1) / Z);
     for (int half = 0; half < 2; ++half) {
         const int t = half == 0 ? T - 1 - p : p;     // the longer block first
         if (half == 1 && t == T - 1 - p) break;      // the middle block of an odd count is alone
-        const int nk = KPB * (t + 1), k0 = (int)((int64_t)nk * z / Z), k1 = (int)((int64_t)nk * (z + 1) / Z);
+        const int nk = KPB * (t + 1), before = half == 0 ? 0 : KPB * (T - p);
+        const int k0 = min(max(r0 - before, 0), nk), k1 = min(max(r1 - before, 0), nk);
         if (k0 == k1) continue;
         const int n0 = t * GEMM_BN, kd = KPB * t;    // from K tile kd on: the block's own spins
         const double *jrow = J + (int64_t)(n0 + jr) * Np + 2 * jc;
@@ -1299,10 +1303,15 @@ EnergyPlan energy_plan(int N, int count) {
     EnergyPlan e;
     e.T = (N + GEMM_BN - 1) / GEMM_BN;
     e.cp = (count + GEMM_BM - 1) / GEMM_BM * GEMM_BM;
-    // two workgroups per CU where the K tiles allow it (at least 8 each, at
-    // most 16 ranges)
+    // two workgroups per CU where the K tiles allow it (at least 8 each, at most
+    // 16 ranges); up to 8 blocks down to one or two tiles each while that makes no more than 5
+    // workgroups per 2 CUs, since a K tile is 2 to 3 us of latency there. us of a readout
+    // with 8, 1 at least: N = 130 68 and 46, N = 700 74 and 51, N = 1000 65 and 51
     const int64_t pairs = (e.T + 1) / 2, tiles = pairs * (e.cp / GEMM_BM);
-    while (tiles * e.Z < 512 && e.Z < 16 && (int64_t)(e.T + 1) * (GEMM_BN / (GEMM_KB / 8)) >= 16 * e.Z) e.Z *= 2;
+    const int64_t ktiles = (int64_t)(e.T + 1) * (GEMM_BN / (GEMM_KB / 8));   // of a pair
+    while (e.Z < 16 && ((ktiles >= 16 * e.Z && tiles * e.Z < 512) ||
+                        (e.T <= 8 && ktiles > 2 * e.Z && tiles * e.Z <= 320)))
+        e.Z *= 2;
     e.units = (int)pairs * e.Z;
     return e;
 }

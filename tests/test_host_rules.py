@@ -37,3 +37,25 @@ def test_real_paths_never_split_k(path):
     for Np in (128, 1536, 8192):
         for C64 in range(1, 20):
             assert _form(path, Np, 64 * C64) <= TILE
+
+
+class _EnergyPlan(ct.Structure):
+    _fields_ = [("T", ct.c_int), ("Z", ct.c_int), ("units", ct.c_int), ("cp", ct.c_int)]
+
+
+def test_energy_plan_splits_small_instances():
+    """The K tiles (16 spins) that one work unit of the float64 energies walks
+    one after the other are few in small instances, and the partial
+    sums stay within the scratch that the allocation-free entry point allows."""
+    plan = sb.lib._ZN4sbqa11energy_planEii
+    plan.restype = _EnergyPlan
+    for N in list(range(1, 300, 7)) + [511, 512, 700, 1000, 1500, 2000, 4100, 16384]:
+        for count in (1, 128, 129, 1000, 5000):
+            e = plan(N, count)
+            T, cp = -(-N // 128), -(-count // 128) * 128
+            assert (e.T, e.cp, e.units) == (T, cp, (T + 1) // 2 * e.Z) and 1 <= e.Z <= 16
+            chain = -(-8 * (T + 1) // e.Z)       # of the pair of spin blocks of a unit
+            if N <= 1024 and count <= 1000:
+                assert chain <= 5, (N, count, chain)
+            Np = -(-N // 128) * 128
+            assert e.units <= Np                 # doubles per row: the smallest allowance is Np
