@@ -77,7 +77,7 @@ struct DenseScan {
 // pays for starting them.
 template <class F>
 static void over_blocks(int64_t nb, int64_t work, F &&f) {
-    const int64_t nt = std::min<int64_t>({nb, work / (1 << 17), 16, (int64_t)std::thread::hardware_concurrency()});
+    const int64_t nt = std::min<int64_t>({nb, work / (1 << 16), 16, (int64_t)std::thread::hardware_concurrency()});
     if (nt <= 1) {
         for (int64_t b = 0; b < nb; ++b) f(b);
         return;
