@@ -12,9 +12,11 @@
 #include <cstdlib>
 #include <limits>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <set>
+#include <system_error>
 #include <tuple>
 #include <string>
 
@@ -74,7 +76,7 @@ struct DenseScan {
 };
 
 // f(0), ..., f(nb - 1), on several threads when the work (matrix elements)
-// pays for starting them.
+// pays for starting them. Where the system refuses a thread the others do its share.
 template <class F>
 static void over_blocks(int64_t nb, int64_t work, F &&f) {
     const int64_t nt = std::min<int64_t>({nb, work / (1 << 16), 16, (int64_t)std::thread::hardware_concurrency()});
@@ -87,7 +89,11 @@ static void over_blocks(int64_t nb, int64_t work, F &&f) {
         for (int64_t b; (b = next.fetch_add(1)) < nb;) f(b);
     };
     std::vector<std::thread> pool;
-    for (int64_t t = 1; t < nt; ++t) pool.emplace_back(run);
+    pool.reserve((size_t)nt);
+    try {
+        for (int64_t t = 1; t < nt; ++t) pool.emplace_back(run);
+    } catch (const std::system_error &) {
+    }
     run();
     for (std::thread &t : pool) t.join();
 }
@@ -687,18 +693,9 @@ void build_schedule_host(const sbqa_schedule *s, int32_t runs, std::vector<doubl
     // Eq. 5 takes about 0.1 us an entry (0.8 ms for 8 runs of 1000 steps, more
     // than the rest of a small context's creation): in parallel from 2048
     // entries on, where it saves more than the threads cost to start (20 us each)
-    const int64_t total = (int64_t)runs * S;
-    const int nt = s->jp_kind != SBQA_JP_PAPER || total < 2048
-                       ? 1
-                       : (int)std::min<int64_t>({8, total / 1024, (int64_t)std::max(1u, std::thread::hardware_concurrency())});
-    if (nt <= 1) {
-        fill(0, total);
-        return;
-    }
-    std::vector<std::thread> pool;
-    for (int t = 1; t < nt; ++t) pool.emplace_back(fill, total * t / nt, total * (t + 1) / nt);
-    fill(0, total / nt);
-    for (std::thread &t : pool) t.join();
+    const int64_t total = (int64_t)runs * S, per = 1024;
+    const int64_t nb = s->jp_kind == SBQA_JP_PAPER ? (total + per - 1) / per : 1;
+    over_blocks(nb, total / per << 16, [&](int64_t b) { fill(nb == 1 ? 0 : b * per, nb == 1 ? total : std::min(total, (b + 1) * per)); });
 }
 
 StepCoef step_coef(const sbqa_schedule *s, double c0, int R, uint32_t n) {
@@ -1481,11 +1478,11 @@ static hipError_t library_stream(int device, hipStream_t *out) {
     return hipSuccess;
 }
 
-sbqa_status ctx_create(const sbqa_coupling *J, const double *h, int32_t N, int32_t R, int32_t runs,
-                       const sbqa_schedule *s, const InstanceFacts &facts, hipStream_t stream, sbqa_ctx **out,
-                       bool allow_resident, const uint32_t *jbits) {
-    sbqa_ctx *c = new (std::nothrow) sbqa_ctx();
-    if (!c) return fail(SBQA_ENOMEM, "out of host memory");
+static sbqa_status create(const sbqa_coupling *J, const double *h, int32_t N, int32_t R, int32_t runs,
+                          const sbqa_schedule *s, const InstanceFacts &facts, hipStream_t stream, sbqa_ctx **out,
+                          bool allow_resident, const uint32_t *jbits) {
+    std::unique_ptr<sbqa_ctx> owner(new sbqa_ctx());
+    sbqa_ctx *c = owner.get();
     c->N = N;
     c->R = R;
     c->runs = runs;
@@ -1497,11 +1494,11 @@ sbqa_status ctx_create(const sbqa_coupling *J, const double *h, int32_t N, int32
     plan_layout(N, R, runs, facts, &c->L);
     build_schedule_host(s, runs, c->beta, c->alpha, c->jp_host);
     sbqa_status st = check_device(&c->device);
-    if (st != SBQA_OK) { delete c; return st; }
+    if (st != SBQA_OK) return st;
     if (stream) c->stream = stream;
     else {
         hipError_t e = library_stream(c->device, &c->default_stream);
-        if (e != hipSuccess) { delete c; return fail(SBQA_EDEVICE, "hipStreamCreate: %s", hipGetErrorString(e)); }
+        if (e != hipSuccess) return fail(SBQA_EDEVICE, "hipStreamCreate: %s", hipGetErrorString(e));
         c->stream = c->default_stream;
     }
     Relabelled rl;
@@ -1520,7 +1517,6 @@ sbqa_status ctx_create(const sbqa_coupling *J, const double *h, int32_t N, int32
         const bool plan = facts.path == PATH_CSR ? resident_plan(c, J, &why) : small_plan(c, &why);
         c->resident = allow_resident && s->loop_kernel != SBQA_LOOP_STREAM && plan;
         if (!c->resident && s->loop_kernel == SBQA_LOOP_RESIDENT) {
-            delete c;
             return fail(SBQA_EINVAL, "instance does not fit a resident loop: %s",
                         allow_resident ? why.c_str() : "contexts of the serving loop step one launch at a time");
         }
@@ -1558,9 +1554,15 @@ sbqa_status ctx_create(const sbqa_coupling *J, const double *h, int32_t N, int32
     }
     if (st == SBQA_OK) st = rebuild_operand(c);
     if (st == SBQA_OK) st = ctx_reset_best(c);
-    if (st != SBQA_OK) { delete c; return st; }
-    *out = c;
+    if (st != SBQA_OK) return st;
+    *out = owner.release();
     return SBQA_OK;
+}
+
+sbqa_status ctx_create(const sbqa_coupling *J, const double *h, int32_t N, int32_t R, int32_t runs,
+                       const sbqa_schedule *s, const InstanceFacts &facts, hipStream_t stream, sbqa_ctx **out,
+                       bool allow_resident, const uint32_t *jbits) {
+    return guarded([&] { return create(J, h, N, R, runs, s, facts, stream, out, allow_resident, jbits); });
 }
 
 // K steps of the small dense loop in one launch (one workgroup per run).
@@ -1952,7 +1954,7 @@ sbqa_status sbqa_create(const sbqa_coupling *J, const double *h, int32_t N, int3
     if (!out) return fail(SBQA_EINVAL, "out must be non-NULL");
     *out = nullptr;
     InstanceFacts facts;
-    sbqa_status st = validate_instance(J, h, N, R, runs, s, &facts);
+    sbqa_status st = guarded([&] { return validate_instance(J, h, N, R, runs, s, &facts); });
     if (st != SBQA_OK) return st;
     return ctx_create(J, h, N, R, runs, s, facts, nullptr, out, true);
 }
@@ -1977,8 +1979,7 @@ sbqa_status sbqa_best_step(sbqa_ctx *c, int64_t *step_of_best) {
     return SBQA_OK;
 }
 
-sbqa_status sbqa_energy(sbqa_ctx *c, const int8_t *spins, int32_t count, double *out) {
-    clear_error();
+static sbqa_status host_energies(sbqa_ctx *c, const int8_t *spins, int32_t count, double *out) {
     if (!c || (!spins && count) || (!out && count)) return fail(SBQA_EINVAL, "NULL argument");
     if (count < 0) return fail(SBQA_EINVAL, "count must be >= 0");
     if (count == 0) return SBQA_OK;
@@ -2034,8 +2035,12 @@ sbqa_status sbqa_energy(sbqa_ctx *c, const int8_t *spins, int32_t count, double 
     return SBQA_OK;
 }
 
-sbqa_status sbqa_fields(sbqa_ctx *c, float *phi) {
+sbqa_status sbqa_energy(sbqa_ctx *c, const int8_t *spins, int32_t count, double *out) {
     clear_error();
+    return guarded([&] { return host_energies(c, spins, count, out); });
+}
+
+static sbqa_status host_fields(sbqa_ctx *c, float *phi) {
     if (!c || !phi) return fail(SBQA_EINVAL, "NULL argument");
     const int N = c->N, C = c->L.C;
     std::vector<float> buf;
@@ -2091,10 +2096,15 @@ sbqa_status sbqa_fields(sbqa_ctx *c, float *phi) {
     return SBQA_OK;
 }
 
+sbqa_status sbqa_fields(sbqa_ctx *c, float *phi) {
+    clear_error();
+    return guarded([&] { return host_fields(c, phi); });
+}
+
 sbqa_status sbqa_get_state(sbqa_ctx *c, float *x, float *y) {
     clear_error();
     if (!c) return fail(SBQA_EINVAL, "NULL context");
-    return transfer_state(c, x, y, false);
+    return guarded([&] { return transfer_state(c, x, y, false); });
 }
 
 sbqa_status sbqa_set_state(sbqa_ctx *c, const float *x, const float *y) {
@@ -2112,7 +2122,7 @@ sbqa_status sbqa_set_state(sbqa_ctx *c, const float *x, const float *y) {
     }
     c->sbits_step = -1;
     // (transfer_state only reads what it is given in this direction)
-    sbqa_status st = transfer_state(c, const_cast<float *>(x), const_cast<float *>(y), true);
+    sbqa_status st = guarded([&] { return transfer_state(c, const_cast<float *>(x), const_cast<float *>(y), true); });
     if (st != SBQA_OK) return st;
     c->last_eval_step = -1;
     return SBQA_OK;

@@ -6,6 +6,7 @@
 #include "pool.h"
 #include "sbqa_internal.h"
 
+#include <exception>
 #include <string>
 #include <vector>
 
@@ -50,6 +51,16 @@ struct Layout {
 sbqa_status fail(sbqa_status st, const char *fmt, ...);
 void clear_error();
 const char *last_error();
+
+// f()'s status; ENOMEM where it throws (a C caller cannot take an exception).
+template <class F>
+sbqa_status guarded(F &&f) {
+    try {
+        return f();
+    } catch (const std::exception &e) {
+        return fail(SBQA_ENOMEM, "out of host memory or threads (%s)", e.what());
+    }
+}
 
 // sign_bits (may be null): for a dense +-1 J (facts->pm1), its row-major sign
 // bits, ceil(N/32) words per row.

@@ -598,15 +598,21 @@ sbqa_status sbqa_server_create(size_t hbm_budget_bytes, int32_t max_slots, sbqa_
         release(srv);
         return fail(e == hipErrorOutOfMemory ? SBQA_ENOMEM : SBQA_EDEVICE, "server set-up: %s", hipGetErrorString(e));
     }
-    srv->worker = std::thread(scheduler, srv);
-    srv->creator = std::thread(creator, srv);
+    const sbqa_status st = guarded([&] {
+        srv->worker = std::thread(scheduler, srv);
+        srv->creator = std::thread(creator, srv);
+        return SBQA_OK;
+    });
+    if (st != SBQA_OK) {
+        sbqa_server_destroy(srv);   // stops the scheduler if it runs
+        return st;
+    }
     *out = srv;
     return SBQA_OK;
 }
 
-sbqa_status sbqa_submit(sbqa_server *srv, const sbqa_coupling *J, const double *h, int32_t N, int32_t R, int32_t runs,
+static sbqa_status submit(sbqa_server *srv, const sbqa_coupling *J, const double *h, int32_t N, int32_t R, int32_t runs,
                         const sbqa_schedule *s, uint64_t *ticket) {
-    clear_error();
     const Clock::time_point t_arrival = Clock::now();   // latency includes validation and copies
     if (!srv || !ticket) return fail(SBQA_EINVAL, "NULL argument");
     std::unique_ptr<Request> r(new (std::nothrow) Request());
@@ -650,6 +656,12 @@ sbqa_status sbqa_submit(sbqa_server *srv, const sbqa_coupling *J, const double *
     }
     srv->cv.notify_one();
     return SBQA_OK;
+}
+
+sbqa_status sbqa_submit(sbqa_server *srv, const sbqa_coupling *J, const double *h, int32_t N, int32_t R, int32_t runs,
+                        const sbqa_schedule *s, uint64_t *ticket) {
+    clear_error();
+    return guarded([&] { return submit(srv, J, h, N, R, runs, s, ticket); });
 }
 
 sbqa_status sbqa_poll(sbqa_server *srv, uint64_t ticket, double *energies, int8_t *spins, double *latency_s) {
