@@ -252,8 +252,8 @@ sbqa_status sbqa_create(const sbqa_coupling *J, const double *h, int32_t N, int3
  * Advance every run and replica by n steps of Eqs. 6-7 (contraction J.f(X),
  * fused pump/ring/kick/drift/wall update). Asynchronous on the context stream.
  * Errors: ESTATE if step + n > steps (nothing is done), EDEVICE (also reported
- * by the next synchronising call when a resident launch could not complete a
- * step: the state is then invalid).
+ * by the next synchronising call when a many-step launch could not complete a
+ * step: the state is then invalid; see sbqa_sync).
  */
 sbqa_status sbqa_step(sbqa_ctx *ctx, uint32_t n);
 
@@ -331,18 +331,24 @@ sbqa_status sbqa_set_stream(sbqa_ctx *ctx, void *hip_stream);
 
 sbqa_status sbqa_info(sbqa_ctx *ctx, sbqa_info_t *info);
 
-/* Block until the context's device work has finished. EDEVICE when a
- * resident sparse launch could not complete a step (a ring-neighbour wait
- * timed out); the state is then invalid. */
+/* Block until the context's device work has finished. EDEVICE when a launch of a
+ * many-step loop (the resident sparse loop, or the loop of dense +-1 instances
+ * with several workgroups per column group) could not complete a step: its
+ * workgroups wait for each other, within a bound of seconds, and one of them was
+ * kept off the device for longer; the state is then invalid. The library keeps
+ * its own launches of that kind from standing in each other's way, on any number
+ * of streams and threads of a process (a launch waits for another stream's
+ * where both would not fit on the device); launches replayed from a graph are
+ * ordered by the caller, and other kernels that hold the device for seconds are
+ * not seen. */
 sbqa_status sbqa_sync(sbqa_ctx *ctx);
 
-/* Failure-path test hook of the resident sparse loop: sets the context's
- * device error word as a ring-neighbour wait timeout would (a neighbouring
- * workgroup that never published its step), so that the next resident launch
- * skips its waits and the next call that synchronises (sbqa_best, sbqa_sync)
- * reports SBQA_EDEVICE; every kernel still runs to its end. The state is
- * invalid afterwards. EINVAL on a context without the resident sparse loop.
- * Asynchronous on the context stream. */
+/* Failure-path test hook of those loops: sets the context's device error word as
+ * a wait timeout would (a neighbouring workgroup that never published its step),
+ * so that the next launch ends its waits early and the next call that
+ * synchronises (sbqa_best, sbqa_sync) reports SBQA_EDEVICE; every kernel still
+ * runs to its end. The state is invalid afterwards. EINVAL on a context without
+ * such a loop. Asynchronous on the context stream. */
 sbqa_status sbqa_inject_wait_timeout(sbqa_ctx *ctx);
 
 /* Thread-local message of the last failed call on this thread ("" if none). */

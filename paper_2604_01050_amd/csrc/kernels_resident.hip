@@ -37,7 +37,7 @@ using namespace csr;
 // ---------------------------------------------------------------------------
 constexpr int RES_COLS = 8;
 constexpr int RES_MAX_ROWS = 4096;   // padded rows: a power of two from 512 to this
-constexpr int RES_SPIN_LIMIT = 1 << 22;
+constexpr int RES_SPIN_LIMIT = 1 << 23;   // looks at the counters, 0.7 us or more each
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));

@@ -37,8 +37,11 @@ __device__ __forceinline__ uint64_t get_word(const uint64_t *p) {
 
 // After a poll that found a word missing: whether the wave stops waiting.
 // Bounded: on timeout the error word is set, and once it is set every later
-// wait ends within 16 polls, so the grid always drains.
-constexpr int RING_POLL_LIMIT = 1 << 20;
+// wait ends within 16 polls, so the grid always drains. A poll is 0.7 us or more,
+// the bound 6 s: launches that could hold each other up are kept in order
+// (launch_order.h) and none lasts a tenth of a second (MAX_EXCHANGE_STEPS), so only
+// the kernels of others can keep a workgroup off the device for long.
+constexpr int RING_POLL_LIMIT = 1 << 23;
 __device__ __forceinline__ bool stop_waiting(int polls, int *err) {
     if ((polls & 15) == 15 && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return true;
     if (polls > RING_POLL_LIMIT) {

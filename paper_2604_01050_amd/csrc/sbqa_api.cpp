@@ -721,11 +721,65 @@ using namespace sbqa;
 //                                 context                                     //
 // =========================================================================== //
 
+namespace sbqa {
+
+// Launches whose workgroups wait for each other, per device (launch_order.h).
+struct DeviceOrder {
+    std::mutex mu;
+    LaunchOrder<hipStream_t> order;
+    hipEvent_t passed = nullptr;   // recorded and waited for under mu
+};
+static DeviceOrder &device_order(int device) {
+    static std::mutex mu;
+    static auto *all = new std::map<int, std::unique_ptr<DeviceOrder>>();   // (outlives the contexts)
+    std::lock_guard<std::mutex> lk(mu);
+    auto &d = (*all)[device];
+    if (!d) d.reset(new DeviceOrder());
+    return *d;
+}
+
+static void forget_launches(const sbqa_ctx *c) {
+    if (!c->exchanging.workgroups) return;
+    DeviceOrder &d = device_order(c->device);
+    std::lock_guard<std::mutex> lk(d.mu);
+    d.order.forget(c);
+}
+
+static bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &s) != hipSuccess) (void)hipGetLastError();
+    return s != hipStreamCaptureStatusNone;
+}
+
+// launch() on the context's stream, behind what it must not meet on the device.
+// (Recorded launches are ordered by whoever replays them.)
+template <class F>
+static hipError_t launch_in_order(sbqa_ctx *c, const Exchanging &need, F &&launch) {
+    if (!need.workgroups) return launch();
+    DeviceOrder &d = device_order(c->device);
+    std::lock_guard<std::mutex> lk(d.mu);
+    hipError_t e = hipSuccess;
+    d.order.before(c, c->stream, need, c->cus, [&](hipStream_t other) {
+        if (e != hipSuccess || capturing(c->stream) || capturing(other)) return;
+        if (!d.passed) e = hipEventCreateWithFlags(&d.passed, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventRecord(d.passed, other);
+        if (e == hipSuccess) e = hipStreamWaitEvent(c->stream, d.passed, 0);
+    });
+    return e == hipSuccess ? launch() : e;
+}
+
+// Steps of one such launch at most: none lasts long (11 us a step or less), so that
+// another one's wait for a place on the device stays far below its bound.
+constexpr uint32_t MAX_EXCHANGE_STEPS = 4096;
+
+}  // namespace sbqa
+
 sbqa_ctx::~sbqa_ctx() {
     // the pool hands the blocks to other contexts, on other streams: the work
     // on them ends first (blocks of a stream that reports an error are left
     // to the runtime, which waits for the device)
     const bool done = idle || !stream || hipStreamSynchronize(stream) == hipSuccess;
+    forget_launches(this);
     auto back = [&](bool host, Block b) {
         if (done) pool_put(device, host, b);
         else if (host) (void)hipHostFree(b.p);
@@ -1252,12 +1306,13 @@ static bool resident_plan(sbqa_ctx *c, const sbqa_coupling *J, std::string *why)
     c->res_rows = resident_rows(c->N);
     c->res_nwg = nwg;
     c->res_W = resident_cols();
+    c->cus = cus;
+    c->exchanging = Exchanging{nwg, ((uint64_t)1 << 60) | (uint64_t)c->res_rows << 8 | (uint64_t)D, bpc};
+    c->exchanging_wide = c->exchanging;
     // Fewer columns per workgroup (the narrow loop) while the workgroups of
-    // four launches still fit on the device together: launches of different
-    // streams reach it through four hardware queues, each of which hands out
-    // its workgroups in order, so the ring neighbours of every launch then get
-    // to run whatever the other queues hold. Two columns up to a quarter of
-    // the CUs (128 columns), else four. us per step for W = 8 / 4 / 2: N =
+    // four launches still fit on the device together, so that four contexts on
+    // streams of their own need not wait for each other (launch_in_order). Two
+    // columns up to a quarter of the CUs (128 columns), else four. us per step for W = 8 / 4 / 2: N =
     // 1000, degree 3, C = 128 2.48 / 1.20 / 1.12; N = 4096, degree 6, C = 128
     // 6.20 / 4.35 / 2.94; C = 256 6.33 / 4.41 / 3.81 (two columns do not fit
     // four times there); N = 1000, degree 6, C = 512 2.81 / 1.41 / 1.93 (twice
@@ -1268,6 +1323,7 @@ static bool resident_plan(sbqa_ctx *c, const sbqa_coupling *J, std::string *why)
         if ((int64_t)c->L.C / W * 4 > (int64_t)cus * (W == 2 ? 1 : nb)) continue;
         c->res_W = W;
         c->res_nwg = c->L.C / W;
+        c->exchanging = Exchanging{c->res_nwg, ((uint64_t)2 << 60) | (uint64_t)narrow_rows(c->N) << 16 | (uint64_t)D << 8 | (uint64_t)W, nb};
         break;
     }
     return true;
@@ -1301,7 +1357,7 @@ static void mid_plan(sbqa_ctx *c) {
     p.NS = ns <= 2 ? ns : 4;
     // Fewest row blocks per workgroup first, so that a step is short, while
     // the workgroups of four launches still fit on the device together (see
-    // resident_plan); one workgroup per group needs nobody else's. us per
+    // resident_plan); one workgroup per group waits for nobody. us per
     // step, one launch per step / this loop, at C = 128: N = 300 6.5 / 1.7, N
     // = 601 7.2 / 1.9, N = 1024 7.2 / 2.2, N = 2048 8.6 / 3.0; C = 1600, N =
     // 1000 11.1 / 6.1 (four row blocks per wave, one workgroup per group).
@@ -1317,12 +1373,21 @@ static void mid_plan(sbqa_ctx *c) {
         if ((p.G == 1) != alone) return false;
         int nb = 0;
         if (mid_max_blocks(p, &nb) != hipSuccess || nb < 1) return false;
+        c->exchanging = alone ? Exchanging{}
+                              : Exchanging{groups * p.G,
+                                           ((uint64_t)3 << 60) | (uint64_t)p.NT << 20 | (uint64_t)p.RBW << 16 |
+                                               (uint64_t)p.NS << 12 | (uint64_t)p.MB << 8 | (uint64_t)p.rot,
+                                           nb};
         return alone || (int64_t)groups * p.G * 4 <= (int64_t)cus * nb;
     };
     bool ok = fits({1024, 1}, true);                       // up to 256 spins
     for (int q = 0; q < 3 && !ok; ++q) ok = fits(shapes[q], false);
     for (int q = 2; q < 4 && !ok; ++q) ok = fits(shapes[q], true);
-    if (!ok) return;
+    if (!ok) {
+        c->exchanging = Exchanging{};
+        return;
+    }
+    c->cus = cus;
     c->mid = p;
     c->mid_cols = cols;
     c->mid_groups = groups;
@@ -1520,6 +1585,7 @@ static sbqa_status create(const sbqa_coupling *J, const double *h, int32_t N, in
             return fail(SBQA_EINVAL, "instance does not fit a resident loop: %s",
                         allow_resident ? why.c_str() : "contexts of the serving loop step one launch at a time");
         }
+        if (!c->resident) c->exchanging = Exchanging{};
         if (facts.path != PATH_CSR && !c->resident && allow_resident && s->loop_kernel == SBQA_LOOP_AUTO) mid_plan(c);
     }
     if (facts.path != PATH_CSR)
@@ -1619,9 +1685,7 @@ static uint32_t mid_min_steps(const sbqa_ctx *c) {
 // loops step the state in place and, when recorded, can be replayed; once they have
 // been, every call keeps to them.
 static bool recorded(sbqa_ctx *c) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
-    c->recorded = c->recorded || st != hipStreamCaptureStatusNone;
+    c->recorded = c->recorded || capturing(c->stream);
     return c->recorded;
 }
 
@@ -1654,7 +1718,7 @@ static sbqa_status ctx_step_mid(sbqa_ctx *c, uint32_t K) {
     a.words = c->words;
     a.rings = c->rings;
     a.err = c->err;
-    HIP_TRY(launch_dense_mid(c->mid, a, c->stream));
+    HIP_TRY(launch_in_order(c, c->exchanging, [&] { return launch_dense_mid(c->mid, a, c->stream); }));
     c->step += K;
     c->g_stale = true;
     return SBQA_OK;
@@ -1717,11 +1781,13 @@ static sbqa_status ctx_step_resident(sbqa_ctx *c, uint32_t K) {
     a.nr = c->res_rows;
     a.sbits = c->sbits;
     if (narrow) {
-        HIP_TRY(launch_csr_narrow(a, c->res_D, c->res_W, c->words, c->rings, c->stream));
+        HIP_TRY(launch_in_order(c, c->exchanging, [&] {
+            return launch_csr_narrow(a, c->res_D, c->res_W, c->words, c->rings, c->stream);
+        }));
         c->step += K;
         return SBQA_OK;
     }
-    HIP_TRY(launch_csr_resident(a, c->res_D, c->stream));
+    HIP_TRY(launch_in_order(c, c->exchanging_wide, [&] { return launch_csr_resident(a, c->res_D, c->stream); }));
     c->step += K;
     c->sbits_step = c->step;
     return SBQA_OK;
@@ -1746,6 +1812,7 @@ sbqa_status ctx_step(sbqa_ctx *c, uint32_t n) {
         uint32_t left = n;
         while (left) {
             uint32_t K = left;
+            if (c->exchanging.workgroups) K = std::min(K, MAX_EXCHANGE_STEPS);
             if (c->s.energy_every) K = std::min(K, c->s.energy_every - c->step % c->s.energy_every);
             sbqa_status st = ctx_step_resident(c, K);
             if (st != SBQA_OK) return st;
@@ -2147,6 +2214,7 @@ sbqa_status sbqa_set_stream(sbqa_ctx *c, void *hip_stream) {
     clear_error();
     if (!c) return fail(SBQA_EINVAL, "NULL context");
     HIP_TRY(hipStreamSynchronize(c->stream));
+    forget_launches(c);
     c->stream = hip_stream ? (hipStream_t)hip_stream : c->default_stream;
     if (!c->stream) return fail(SBQA_ESTATE, "context has no default stream");
     return SBQA_OK;
@@ -2180,8 +2248,8 @@ sbqa_status sbqa_sync(sbqa_ctx *c) {
 sbqa_status sbqa_inject_wait_timeout(sbqa_ctx *c) {
     clear_error();
     if (!c) return fail(SBQA_EINVAL, "NULL context");
-    if (!c->resident || c->facts.path != PATH_CSR || !c->err)
-        return fail(SBQA_EINVAL, "the context does not run the resident sparse loop");
+    if (!c->exchanging.workgroups || !c->err)
+        return fail(SBQA_EINVAL, "the context runs no loop whose workgroups wait for each other");
     static const int timed_out = 1;   // the value a timed-out wait stores
     HIP_TRY(hipMemcpyAsync(c->err, &timed_out, sizeof(int), hipMemcpyHostToDevice, c->stream));
     return SBQA_OK;

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "../../include/sbqa.h"
+#include "launch_order.h"
 #include "pool.h"
 #include "sbqa_internal.h"
 
@@ -182,6 +183,11 @@ struct sbqa_ctx {
     // mid.NT > 0; Jmid its bits of J, words its operand exchange
     sbqa::MidPlan mid;
     int mid_cols = 0, mid_groups = 0, mid_ns = 0;
+    // what launches of the loops ask of the device when their workgroups wait for
+    // each other (no workgroups: they do not): the context's loop, and the 8-column
+    // loop where the narrow one is the context's
+    sbqa::Exchanging exchanging, exchanging_wide;
+    int cus = 0;
     uint4 *Jmid = nullptr;
     // the fragment-tiled operand lags behind the state (the dense many-step
     // loops do not use it): rebuilt where it is read

@@ -180,3 +180,87 @@ def test_recorded_steps_between_direct_ones(sb, kind, N):
         sb.sbqa_step(ref, 7)
         for a, b in zip(sb.sbqa_get_state(ref), sb.sbqa_get_state(ctx)):
             assert np.array_equal(a, b)
+
+
+def test_exchanging_launches_on_several_streams(sb):
+    """Contexts whose loops' workgroups wait for each other, on streams of their
+    own and from two threads: more of them than fit on the device together give
+    what each gives alone."""
+    import threading
+
+    import torch
+
+    def sparse(N, d, seed):
+        E = inst.regular_graph(N, d, seed)
+        return dict(csr=inst.edges_to_csr(N, E, inst.gaussian_edges(len(E), seed + 1)), h=inst.gaussian_fields(N, 0.1, seed + 2))
+
+    kinds = [dict(sparse(4096, 6, 51), R=2048, runs=1),               # 8 columns: a ring of 256 workgroups
+             dict(J=inst.sk_pm1(2048, 52), R=16, runs=8),             # many-step dense loop
+             dict(sparse(1000, 3, 53), R=16, runs=8),                 # narrow loop
+             dict(sparse(4096, 6, 54), R=32, runs=64),                # 8 columns: 256 workgroups
+             dict(J=inst.sk_pm1(601, 55), R=16, runs=16)]
+
+    def advance(ctx, get):
+        for K in (20, 1, 150, 7, 60):
+            sb.sbqa_step(ctx, K)
+        return get(ctx)
+
+    make = lambda kw: sb.sbqa_create(steps=240, seed=5, **kw)
+    alone = []
+    for kw in kinds:
+        _log("alone R=%d runs=%d" % (kw["R"], kw["runs"]))
+        alone.append(advance(make(kw), lambda c: (*sb.sbqa_get_state(c), *sb.sbqa_best(c))))
+    streams = [torch.cuda.Stream() for _ in kinds]
+    for rep in range(3):
+        _log("together, pass %d" % rep)
+        ctxs = [make(kw) for kw in kinds]
+        for c, st in zip(ctxs, streams):
+            sb.sbqa_set_stream(c, st)
+        ts = [threading.Thread(target=lambda part: [advance(c, lambda _: None) for c in part], args=(ctxs[q::2],)) for q in range(2)]
+        for t in ts:
+            t.start()
+        for t in ts:
+            t.join()
+        for c, ref in zip(ctxs, alone):
+            for a, b in zip(ref, (*sb.sbqa_get_state(c), *sb.sbqa_best(c))):
+                assert np.array_equal(a, b)
+        for c in ctxs:
+            sb.sbqa_destroy(c)
+
+
+@pytest.mark.parametrize("kind", ["dense", "sparse"])
+def test_steps_above_the_longest_launch(sb, kind):
+    """A call of more steps than one launch of an exchanging loop takes."""
+    N = 300
+    E = inst.regular_graph(N, 3, 61)
+    kw = dict(J=inst.sk_pm1(N, 62)) if kind == "dense" else dict(csr=inst.edges_to_csr(N, E, inst.gaussian_edges(len(E), 63)))
+    _log("9000 steps in one call, %s" % kind)
+    out = []
+    for kern in (sb.LOOP_STREAM, sb.LOOP_AUTO):
+        ctx = sb.sbqa_create(R=8, runs=2, steps=9000, loop_kernel=kern, seed=3, **kw)
+        sb.sbqa_step(ctx, 9000)
+        out.append((*sb.sbqa_get_state(ctx), *sb.sbqa_best(ctx)))
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+
+
+def test_wait_timeout_of_the_dense_loop_is_reported(sb):
+    """A wait of the many-step dense loop that timed out: the next calls that
+    synchronise report it, the kernels end normally, and the context of another
+    instance is not touched. One workgroup per group waits for nobody."""
+    _log("injected wait timeout, dense loop")
+    kw = dict(J=inst.sk_pm1(601, 64), R=16, runs=8, steps=40)
+    ctx, other = sb.sbqa_create(**kw), sb.sbqa_create(**kw)
+    sb.sbqa_step(ctx, 9)
+    sb.sbqa_best(ctx)
+    sb.sbqa_inject_wait_timeout(ctx)
+    sb.sbqa_step(ctx, 9)
+    for call in (sb.sbqa_best, sb.sbqa_sync, sb.sbqa_get_state):
+        with pytest.raises(sb.SbqaError) as ei:
+            call(ctx)
+        assert ei.value.status == sb.EDEVICE and "wait timed out" in ei.value.message
+    sb.sbqa_step(other, 18)
+    sb.sbqa_best(other)
+    with pytest.raises(sb.SbqaError) as ei:
+        sb.sbqa_inject_wait_timeout(sb.sbqa_create(J=inst.sk_pm1(200, 65), R=16, runs=8, steps=40))
+    assert ei.value.status == sb.EINVAL
