@@ -363,7 +363,9 @@ void sbqa_destroy(sbqa_ctx *ctx);
 
 /*
  * Create a server with a device-memory budget (bytes) and at most max_slots
- * instances resident at once. A scheduler thread admits queued requests in
+ * instances resident at once. The budget counts what the instances' buffers ask
+ * for; the allocator adds up to 6% and 64 KiB a buffer, and the library may keep
+ * freed blocks (sbqa_destroy). A scheduler thread admits queued requests in
  * arrival order while their device footprint fits the budget and a slot is
  * free, steps all resident instances together in batched launches, retires
  * finished ones and admits the next. out receives the handle.

@@ -794,9 +794,14 @@ sbqa_ctx::~sbqa_ctx() {
 }
 
 // Zeroed device buffer of the context. During creation, buffers up to
-// SMALL_BYTES are packed into chunks of CHUNK_BYTES and become valid with the
-// next flush.
+// SMALL_BYTES are packed into chunks and become valid with the next flush. A chunk
+// holds CHUNK_BYTES, for a small instance what its buffers come to (its estimate,
+// a quarter more and 16 KiB for their alignment).
 constexpr size_t SMALL_BYTES = (size_t)256 << 10, CHUNK_BYTES = (size_t)1 << 20;
+static size_t chunk_bytes(const sbqa_ctx *c) {
+    const size_t est = instance_bytes(c->N, c->R, c->runs, c->facts, c->s.steps);
+    return std::min(CHUNK_BYTES, (est + est / 4 + ((size_t)16 << 10) + 65535) / 65536 * 65536);
+}
 // Largest copy that a call takes through pinned memory.
 constexpr size_t STAGE_BYTES = (size_t)8 << 20;
 // Device buffer of a larger state on its way in (of those that the pool keeps).
@@ -807,10 +812,11 @@ static hipError_t dalloc(sbqa_ctx *c, T **p, size_t n) {
     const size_t bytes = std::max<size_t>(n * sizeof(T), 256), room = (bytes + 255) / 256 * 256;
     hipError_t e;
     if (c->creating && room <= SMALL_BYTES) {
-        if (c->chunks.empty() || c->chunks.back().used + room > CHUNK_BYTES) {
+        if (c->chunks.empty() || c->chunks.back().used + room > c->chunks.back().dev.bytes) {
             sbqa_ctx::Chunk k;
-            if ((e = pool_get(c->device, false, CHUNK_BYTES, &k.dev)) != hipSuccess) return e;
-            if ((e = pool_get(c->device, true, CHUNK_BYTES, &k.host)) != hipSuccess) {
+            const size_t bytes = std::max(chunk_bytes(c), room);
+            if ((e = pool_get(c->device, false, bytes, &k.dev)) != hipSuccess) return e;
+            if ((e = pool_get(c->device, true, bytes, &k.host)) != hipSuccess) {
                 pool_put(c->device, false, k.dev);
                 return e;
             }

