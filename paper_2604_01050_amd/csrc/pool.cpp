@@ -33,8 +33,15 @@ size_t size_class(size_t bytes, size_t limit) {
 
 constexpr size_t limit_of(bool host) { return host ? POOL_HOST_BYTES : POOL_DEVICE_BYTES; }
 
-hipError_t raw_get(bool host, size_t bytes, void **p) {
-    return host ? hipHostMalloc(p, bytes, hipHostMallocCoherent) : hipMalloc(p, bytes);
+// (a device block on its own device, whichever the calling thread has current)
+hipError_t raw_get(int device, bool host, size_t bytes, void **p) {
+    if (host) return hipHostMalloc(p, bytes, hipHostMallocCoherent);
+    int cur = device;
+    hipError_t e = hipGetDevice(&cur);
+    if (e == hipSuccess && cur != device) e = hipSetDevice(device);
+    if (e == hipSuccess) e = hipMalloc(p, bytes);
+    if (cur != device) (void)hipSetDevice(cur);
+    return e;
 }
 
 void raw_free(bool host, const std::vector<Block> &bs) {
@@ -60,7 +67,7 @@ hipError_t pool_get(int device, bool host, size_t bytes, Block *b) {
             }
     }
     void *p = nullptr;
-    hipError_t e = raw_get(host, want, &p);
+    hipError_t e = raw_get(device, host, want, &p);
     if (e != hipSuccess) {
         // out of memory: give everything cached back and try once more
         std::vector<Block> all;
@@ -74,7 +81,7 @@ hipError_t pool_get(int device, bool host, size_t bytes, Block *b) {
         if (all.empty()) return e;
         (void)hipGetLastError();
         raw_free(host, all);
-        e = raw_get(host, want, &p);
+        e = raw_get(device, host, want, &p);
         if (e != hipSuccess) return e;
     }
     b->p = p;

@@ -21,8 +21,8 @@ struct Block {
     size_t bytes = 0;   // size class, >= the size asked for
 };
 
-// A block of at least `bytes` on `device` (the current device), or of pinned
-// coherent host memory; contents undefined.
+// A block of at least `bytes` on `device`, or of pinned coherent host memory;
+// contents undefined.
 hipError_t pool_get(int device, bool host, size_t bytes, Block *b);
 
 // Gives a block back. Every use of it, on any stream, has completed.

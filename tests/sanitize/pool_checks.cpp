@@ -84,8 +84,23 @@ static void check_sizes() {
     }
 }
 
+// Blocks lie on the device that was asked for, whichever the thread has current,
+// which stays as it was.
+static void check_devices() {
+    for (int device = 0; device < 3; ++device)
+        for (int cur = 0; cur < 3; ++cur) {
+            current = cur;
+            Block b[3];
+            for (Block &x : b) CHECK(pool_get(device, false, 70000, &x) == hipSuccess && live[x.p].device == device);
+            CHECK(current == cur);
+            for (const Block &x : b) pool_put(device, false, x);
+        }
+    current = 0;
+}
+
 int main() {
     check_sizes();
+    check_devices();
     std::printf("pool checks passed\n");
     return 0;
 }
