@@ -354,8 +354,16 @@ sbqa_status sbqa_inject_wait_timeout(sbqa_ctx *ctx);
 /* Thread-local message of the last failed call on this thread ("" if none). */
 const char *sbqa_last_error(void);
 
-/* Release the context and its device memory. NULL is a no-op. */
+/* Release the context, once its work has ended. NULL is a no-op. Its device memory
+ * goes back to the device except for up to 256 MiB per device (and 64 MiB of
+ * pinned host memory) of freed blocks that the library keeps for later contexts;
+ * it gives them back when an allocation of its own fails, or when asked. */
 void sbqa_destroy(sbqa_ctx *ctx);
+
+/* Give every block that the library keeps for reuse back to its device and to the
+ * host, for other allocators of the process. Contexts and servers are not
+ * affected. Any thread may call it. */
+void sbqa_release_cached(void);
 
 /* ------------------------------------------------------------------------ */
 /* Serving: continuous batching of many instances on one GPU.               */

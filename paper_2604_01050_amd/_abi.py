@@ -90,6 +90,7 @@ def _load() -> ct.CDLL:
         "sbqa_inject_wait_timeout": ([vp], i32),
         "sbqa_last_error": ([], ct.c_char_p),
         "sbqa_destroy": ([vp], None),
+        "sbqa_release_cached": ([], None),
         "sbqa_server_create": ([ct.c_size_t, i32, ct.POINTER(vp)], i32),
         "sbqa_submit": ([vp, ct.POINTER(Coupling), vp, i32, i32, i32, ct.POINTER(Schedule), ct.POINTER(u64)], i32),
         "sbqa_poll": ([vp, u64, vp, vp, vp], i32),
@@ -287,6 +288,12 @@ def sbqa_destroy(ctx: Context) -> None:
     if ctx.ptr:
         lib.sbqa_destroy(ctx.ptr)
         ctx.ptr = None
+
+
+def sbqa_release_cached() -> None:
+    """Gives the memory that destroyed contexts left cached back to the device and
+    the host."""
+    lib.sbqa_release_cached()
 
 
 # ------------------------------------------------------------------ serving

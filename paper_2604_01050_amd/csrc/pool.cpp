@@ -109,4 +109,18 @@ void pool_put(int device, bool host, Block b) {
     raw_free(host, out);
 }
 
+void pool_trim() {
+    std::vector<Block> dev, host;
+    {
+        std::lock_guard<std::mutex> lk(g_pool_mu);
+        for (auto &kv : caches()) {
+            std::vector<Block> &to = kv.first.second ? host : dev;
+            to.insert(to.end(), kv.second.blocks.begin(), kv.second.blocks.end());
+            kv.second = Cache();
+        }
+    }
+    raw_free(false, dev);
+    raw_free(true, host);
+}
+
 }  // namespace sbqa

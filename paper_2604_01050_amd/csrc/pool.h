@@ -4,8 +4,8 @@
 // the whole device, so that retiring a served instance stalled the others) and
 // 0.05 to 0.8 ms per pinned block. Blocks given back are cached per device, up
 // to POOL_DEVICE_BYTES and POOL_HOST_BYTES, the oldest returned to the runtime
-// beyond that, all of a device's when one of its allocations fails. Any thread
-// may call.
+// beyond that, all of a device's when one of its allocations fails, all there are
+// at sbqa_release_cached. Any thread may call.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -27,6 +27,9 @@ hipError_t pool_get(int device, bool host, size_t bytes, Block *b);
 
 // Gives a block back. Every use of it, on any stream, has completed.
 void pool_put(int device, bool host, Block b);
+
+// Returns every cached block, of all devices and the host's, to the runtime.
+void pool_trim();
 
 // A block for the length of a scope. The scope's end must lie behind a
 // synchronisation with every use.

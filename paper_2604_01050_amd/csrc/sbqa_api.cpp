@@ -2266,4 +2266,6 @@ void sbqa_destroy(sbqa_ctx *c) {
     delete c;   // waits for the context's work
 }
 
+void sbqa_release_cached(void) { pool_trim(); }
+
 }  // extern "C"

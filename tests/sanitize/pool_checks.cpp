@@ -98,9 +98,70 @@ static void check_devices() {
     current = 0;
 }
 
+// An allocation that fails takes what is cached on its device and tries again.
+static void check_full_device() {
+    pool_trim();
+    std::vector<Block> bs(40);
+    for (Block &b : bs) CHECK(pool_get(1, false, (size_t)4 << 20, &b) == hipSuccess);
+    for (const Block &b : bs) pool_put(1, false, b);
+    CHECK(held[1] == (size_t)160 << 20);
+    capacity = (size_t)200 << 20;
+    Block big;
+    CHECK(pool_get(1, false, (size_t)190 << 20, &big) == hipSuccess && held[1] == (size_t)190 << 20);
+    Block more;
+    CHECK(pool_get(1, false, (size_t)20 << 20, &more) == hipErrorOutOfMemory && !more.p);
+    capacity = (size_t)1 << 60;
+    pool_put(1, false, big);
+}
+
+// What is cached is bounded, of the host's blocks too, and goes back when asked.
+static void check_bounds() {
+    for (bool host : {false, true}) {
+        std::vector<Block> bs(600);
+        for (Block &b : bs) CHECK(pool_get(0, host, (size_t)1 << 20, &b) == hipSuccess);
+        for (const Block &b : bs) pool_put(0, host, b);
+        CHECK((host ? held_host : held[0]) <= (host ? POOL_HOST_BYTES : POOL_DEVICE_BYTES));
+    }
+    CHECK(held[0] && held_host);
+    pool_trim();
+    CHECK(!held[0] && !held[1] && !held[2] && !held_host && live.empty());
+}
+
+// A block is with one holder at a time, whatever the threads do.
+static void check_threads() {
+    std::vector<std::thread> ts;
+    for (int t = 0; t < 4; ++t)
+        ts.emplace_back([t] {
+            std::mt19937 g(t);
+            std::vector<std::pair<Block, bool>> mine;
+            for (int n = 0; n < 3000; ++n) {
+                const bool host = g() % 4 == 0;
+                if (g() % 2 || mine.empty()) {
+                    Block b;
+                    CHECK(pool_get(0, host, (size_t)1 << (10 + g() % 12), &b) == hipSuccess);
+                    *static_cast<char *>(b.p) = (char)t;   // (a race here is a block with two holders)
+                    mine.push_back({b, host});
+                } else {
+                    const size_t k = g() % mine.size();
+                    CHECK(*static_cast<char *>(mine[k].first.p) == (char)t);
+                    pool_put(0, mine[k].second, mine[k].first);
+                    mine.erase(mine.begin() + (long)k);
+                }
+                if (n % 700 == 0) pool_trim();
+            }
+            for (auto &m : mine) pool_put(0, m.second, m.first);
+        });
+    for (std::thread &t : ts) t.join();
+    pool_trim();
+    CHECK(live.empty());
+}
+
 int main() {
     check_sizes();
     check_devices();
+    check_full_device();
+    check_bounds();
+    check_threads();
     std::printf("pool checks passed\n");
     return 0;
 }

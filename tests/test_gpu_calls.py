@@ -264,3 +264,26 @@ def test_wait_timeout_of_the_dense_loop_is_reported(sb):
     with pytest.raises(sb.SbqaError) as ei:
         sb.sbqa_inject_wait_timeout(sb.sbqa_create(J=inst.sk_pm1(200, 65), R=16, runs=8, steps=40))
     assert ei.value.status == sb.EINVAL
+
+
+def test_cached_memory_goes_back(sb):
+    """What destroyed contexts leave cached is bounded and goes back when asked."""
+    import gc
+
+    import torch
+    _log("cached memory")
+    make = lambda: sb.sbqa_create(J=inst.sk_pm1(1500, 71), R=16, runs=16, steps=10, precision=sb.PREC_FP32)
+    sb.sbqa_destroy(make())
+    gc.collect()
+    sb.sbqa_release_cached()
+    free0 = torch.cuda.mem_get_info()[0]
+    kept = [make() for _ in range(3)]
+    for c in kept:
+        sb.sbqa_destroy(c)
+    free1 = torch.cuda.mem_get_info()[0]
+    sb.sbqa_release_cached()
+    free2 = torch.cuda.mem_get_info()[0]
+    assert 0 < free0 - free1 <= 288 << 20 and free2 >= free0 - (4 << 20), (free0, free1, free2)
+    c = make()
+    sb.sbqa_step(c, 3)
+    sb.sbqa_best(c)
