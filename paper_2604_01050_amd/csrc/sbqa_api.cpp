@@ -581,13 +581,15 @@ static DenseChoice tune_dense(Path path, int C, int Np, bool served, hipStream_t
     if (cand.size() > 1) {
         const int planes = path == PATH_BF16X3 ? 2 : 1;
         const int Cgm = (int)round_up(C, 256), nkc = dense_nkc(path, Np);
-        std::vector<void *> bufs;
+        std::vector<Block> bufs;
+        int device = 0;
+        const bool known = hipGetDevice(&device) == hipSuccess;
         auto grab = [&](size_t bytes) -> void * {
-            void *p = nullptr;
-            if (hipMalloc(&p, std::max<size_t>(bytes, 256)) != hipSuccess) return nullptr;
-            bufs.push_back(p);
-            (void)hipMemsetAsync(p, 0, std::max<size_t>(bytes, 256), st);
-            return p;
+            Block b;
+            if (!known || pool_get(device, false, bytes, &b) != hipSuccess) return nullptr;
+            bufs.push_back(b);
+            (void)hipMemsetAsync(b.p, 0, b.bytes, st);
+            return b.p;
         };
         const size_t jb = (size_t)dense_j_bytes(path, Np), gb = (size_t)dense_plane_bytes(path, Cgm, Np),
                      sb = (size_t)C * Np * 4;
@@ -630,10 +632,13 @@ static DenseChoice tune_dense(Path path, int C, int Np, bool served, hipStream_t
                 if (ok) us[q] = std::min(us[q], ms * 1000.0f / 3.0f);
             }
         if (ok) best = cand[(size_t)(std::min_element(us.begin(), us.end()) - us.begin())];
-        (void)hipStreamSynchronize(st);
+        const bool done = hipStreamSynchronize(st) == hipSuccess;
         if (e0) (void)hipEventDestroy(e0);
         if (e1) (void)hipEventDestroy(e1);
-        for (void *p : bufs) (void)hipFree(p);
+        for (const Block &b : bufs) {
+            if (done) pool_put(device, false, b);
+            else (void)hipFree(b.p);
+        }
         timed = ok;
         (void)hipGetLastError();
     }

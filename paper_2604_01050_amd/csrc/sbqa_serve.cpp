@@ -191,6 +191,7 @@ struct sbqa_server {
     GroupTask *h_tasks[2] = {nullptr, nullptr};
     GroupHeader *h_hdr[2] = {nullptr, nullptr};
     hipEvent_t h_free[2] = {nullptr, nullptr};   // the copy out of host table q has completed
+    Block d_tasks_block, d_hdr_block;
     GroupTask *d_tasks = nullptr;
     GroupHeader *d_hdr = nullptr;
     // full step blocks are replayed from HIP graphs, one per set of groups
@@ -562,8 +563,8 @@ static void release(sbqa_server *srv) {
         if (srv->h_hdr[q]) (void)hipHostFree(srv->h_hdr[q]);
         if (srv->h_free[q]) (void)hipEventDestroy(srv->h_free[q]);
     }
-    if (srv->d_tasks) (void)hipFree(srv->d_tasks);
-    if (srv->d_hdr) (void)hipFree(srv->d_hdr);
+    pool_put(srv->device, false, srv->d_tasks_block);
+    pool_put(srv->device, false, srv->d_hdr_block);
     if (srv->stream) (void)hipStreamDestroy(srv->stream);
     if (srv->create_stream) (void)hipStreamDestroy(srv->create_stream);
     delete srv;
@@ -592,8 +593,10 @@ sbqa_status sbqa_server_create(size_t hbm_budget_bytes, int32_t max_slots, sbqa_
     if (e == hipSuccess) e = launch_hold(0, srv->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(srv->stream);
     if (e == hipSuccess) e = open_create_stream(srv, srv->h_free[0]);
-    if (e == hipSuccess) e = hipMalloc(&srv->d_tasks, sizeof(GroupTask) * ntask);
-    if (e == hipSuccess) e = hipMalloc(&srv->d_hdr, sizeof(GroupHeader) * NGROUPS);
+    if (e == hipSuccess) e = pool_get(srv->device, false, sizeof(GroupTask) * ntask, &srv->d_tasks_block);
+    if (e == hipSuccess) e = pool_get(srv->device, false, sizeof(GroupHeader) * NGROUPS, &srv->d_hdr_block);
+    srv->d_tasks = static_cast<GroupTask *>(srv->d_tasks_block.p);
+    srv->d_hdr = static_cast<GroupHeader *>(srv->d_hdr_block.p);
     if (e != hipSuccess) {
         release(srv);
         return fail(e == hipErrorOutOfMemory ? SBQA_ENOMEM : SBQA_EDEVICE, "server set-up: %s", hipGetErrorString(e));
