@@ -782,8 +782,15 @@ constexpr uint32_t MAX_EXCHANGE_STEPS = 4096;
 sbqa_ctx::~sbqa_ctx() {
     // the pool hands the blocks to other contexts, on other streams: the work
     // on them ends first (blocks of a stream that reports an error are left
-    // to the runtime, which waits for the device)
-    const bool done = idle || !stream || hipStreamSynchronize(stream) == hipSuccess;
+    // to the runtime, which waits for the device); recorded work may be
+    // replaying on any of the device's streams
+    bool done = idle || !stream || hipStreamSynchronize(stream) == hipSuccess;
+    if (recorded) {
+        int cur = device;
+        done = done && hipGetDevice(&cur) == hipSuccess && (cur == device || hipSetDevice(device) == hipSuccess) &&
+               hipDeviceSynchronize() == hipSuccess;
+        if (cur != device) (void)hipSetDevice(cur);
+    }
     forget_launches(this);
     auto back = [&](bool host, Block b) {
         if (done) pool_put(device, host, b);
@@ -896,6 +903,8 @@ static sbqa_status check_device(int *dev) {
 }
 
 namespace sbqa {
+
+void note_recording(sbqa_ctx *c) { c->recorded = c->recorded || capturing(c->stream); }
 
 // Build operand f(X) of the current step from the current state.
 sbqa_status rebuild_operand(sbqa_ctx *c) {
@@ -1692,14 +1701,6 @@ static uint32_t mid_min_steps(const sbqa_ctx *c) {
     return c->mid.RBW == 2 && c->mid.G > 1 ? (c->N > 1024 ? 4 : 3) : 2;
 }
 
-// Whether steps of the context have been recorded into a graph. Its many-step
-// loops step the state in place and, when recorded, can be replayed; once they have
-// been, every call keeps to them.
-static bool recorded(sbqa_ctx *c) {
-    c->recorded = c->recorded || capturing(c->stream);
-    return c->recorded;
-}
-
 // K steps of the many-step loop of a dense +-1 instance in one launch.
 static sbqa_status ctx_step_mid(sbqa_ctx *c, uint32_t K) {
     MidArgs a;
@@ -1744,7 +1745,7 @@ static sbqa_status ctx_step_mid(sbqa_ctx *c, uint32_t K) {
 // the counters of the 8-column loop tell a launch from the one before it, not from
 // the same one replayed. Its buffers are taken at the first such call.
 static bool wide_step(sbqa_ctx *c, uint32_t K) {
-    if (c->L.C < 128 || recorded(c) || (int64_t)K > c->L.C / 256 + (c->L.C < 256)) return false;
+    if (c->L.C < 128 || c->recorded || (int64_t)K > c->L.C / 256 + (c->L.C < 256)) return false;
     if (c->sbits) return true;
     if (alloc_wide(c) == hipSuccess) return true;
     (void)hipGetLastError();   // no room: the narrow loop does it
@@ -1757,7 +1758,7 @@ static bool wide_step(sbqa_ctx *c, uint32_t K) {
 // copies back and reports.
 static sbqa_status ctx_step_resident(sbqa_ctx *c, uint32_t K) {
     if (c->mid.NT) {
-        if (recorded(c) || K >= mid_min_steps(c)) return ctx_step_mid(c, K);
+        if (c->recorded || K >= mid_min_steps(c)) return ctx_step_mid(c, K);
         sbqa_status st = c->g_stale ? rebuild_operand(c) : SBQA_OK;
         for (uint32_t q = 0; q < K && st == SBQA_OK; ++q) st = ctx_step_once(c);
         return st;
@@ -1819,6 +1820,7 @@ sbqa_status ctx_sync(sbqa_ctx *c) {
 sbqa_status ctx_step(sbqa_ctx *c, uint32_t n) {
     if ((uint64_t)c->step + n > c->s.steps)
         return fail(SBQA_ESTATE, "step %u + %u exceeds the schedule of %u steps", c->step, n, c->s.steps);
+    note_recording(c);
     if (c->resident || c->mid.NT) {
         uint32_t left = n;
         while (left) {

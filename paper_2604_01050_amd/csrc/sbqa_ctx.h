@@ -87,6 +87,7 @@ sbqa_status ctx_best(sbqa_ctx *c, double *energies, int8_t *spins);
 sbqa_status ctx_readout_async(sbqa_ctx *c);
 sbqa_status ctx_readout_collect(sbqa_ctx *c, double *energies, int8_t *spins);
 sbqa_status ctx_check_async(sbqa_ctx *c);  // after a readout copy and a stream synchronisation
+void note_recording(sbqa_ctx *c);          // sets recorded while the stream is capturing
 sbqa_status ctx_sync(sbqa_ctx *c);         // fetch the error word, synchronise, check it
 // energies of the current state -> best tracking (reset: the previous best is discarded)
 sbqa_status ctx_evaluate(sbqa_ctx *c, bool reset = false);
@@ -192,7 +193,10 @@ struct sbqa_ctx {
     // the fragment-tiled operand lags behind the state (the dense many-step
     // loops do not use it): rebuilt where it is read
     bool g_stale = false;
-    bool recorded = false;              // steps have been captured into a graph
+    // work of the context has been captured into a graph: it may be replayed on any
+    // stream while the context lives, and steps keep to the many-step loops, which
+    // step the state in place
+    bool recorded = false;
     int res_D = 0, res_rows = 0, res_nwg = 0;
     int res_W = 8;                      // columns per workgroup: 8, or 4 or 2 in the narrow loop
     int32_t *colpad = nullptr;          // [rows][D]

@@ -82,6 +82,7 @@ extern "C" sbqa_status sbqa_energy_noalloc(sbqa_ctx *c, const int8_t *spins, int
                     count, N, need, (size_t)SBQA_NOALLOC_SCRATCH_BYTES);
     if (!is_device_memory(spins, c->device) || !is_device_memory(out, c->device))
         return fail(SBQA_EINVAL, "spins and out must be device memory on the context's device %d", c->device);
+    note_recording(c);
     uint8_t *base = nullptr;
     sbqa_status st = scratch_on(c->device, &base);
     if (st != SBQA_OK) return st;

@@ -287,3 +287,38 @@ def test_cached_memory_goes_back(sb):
     c = make()
     sb.sbqa_step(c, 3)
     sb.sbqa_best(c)
+
+
+@pytest.mark.parametrize("kind,kern", [("dense", "AUTO"), ("dense", "STREAM"), ("small", "AUTO"), ("sparse", "AUTO"),
+                                       ("sparse", "STREAM")])
+def test_destroy_while_a_recorded_block_replays(sb, kind, kern):
+    """A context destroyed while its recorded steps replay on another stream: its
+    memory reaches later contexts only once they have ended."""
+    import torch
+    _log("destroy under replays, %s %s" % (kind, kern))
+    N = 60 if kind == "small" else 1000
+    E = inst.regular_graph(N, 3, 81)
+    kw = dict(csr=inst.edges_to_csr(N, E, inst.gaussian_edges(len(E), 82))) if kind == "sparse" else dict(J=inst.sk_pm1(N, 83))
+    kw.update(R=16, runs=8, steps=400, seed=6, loop_kernel=getattr(sb, "LOOP_" + kern))
+
+    def solve():
+        c = sb.sbqa_create(**kw)
+        sb.sbqa_step(c, 30)
+        return (*sb.sbqa_get_state(c), *sb.sbqa_best(c))
+
+    ref = solve()
+    for rep in range(2):
+        ctx = sb.sbqa_create(**kw)
+        A, B = torch.cuda.Stream(), torch.cuda.Stream()
+        sb.sbqa_set_stream(ctx, A)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=A):
+            sb.sbqa_step(ctx, 200)
+        sb.sbqa_sync(ctx)
+        with torch.cuda.stream(B):
+            for _ in range(20):
+                graph.replay()
+        sb.sbqa_destroy(ctx)
+        for a, b in zip(ref, solve()):
+            assert np.array_equal(a, b)
+        torch.cuda.synchronize()
