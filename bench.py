@@ -194,28 +194,65 @@ def small_kernel_name(w):
     return "k_dense_small_bits" if bits else "k_dense_small"
 
 
-def dense_kernel_name(info):
-    """The dense step kernel the library launches. Exact paths (spins padded to a
-    multiple of 512): a finer tile on small grids, else K split over the waves
-    (from 128 tiles of 64 spins x 64 columns on; bit-packed fp4 from 256). The
-    others: 16 spins per workgroup up to one workgroup per CU, else 32 up to
-    one. Without R and runs, by the tile alone: split-K where bit-packed J at the
-    128-column tile has an even count of K chunks (128 spins each in fp8, 256
-    in fp4) in either half."""
+_PATH_CODES = {"dense_fp32": 0, "dense_fp8": 1, "dense_bf16x3": 2, "dense_int8": 4, "dense_fp8_packed": 5,
+               "dense_fp4": 6, "dense_fp4_packed": 7}
+
+
+def tuned_form(info):
+    """The form of the dense step that the library's autotuner chose for this
+    shape (1, 2: 16- and 32-spin tiles, 3: the 64-spin tile, 4..7: split-K), from
+    its tile file; None without one. Lines are <tag> <arch> <CUs> <path + 16 form> <C>
+    <padded N> <tile_cols / 64>; the last one of a shape counts."""
+    f = os.environ.get("SBQA_TUNE_CACHE")
+    if f is None:
+        base = os.environ.get("XDG_CACHE_HOME") or os.path.join(os.environ.get("HOME", ""), ".cache")
+        f = os.path.join(base, "sbqa", "dense_tiles.txt")
+    form = None
+    try:
+        with open(f) as fp:
+            for line in fp:
+                v = line.split()
+                if len(v) != 7 or v[0] != "sbqa-tile-v1":
+                    continue
+                code, C, rows, mbw = (int(x) for x in v[3:])
+                if (code >= 16 and code % 16 == _PATH_CODES.get(info["path"]) and C == info["R"] * info["runs"]
+                        and 0 <= rows - info["N"] < 512 and 64 * mbw == info["tile_cols"]):
+                    form = code // 16
+    except (OSError, ValueError):
+        pass
+    return form
+
+
+def dense_kernel_name(info, form=None):
+    """The dense step kernel the library launches for single steps: that of the
+    form its autotuner chose, else of the form it takes where the caller names the
+    tile. Exact paths (spins padded to a multiple of 512): a finer tile on small
+    grids, else K split over the waves up to two tiles of 64 spins x 64 columns per
+    CU, and above that in nearly full rounds of four (bit-packed J). The others: 16
+    spins per workgroup up to one workgroup per CU, else 32 up to one. Without R
+    and runs, by the tile alone: split-K where bit-packed J at the 128-column
+    tile has an even count of K chunks (128 spins each in fp8, 256 in fp4) in
+    either half."""
     exact = "fp8" in info["path"] or "fp4" in info["path"] or "int8" in info["path"]
+    if form is not None and form != 3:
+        return "k_dense_step_fine" if form < 3 else "k_dense_step_sk"
     if "R" in info and "runs" in info:
         pad = 512 if exact else 128
         rows = -(-info["N"] // pad) * pad
         cb = -(-(info["R"] * info["runs"]) // info["tile_cols"]) * info["tile_cols"] // 64
-        if exact:
-            least = 256 if info["path"] == "dense_fp4_packed" else 128
-            return "k_dense_step_sk" if rows // 64 * cb >= least else "k_dense_step_fine"
-        if rows // 32 * cb <= 256:
+        n = rows // 64 * cb
+        if form is None and exact:
+            if n < (256 if info["path"] == "dense_fp4_packed" else 128):
+                return "k_dense_step_fine"
+            full = info["path"].endswith("_packed") and cb % 2 == 0 and 20 * n >= 17 * 1024 * -(-n // 1024)
+            return "k_dense_step_sk" if n <= 512 or full else "k_dense_step"
+        if form is None and rows // 32 * cb <= 256:
             return "k_dense_step_fine"
-    Np = -(-info["N"] // 512) * 512
-    nkc = {"dense_fp8_packed": Np // 128, "dense_fp4_packed": Np // 256}.get(info["path"], 1)
-    if info["path"] in ("dense_fp8_packed", "dense_fp4_packed") and info["tile_cols"] == 128 and nkc % 4 == 0:
-        return "k_dense_step_sk"
+    elif exact:
+        Np = -(-info["N"] // 512) * 512
+        nkc = {"dense_fp8_packed": Np // 128, "dense_fp4_packed": Np // 256}.get(info["path"], 1)
+        if info["path"].endswith("_packed") and info["tile_cols"] == 128 and nkc % 4 == 0:
+            return "k_dense_step_sk"
     # two J planes at the 128-column tile: two column groups per workgroup
     # when the padded columns make whole pairs of 128-column chunks
     if info["path"] == "dense_bf16x3" and info["tile_cols"] == 128:
@@ -585,7 +622,8 @@ def measure(sb, w, K, warmup, stream, loop_kernel="auto", events=True, workload=
             out["roofline"] = {"bound": "mfma", "achieved": fl / avg_s / 1e12, "peak": peak, "unit": unit,
                                "frac": fl / avg_s / 1e12 / peak,
                                "traffic": measured_traffic(workload, info["path"]) if workload else None,
-                               "kernel": dense_kernel_name(info), "avg_step_us": avg_s * 1e6,
+                               "kernel": dense_kernel_name(info, None if w.get("dense_tile") else tuned_form(info)),
+                               "avg_step_us": avg_s * 1e6,
                                "algorithmic_flops_per_step": fl}
     return out, ctx
 
