@@ -67,6 +67,7 @@ __device__ __forceinline__ Frag32 unpack_pm1_fp4(uint2 w) {
 // ---------------------------------------------------------------------------
 // fp64 energies of spin rows (Eq. 2 at the corners).
 // ---------------------------------------------------------------------------
+constexpr int ENERGY_SMALL_T = 8;         // spin blocks up to which the latency of K tiles counts
 constexpr int LDS_STRIDE = GEMM_KB + 16;  // padded LDS row (bytes): spreads rows over banks
 constexpr int TILE_BYTES = GEMM_BM * LDS_STRIDE;
 static_assert(GEMM_BM == GEMM_BN, "square block tile assumed by the loaders");
@@ -82,16 +83,16 @@ __device__ __forceinline__ Frag32 lds_frag(const uint8_t *tile, int row, int g) 
 // -1/2 s^T J s of GEMM_BM spin rows at a time, from the lower triangle of the
 // symmetric J alone: part[u][c] = -sum over work unit u of s_n (L_n + D_n / 2),
 // L_n the sum over the 128-spin blocks below n's and D_n the one over its own.
-// A unit is one of Z ranges of the K tiles of a pair of spin blocks (p, T - 1 - p),
-// so that all units are equally long; the sums over n happen here, so that no
-// field is written. 8 waves in 2 (rows) x 4 (spins) tiles of 64 x 32,
+// A unit is a pair of spin blocks (p, T - 1 - p), so that all units are equally
+// long, and one of Z ranges of their K tiles; the sums over n happen here, so that
+// no field is written. 8 waves in 2 (rows) x 4 (spins) tiles of 64 x 32,
 // K tiles of 16 spins double-buffered in LDS with one barrier each. Bound by
 // the fp64 matrix rate: N = 8192, 512 rows 3.5e10 flop in 0.64 ms, 54 of the 70
 // TFLOP/s of a large library product (the full product by 4 waves took 1.79 ms:
 // twice the flops, and its prefetched operands lived in scratch memory).
 // Two workgroups per CU (128 registers); one (185 registers) took 0.75 ms.
-// The energies stay as near float64's (relative 2-norm against numpy's float64,
-// N = 3000: 6e-16, 5e-16 for the full product). Lane group g = lane/16 holds the same 32-byte K slice for
+// Error (relative 2-norm against 80-bit sums, three seeds of 60 rows): N = 130 1.6e-16, N =
+// 1000 3.0e-16, N = 3000 4.1 to 5.0e-16; the full product 2.4, 3.1 and 5.1 to 5.4e-16. Lane group g = lane/16 holds the same 32-byte K slice for
 // A and B, so the products pair correctly whatever K order the instruction
 // uses in a slice.
 __global__ __launch_bounds__(GEMM_THREADS, 4) void k_energy_gemm(const int8_t *__restrict__ S,
@@ -108,14 +109,16 @@ __global__ __launch_bounds__(GEMM_THREADS, 4) void k_energy_gemm(const int8_t *_
     const int so = (tid >> 2) * LDS_STRIDE + (tid & 3) * 32;
     const int jr = tid >> 3, jc = tid & 7, jo = TILE_BYTES + jr * LDS_STRIDE + jc * 16;
     red[tid] = 0.0;
-    // this unit's K tiles of the pair's, the longer block's first
+    // this unit's K tiles: of up to ENERGY_SMALL_T blocks a range of the pair's, the
+    // longer block's first; else one of either block's
     const int64_t all = KPB * (T - p) + (2 * p == T - 1 ? 0 : KPB * (p + 1));
     const int r0 = (int)(all * z / Z), r1 = (int)(all * (z + 1) / Z);
     for (int half = 0; half < 2; ++half) {
         const int t = half == 0 ? T - 1 - p : p;     // the longer block first
         if (half == 1 && t == T - 1 - p) break;      // the middle block of an odd count is alone
         const int nk = KPB * (t + 1), before = half == 0 ? 0 : KPB * (T - p);
-        const int k0 = min(max(r0 - before, 0), nk), k1 = min(max(r1 - before, 0), nk);
+        const int k0 = T > ENERGY_SMALL_T ? (int)((int64_t)nk * z / Z) : min(max(r0 - before, 0), nk);
+        const int k1 = T > ENERGY_SMALL_T ? (int)((int64_t)nk * (z + 1) / Z) : min(max(r1 - before, 0), nk);
         if (k0 == k1) continue;
         const int n0 = t * GEMM_BN, kd = KPB * t;    // from K tile kd on: the block's own spins
         const double *jrow = J + (int64_t)(n0 + jr) * Np + 2 * jc;
@@ -856,12 +859,13 @@ __global__ __launch_bounds__(DENSE_THREADS) void k_dense_step_fine(const DenseSt
 // products leave room for, and the two overlap only beside 32 x 32 products: on
 // one SIMD, 32 16x16x128 fp4 products with 4 vector instructions each take 981 x 2
 // clocks, 16 32x32x64 products of the same work with 7 each 682 x 2. Then the
-// epilogue's state traffic at the end of a launch. us per step before (64-spin or
-// fine tile; at 16384 x 256 split-K through LDS) and now, N x C:
-//            16384 x 256  16384 x 128  8192 x 256  8192 x 128  4096 x 256
-//   fp4      53.0  44.3   35.4  27.3   22.9  19.4  16.3  12.4  11.2   9.5
-//   fp8      78.9  71.7   58.6  38.0   34.4  24.3  22.6  14.0  14.5  10.6
-//   int8     6000 x 256: 24.1  22.4; 4096 x 256: 14.3  11.8; 3000 x 256: 11.9  10.2
+// epilogue's state traffic at the end of a launch. us per step, the better of the
+// 64-spin and the fine tile / split-K, N x C (launches back to back):
+//                16384 x 256  16384 x 128  8192 x 256   8192 x 128   4096 x 256
+//   fp4, 1 bit   51.0 / 41.4  33.3 / 25.3  20.6 / 17.7  13.9 / 11.4  10.3 /  8.8
+//   fp8, 1 bit   72.7 / 58.5  53.7 / 33.4  31.8 / 22.1  21.3 / 13.0  13.9 / 10.2
+//   int8         88.1 / 89.0  58.6 / 50.7  28.2 / 25.8  21.6 / 16.7  14.2 / 11.1
+// (default_dense_form has the sizes where the tiles are faster)
 template <int PATH, int SG, int CG, int EPI>
 __global__ __launch_bounds__(2 * DENSE_THREADS) void k_dense_step_sk(const DenseStepArgs a, int nx, int ny) {
     constexpr int KS = 8 / (SG * CG), MB = 4, RB = DENSE_TN / 16;
@@ -1029,11 +1033,6 @@ __global__ __launch_bounds__(2 * DENSE_THREADS) void k_dense_step_sk(const Dense
     }
 }
 
-// Grouped step of every dense instance of one serving group (same path and
-// m-blocks per wave): a grid-stride loop over the tiles of all tasks (task q
-// owns virtual blocks [first, first + nblocks), nchunk spin tiles per column
-// chunk), each running exactly the workgroup of the standalone kernel for the
-// task's step n = n_base + offset; tasks past their last step skip.
 // J in the contraction precision, fragment-tiled (groups of DENSE_TN/16 row
 // blocks), from the zero-padded row-major float64 copy: one thread per 4
 // consecutive K elements of a row. e4m3 for ternary J, int8 for integer J
@@ -1182,6 +1181,11 @@ __device__ __forceinline__ void group_blocks(const GroupHeader *hdr, const Group
     }
 }
 
+// Grouped step of every dense instance of one serving group (same path and
+// m-blocks per wave): a grid-stride loop over the tiles of all tasks (task q
+// owns virtual blocks [first, first + nblocks), nchunk spin tiles per column
+// chunk), each running exactly the workgroup of the standalone kernel for the
+// task's step n = n_base + offset; tasks past their last step skip.
 template <int PATH, int MBW>
 __global__ __launch_bounds__(DENSE_THREADS) void k_group_dense(const GroupHeader *__restrict__ hdr,
                                                                const GroupTask *__restrict__ tasks, int offset) {
@@ -1310,7 +1314,7 @@ EnergyPlan energy_plan(int N, int count) {
     const int64_t pairs = (e.T + 1) / 2, tiles = pairs * (e.cp / GEMM_BM);
     const int64_t ktiles = (int64_t)(e.T + 1) * (GEMM_BN / (GEMM_KB / 8));   // of a pair
     while (e.Z < 16 && ((ktiles >= 16 * e.Z && tiles * e.Z < 512) ||
-                        (e.T <= 8 && ktiles > 2 * e.Z && tiles * e.Z <= 320)))
+                        (e.T <= ENERGY_SMALL_T && ktiles > 2 * e.Z && tiles * e.Z <= 320)))
         e.Z *= 2;
     e.units = (int)pairs * e.Z;
     return e;
