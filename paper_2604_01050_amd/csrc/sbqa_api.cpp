@@ -99,7 +99,8 @@ static void over_blocks(int64_t nb, int64_t work, F &&f) {
 }
 
 // Transpose of a 64 x 64 bit matrix, row r in a[r] (bit c: column c): the
-// off-diagonal quadrants swapped at block sizes 32, 16, ..., 1.
+// off-diagonal quadrants swapped at block sizes 32, 16, ..., 1 (the recursive
+// bit-matrix transpose of H. S. Warren, Hacker's Delight, chapter 7).
 static void transpose64(uint64_t (&a)[64]) {
     uint64_t m = 0x00000000FFFFFFFFull;
     for (int w = 32; w; w >>= 1, m ^= m << w)
@@ -118,8 +119,9 @@ static void transpose64(uint64_t (&a)[64]) {
 static bool scan_pm1(const double *A, int64_t N, std::vector<uint64_t> *bits) {
     constexpr uint64_t SIGN = (uint64_t)1 << 63, ONE = 0x3FF0000000000000ull;
     const int64_t words = (N + 63) / 64, nb = words;
+    if (N < 2 || std::fabs(A[1]) != 1.0) return false;   // (most others end here, before N^2 / 8 bytes are taken)
     bits->assign((size_t)(N * words), 0);
-    std::atomic<bool> good{N > 1};
+    std::atomic<bool> good{true};
     auto raw = [](const double *p) {
         uint64_t u;
         std::memcpy(&u, p, sizeof u);
