@@ -60,9 +60,9 @@ def build(verbose: bool = False, jobs: int | None = None) -> str:
     return OUT
 
 
-# Host sanitizers for the test driver tests/sanitize/host_checks.cpp: only
-# the host part of each source is instrumented (each -fsanitize= behind
-# -Xarch_host); device code is built as above.
+# Host sanitizers for the test drivers tests/sanitize/*.cpp that include the
+# runtime's API source: only the host part of each source is instrumented (each
+# -fsanitize= behind -Xarch_host); device code is built as above.
 SANITIZERS = {
     "asan": ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
              "-Xarch_host", "-fno-sanitize-recover=all", "-Xarch_host", "-fno-omit-frame-pointer"],
@@ -70,19 +70,24 @@ SANITIZERS = {
 }
 
 
-def build_sanitized(kind: str, verbose: bool = False) -> str:
-    """Build the host-check driver (which includes the runtime's API source)
-    with the other sources, host parts instrumented by `kind` ("asan": address
-    + undefined behaviour, "tsan": threads). Returns the executable's path."""
+def build_sanitized(kind: str, verbose: bool = False, driver: str = "host_checks") -> str:
+    """Build a host-check driver (which includes the runtime's API source) with
+    the other sources, host parts instrumented by `kind` ("asan": address +
+    undefined behaviour, "tsan": threads). The other sources' objects are shared
+    by the drivers and compiled again when a source is newer. Returns the
+    executable's path."""
     san = SANITIZERS[kind]
     bdir = os.path.join(BUILD, "sanitize_" + kind)
     os.makedirs(bdir, exist_ok=True)
-    driver = os.path.join(ROOT, "tests", "sanitize", "host_checks.cpp")
+    dsrc = os.path.join(ROOT, "tests", "sanitize", driver + ".cpp")
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.cpp")))
-    srcs = [x for x in srcs if os.path.basename(x) != "sbqa_api.cpp"] + [driver]
+    srcs = [x for x in srcs if os.path.basename(x) != "sbqa_api.cpp"]
+    newest = max(os.path.getmtime(x) for x in glob.glob(os.path.join(CSRC, "*")) + [os.path.join(INCLUDE, "sbqa.h"), __file__])
 
     def comp(src):
         obj = os.path.join(bdir, os.path.basename(src) + ".o")
+        if src != dsrc and os.path.exists(obj) and os.path.getmtime(obj) > newest:
+            return obj
         cmd = [HIPCC, *COMMON, *san, "-Xarch_host", "-g"]
         if src.endswith(".cpp"):
             cmd += ["-x", "hip"]
@@ -92,9 +97,9 @@ def build_sanitized(kind: str, verbose: bool = False) -> str:
             raise RuntimeError("compile failed: %s\n%s\n%s" % (" ".join(cmd), r.stdout, r.stderr))
         return obj
 
-    with cf.ThreadPoolExecutor(min(8, len(srcs))) as ex:
-        objs = list(ex.map(comp, srcs))
-    exe = os.path.join(bdir, "host_checks")
+    with cf.ThreadPoolExecutor(min(8, len(srcs) + 1)) as ex:
+        objs = list(ex.map(comp, srcs + [dsrc]))
+    exe = os.path.join(bdir, driver)
     cmd = [HIPCC, "--offload-arch=" + ARCH, *san, "-o", exe, *objs, "-lpthread"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
