@@ -198,11 +198,12 @@ _PATH_CODES = {"dense_fp32": 0, "dense_fp8": 1, "dense_bf16x3": 2, "dense_int8":
                "dense_fp4": 6, "dense_fp4_packed": 7}
 
 
-def tuned_form(info):
+def tuned_form(info, given=False):
     """The form of the dense step that the library's autotuner chose for this
     shape (1, 2: 16- and 32-spin tiles, 3: the 64-spin tile, 4..7: split-K), from
-    its tile file; None without one. Lines are <tag> <arch> <CUs> <path + 16 form> <C>
-    <padded N> <tile_cols / 64>; the last one of a shape counts."""
+    its tile file; None without one. Lines are <tag> <arch> <CUs> <path + 16 form (+
+    256: a tile given by the caller)> <C> <padded N> <tile_cols / 64>; the last one
+    of a shape counts."""
     f = os.environ.get("SBQA_TUNE_CACHE")
     if f is None:
         base = os.environ.get("XDG_CACHE_HOME") or os.path.join(os.environ.get("HOME", ""), ".cache")
@@ -215,24 +216,24 @@ def tuned_form(info):
                 if len(v) != 7 or v[0] != "sbqa-tile-v1":
                     continue
                 code, C, rows, mbw = (int(x) for x in v[3:])
-                if (code >= 16 and code % 16 == _PATH_CODES.get(info["path"]) and C == info["R"] * info["runs"]
-                        and 0 <= rows - info["N"] < 512 and 64 * mbw == info["tile_cols"]):
-                    form = code // 16
+                if (code // 16 % 16 and (code >= 256) == given and code % 16 == _PATH_CODES.get(info["path"])
+                        and C == info["R"] * info["runs"] and 0 <= rows - info["N"] < 512 and 64 * mbw == info["tile_cols"]):
+                    form = code // 16 % 16
     except (OSError, ValueError):
         pass
     return form
 
 
 def dense_kernel_name(info, form=None):
-    """The dense step kernel the library launches for single steps: that of the
-    form its autotuner chose, else of the form it takes where the caller names the
-    tile. Exact paths (spins padded to a multiple of 512): a finer tile on small
-    grids, else K split over the waves up to two tiles of 64 spins x 64 columns per
-    CU, and above that in nearly full rounds of four (bit-packed J). The others: 16
-    spins per workgroup up to one workgroup per CU, else 32 up to one. Without R
-    and runs, by the tile alone: split-K where bit-packed J at the 128-column
-    tile has an even count of K chunks (128 spins each in fp8, 256 in fp4) in
-    either half."""
+    """The dense step kernel the library launches for single steps, from the form
+    that its autotuner chose. Without a form, the rule that it falls back on. Exact
+    paths (spins padded to a multiple of 512): a finer tile on small grids, else K
+    split over the waves up to two tiles of 64 spins x 64 columns per CU, and above
+    that in nearly full rounds of four (bit-packed J) or beside the 256-column tile.
+    The others: 16 spins per workgroup up to one workgroup per CU, else 32 up to
+    one. Without R and runs, by the tile alone: split-K where bit-packed J at the
+    128-column tile has an even count of K chunks (128 spins each in fp8, 256 in
+    fp4) in either half."""
     exact = "fp8" in info["path"] or "fp4" in info["path"] or "int8" in info["path"]
     if form is not None and form != 3:
         return "k_dense_step_fine" if form < 3 else "k_dense_step_sk"
@@ -245,7 +246,8 @@ def dense_kernel_name(info, form=None):
             if n < (256 if info["path"] == "dense_fp4_packed" else 128):
                 return "k_dense_step_fine"
             full = info["path"].endswith("_packed") and cb % 2 == 0 and 20 * n >= 17 * 1024 * -(-n // 1024)
-            return "k_dense_step_sk" if n <= 512 or full else "k_dense_step"
+            wide = info["tile_cols"] == 256 and n <= 1024
+            return "k_dense_step_sk" if n <= 512 or full or wide else "k_dense_step"
         if form is None and rows // 32 * cb <= 256:
             return "k_dense_step_fine"
     elif exact:
@@ -622,7 +624,7 @@ def measure(sb, w, K, warmup, stream, loop_kernel="auto", events=True, workload=
             out["roofline"] = {"bound": "mfma", "achieved": fl / avg_s / 1e12, "peak": peak, "unit": unit,
                                "frac": fl / avg_s / 1e12 / peak,
                                "traffic": measured_traffic(workload, info["path"]) if workload else None,
-                               "kernel": dense_kernel_name(info, None if w.get("dense_tile") else tuned_form(info)),
+                               "kernel": dense_kernel_name(info, tuned_form(info, given=bool(w.get("dense_tile")))),
                                "avg_step_us": avg_s * 1e6,
                                "algorithmic_flops_per_step": fl}
     return out, ctx

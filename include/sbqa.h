@@ -97,7 +97,8 @@ typedef enum { SBQA_JP_LINEAR = 0, SBQA_JP_PAPER = 1, SBQA_JP_TABLE = 2 } sbqa_j
  *             dense +-1 instances of up to 2048 spins (R <= 32, f ternary or
  *             sign, every precision but BF16X3) then also take many steps per
  *             launch, J as one bit per coupling in registers (the same bits as
- *             STREAM; sbqa_info_t.resident stays 0).
+ *             STREAM; sbqa_info_t.resident stays 0). Calls of few steps, for
+ *             which a many-step launch does not pay, take other launches.
  *   STREAM    one fused launch per step, state streamed through HBM.
  *   RESIDENT  many steps per launch with the state on chip:
  *             - sparse (CSR): the register-resident loop (ternary or sign f,
@@ -191,12 +192,13 @@ typedef struct {
                                 track the best after every K-th step              */
     int32_t loop_kernel;     /* sbqa_loop_kernel                                   */
     int32_t dense_tile;      /* dense path: replica columns of the 64-spin workgroup
-                                tile, 64, 128 or 256; grids that leave it idle
-                                take 16 or 32 spins x 64 columns or split K instead.
-                                0 = kernel and tile autotuned (each candidate's
-                                step timed on scratch buffers of the instance's
-                                shape once per device and shape). Every choice
-                                gives the same bits. Choices persist across
+                                tile, 64, 128 or 256; 0 = autotuned. The kernel
+                                form is autotuned either way (that tile, 16 or 32
+                                spins x 64 columns, or K split over the waves):
+                                each candidate's step is timed on scratch buffers
+                                of the instance's shape once per device and
+                                shape. Every choice gives the same bits. Choices
+                                persist across
                                 processes in a text file: the path in the
                                 environment variable SBQA_TUNE_CACHE ("off":
                                 none), else $XDG_CACHE_HOME/sbqa/dense_tiles.txt,

@@ -1343,13 +1343,16 @@ hipError_t launch_energy_gemm(const EnergyPlan &e, const int8_t *S, const double
 //   Real J: fp32, 64-spin tile / 16 / 32 spins: N = 1500, C = 60 32.2 / 10.3 / 16.2; N =
 //     2000, C = 128 41.8 / 13.7 / 21.4; N = 4096, C = 128 (512 and 256 fine workgroups) 78.9 /
 //     49.1 / 39.8; N = 5000, C = 128 97 / 89 / 127; bf16 hi+lo N = 4096, C = 128 34.2 / 40.7 / 30.6.
-DenseForm default_dense_form(Path path, int Np, int Cg) {
+// The 64-spin tile of 256 columns has one wave per SIMD: with up to 4 tiles of 64 x 64
+// per CU it takes 1.2 to 1.7 times as long as split-K in one round.
+DenseForm default_dense_form(Path path, int Np, int mbw, int Cg) {
     const int64_t n16 = (int64_t)Np / 16 * (Cg / 64), n = n16 / 4;   // fine workgroups; 64 x 64 tiles
     if (!path_op2(path)) return n16 <= MI355X_CUS ? FORM_FINE16 : n16 / 2 <= MI355X_CUS ? FORM_FINE32 : FORM_TILE;
     if (n < (path == PATH_FP4PK ? MI355X_CUS : MI355X_CUS / 2)) return n16 <= MI355X_CUS ? FORM_FINE16 : FORM_FINE32;
     if (n <= MI355X_CUS) return FORM_SK11;
     if (n <= 2 * MI355X_CUS) return Cg % 128 == 0 ? FORM_SK12 : FORM_SK21;
     const int64_t round = 4 * MI355X_CUS, rounds = (n + round - 1) / round;
+    if (mbw == 4 && rounds == 1) return FORM_SK22;
     return path_packed(path) && Cg % 128 == 0 && 20 * n >= 17 * rounds * round ? FORM_SK22 : FORM_TILE;
 }
 

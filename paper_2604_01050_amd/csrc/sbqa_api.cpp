@@ -444,14 +444,14 @@ void plan_layout(int32_t N, int32_t R, int32_t runs, const InstanceFacts &f, Lay
 
 // ------------------------------------------------------------ tile autotuner
 // Kernel form of a context's dense step (DenseForm) and row blocks per operand
-// group, mbw. Candidates that pad C by at most 2x are timed once per (device,
-// path, C, Np) on scratch buffers of the instance's shape (the MFMA step's time
-// does not depend on the values); the fastest is kept. Contexts of the serving
-// loop are stepped by the grouped launches, whose 64-spin tiles have 64 * mbw
-// columns: their mbw alone is timed, per power of two that holds Np. Every form
-// gives the same bits, so a choice never changes results. Choices persist across
-// processes in a tile file (below), so a new process (a server restart) does not
-// time them again.
+// group, mbw (64 * mbw columns of the 64-spin tile). Candidates that pad C by at
+// most 2x, or the forms of the tile that the caller gave, are timed once per
+// (device, path, C, Np, given tile) on scratch buffers of the instance's shape; the
+// fastest is kept. Contexts of the serving loop are stepped by the grouped launches,
+// whose 64-spin tiles have 64 * mbw columns: their mbw alone is timed, per power
+// of two that holds Np. Every form gives the same bits, so a choice never changes
+// results. Choices persist across processes in a tile file (below), so a new
+// process (a server restart) does not time them again.
 struct DenseChoice {
     int mbw = 0;
     int form = 0;   // DenseForm; 0: served
@@ -477,7 +477,7 @@ static std::string tile_device_tag() {
 // The tile file: SBQA_TUNE_CACHE names it ("" or "off": choices stay in the
 // process), else $XDG_CACHE_HOME/sbqa/dense_tiles.txt, else
 // $HOME/.cache/sbqa/dense_tiles.txt. One line per choice,
-//   sbqa-tile-v1 <arch> <CUs> <path + 16 form> <C> <padded N> <mbw>
+//   sbqa-tile-v1 <arch> <CUs> <path + 16 form (+ 256: a given tile)> <C> <padded N> <mbw>
 // (form 0: served) appended with one write; unreadable files and malformed lines are ignored
 // (a choice is used only when it is one of the key's candidates).
 static std::string tile_file(bool make_dir) {
@@ -495,8 +495,9 @@ static std::string tile_file(bool make_dir) {
     return dir + "/dense_tiles.txt";
 }
 
-// (device, path, C, padded N, served)
-typedef std::tuple<std::string, int, int, int, bool> ChoiceKey;
+// (device, path, C, padded N, served, mbw of a given tile or 0)
+typedef std::tuple<std::string, int, int, int, bool, int> ChoiceKey;
+constexpr int GIVEN_TILE = 256;
 
 static void load_tile_file(const std::string &dev, std::map<ChoiceKey, DenseChoice> *cache) {
     const std::string f = tile_file(false);
@@ -509,9 +510,11 @@ static void load_tile_file(const std::string &dev, std::map<ChoiceKey, DenseChoi
         int cus = 0, path = 0, C = 0, npb = 0, mbw = 0;
         if (std::sscanf(line, "%31s %255s %d %d %d %d %d", tag, arch, &cus, &path, &C, &npb, &mbw) != 7) continue;
         if (std::strcmp(tag, "sbqa-tile-v1") != 0 || std::string(arch) + " " + std::to_string(cus) != dev) continue;
-        const int form = path >> 4;
-        if (path < 0 || form > FORM_SK22) continue;
-        if (mbw == 1 || mbw == 2 || mbw == 4) (*cache)[ChoiceKey(dev, path & 15, C, npb, form == 0)] = DenseChoice{mbw, form};
+        const bool given = path >= GIVEN_TILE;
+        const int form = (given ? path - GIVEN_TILE : path) >> 4;
+        if (path < 0 || form > FORM_SK22 || (given && !form)) continue;
+        if (mbw == 1 || mbw == 2 || mbw == 4)
+            (*cache)[ChoiceKey(dev, path & 15, C, npb, form == 0, given ? mbw : 0)] = DenseChoice{mbw, form};
     }
     std::fclose(fp);
 }
@@ -528,39 +531,39 @@ static void append_tile_file(const std::string &dev, int path, int C, int npb, i
     ::close(fd);
 }
 
-// The candidates of a shape. The operand grouping hardly matters outside the
-// 64-spin tile: there the largest that adds no padding. Forms that were nowhere near
-// the fastest at a grid's size are left out.
-static std::vector<DenseChoice> dense_candidates(Path path, int C, int Np, bool served) {
+// The candidates of a shape, of the tile given (its mbw) if there is one. The operand
+// grouping hardly matters outside the 64-spin tile: there the largest that adds no
+// padding. Forms that were nowhere near the fastest at a grid's size are left out.
+static std::vector<DenseChoice> dense_candidates(Path path, int C, int Np, bool served, int given) {
     std::vector<int> ms;
     for (int m : {1, 2, 4})
-        if (m == dense_mbw(C) || round_up(C, 64 * m) <= 2 * round_up(C, 64)) ms.push_back(m);
+        if (given ? m == given : m == dense_mbw(C) || round_up(C, 64 * m) <= 2 * round_up(C, 64)) ms.push_back(m);
     std::vector<DenseChoice> out;
     if (!served) {
-        const int64_t C64 = round_up(C, 64);
-        const int m0 = C64 % 256 == 0 ? 4 : C64 % 128 == 0 ? 2 : 1;
+        const int64_t C64 = round_up(C, given ? 64 * given : 64);
+        const int m0 = given ? given : C64 % 256 == 0 ? 4 : C64 % 128 == 0 ? 2 : 1;
         const int64_t n = (int64_t)Np / 64 * (C64 / 64);
         if (n <= 1024)
             for (int f : {FORM_FINE16, FORM_FINE32}) out.push_back({m0, f});
         if (path_op2(path) && n >= 64)
             for (int f : {FORM_SK11, FORM_SK21, FORM_SK12, FORM_SK22})
-                if (m0 > 1 || f <= FORM_SK21) out.push_back({m0, f});
+                if (C64 % 128 == 0 || f <= FORM_SK21) out.push_back({m0, f});
         if (n < 96) return out;
     }
     for (int m : ms) out.push_back({m, served ? 0 : (int)FORM_TILE});
     return out;
 }
 
-static DenseChoice tune_dense(Path path, int C, int Np, bool served, hipStream_t st) {
+static DenseChoice tune_dense(Path path, int C, int Np, bool served, int given, hipStream_t st) {
     static std::mutex mu;
     static std::map<ChoiceKey, DenseChoice> cache;
     static std::set<std::string> loaded;
     int npk = Np;
     if (served)
         for (npk = 128; npk < Np;) npk *= 2;
-    const std::vector<DenseChoice> cand = dense_candidates(path, C, Np, served);
+    const std::vector<DenseChoice> cand = dense_candidates(path, C, Np, served, given);
     const std::string dev = tile_device_tag();
-    const ChoiceKey key(dev, (int)path, C, npk, served);
+    const ChoiceKey key(dev, (int)path, C, npk, served, given);
     {
         std::lock_guard<std::mutex> lk(mu);
         if (!dev.empty() && !loaded.count(dev)) {
@@ -571,14 +574,14 @@ static DenseChoice tune_dense(Path path, int C, int Np, bool served, hipStream_t
         if (it != cache.end()) {
             const DenseChoice k = it->second;
             const int64_t Cg = round_up(C, 64 * k.mbw);
-            if (Cg <= std::max<int64_t>(2 * round_up(C, 64), round_up(C, 64 * dense_mbw(C))) &&
+            if ((given || Cg <= std::max<int64_t>(2 * round_up(C, 64), round_up(C, 64 * dense_mbw(C)))) &&
                 (k.form < FORM_SK11 || path_op2(path)) && (k.form < FORM_SK12 || Cg % 128 == 0))
                 return k;
         }
     }
     DenseChoice best;
-    best.mbw = dense_mbw(C);
-    best.form = served ? 0 : (int)default_dense_form(path, Np, (int)round_up(C, 64 * best.mbw));
+    best.mbw = given ? given : dense_mbw(C);
+    best.form = served ? 0 : (int)default_dense_form(path, Np, best.mbw, (int)round_up(C, 64 * best.mbw));
     bool timed = false;
     if (cand.size() > 1) {
         const int planes = path == PATH_BF16X3 ? 2 : 1;
@@ -646,18 +649,18 @@ static DenseChoice tune_dense(Path path, int C, int Np, bool served, hipStream_t
     }
     std::lock_guard<std::mutex> lk(mu);
     cache[key] = best;
-    if (timed && !dev.empty()) append_tile_file(dev, (int)path + 16 * best.form, C, npk, best.mbw);
+    if (timed && !dev.empty()) append_tile_file(dev, (int)path + 16 * best.form + (given ? GIVEN_TILE : 0), C, npk, best.mbw);
     return best;
 }
 
-// Tile of a context: the caller's (dense_tile columns, 0: chosen by timing).
+// Tile and form of a context (dense_tile: the caller's columns, 0: none given).
 static void set_tile(Layout *L, Path path, int dense_tile, bool served, hipStream_t st) {
     DenseChoice k;
-    if (dense_tile) k.mbw = dense_tile / 64;
-    else k = tune_dense(path, L->C, L->Np, served, st);
+    if (served && dense_tile) k.mbw = dense_tile / 64;
+    else k = tune_dense(path, L->C, L->Np, served, dense_tile / 64, st);
     L->mbw = k.mbw;
     L->Cg = (int)round_up(L->C, 64 * L->mbw);
-    L->form = k.form ? (DenseForm)k.form : default_dense_form(path, L->Np, L->Cg);
+    L->form = k.form ? (DenseForm)k.form : default_dense_form(path, L->Np, L->mbw, L->Cg);
 }
 
 size_t instance_bytes(int32_t N, int32_t R, int32_t runs, const InstanceFacts &f, uint32_t steps) {

@@ -141,9 +141,9 @@ struct DenseStepArgs {
 enum DenseForm : int32_t {
     FORM_FINE16 = 1, FORM_FINE32 = 2, FORM_TILE = 3, FORM_SK11 = 4, FORM_SK21 = 5, FORM_SK12 = 6, FORM_SK22 = 7
 };
-// The form where none has been timed: with a tile given by the caller, and for the
-// readouts of served instances.
-DenseForm default_dense_form(Path path, int Np, int Cg);
+// The form where none has been timed: the readouts of served instances, or where
+// timing failed.
+DenseForm default_dense_form(Path path, int Np, int mbw, int Cg);
 hipError_t launch_dense_step(Path path, DenseEpilogue epi, DenseForm form, int mbw, int Cg, const DenseStepArgs &a,
                              hipStream_t st);
 

@@ -10,33 +10,37 @@ FINE16, FINE32, TILE, SK11, SK21, SK12, SK22 = range(1, 8)
 F32, FP8, BF16X3, I8, FP8PK, FP4, FP4PK = 0, 1, 2, 4, 5, 6, 7
 
 
-def _form(path, Np, Cg):
-    return sb.lib._ZN4sbqa18default_dense_formENS_4PathEii(path, Np, Cg)
+def _form(path, Np, mbw, Cg):
+    return sb.lib._ZN4sbqa18default_dense_formENS_4PathEiii(path, Np, mbw, Cg)
 
 
 @pytest.mark.parametrize("path", [FP8, I8, FP8PK, FP4, FP4PK])
 def test_split_k_only_in_full_rounds(path):
     """A split-K workgroup has a CU to itself: with two or fewer 64 x 64 tiles
     per CU it takes them, above that only where its rounds are nearly full (and J
-    bit-packed); every other grid keeps the tiles of which a CU runs several."""
+    bit-packed) or the 64-spin tile is one of 256 columns; every other grid keeps
+    the tiles of which a CU runs several."""
     for Np in (512, 1536, 4096, 5120, 16384):
         for C64 in range(1, 49):
-            n, form = Np // 64 * C64, _form(path, Np, 64 * C64)
-            if n <= 512:
-                assert form != TILE
-                assert form not in (SK11, SK22) or n <= 256
-            elif path in (FP8PK, FP4PK) and C64 % 2 == 0 and n / 1024 >= 0.85 * -(-n // 1024):
-                assert form == SK22
-            else:
-                assert form == TILE
-            assert form not in (SK12, SK22) or C64 % 2 == 0   # whole column pairs
+            for mbw in (1, 2, 4):
+                if C64 % mbw:
+                    continue
+                n, form = Np // 64 * C64, _form(path, Np, mbw, 64 * C64)
+                if n <= 512:
+                    assert form != TILE
+                    assert form not in (SK11, SK22) or n <= 256
+                elif path in (FP8PK, FP4PK) and C64 % 2 == 0 and n / 1024 >= 0.85 * -(-n // 1024):
+                    assert form == SK22
+                else:
+                    assert form == (SK22 if mbw == 4 and n <= 1024 else TILE)
+                assert form not in (SK12, SK22) or C64 % 2 == 0   # whole column pairs
 
 
 @pytest.mark.parametrize("path", [F32, BF16X3])
 def test_real_paths_never_split_k(path):
     for Np in (128, 1536, 8192):
         for C64 in range(1, 20):
-            assert _form(path, Np, 64 * C64) <= TILE
+            assert _form(path, Np, 1, 64 * C64) <= TILE
 
 
 class _EnergyPlan(ct.Structure):
