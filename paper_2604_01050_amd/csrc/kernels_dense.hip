@@ -110,15 +110,16 @@ __global__ __launch_bounds__(GEMM_THREADS, 4) void k_energy_gemm(const int8_t *_
     const int jr = tid >> 3, jc = tid & 7, jo = TILE_BYTES + jr * LDS_STRIDE + jc * 16;
     red[tid] = 0.0;
     // this unit's K tiles: of up to ENERGY_SMALL_T blocks a range of the pair's, the
-    // longer block's first; else one of either block's
-    const int64_t all = KPB * (T - p) + (2 * p == T - 1 ? 0 : KPB * (p + 1));
-    const int r0 = (int)(all * z / Z), r1 = (int)(all * (z + 1) / Z);
+    // longer block's first; else one of either block's. (Z is a power of two: with 64-bit
+    // divisions for the ranges 200 rows of N = 3000 took 192 us, 187 so.)
+    const int lz = __builtin_ctz(Z), all = KPB * (T - p) + (2 * p == T - 1 ? 0 : KPB * (p + 1));
+    const int r0 = (all * z) >> lz, r1 = (all * (z + 1)) >> lz;
     for (int half = 0; half < 2; ++half) {
         const int t = half == 0 ? T - 1 - p : p;     // the longer block first
         if (half == 1 && t == T - 1 - p) break;      // the middle block of an odd count is alone
         const int nk = KPB * (t + 1), before = half == 0 ? 0 : KPB * (T - p);
-        const int k0 = T > ENERGY_SMALL_T ? (int)((int64_t)nk * z / Z) : min(max(r0 - before, 0), nk);
-        const int k1 = T > ENERGY_SMALL_T ? (int)((int64_t)nk * (z + 1) / Z) : min(max(r1 - before, 0), nk);
+        const int k0 = T > ENERGY_SMALL_T ? (nk * z) >> lz : min(max(r0 - before, 0), nk);
+        const int k1 = T > ENERGY_SMALL_T ? (nk * (z + 1)) >> lz : min(max(r1 - before, 0), nk);
         if (k0 == k1) continue;
         const int n0 = t * GEMM_BN, kd = KPB * t;    // from K tile kd on: the block's own spins
         const double *jrow = J + (int64_t)(n0 + jr) * Np + 2 * jc;
@@ -1322,7 +1323,8 @@ EnergyPlan energy_plan(int N, int count) {
 
 hipError_t launch_energy_gemm(const EnergyPlan &e, const int8_t *S, const double *J, int Np, double *part,
                               hipStream_t st) {
-    if (Np % 16 || e.T < 1 || e.T * GEMM_BN > Np || e.cp % GEMM_BM || e.units != (e.T + 1) / 2 * e.Z)
+    if (Np % 16 || e.T < 1 || e.T * GEMM_BN > Np || e.cp % GEMM_BM || e.Z < 1 || (e.Z & (e.Z - 1)) ||
+        e.units != (e.T + 1) / 2 * e.Z)
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_energy_gemm, dim3(e.units, e.cp / GEMM_BM), dim3(GEMM_THREADS), 0, st, S, J, Np, e.cp, e.T, e.Z,
                        part);
